@@ -19,6 +19,7 @@
 #include "../../include/wg.h"
 #include "wg_internal.h"
 #include "wg_launch.h"
+#include "wg_reach.h"
 
 using namespace wg;
 
@@ -50,6 +51,17 @@ enum : uint8_t { kSortLsd = 0, kSortSmall = 1, kSortOneBlock = 2, kSortSegmented
 // pass and the segmented sort + compaction), the device picking one by kRowMin
 constexpr uint64_t kDualAbove = kRowMin / 8;
 constexpr uint64_t kDenseRowsMax = 1ull << 28;  // largest dense edge index (1 GB)
+// The row-at-a-time closure (wg_reach.h): ids of at most this many bits (a bitmap of the id space
+// fits one workgroup's LDS) ...
+constexpr int kReachBitsMax = 20;
+// ... over at least this many ids, four rows for every CU: a row's levels are a serial chain in
+// one workgroup, so a graph of fewer rows leaves CUs idle where an iteration's launches spread
+// its candidates over the chip
+constexpr uint32_t kReachMinIds = 1024;
+constexpr uint32_t kReachHub = 256;      // a vertex of this degree sends its rows to the widest tier
+constexpr uint32_t kReachLevels = 4096;  // levels allotted at first (grown eightfold when passed)
+constexpr uint32_t kReachLevelsMax = 1u << 21;
+constexpr uint32_t kReachReadLevels = 126;  // levels read back with the control block
 // fixed arrays of an engine: control block, join and compaction block totals, radix counts
 // and totals (the triangle hits depend on the grid)
 constexpr size_t kFixedBytes[6] = {sizeof(Ctrl), sizeof(uint64_t) * kScanBlocksMax,
@@ -90,6 +102,12 @@ struct wg_engine {
   uint64_t* d_hits = nullptr;  // triangle probe: hits per emit block (grid.stream entries)
   uint64_t tri_count = 0;      // the latest triangle count
   DevBuf cand[2], full[2], fullB[2], delta[2], E, U, R, Edst, rowa, rowb, off, rec, htab, tailrun;
+  // the row-at-a-time closure: control block and levels, the pool of ids, the bitmap rows
+  DevBuf rctl, rpool, rbits;
+  uint8_t* h_reach = nullptr;  // pinned: ReachCtl and the first kReachReadLevels levels
+  uint32_t reach_levels = kReachLevels;
+  bool res_is_reach = false;   // the latest result is in that form
+  ReachResult res_reach{};
   uint64_t hash_slots = 0;  // hash-join variant: table slots of the current solve (0: off)
   uint32_t hrows_mask = 0;  // fair hash variant: row-table slots - 1 (0: off)
   uint32_t hpairs_mask = 0; // ... and pair-set slots - 1 (triangles; 0: none)
@@ -118,6 +136,7 @@ struct wg_engine {
   hipGraphExec_t graph_exec = nullptr;   // the recorded iteration (see iteration_graph)
   std::vector<uint8_t> graph_key;        // the kernel arguments it was recorded with
   uint64_t graph_builds = 0;
+  bool row_wise = false;    // the current solve may take its closure one source row at a time
   bool unfused = false;     // WG_UNFUSED_DEDUP: dedup and set difference as two passes
   bool stage_sync = false;  // WG_LOOP_STAGE: host round trips inside each iteration
   size_t allocated = 0;
@@ -173,6 +192,9 @@ struct wg_result {
   int device = 0;
   Grid grid{};
   std::function<void(uint64_t)> release;
+  // a row-at-a-time closure still in its engine (keys: the edges E then)
+  bool is_reach = false;
+  ReachResult reach{};
 };
 
 namespace {
@@ -298,7 +320,8 @@ void release_relations(wg_engine* e) {
     free_buf(e, e->fullB[s]);
     free_buf(e, e->delta[s]);
   }
-  for (DevBuf* b : {&e->E, &e->U, &e->R, &e->Edst, &e->rowa, &e->rowb, &e->off, &e->rec, &e->htab, &e->tailrun})
+  for (DevBuf* b : {&e->E, &e->U, &e->R, &e->Edst, &e->rowa, &e->rowb, &e->off, &e->rec, &e->htab, &e->tailrun,
+                    &e->rctl, &e->rpool, &e->rbits})
     free_buf(e, *b);
   e->cand_cap = e->full_cap = e->edge_cap = e->row_cap = e->rec_cap = 0;
 }
@@ -692,6 +715,163 @@ void bytes_model(wg_stats* st, int query, uint32_t kb, int passes, uint64_t m,
   if (final_union && fin.F > fin.FA) add_bytes(st, WG_STAGE_MERGE, 2.0 * (double)fin.F * kb);
 }
 
+// Capacities the iterations' launches grow to for a fixpoint of F tuples and at most C candidates
+// per iteration, and the bytes that takes beyond what the engine holds.  The row-at-a-time
+// closure keeps these buffers at the same sizes, so that a memory budget means the same and
+// refuses the same whichever way a closure is computed, a server's reservations are learned from
+// the same sizes, and a solve with other options finds its buffers grown.
+uint64_t staged_growth(const wg_engine* e, uint64_t F, uint64_t C, uint64_t* cand_cap, uint64_t* full_cap) {
+  const uint64_t kb = e->key_bytes;
+  *cand_cap = C > e->cand_cap ? std::min(std::max(e->cand_cap * 2, C + C / 4), kMaxKeys) : e->cand_cap;
+  *full_cap = F > e->full_cap ? std::min(std::max(e->full_cap * 2, F + F / 4), kMaxKeys) : e->full_cap;
+  return ((*cand_cap - e->cand_cap) + (*full_cap - e->full_cap)) * 4 * kb +
+         (std::max(*cand_cap, e->row_cap) - e->row_cap) * 12;
+}
+
+// TC one source row at a time (wg_reach.h), after E, its dense index and the seed.  Returns false
+// where the iterations' launches have to take over (an id width or depth beyond the tiers, no
+// memory for the pool or the bitmaps): E, the index and the seed are as they were.
+template <typename K>
+bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
+  Bufs<K> b = make_bufs<K>(e);
+  ReachArgs a{};
+  a.w = w;
+  // the widest tier holds three bitmaps (up to 18 bits); above, one with queues in LDS
+  a.tier_after[0] = 0;
+  a.tier_after[1] = 1;
+  a.tier_after[2] = a.hub_tier = w <= 18 ? 2 : -1;
+  if (w > 18) a.hub_tier = 1;
+  a.hub = kReachHub;
+  a.words = w > 5 ? 1u << (w - 5) : 1u;
+  uint64_t pool = std::max<uint64_t>(e->rpool.bytes / 4, std::max<uint64_t>(4 * m, 1u << 20));
+  uint64_t slots = e->rbits.bytes / (4ull * a.words);
+  const ReachCtl* rc = (const ReachCtl*)e->h_reach;
+  std::vector<ReachLevel> lev;
+  try {
+    uint64_t F = 0, C = 0, cand_total = 0;
+    for (int attempt = 0;; ++attempt) {
+      b = make_bufs<K>(e);
+      a.R = b.R;
+      a.Edst = b.Edst;
+      a.cnt = b.rowa;
+      a.seg = b.rowb;
+      // queues of at most m rows each, in the candidate buffers (free once E is sorted)
+      a.queue[0] = (uint32_t*)b.cand[0];
+      a.queue[1] = (uint32_t*)b.cand[0] + m;
+      a.queue[2] = (uint32_t*)b.cand[1];
+      const size_t ctl_bytes = sizeof(ReachCtl) + (size_t)e->reach_levels * sizeof(ReachLevel);
+      ensure(e, e->rctl, ctl_bytes);
+      ensure(e, e->rpool, pool * 4);
+      if (slots) ensure(e, e->rbits, slots * 4ull * a.words);
+      a.rc = (ReachCtl*)e->rctl.p;
+      a.lev = (ReachLevel*)((uint8_t*)e->rctl.p + sizeof(ReachCtl));
+      a.lev_cap = e->reach_levels;
+      a.pool = (uint32_t*)e->rpool.p;
+      a.pool_cap = std::min<uint64_t>(e->rpool.bytes / 4, kMaxKeys);
+      a.bits = (uint32_t*)e->rbits.p;
+      a.slots = slots;
+      hip_check(e, hipMemsetAsync(e->rctl.p, 0, ctl_bytes, e->stream), "memset");
+      launch_reach<K>(e->stream, e->grid, e->d_ctrl, b.E, m, a, b.jtot, b.off);
+      hip_check(e, hipMemcpyAsync(e->h_reach, e->rctl.p,
+                                  sizeof(ReachCtl) + kReachReadLevels * sizeof(ReachLevel), hipMemcpyDeviceToHost,
+                                  e->stream), "readback");
+      sync_stream(e);
+      if (e->cancel && e->cancel->load()) fail(e, WG_ERR_CANCELLED, "cancelled");
+      if (rc->stop & (kReachUnsupported | kReachTooLarge)) return false;
+      if (attempt == 12) return false;
+      if (rc->stop) {
+        // more room, and the rows again
+        if (rc->stop & kReachDeep) {
+          if (e->reach_levels >= kReachLevelsMax) return false;
+          e->reach_levels *= 8;
+        }
+        if (rc->stop & kReachPoolFull) pool = std::max<uint64_t>(pool, rc->cursor + rc->cursor / 8);
+        if (rc->stop & kReachSlotsFull) slots = rc->queued[2] + rc->queued[2] / 8;
+        if (pool > kMaxKeys) return false;
+        continue;
+      }
+      const ReachLevel* first = (const ReachLevel*)(e->h_reach + sizeof(ReachCtl));
+      uint32_t n = 0;
+      while (n < kReachReadLevels && first[n].n) ++n;
+      lev.assign(first, first + n);
+      if (n == kReachReadLevels) {
+        lev.resize(e->reach_levels);
+        hip_check(e, hipMemcpyAsync(lev.data(), a.lev, lev.size() * sizeof(ReachLevel), hipMemcpyDeviceToHost,
+                                    e->stream), "readback");
+        sync_stream(e);
+        n = 0;
+        while (n < lev.size() && lev[n].n) ++n;
+        lev.resize(n);
+      }
+      F = C = cand_total = 0;
+      for (const ReachLevel& l : lev) {
+        F += l.n;
+        C = std::max<uint64_t>(C, l.d);
+        cand_total += l.d;
+      }
+      if (F > kMaxKeys || C > kMaxKeys) return false;  // (the iterations' launches say so)
+      uint64_t cand_cap, full_cap;
+      const uint64_t more = staged_growth(e, F, C, &cand_cap, &full_cap);
+      if (more == 0) break;
+      if (e->budget && e->allocated + more > e->budget) {
+        const uint64_t granted = e->grow_hook ? e->grow_hook(e->allocated + more) : 0;
+        if (granted < e->allocated + more) {
+          free_buf(e, e->rpool);
+          free_buf(e, e->rbits);
+          return false;
+        }
+        e->budget = granted;
+      }
+      // (once per size: the growth takes the buffers that hold the rows' counts along)
+      e->cand_cap = cand_cap;
+      e->full_cap = full_cap;
+      IterRec seed{};
+      seed.N = seed.F = seed.FA = rc->edges;
+      size_buffers(e, true, 0, &seed);
+      launch_resume(e->stream, e->d_ctrl, e->cand_cap, e->full_cap, 0);
+    }
+    e->seen_cand.store(C, std::memory_order_relaxed);
+    // round j of the loop joins level j - 1; the last round finds nothing
+    if (o.max_iterations && lev.size() > o.max_iterations)
+      fail(e, WG_ERR_ITER_LIMIT, "max_iterations reached before the fixpoint");
+    ReachResult& r = e->res_reach;
+    r.cnt = a.cnt;
+    r.seg = a.seg;
+    r.off = b.off;
+    r.R = a.R;
+    r.pool = a.pool;
+    r.bits = a.bits;
+    r.bit_rows = a.queue[2];
+    r.n_bits = rc->queued[2];
+    r.words = a.words;
+    r.m = rc->edges;
+    r.w = w;
+    e->res_is_reach = true;
+    e->res_keys = b.E;
+    e->res_n = F;
+    e->res_w = w;
+    if (st) {
+      st->iterations = lev.size();
+      st->result_tuples = F;
+      st->base_tuples = rc->edges;
+      st->join_candidates = cand_total;
+      // tiers that took over rows the one before could not hold
+      for (int t = 0; t < kReachTiers; ++t) st->resumes += rc->queued[t] ? 1u : 0u;
+      if (st->delta_sizes)
+        for (uint64_t i = 0; i < std::min<uint64_t>(st->delta_sizes_cap, lev.size() + 1); ++i)
+          st->delta_sizes[i] = i < lev.size() ? lev[i].n : 0;
+    }
+    return true;
+  } catch (const Fail& f) {
+    if (f.st != WG_ERR_CAPACITY && f.st != WG_ERR_OUT_OF_MEMORY) throw;
+    // no memory for this form: the iterations' launches grow their own buffers
+    e->err.clear();
+    free_buf(e, e->rpool);
+    free_buf(e, e->rbits);
+    return false;
+  }
+}
+
 template <typename K>
 wg_status run(wg_engine* e, int query, const uint32_t* src, const uint32_t* dst, uint64_t m,
               const wg_options& o, int w, int ib, wg_stats* st) {
@@ -800,6 +980,20 @@ wg_status run(wg_engine* e, int query, const uint32_t* src, const uint32_t* dst,
       collect_timing(e, st);
     }
     return WG_OK;
+  }
+
+  if (query == WG_QUERY_TC && e->row_wise) {
+    if (reach<K>(e, m, w, o, st)) {
+      if (st) {
+        st->field_bits = (uint32_t)w;
+        st->key_bytes = (uint32_t)sizeof(K);
+        st->digit_bits = (uint32_t)e->sort.rb;
+        st->sort_passes = (uint32_t)passes;
+      }
+      return WG_OK;
+    }
+    if (st) st->resumes = 0;
+    b = make_bufs<K>(e);
   }
 
   uint64_t seed_n = m;  // |Delta^0| (TC: at most m; SG: read back below)
@@ -1175,6 +1369,7 @@ wg_status solve(wg_engine* e, int query, uint32_t num, const uint64_t* d_offsets
     e->generation++;
     e->res_keys = e->res_keys2 = nullptr;
     e->res_n = e->res_n2 = 0;
+    e->res_is_reach = false;
     e->syncs = 0;
     e->budget = o.mem_budget_bytes;
     // the budget bounds everything the engine holds: buffers kept from earlier solves
@@ -1225,6 +1420,12 @@ wg_status solve(wg_engine* e, int query, uint32_t num, const uint64_t* d_offsets
                        space <= 16 * m + (1u << 20))
                           ? space
                           : 0;
+      // The row-at-a-time closure: TC asked for without any of the options that describe the
+      // iterations' launches, over an id range with a dense index (see kReachBitsMax,
+      // kReachMinIds; a batch has its instances' rows side by side).
+      e->row_wise = query == WG_QUERY_TC && e->dense_rows && w <= kReachBitsMax &&
+                    (num > 1 || e->h_rb[0].c.maxid + 1 >= kReachMinIds) && o.flags == 0 &&
+                    o.loop_mode == WG_LOOP_AUTO && o.batch_k == 0 && o.force_overflow_at_iter == 0 && !e->trial;
       wg_status r = (ib + 2 * w <= 32) ? run<uint32_t>(e, query, d_src, d_dst, m, o, w, ib, st)
                                        : run<uint64_t>(e, query, d_src, d_dst, m, o, w, ib, st);
       if (r != WG_OK) return r;
@@ -1235,6 +1436,8 @@ wg_status solve(wg_engine* e, int query, uint32_t num, const uint64_t* d_offsets
                                    num ? num : 1u};
     res->keys2 = e->res_keys2;
     res->n2 = e->res_n2;
+    res->is_reach = e->res_is_reach;
+    res->reach = e->res_reach;
     *out = res;
     if (st) {
       st->host_syncs = e->syncs;
@@ -1339,8 +1542,16 @@ wg_status result_detach(const wg_result* r, hipStream_t s, std::function<void(ui
     return WG_ERR_OUT_OF_MEMORY;
   }
   // both runs, back to back
-  const uint64_t na = r->n - r->n2;
+  const uint64_t na = r->is_reach ? 0 : r->n - r->n2;
   hipError_t err = wait_engine(r, s);
+  if (r->is_reach) {
+    if (r->key_bytes == 4)
+      launch_reach_keys<uint32_t>(s, c->grid, r->reach, (const uint32_t*)r->keys, (uint32_t*)c->owned);
+    else
+      launch_reach_keys<uint64_t>(s, c->grid, r->reach, (const uint64_t*)r->keys, (uint64_t*)c->owned);
+    err = hipGetLastError();
+    c->is_reach = false;
+  }
   if (na) err = hipMemcpyAsync(c->owned, r->keys, na * r->key_bytes, hipMemcpyDeviceToDevice, s);
   if (err == hipSuccess && r->n2)
     err = hipMemcpyAsync((uint8_t*)c->owned + na * r->key_bytes, r->keys2, r->n2 * r->key_bytes,
@@ -1476,6 +1687,8 @@ wg_status wg_engine_create_ex(int device, const wg_allocator* allocator, wg_engi
     fixed((void**)&e->d_hits, sizeof(uint64_t) * e->grid.stream);
     fixed((void**)&e->d_bstart, kFixedBytes[5]);
     hip_check(e, hipHostMalloc((void**)&e->h_rb, 3 * sizeof(Readback)), "hipHostMalloc");
+    hip_check(e, hipHostMalloc((void**)&e->h_reach, sizeof(ReachCtl) + kReachReadLevels * sizeof(ReachLevel)),
+              "hipHostMalloc");
     hip_check(e, hipMemsetAsync(e->d_ctrl, 0, sizeof(Ctrl), nullptr), "hipMemsetAsync");
     for (int s = 0; s < 2; ++s)
       hip_check(e, hipEventCreateWithFlags(&e->ev_batch[s], hipEventDisableTiming), "hipEventCreate");
@@ -1515,6 +1728,9 @@ void wg_engine_destroy(wg_engine* e) {
   release(e->rec);
   release(e->htab);
   release(e->tailrun);
+  release(e->rctl);
+  release(e->rpool);
+  release(e->rbits);
   dev_free(e, e->d_ctrl, kFixedBytes[0], nullptr);
   dev_free(e, e->d_jtot, kFixedBytes[1], nullptr);
   dev_free(e, e->d_bcnt, kFixedBytes[2], nullptr);
@@ -1524,6 +1740,7 @@ void wg_engine_destroy(wg_engine* e) {
   dev_free(e, e->d_bstart, kFixedBytes[5], nullptr);
   if (e->h_rb) (void)hipHostFree(e->h_rb);
   if (e->h_rec) (void)hipHostFree(e->h_rec);
+  if (e->h_reach) (void)hipHostFree(e->h_reach);
   for (int s = 0; s < 2; ++s)
     if (e->ev_batch[s]) (void)hipEventDestroy(e->ev_batch[s]);
   if (e->ev_done) (void)hipEventDestroy(e->ev_done);
@@ -1798,7 +2015,9 @@ wg_status wg_result_offsets(const wg_result* r, uint64_t* offsets_out, uint64_t 
   if (host && hipMallocAsync((void**)&dst, bytes, s) != hipSuccess) return device_error(r, "hipMallocAsync");
   const Grid g = result_grid(r);
   if (wait_engine(r, s) != hipSuccess) return device_error(r, "hipStreamWaitEvent");
-  if (r->key_bytes == 4)
+  if (r->is_reach)
+    launch_reach_instances(s, g, r->reach, r->num_inst, dst);
+  else if (r->key_bytes == 4)
     launch_offsets<uint32_t>(s, g, (const uint32_t*)r->keys, r->n - r->n2, (const uint32_t*)r->keys2, r->n2,
                              2 * r->w, r->num_inst, dst);
   else
@@ -1838,7 +2057,11 @@ wg_status wg_result_copy(const wg_result* r, uint32_t* src_out, uint32_t* dst_ou
     dd = tmp + r->n;
   }
   if (wait_engine(r, s) != hipSuccess) return device_error(r, "hipStreamWaitEvent");
-  if (r->key_bytes == 4)
+  if (r->is_reach && r->key_bytes == 4)
+    launch_reach_unpack<uint32_t>(s, g, r->reach, (const uint32_t*)r->keys, ds, dd);
+  else if (r->is_reach)
+    launch_reach_unpack<uint64_t>(s, g, r->reach, (const uint64_t*)r->keys, ds, dd);
+  else if (r->key_bytes == 4)
     launch_unpack<uint32_t>(s, g, (const uint32_t*)r->keys, r->n - r->n2, (const uint32_t*)r->keys2, r->n2,
                             r->w, ds, dd);
   else
