@@ -51,14 +51,14 @@ enum : uint8_t { kSortLsd = 0, kSortSmall = 1, kSortOneBlock = 2, kSortSegmented
 // pass and the segmented sort + compaction), the device picking one by kRowMin
 constexpr uint64_t kDualAbove = kRowMin / 8;
 constexpr uint64_t kDenseRowsMax = 1ull << 28;  // largest dense edge index (1 GB)
-// The row-at-a-time closure (wg_reach.h): ids of at most this many bits (a bitmap of the id space
-// fits one workgroup's LDS) ...
-constexpr int kReachBitsMax = 20;
-// ... over at least this many ids, four rows for every CU: a row's levels are a serial chain in
-// one workgroup, so a graph of fewer rows leaves CUs idle where an iteration's launches spread
-// its candidates over the chip
-constexpr uint32_t kReachMinIds = 1024;
-constexpr uint32_t kReachHub = 256;      // a vertex of this degree sends its rows to the widest tier
+// The row-at-a-time closure (wg_reach.h).  Ids are ranked through flags by id: spans of up to
+// 2^24 ids, or not much wider than the graph (as for the dense index).
+constexpr uint64_t kReachSpan = 1ull << 24;
+constexpr uint64_t kReachColsMax = 1ull << 20;  // columns of one instance: a bitmap fits one CU's LDS
+constexpr uint64_t kReachBitsCols = 1ull << 18; // ... three bitmaps
+// Slabs at once, without the tiers' thread launch first, while a level over all slabs is at most
+// this many word operations (edges x columns / 32): a few microseconds
+constexpr uint64_t kSlabAlways = 3u << 20;
 constexpr uint32_t kReachLevels = 4096;  // levels allotted at first (grown eightfold when passed)
 constexpr uint32_t kReachLevelsMax = 1u << 21;
 constexpr uint32_t kReachReadLevels = 126;  // levels read back with the control block
@@ -102,8 +102,9 @@ struct wg_engine {
   uint64_t* d_hits = nullptr;  // triangle probe: hits per emit block (grid.stream entries)
   uint64_t tri_count = 0;      // the latest triangle count
   DevBuf cand[2], full[2], fullB[2], delta[2], E, U, R, Edst, rowa, rowb, off, rec, htab, tailrun;
-  // the row-at-a-time closure: control block and levels, the pool of ids, the bitmap rows
-  DevBuf rctl, rpool, rbits;
+  // the row-at-a-time closure: control block, levels and flags; the renumbered graph; the pool of
+  // columns; bitmaps
+  DevBuf rctl, rgraph, rpool, rbits;
   uint8_t* h_reach = nullptr;  // pinned: ReachCtl and the first kReachReadLevels levels
   uint32_t reach_levels = kReachLevels;
   bool res_is_reach = false;   // the latest result is in that form
@@ -111,6 +112,7 @@ struct wg_engine {
   uint64_t hash_slots = 0;  // hash-join variant: table slots of the current solve (0: off)
   uint32_t hrows_mask = 0;  // fair hash variant: row-table slots - 1 (0: off)
   uint32_t hpairs_mask = 0; // ... and pair-set slots - 1 (triangles; 0: none)
+  uint64_t key_space = 0;   // row ids (instance << w | src) of the current solve are below this
   uint64_t dense_rows = 0;  // rows of the dense edge index of the current solve (0: U + search)
   // how the loop's iterations join and sort: 0 the LSD passes; 1 the one-block sort,
   // then the passes (no-ops when it fit); 2 the one-block sort alone; 3 the join and the
@@ -192,7 +194,7 @@ struct wg_result {
   int device = 0;
   Grid grid{};
   std::function<void(uint64_t)> release;
-  // a row-at-a-time closure still in its engine (keys: the edges E then)
+  // a row-at-a-time closure still in its engine (no keys then)
   bool is_reach = false;
   ReachResult reach{};
 };
@@ -321,7 +323,7 @@ void release_relations(wg_engine* e) {
     free_buf(e, e->delta[s]);
   }
   for (DevBuf* b : {&e->E, &e->U, &e->R, &e->Edst, &e->rowa, &e->rowb, &e->off, &e->rec, &e->htab, &e->tailrun,
-                    &e->rctl, &e->rpool, &e->rbits})
+                    &e->rctl, &e->rgraph, &e->rpool, &e->rbits})
     free_buf(e, *b);
   e->cand_cap = e->full_cap = e->edge_cap = e->row_cap = e->rec_cap = 0;
 }
@@ -728,50 +730,74 @@ uint64_t staged_growth(const wg_engine* e, uint64_t F, uint64_t C, uint64_t* can
          (std::max(*cand_cap, e->row_cap) - e->row_cap) * 12;
 }
 
-// TC one source row at a time (wg_reach.h), after E, its dense index and the seed.  Returns false
-// where the iterations' launches have to take over (an id width or depth beyond the tiers, no
-// memory for the pool or the bitmaps): E, the index and the seed are as they were.
+// TC one source row at a time (wg_reach.h), from the sorted distinct edges E and the seed.
+// Returns false where the iterations' launches have to take over (few rows, rows beyond the tiers,
+// no memory for the pool or the bitmaps): E and the seed are as they were.
 template <typename K>
 bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
   Bufs<K> b = make_bufs<K>(e);
   ReachArgs a{};
-  a.w = w;
-  // the widest tier holds three bitmaps (up to 18 bits); above, one with queues in LDS
-  a.tier_after[0] = 0;
-  a.tier_after[1] = 1;
-  a.tier_after[2] = a.hub_tier = w <= 18 ? 2 : -1;
-  if (w > 18) a.hub_tier = 1;
-  a.hub = kReachHub;
-  a.words = w > 5 ? 1u << (w - 5) : 1u;
+  const uint64_t span = (e->key_space + 31) & ~31ull;
+  const uint64_t cols = std::min<uint64_t>({m, e->num_inst > 1 ? 1ull << w : span, span});
+  a.g.span = span;
+  a.g.instances = e->num_inst;
+  a.g.w = w;
+  a.words = (uint32_t)((cols + 31) / 32);
+  a.bits_tier = cols <= kReachBitsCols;
+  a.min_rows = kReachMinRows;
+  const uint64_t level_ops = m * ((cols + 31) / 32);
+  a.slab_mode = e->num_inst > 1 ? 0 : (level_ops <= kSlabAlways ? 1 : 2);
   uint64_t pool = std::max<uint64_t>(e->rpool.bytes / 4, std::max<uint64_t>(4 * m, 1u << 20));
-  uint64_t slots = e->rbits.bytes / (4ull * a.words);
+  // (the slabs' bits at most, where that is small; else what turns out to be needed)
+  uint64_t bits = std::max<uint64_t>(e->rbits.bytes / 4,
+                                     a.slab_mode == 1 ? (cols + 31) / 32 * std::min(m, span) : 0);
   const ReachCtl* rc = (const ReachCtl*)e->h_reach;
   std::vector<ReachLevel> lev;
   try {
+    // the renumbered graph: 16-byte records first
+    const uint64_t slab_edges = a.slab_mode ? m + kSlabThreads : 0;
+    const uint64_t sizes[] = {(span / 32 + 1) * sizeof(RankWord), (m + kReachEdgePad) * sizeof(uint2), m * 4,
+                              (m + 1) * 4, m * 4, m * 4, slab_edges * 4, slab_edges * 4};
+    uint64_t at[8], total = 0;
+    for (int k = 0; k < 8; ++k) {
+      at[k] = total;
+      total += (sizes[k] + 15) & ~15ull;
+    }
+    ensure(e, e->rgraph, total);
+    uint8_t* const base = (uint8_t*)e->rgraph.p;
+    a.g.rank = (RankWord*)(base + at[0]);
+    a.g.edge = (uint2*)(base + at[1]);
+    a.g.rowkey = (uint32_t*)(base + at[2]);
+    a.g.rstart = (uint32_t*)(base + at[3]);
+    a.g.colkey = (uint32_t*)(base + at[4]);
+    a.g.cstart = (uint32_t*)(base + at[5]);
+    a.g.slab_edge = (uint32_t*)(base + at[6]);
+    a.g.slab_col = (uint32_t*)(base + at[7]);
     uint64_t F = 0, C = 0, cand_total = 0;
     for (int attempt = 0;; ++attempt) {
       b = make_bufs<K>(e);
-      a.R = b.R;
-      a.Edst = b.Edst;
       a.cnt = b.rowa;
       a.seg = b.rowb;
       // queues of at most m rows each, in the candidate buffers (free once E is sorted)
       a.queue[0] = (uint32_t*)b.cand[0];
       a.queue[1] = (uint32_t*)b.cand[0] + m;
       a.queue[2] = (uint32_t*)b.cand[1];
-      const size_t ctl_bytes = sizeof(ReachCtl) + (size_t)e->reach_levels * sizeof(ReachLevel);
-      ensure(e, e->rctl, ctl_bytes);
+      const size_t head_bytes = sizeof(ReachCtl) + (size_t)e->reach_levels * sizeof(ReachLevel);
+      ensure(e, e->rctl, head_bytes + 2 * span);
       ensure(e, e->rpool, pool * 4);
-      if (slots) ensure(e, e->rbits, slots * 4ull * a.words);
+      if (bits) ensure(e, e->rbits, bits * 4);
       a.rc = (ReachCtl*)e->rctl.p;
       a.lev = (ReachLevel*)((uint8_t*)e->rctl.p + sizeof(ReachCtl));
       a.lev_cap = e->reach_levels;
+      a.g.flags = (uint8_t*)e->rctl.p + head_bytes;
       a.pool = (uint32_t*)e->rpool.p;
       a.pool_cap = std::min<uint64_t>(e->rpool.bytes / 4, kMaxKeys);
       a.bits = (uint32_t*)e->rbits.p;
-      a.slots = slots;
-      hip_check(e, hipMemsetAsync(e->rctl.p, 0, ctl_bytes, e->stream), "memset");
-      launch_reach<K>(e->stream, e->grid, e->d_ctrl, b.E, m, a, b.jtot, b.off);
+      a.bits_words = e->rbits.bytes / 4;
+      a.slots = a.bits_words / a.words;
+      hip_check(e, hipMemsetAsync(e->rctl.p, 0, head_bytes + 2 * span, e->stream), "memset");
+      launch_reach_graph<K>(e->stream, e->grid, e->d_ctrl, b.E, m, a, b.jtot);
+      launch_reach(e->stream, e->grid, m, a, b.jtot, b.off);
       hip_check(e, hipMemcpyAsync(e->h_reach, e->rctl.p,
                                   sizeof(ReachCtl) + kReachReadLevels * sizeof(ReachLevel), hipMemcpyDeviceToHost,
                                   e->stream), "readback");
@@ -786,13 +812,16 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
           e->reach_levels *= 8;
         }
         if (rc->stop & kReachPoolFull) pool = std::max<uint64_t>(pool, rc->cursor + rc->cursor / 8);
-        if (rc->stop & kReachSlotsFull) slots = rc->queued[2] + rc->queued[2] / 8;
+        if (rc->stop & kReachSlotsFull) bits = ((uint64_t)rc->queued[2] + rc->queued[2] / 8) * a.words;
+        if (rc->stop & kReachSlabFull)
+          bits = (uint64_t)((rc->cols + rc->slab - 1) / rc->slab) * rc->rows * rc->slab / 32 + 4;
         if (pool > kMaxKeys) return false;
         continue;
       }
+      const int form = rc->slab ? 1 : 0;
       const ReachLevel* first = (const ReachLevel*)(e->h_reach + sizeof(ReachCtl));
       uint32_t n = 0;
-      while (n < kReachReadLevels && first[n].n) ++n;
+      while (n < kReachReadLevels && first[n].n[form]) ++n;
       lev.assign(first, first + n);
       if (n == kReachReadLevels) {
         lev.resize(e->reach_levels);
@@ -800,14 +829,15 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
                                     e->stream), "readback");
         sync_stream(e);
         n = 0;
-        while (n < lev.size() && lev[n].n) ++n;
+        while (n < lev.size() && lev[n].n[form]) ++n;
         lev.resize(n);
       }
       F = C = cand_total = 0;
-      for (const ReachLevel& l : lev) {
-        F += l.n;
-        C = std::max<uint64_t>(C, l.d);
-        cand_total += l.d;
+      for (ReachLevel& l : lev) {
+        l.n[0] = l.n[form];
+        F += l.n[form];
+        C = std::max<uint64_t>(C, l.d[form]);
+        cand_total += l.d[form];
       }
       if (F > kMaxKeys || C > kMaxKeys) return false;  // (the iterations' launches say so)
       uint64_t cand_cap, full_cap;
@@ -838,16 +868,19 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
     r.cnt = a.cnt;
     r.seg = a.seg;
     r.off = b.off;
-    r.R = a.R;
+    r.rowkey = a.g.rowkey;
+    r.colkey = a.g.colkey;
     r.pool = a.pool;
     r.bits = a.bits;
     r.bit_rows = a.queue[2];
-    r.n_bits = rc->queued[2];
+    r.rank = a.g.rank;
+    r.n_bits = rc->slab ? 0 : rc->queued[2];
     r.words = a.words;
-    r.m = rc->edges;
+    r.rows = rc->rows;
+    r.cols = rc->cols;
+    r.slab = rc->slab;
     r.w = w;
     e->res_is_reach = true;
-    e->res_keys = b.E;
     e->res_n = F;
     e->res_w = w;
     if (st) {
@@ -859,7 +892,7 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
       for (int t = 0; t < kReachTiers; ++t) st->resumes += rc->queued[t] ? 1u : 0u;
       if (st->delta_sizes)
         for (uint64_t i = 0; i < std::min<uint64_t>(st->delta_sizes_cap, lev.size() + 1); ++i)
-          st->delta_sizes[i] = i < lev.size() ? lev[i].n : 0;
+          st->delta_sizes[i] = i < lev.size() ? lev[i].n[0] : 0;
     }
     return true;
   } catch (const Fail& f) {
@@ -914,6 +947,19 @@ wg_status run(wg_engine* e, int query, const uint32_t* src, const uint32_t* dst,
   const int mode = query == WG_QUERY_SG ? kModeEdges : (kModeEdges | kModeSeed);
   launch_compact<K>(e->stream, e->grid, mode, e->d_ctrl, &e->d_ctrl->m_in, b.cand[passes & 1],
                     b.cand[(passes & 1) ^ 1], b, w, 0, 0, stage(e, WG_STAGE_DEDUP_DIFF));
+  if (query == WG_QUERY_TC && e->row_wise) {
+    if (reach<K>(e, m, w, o, st)) {
+      if (st) {
+        st->field_bits = (uint32_t)w;
+        st->key_bytes = (uint32_t)sizeof(K);
+        st->digit_bits = (uint32_t)e->sort.rb;
+        st->sort_passes = (uint32_t)passes;
+      }
+      return WG_OK;
+    }
+    if (st) st->resumes = 0;
+    b = make_bufs<K>(e);
+  }
   launch_edge_index<K>(e->stream, e->grid, e->d_ctrl, b, w, stage(e, WG_STAGE_PREPARE));
   e->unfused = (o.flags & WG_UNFUSED_DEDUP) != 0;
   e->stage_sync = false;
@@ -980,20 +1026,6 @@ wg_status run(wg_engine* e, int query, const uint32_t* src, const uint32_t* dst,
       collect_timing(e, st);
     }
     return WG_OK;
-  }
-
-  if (query == WG_QUERY_TC && e->row_wise) {
-    if (reach<K>(e, m, w, o, st)) {
-      if (st) {
-        st->field_bits = (uint32_t)w;
-        st->key_bytes = (uint32_t)sizeof(K);
-        st->digit_bits = (uint32_t)e->sort.rb;
-        st->sort_passes = (uint32_t)passes;
-      }
-      return WG_OK;
-    }
-    if (st) st->resumes = 0;
-    b = make_bufs<K>(e);
   }
 
   uint64_t seed_n = m;  // |Delta^0| (TC: at most m; SG: read back below)
@@ -1421,11 +1453,14 @@ wg_status solve(wg_engine* e, int query, uint32_t num, const uint64_t* d_offsets
                           ? space
                           : 0;
       // The row-at-a-time closure: TC asked for without any of the options that describe the
-      // iterations' launches, over an id range with a dense index (see kReachBitsMax,
-      // kReachMinIds; a batch has its instances' rows side by side).
-      e->row_wise = query == WG_QUERY_TC && e->dense_rows && w <= kReachBitsMax &&
-                    (num > 1 || e->h_rb[0].c.maxid + 1 >= kReachMinIds) && o.flags == 0 &&
-                    o.loop_mode == WG_LOOP_AUTO && o.batch_k == 0 && o.force_overflow_at_iter == 0 && !e->trial;
+      // iterations' launches, over ids and columns the ranking and the tiers hold (kReachSpan,
+      // kReachColsMax; whether there are rows enough, kReachMinRows, shows on the device).
+      e->key_space = space;
+      const uint64_t widest = std::min<uint64_t>(m, num > 1 ? 1ull << w : space);
+      e->row_wise = query == WG_QUERY_TC && m >= kReachMinRows && space >= kReachMinRows &&
+                    (space <= kReachSpan || (space <= kDenseRowsMax && space <= 16 * m + (1u << 20))) &&
+                    widest <= kReachColsMax && o.flags == 0 && o.loop_mode == WG_LOOP_AUTO && o.batch_k == 0 &&
+                    o.force_overflow_at_iter == 0 && !e->trial;
       wg_status r = (ib + 2 * w <= 32) ? run<uint32_t>(e, query, d_src, d_dst, m, o, w, ib, st)
                                        : run<uint64_t>(e, query, d_src, d_dst, m, o, w, ib, st);
       if (r != WG_OK) return r;
@@ -1546,9 +1581,9 @@ wg_status result_detach(const wg_result* r, hipStream_t s, std::function<void(ui
   hipError_t err = wait_engine(r, s);
   if (r->is_reach) {
     if (r->key_bytes == 4)
-      launch_reach_keys<uint32_t>(s, c->grid, r->reach, (const uint32_t*)r->keys, (uint32_t*)c->owned);
+      launch_reach_keys<uint32_t>(s, c->grid, r->reach, r->n, (uint32_t*)c->owned);
     else
-      launch_reach_keys<uint64_t>(s, c->grid, r->reach, (const uint64_t*)r->keys, (uint64_t*)c->owned);
+      launch_reach_keys<uint64_t>(s, c->grid, r->reach, r->n, (uint64_t*)c->owned);
     err = hipGetLastError();
     c->is_reach = false;
   }
@@ -1729,6 +1764,7 @@ void wg_engine_destroy(wg_engine* e) {
   release(e->htab);
   release(e->tailrun);
   release(e->rctl);
+  release(e->rgraph);
   release(e->rpool);
   release(e->rbits);
   dev_free(e, e->d_ctrl, kFixedBytes[0], nullptr);
@@ -2057,10 +2093,8 @@ wg_status wg_result_copy(const wg_result* r, uint32_t* src_out, uint32_t* dst_ou
     dd = tmp + r->n;
   }
   if (wait_engine(r, s) != hipSuccess) return device_error(r, "hipStreamWaitEvent");
-  if (r->is_reach && r->key_bytes == 4)
-    launch_reach_unpack<uint32_t>(s, g, r->reach, (const uint32_t*)r->keys, ds, dd);
-  else if (r->is_reach)
-    launch_reach_unpack<uint64_t>(s, g, r->reach, (const uint64_t*)r->keys, ds, dd);
+  if (r->is_reach)
+    launch_reach_unpack(s, g, r->reach, r->n, ds, dd);
   else if (r->key_bytes == 4)
     launch_unpack<uint32_t>(s, g, (const uint32_t*)r->keys, r->n - r->n2, (const uint32_t*)r->keys2, r->n2,
                             r->w, ds, dd);

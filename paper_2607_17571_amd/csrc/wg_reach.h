@@ -4,21 +4,31 @@
 // by source row: Delta^i restricted to row x is the set of vertices at distance i + 1 from
 // x, its join with E is the expansion of those vertices' edges, and the dedup and the set
 // difference against Full are one membership test in the set of vertices row x already
-// holds.  A row's whole fixpoint therefore runs in one workgroup (or one wave, or one thread)
-// with that set on chip -- no candidate is ever written to memory, sorted or merged, and no
-// launch is needed per iteration.  The sizes the loop reports stay those of the iterations:
-// |Delta^i| is the number of (row, vertex) pairs found at level i over all rows, and the
-// candidates of iteration i + 1 the out-degrees of those vertices, both summed per level.
+// holds.  A row's whole fixpoint therefore runs where that set is on chip -- no candidate is
+// ever written to memory, sorted or merged, and no launch is needed per iteration.  The sizes
+// the loop reports stay those of the iterations: |Delta^i| is the number of (row, vertex)
+// pairs found at level i over all rows, and the candidates of iteration i + 1 the out-degrees of
+// those vertices, both summed per level.
 //
-// Rows differ by orders of magnitude, so they go through tiers; a row that outgrows a tier is
+// The graph is renumbered first: rows are the vertices with out-edges, columns the vertices with
+// in-edges, both in id order, so that ids of any width and spread, and the instances of a batch,
+// become two dense ranges (a column's rank orders like its id, so sorted output stays sorted).
+//
+// Two ways to run the rows:
+//
+// Slabs (k_slab*), where most rows reach much of the graph: a workgroup takes 32 columns and
+// holds, for every row, the bits of those columns found at the last level; a level ORs the bits
+// of each row's successors.  The columns are independent, so a slab runs to its fixpoint alone.
+//
+// Tiers, where rows are short and differ by orders of magnitude: a row that outgrows a tier is
 // queued for the next one and starts over there (nothing of it has been counted yet):
 //   thread  <= 16 tuples: the set in registers                         k_reach_thread
 //   group   <= 128 tuples: 16 lanes, a hash set in LDS                 k_reach_group
-//   wave    any size, thin levels: a bitmap of the id space and two    k_reach_queue
-//           frontier queues in LDS (a block of 16 waves for wide ids)
-//   block   any size, wide levels: three bitmaps in LDS                k_reach_bits
-// The first three write a row's sorted dst ids to a pool of 32-bit entries, the last writes the
-// row's bitmap.  The result stays in that form; reading it unpacks it (k_reach_unpack*).
+//   queue   any size, thin levels: a bitmap of the columns and two
+//           frontier queues in LDS (one wave, or a block for wide ones) k_reach_queue
+//   bits    any size, wide levels: three bitmaps in LDS                k_reach_bits
+// The first three write a row's sorted columns to a pool of 32-bit entries, the last writes the
+// row's bitmap.  The result stays in its form; reading it unpacks it.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -36,84 +46,124 @@ constexpr uint32_t kReachChunk = 4096;      // pool entries a block or wave rese
 constexpr uint32_t kReachLdsLevels = 128;   // levels counted in LDS (deeper ones in memory)
 constexpr uint32_t kReachBitRow = 0x80000000u;  // flag in cnt[]: the row is a bitmap
 constexpr uint32_t kReachNone = 0xFFFFFFFFu;
+constexpr uint32_t kReachLast = 0x80000000u;  // flag in an edge's column: the last of its row
 constexpr int kReachXcds = 8;
+constexpr uint32_t kReachEdgePad = 8;       // edge records readable past the last
+
+// Fewer rows than this are left to the iterations' launches: a row's levels (and a slab's) are a
+// serial chain in one workgroup, so they leave most CUs idle where an iteration's launches spread
+// its candidates over the chip.
+constexpr uint32_t kReachMinRows = 512;
+
+// Slabs: LDS for two words per row (and one idle row).  32 columns per slab while the rows fit
+// at 4 bytes, else 16.
+constexpr uint32_t kSlabThreads = 1024;
+constexpr uint32_t kSlabLdsWords = 36864;                    // 147,456 bytes
+constexpr uint32_t kSlabRows32 = kSlabLdsWords / 2 - 1;      // rows at 32 columns per slab
+constexpr uint32_t kSlabRows16 = kSlabLdsWords - 1;          // ... at 16
+constexpr uint32_t kSlabEdgeRegs = 32;                       // edges a thread keeps in registers
 
 // ReachCtl::stop.  A pool or slots too small leave the counting on (the host then knows what is
 // needed and runs the rows again); the others end every kernel at its next look.
 enum : uint32_t {
   kReachPoolFull = 1,     // the pool is too small: ids were dropped
   kReachSlotsFull = 2,    // more bitmap rows than slots: the bits tier did not run
-  kReachUnsupported = 4,  // a row beyond the tiers this id width has
+  kReachUnsupported = 4,  // a row beyond the tiers
   kReachDeep = 8,         // more levels than the host allotted
   kReachTooLarge = 16,    // more than 2^32 - 16 tuples
+  kReachSlabFull = 32,    // the slabs' bits do not fit their buffer: the slabs did not run
   kReachHalt = kReachUnsupported | kReachDeep | kReachTooLarge,
 };
 constexpr unsigned long long kReachMaxTuples = 0xFFFFFFF0ull;
 
-struct ReachLevel {
-  unsigned long long n;  // tuples found at this level, all rows
-  unsigned long long d;  // their out-degrees: the candidates of the next iteration
+struct ReachLevel {          // [0]: by the tiers, [1]: by the slabs
+  unsigned long long n[2];  // tuples found at this level, all rows
+  unsigned long long d[2];  // their out-degrees: the candidates of the next iteration
 };
 
 struct ReachCtl {
   uint32_t queued[kReachTiers];  // rows queued for each tier
   uint32_t stop;                 // kReach* bits
   unsigned long long cursor;     // pool entries handed out
-  unsigned long long edges;      // distinct edges (for the host, beside the above)
-  unsigned long long pad[4];
+  uint32_t rows, cols, edges;    // of the renumbered graph
+  uint32_t slab;                 // the slabs took the rows: columns per slab (32 or 16), else 0
+  unsigned long long pad[3];
   uint32_t claim[kReachTiers][kReachXcds][16];  // rows handed out, one counter per XCD (a 64 B line
                                                 // each: same-address atomics of all XCDs serialise
                                                 // at 12 ns)
 };
 
+// Ranks of 32 consecutive ids: which are rows and columns, and how many come before them.
+struct RankWord {
+  uint32_t rowbits, colbits, rowpre, colpre;
+};
+
+// The renumbered graph.  Keys are instance << w | id.
+struct ReachGraph {
+  uint32_t* rowkey;   // key of each row
+  uint32_t* rstart;   // first edge of each row, rows + 1 entries
+  uint32_t* colkey;   // key of each column
+  uint32_t* cstart;   // first edge of the row of each column's vertex, kReachNone without one
+  uint2* edge;        // {column | kReachLast, first edge of the column's row or kReachNone}
+  uint32_t* slab_edge;  // slabs: row << 16 | successor row, 1,024 stretches interleaved
+  uint32_t* slab_col;   // ... their columns
+  RankWord* rank;     // by key / 32; one word past the last key
+  uint8_t* flags;     // by key: row flags, then column flags (`span` each)
+  uint64_t span;      // keys (a multiple of 32)
+  uint32_t instances;
+  int w;
+};
+
 struct ReachArgs {
-  const uint32_t* R;     // dense edge index (row v: edges R[v] .. R[v + 1])
-  const uint32_t* Edst;  // dst ids of the sorted, distinct edges
-  int w;                 // id bits: row = instance << w | id
-  int tier_after[kReachTiers];  // tier a row goes to when it outgrows: the thread, group, queue
-                                // tier (0 group, 1 queue, 2 bits, -1 none)
-  uint32_t hub;          // a row meeting a vertex of at least this degree skips to `hub_tier`
-  int hub_tier;
-  uint32_t* cnt;         // per edge: its row's tuples at the row's first edge, 0 elsewhere
-  uint32_t* seg;         // per first edge: pool position of the row's ids, or its bitmap's slot
+  ReachGraph g;
+  int bits_tier;         // rows that outgrow the queue tier go to the bits tier (else they stop)
+  int slab_mode;         // 0: no slabs; 1: slabs; 2: slabs where half the rows outgrew the thread tier
+  uint32_t* cnt;         // per row: its tuples (| kReachBitRow)
+  uint32_t* seg;         // per row: pool position of its columns, or its bitmap's slot
   uint32_t* queue[kReachTiers];
   uint32_t* pool;
   uint64_t pool_cap;
-  uint32_t* bits;        // bitmap slots of `words` words
-  uint32_t words;
+  uint32_t* bits;        // bitmap slots of `words` words, or the slabs' bits
+  uint32_t words;        // words of a row's bitmap: the columns of the widest instance (at most)
   uint64_t slots;
+  uint64_t bits_words;   // words of `bits`
   ReachCtl* rc;
   ReachLevel* lev;
   uint32_t lev_cap;
+  uint32_t min_rows;     // (kReachMinRows)
+  uint32_t form;         // which of a level's counts the kernel adds to
 };
 
 // A closure in this form, for reading it.
 struct ReachResult {
   const uint32_t* cnt;
   const uint32_t* seg;
-  const uint32_t* off;
-  const uint32_t* R;
+  const uint32_t* off;       // first tuple of every row, rows + 1 entries
+  const uint32_t* rowkey;
+  const uint32_t* colkey;
   const uint32_t* pool;
   const uint32_t* bits;
-  const uint32_t* bit_rows;  // queued rows of the bits tier, slot by slot
+  const uint32_t* bit_rows;  // rows of the bits tier, slot by slot
+  const RankWord* rank;
   uint32_t n_bits;           // ... how many
   uint32_t words;
-  uint64_t m;                // distinct edges
+  uint32_t rows, cols;
+  uint32_t slab;             // columns per slab (bits: slab by slab, a word or halfword per row)
   int w;
 };
 
-// Every tier over the m (at most) edges of E, then the row offsets (off: m + 1 entries; part:
-// g.scan entries of scratch).  `a` and its buffers are described above.
+// Renumbers the sorted distinct edges E (ctrl->m_unique of them, at most m).
 template <typename K>
-void launch_reach(hipStream_t s, const Grid& g, const Ctrl* ctrl, const K* E, uint64_t m, const ReachArgs& a,
-                  uint64_t* part, uint32_t* off);
+void launch_reach_graph(hipStream_t s, const Grid& g, const Ctrl* ctrl, const K* E, uint64_t m, const ReachArgs& a,
+                        uint64_t* part);
+// The rows, then their offsets (off: rows + 1 entries; part: g.scan entries of scratch).
+void launch_reach(hipStream_t s, const Grid& g, uint64_t m, const ReachArgs& a, uint64_t* part, uint32_t* off);
 
-// The result as src / dst arrays, as packed keys, and the instances' first tuples (num + 1).
-template <typename K>
-void launch_reach_unpack(hipStream_t s, const Grid& g, const ReachResult& r, const K* E, uint32_t* src,
+// The result (n tuples) as src / dst arrays, as packed keys, and the instances' first tuples (num + 1).
+void launch_reach_unpack(hipStream_t s, const Grid& g, const ReachResult& r, uint64_t n, uint32_t* src,
                          uint32_t* dst);
 template <typename K>
-void launch_reach_keys(hipStream_t s, const Grid& g, const ReachResult& r, const K* E, K* keys);
+void launch_reach_keys(hipStream_t s, const Grid& g, const ReachResult& r, uint64_t n, K* keys);
 void launch_reach_instances(hipStream_t s, const Grid& g, const ReachResult& r, uint32_t num, uint64_t* out);
 
 }  // namespace wg

@@ -10,75 +10,107 @@ namespace wg {
 
 namespace {
 
-// Rows of the queue tier by id width: one wave per row up to 16 bits (bitmaps of at most 8 KB, as
-// many rows per CU as their LDS allows), wider blocks above, where one bitmap takes a CU's LDS.
+// Rows of the queue tier by the widest instance's columns: one wave per row up to 65,536 (bitmaps
+// of at most 8 KB, as many rows per CU as their LDS allows), wider blocks above, where one bitmap
+// takes much of a CU's LDS.
 void launch_queue(hipStream_t s, int cu, const ReachArgs& a) {
-  if (a.w <= 13) hipLaunchKernelGGL((k_reach_queue<1, 256, 1024, uint16_t>), dim3(cu * 24), dim3(kWave), 0, s, a);
-  else if (a.w == 14)
-    hipLaunchKernelGGL((k_reach_queue<1, 512, 1024, uint16_t>), dim3(cu * 20), dim3(kWave), 0, s, a);
-  else if (a.w == 15)
-    hipLaunchKernelGGL((k_reach_queue<1, 1024, 1024, uint16_t>), dim3(cu * 16), dim3(kWave), 0, s, a);
-  else if (a.w == 16)
-    hipLaunchKernelGGL((k_reach_queue<1, 2048, 1024, uint16_t>), dim3(cu * 12), dim3(kWave), 0, s, a);
-  else if (a.w <= 18)
-    hipLaunchKernelGGL((k_reach_queue<4, 8192, 3072, uint32_t>), dim3(cu * 2), dim3(4 * kWave), 0, s, a);
-  else
-    hipLaunchKernelGGL((k_reach_queue<16, 32768, 3072, uint32_t>), dim3(cu), dim3(16 * kWave), 0, s, a);
+  const dim3 B(kWave);
+  if (a.words <= 256) hipLaunchKernelGGL((k_reach_queue<1, 256, 512>), dim3(cu * 24), B, 0, s, a);
+  else if (a.words <= 512) hipLaunchKernelGGL((k_reach_queue<1, 512, 512>), dim3(cu * 20), B, 0, s, a);
+  else if (a.words <= 1024) hipLaunchKernelGGL((k_reach_queue<1, 1024, 512>), dim3(cu * 16), B, 0, s, a);
+  else if (a.words <= 2048) hipLaunchKernelGGL((k_reach_queue<1, 2048, 512>), dim3(cu * 12), B, 0, s, a);
+  else if (a.words <= 8192) hipLaunchKernelGGL((k_reach_queue<4, 8192, 3072>), dim3(cu * 2), dim3(4 * kWave), 0, s, a);
+  else hipLaunchKernelGGL((k_reach_queue<16, 32768, 3072>), dim3(cu), dim3(16 * kWave), 0, s, a);
 }
 
 void launch_bits(hipStream_t s, int cu, const ReachArgs& a) {
   const dim3 B(kReachBitsWaves * kWave);
-  if (a.w <= 13) hipLaunchKernelGGL((k_reach_bits<256, uint16_t>), dim3(cu * 8), B, 0, s, a);
-  else if (a.w == 14) hipLaunchKernelGGL((k_reach_bits<512, uint16_t>), dim3(cu * 8), B, 0, s, a);
-  else if (a.w == 15) hipLaunchKernelGGL((k_reach_bits<1024, uint16_t>), dim3(cu * 8), B, 0, s, a);
-  else if (a.w == 16) hipLaunchKernelGGL((k_reach_bits<2048, uint16_t>), dim3(cu * 8), B, 0, s, a);
+  if (a.words <= 512) hipLaunchKernelGGL((k_reach_bits<512, uint16_t>), dim3(cu * 8), B, 0, s, a);
+  else if (a.words <= 2048) hipLaunchKernelGGL((k_reach_bits<2048, uint16_t>), dim3(cu * 8), B, 0, s, a);
   else hipLaunchKernelGGL((k_reach_bits<8192, uint32_t>), dim3(cu), B, 0, s, a);
 }
 
-uint32_t list_blocks(const Grid& g, uint64_t m) {
-  return (uint32_t)std::min<uint64_t>(std::max<uint64_t>((m + kBlock - 1) / kBlock, 1), (uint64_t)g.stream);
+uint32_t blocks_for(const Grid& g, uint64_t n) {
+  return (uint32_t)std::min<uint64_t>(std::max<uint64_t>((n + kBlock - 1) / kBlock, 1), (uint64_t)g.stream);
 }
+
+template <typename Put>
+void unpack(hipStream_t s, const Grid& g, const ReachResult& r, uint64_t n, Put put) {
+  if (r.slab) {
+    const uint32_t b = (r.rows + kSlabOutWaves - 1) / kSlabOutWaves;
+    hipLaunchKernelGGL(k_slab_unpack<Put>, dim3(b), dim3(kSlabOutWaves * kWave), 0, s, r, put);
+    return;
+  }
+  const uint32_t lb = (uint32_t)std::min<uint64_t>((n + kReachOutTile - 1) / kReachOutTile, (uint64_t)g.stream);
+  const uint32_t bb = std::min<uint32_t>(r.n_bits, (uint32_t)g.stream);
+  hipLaunchKernelGGL(k_reach_unpack<Put>, dim3(lb + bb), dim3(kBlock), 0, s, r, lb, put);
+}
+
+// id ranges of up to this many words are ranked by one block, without a launch for the totals
+constexpr uint64_t kRankOneBlock = 4096;
+constexpr uint64_t kOffsetsOneBlock = 16384;
 
 }  // namespace
 
 template <typename K>
-void launch_reach(hipStream_t s, const Grid& g, const Ctrl* ctrl, const K* E, uint64_t m, const ReachArgs& a,
-                  uint64_t* part, uint32_t* off) {
+void launch_reach_graph(hipStream_t s, const Grid& g, const Ctrl* ctrl, const K* E, uint64_t m, const ReachArgs& a,
+                        uint64_t* part) {
+  const uint32_t b = blocks_for(g, m);
+  hipLaunchKernelGGL(k_reach_mark<K>, dim3(b), dim3(kBlock), 0, s, ctrl, E, a.g);
+  if (a.g.span / 32 <= kRankOneBlock) {
+    hipLaunchKernelGGL(k_reach_rank, dim3(1), dim3(kBlock), 0, s, ctrl, a.g,
+                       (const uint64_t*)nullptr, a.rc);
+  } else {
+    hipLaunchKernelGGL(k_reach_rank_sum, dim3(g.scan), dim3(kBlock), 0, s, a.g, part);
+    hipLaunchKernelGGL(k_reach_rank, dim3(g.scan), dim3(kBlock), 0, s, ctrl, a.g,
+                       (const uint64_t*)part, a.rc);
+  }
+  hipLaunchKernelGGL(k_reach_rows<K>, dim3(b), dim3(kBlock), 0, s, ctrl, E, a.g, (const ReachCtl*)a.rc);
+  hipLaunchKernelGGL(k_reach_edges<K>, dim3(b), dim3(kBlock), 0, s, ctrl, E, a.g, (const ReachCtl*)a.rc,
+                     a.slab_mode);
+}
+
+void launch_reach(hipStream_t s, const Grid& g, uint64_t m, const ReachArgs& a, uint64_t* part, uint32_t* off) {
   const int cu = std::max(1, g.stream / 8);
-  hipLaunchKernelGGL(k_reach_thread<K>, dim3(list_blocks(g, m)), dim3(kBlock), 0, s, ctrl, E, a);
-  hipLaunchKernelGGL(k_reach_group, dim3(cu * 6), dim3(kBlock), 0, s, a);
-  launch_queue(s, cu, a);
-  if (a.tier_after[2] >= 0 || a.hub_tier == 2) launch_bits(s, cu, a);
-  hipLaunchKernelGGL(k_reach_sum, dim3(g.scan), dim3(kBlock), 0, s, ctrl, a, part);
-  hipLaunchKernelGGL((k_reach_offsets<kScanBlocksMax>), dim3(g.scan), dim3(kBlock), 0, s, ctrl, a,
-                     (const uint64_t*)part, off);
+  if (a.slab_mode != 1) hipLaunchKernelGGL(k_reach_thread, dim3(blocks_for(g, m)), dim3(kBlock), 0, s, a);
+  if (a.slab_mode != 0) {
+    hipLaunchKernelGGL(k_slab<uint32_t>, dim3(cu), dim3(kSlabThreads), 0, s, a);
+    if (m > kSlabRows32) hipLaunchKernelGGL(k_slab<uint16_t>, dim3(cu), dim3(kSlabThreads), 0, s, a);
+    hipLaunchKernelGGL(k_slab_count, dim3(std::max<uint32_t>(1, blocks_for(g, 4 * m))), dim3(kBlock), 0, s, a);
+  }
+  if (a.slab_mode != 1) {
+    hipLaunchKernelGGL(k_reach_group, dim3(cu * 4), dim3(kBlock), 0, s, a);
+    launch_queue(s, cu, a);
+    if (a.bits_tier) launch_bits(s, cu, a);
+  }
+  if (m <= kOffsetsOneBlock) {
+    hipLaunchKernelGGL((k_reach_offsets<kScanBlocksMax>), dim3(1), dim3(kBlock), 0, s, a, (const uint64_t*)nullptr,
+                       off);
+  } else {
+    hipLaunchKernelGGL(k_reach_sum, dim3(g.scan), dim3(kBlock), 0, s, a, part);
+    hipLaunchKernelGGL((k_reach_offsets<kScanBlocksMax>), dim3(g.scan), dim3(kBlock), 0, s, a,
+                       (const uint64_t*)part, off);
+  }
 }
 
-template <typename K>
-void launch_reach_unpack(hipStream_t s, const Grid& g, const ReachResult& r, const K* E, uint32_t* src,
+void launch_reach_unpack(hipStream_t s, const Grid& g, const ReachResult& r, uint64_t n, uint32_t* src,
                          uint32_t* dst) {
-  const uint32_t lb = list_blocks(g, r.m), bb = std::min<uint32_t>(r.n_bits, (uint32_t)g.stream);
-  hipLaunchKernelGGL(k_reach_unpack<K>, dim3(lb + bb), dim3(kBlock), 0, s, r, E, lb, src, dst);
+  unpack(s, g, r, n, PutPairs{src, dst, id_mask(r.w)});
 }
 
 template <typename K>
-void launch_reach_keys(hipStream_t s, const Grid& g, const ReachResult& r, const K* E, K* keys) {
-  const uint32_t lb = list_blocks(g, r.m), bb = std::min<uint32_t>(r.n_bits, (uint32_t)g.stream);
-  hipLaunchKernelGGL(k_reach_keys<K>, dim3(lb + bb), dim3(kBlock), 0, s, r, E, lb, keys);
+void launch_reach_keys(hipStream_t s, const Grid& g, const ReachResult& r, uint64_t n, K* keys) {
+  unpack(s, g, r, n, PutKeys<K>{keys, r.w, id_mask(r.w)});
 }
 
 void launch_reach_instances(hipStream_t s, const Grid& g, const ReachResult& r, uint32_t num, uint64_t* out) {
-  const uint64_t need = ((uint64_t)num + kBlock) / kBlock;
-  hipLaunchKernelGGL(k_reach_instances, dim3((uint32_t)std::min<uint64_t>(need, (uint64_t)g.stream)), dim3(kBlock), 0,
-                     s, r, num, out);
+  hipLaunchKernelGGL(k_reach_instances, dim3(blocks_for(g, (uint64_t)num + 1)), dim3(kBlock), 0, s, r, num, out);
 }
 
-#define WG_REACH_INSTANTIATE(K)                                                                          \
-  template void launch_reach<K>(hipStream_t, const Grid&, const Ctrl*, const K*, uint64_t, const ReachArgs&, \
-                                uint64_t*, uint32_t*);                                                    \
-  template void launch_reach_unpack<K>(hipStream_t, const Grid&, const ReachResult&, const K*, uint32_t*, \
-                                       uint32_t*);                                                        \
-  template void launch_reach_keys<K>(hipStream_t, const Grid&, const ReachResult&, const K*, K*);
+#define WG_REACH_INSTANTIATE(K)                                                                              \
+  template void launch_reach_graph<K>(hipStream_t, const Grid&, const Ctrl*, const K*, uint64_t, const ReachArgs&, \
+                                      uint64_t*);                                                            \
+  template void launch_reach_keys<K>(hipStream_t, const Grid&, const ReachResult&, uint64_t, K*);
 WG_REACH_INSTANTIATE(uint32_t)
 WG_REACH_INSTANTIATE(uint64_t)
 

@@ -4,6 +4,14 @@
 #include "wg_device.h"
 #include "wg_reach.h"
 
+// Makes a register's value unknown to the compiler from here on (it would otherwise keep what it
+// derives from a loop's invariants in registers of their own).
+#ifndef WG_OPAQUE
+#define WG_OPAQUE(x) asm volatile("" : "+v"(x))
+#endif
+// Keeps loads on their side of this point (fewer of them, and of their registers, in flight).
+#define WG_FENCE_LOADS asm volatile("" ::: "memory")
+
 namespace wg {
 
 // LDS written by one lane of a wave, read by another: the wave's LDS instructions execute in
@@ -12,6 +20,11 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A value that every lane holds, in a scalar register.
+__device__ __forceinline__ uint32_t wave_uniform(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
 
 __device__ __forceinline__ bool reach_halted(const ReachCtl* rc) {
@@ -33,8 +46,8 @@ __device__ __forceinline__ void reach_count(unsigned long long (*s_lev)[2], cons
     if (n) atomicAdd(&s_lev[lv][0], (unsigned long long)n);
     if (d) atomicAdd(&s_lev[lv][1], (unsigned long long)d);
   } else if (lv < a.lev_cap) {
-    if (n) atomicAdd(&a.lev[lv].n, (unsigned long long)n);
-    if (d) atomicAdd(&a.lev[lv].d, (unsigned long long)d);
+    if (n) atomicAdd(&a.lev[lv].n[a.form], (unsigned long long)n);
+    if (d) atomicAdd(&a.lev[lv].d[a.form], (unsigned long long)d);
   } else {
     atomicOr(&a.rc->stop, (uint32_t)kReachDeep);
   }
@@ -47,8 +60,8 @@ __device__ __forceinline__ void reach_levels_clear(unsigned long long (*s_lev)[2
 // (after a barrier) the block's level counts into memory
 __device__ __forceinline__ void reach_levels_flush(const unsigned long long (*s_lev)[2], const ReachArgs& a) {
   for (uint32_t x = threadIdx.x; x < kReachLdsLevels && x < a.lev_cap; x += blockDim.x) {
-    if (s_lev[x][0]) atomicAdd(&a.lev[x].n, s_lev[x][0]);
-    if (s_lev[x][1]) atomicAdd(&a.lev[x].d, s_lev[x][1]);
+    if (s_lev[x][0]) atomicAdd(&a.lev[x].n[a.form], s_lev[x][0]);
+    if (s_lev[x][1]) atomicAdd(&a.lev[x].d[a.form], s_lev[x][1]);
   }
 }
 
@@ -65,12 +78,184 @@ __device__ __forceinline__ uint32_t reach_claim(ReachCtl* rc, int tier, uint32_t
 }
 
 // ---------------------------------------------------------------------------
-// Thread tier: thread t of a tile takes edge t if it is the first of its row, holds the row's
-// ids in 16 registers (a membership test is 16 compares) with a copy in LDS to pop them by
-// index, and sorts them with a network over the registers at the end.  A tile's rows are
-// consecutive, so their sorted ids are packed into one stretch of the pool.  Bound by the
-// dependent loads of a pop (index entry, then edges): 64 rows advance per wave, and blocks of
-// 16 KB of LDS keep 8 in flight per CU.
+// Renumbering.  Every edge flags its row's and its column's key (plain byte stores: no atomics);
+// the flags become one 16-byte word per 32 keys with the bits and the ranks before them, so that
+// a key's row or column number is one load; then the rows' starts, then the edge records.  A few
+// launches of streaming work over the edges and the id range.
+// ---------------------------------------------------------------------------
+__host__ __device__ __forceinline__ uint32_t id_mask(int w) { return w >= 32 ? 0xFFFFFFFFu : (1u << w) - 1u; }
+
+template <typename K>
+__device__ __forceinline__ uint32_t col_key(K k, int w) {  // instance << w | dst
+  const uint32_t m = id_mask(w);
+  return (head_row<K>(k, w) & ~m) | ((uint32_t)k & m);
+}
+
+__device__ __forceinline__ uint32_t bits_below(uint32_t v, uint32_t key) {
+  return (uint32_t)__popc(v & ((1u << (key & 31u)) - 1u));
+}
+__device__ __forceinline__ uint32_t rank_col(const RankWord* __restrict__ rank, uint64_t key) {
+  const RankWord r = rank[key >> 5];
+  return r.colpre + bits_below(r.colbits, (uint32_t)key);
+}
+
+template <typename K>
+__global__ __launch_bounds__(kBlock) void k_reach_mark(const Ctrl* ctrl, const K* __restrict__ E, ReachGraph g) {
+  const uint64_t n = ctrl->m_unique;
+  for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (uint64_t)gridDim.x * kBlock) {
+    const K e = E[i];
+    const uint32_t row = head_row<K>(e, g.w);
+    if (i == 0 || head_row<K>(E[i - 1], g.w) != row) g.flags[row] = 1;
+    g.flags[g.span + col_key<K>(e, g.w)] = 1;
+  }
+}
+
+// The bits of 32 flags (bytes 0 or 1).
+__device__ __forceinline__ uint32_t flag_bits(const uint8_t* __restrict__ f) {
+  const uint4* __restrict__ p = (const uint4*)f;
+  uint32_t bits = 0;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const uint4 v = p[q];
+    const uint32_t x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      bits |= ((x[k] | (x[k] >> 7) | (x[k] >> 14) | (x[k] >> 21)) & 0xFu) << (16 * q + 4 * k);
+  }
+  return bits;
+}
+
+constexpr uint32_t kReachRankTile = kBlock;  // words
+
+__global__ __launch_bounds__(kBlock) void k_reach_rank_sum(ReachGraph g, uint64_t* __restrict__ part) {
+  __shared__ uint64_t s_wave[kWavesPerBlock];
+  uint64_t lo, hi;
+  block_range(g.span / 32, kReachRankTile, lo, hi);
+  uint64_t sum = 0;  // rows << 32 | columns
+  for (uint64_t x = lo + threadIdx.x; x < hi; x += kBlock) {
+    const uint32_t rb = flag_bits(g.flags + 32 * x), cb = flag_bits(g.flags + g.span + 32 * x);
+    sum += ((uint64_t)__popc(rb) << 32) | (uint32_t)__popc(cb);
+  }
+  uint64_t total;
+  (void)block_excl_scan<uint64_t>(sum, s_wave, total);
+  if (threadIdx.x == 0) part[blockIdx.x] = total;
+}
+
+// (one block needs no totals: part nullptr)
+__global__ __launch_bounds__(kBlock) void k_reach_rank(const Ctrl* ctrl, ReachGraph g,
+                                                       const uint64_t* __restrict__ part, ReachCtl* rc) {
+  __shared__ uint64_t s_wave[kWavesPerBlock];
+  const uint64_t words = g.span / 32;
+  uint64_t run = 0;
+  if (part) {
+    // (block_prefix saturates at 40 bits: sum the halves apart)
+    uint64_t rows = 0, cols = 0;
+    for (uint32_t x = threadIdx.x; x < blockIdx.x; x += kBlock) {
+      rows += part[x] >> 32;
+      cols += part[x] & 0xFFFFFFFFull;
+    }
+    uint64_t tr, tc;
+    (void)block_excl_scan<uint64_t>(rows, s_wave, tr);
+    (void)block_excl_scan<uint64_t>(cols, s_wave, tc);
+    run = (tr << 32) | tc;
+  }
+  uint64_t lo, hi;
+  block_range(words, kReachRankTile, lo, hi);
+  for (uint64_t x0 = lo; x0 < hi; x0 += kBlock) {
+    const uint64_t x = x0 + threadIdx.x;
+    uint32_t rb = 0, cb = 0;
+    if (x < hi) {
+      rb = flag_bits(g.flags + 32 * x);
+      cb = flag_bits(g.flags + g.span + 32 * x);
+    }
+    uint64_t total;
+    const uint64_t at = run + block_excl_scan<uint64_t>(((uint64_t)__popc(rb) << 32) | (uint32_t)__popc(cb), s_wave, total);
+    if (x < hi) {
+      RankWord r;
+      r.rowbits = rb;
+      r.colbits = cb;
+      r.rowpre = (uint32_t)(at >> 32);
+      r.colpre = (uint32_t)at;
+      g.rank[x] = r;
+      for (uint32_t k = r.colpre; cb; cb &= cb - 1, ++k) g.colkey[k] = (uint32_t)x * 32u + (uint32_t)__ffs(cb) - 1u;
+    }
+    run += total;
+  }
+  if (hi == words && lo < hi && threadIdx.x == 0) {  // the last block with words
+    RankWord r;
+    r.rowbits = r.colbits = 0;
+    r.rowpre = rc->rows = (uint32_t)(run >> 32);
+    r.colpre = rc->cols = (uint32_t)run;
+    g.rank[words] = r;
+    rc->edges = (uint32_t)ctrl->m_unique;
+  }
+}
+
+template <typename K>
+__global__ __launch_bounds__(kBlock) void k_reach_rows(const Ctrl* ctrl, const K* __restrict__ E, ReachGraph g,
+                                                       const ReachCtl* rc) {
+  const uint64_t n = ctrl->m_unique;
+  for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (uint64_t)gridDim.x * kBlock) {
+    const uint32_t row = head_row<K>(E[i], g.w);
+    if (i == 0 || head_row<K>(E[i - 1], g.w) != row) {
+      const RankWord r = g.rank[row >> 5];
+      const uint32_t at = r.rowpre + bits_below(r.rowbits, row);
+      g.rowkey[at] = row;
+      g.rstart[at] = (uint32_t)i;
+    }
+    if (i + 1 == n) g.rstart[rc->rows] = (uint32_t)n;
+  }
+}
+
+// Edge i's place among the slabs' 1,024 stretches of `per` edges: thread i / per reads its k-th edge
+// at k * 1,024 + thread.
+__device__ __forceinline__ uint32_t slab_per(uint32_t edges) { return (edges + kSlabThreads - 1) / kSlabThreads; }
+
+template <typename K>
+__global__ __launch_bounds__(kBlock) void k_reach_edges(const Ctrl* ctrl, const K* __restrict__ E, ReachGraph g,
+                                                        const ReachCtl* rc, int slabs) {
+  const uint64_t n = ctrl->m_unique;
+  const uint32_t rows = rc->rows;
+  const bool slab = slabs && rows <= kSlabRows16;
+  const uint32_t per = slab_per((uint32_t)n);
+  const uint64_t end = slab ? (uint64_t)per * kSlabThreads : n;
+  for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < end; i += (uint64_t)gridDim.x * kBlock) {
+    uint32_t from = rows, to = rows, c = kReachNone;  // (past the edges: an idle row)
+    if (i < n) {
+      const K e = E[i];
+      const uint32_t row = head_row<K>(e, g.w), ck = col_key<K>(e, g.w);
+      const bool last = i + 1 == n || head_row<K>(E[i + 1], g.w) != row;
+      const RankWord r = g.rank[ck >> 5];
+      c = r.colpre + bits_below(r.colbits, ck);
+      uint32_t start = kReachNone;
+      if ((r.rowbits >> (ck & 31u)) & 1u) {
+        to = r.rowpre + bits_below(r.rowbits, ck);
+        start = g.rstart[to];
+      }
+      uint2 rec;
+      rec.x = c | (last ? kReachLast : 0u);
+      rec.y = start;
+      g.edge[i] = rec;
+      g.cstart[c] = start;  // (every edge into c writes the same)
+      if (slab) {
+        const RankWord q = g.rank[row >> 5];
+        from = q.rowpre + bits_below(q.rowbits, row);
+      }
+    }
+    if (slab) {
+      const uint64_t at = (i % per) * kSlabThreads + i / per;
+      g.slab_edge[at] = (from << 16) | to;
+      g.slab_col[at] = c;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Thread tier: thread t takes row t, holds its columns in 16 registers (a membership test is 16
+// compares) and the starts of the rows still to expand in LDS, and sorts the columns with a network
+// over the registers at the end.  A block's rows are consecutive, so their sorted columns are
+// packed into one stretch of the pool.  Bound by one dependent load per expansion (four edge
+// records at a time); 64 rows advance per wave.
 // ---------------------------------------------------------------------------
 template <int N>
 __device__ __forceinline__ void sort_regs(uint32_t (&v)[N]) {
@@ -91,103 +276,86 @@ __device__ __forceinline__ void sort_regs(uint32_t (&v)[N]) {
   }
 }
 
-constexpr uint32_t kReachFailBuf = 512;   // rows a block buffers before it appends them to a queue
-constexpr int kReachLevCopies = 16;       // copies of a block's level counts (spread over the lanes)
+constexpr uint32_t kReachFailBuf = 512;  // rows a block buffers before it appends them to a queue
+constexpr int kReachLevCopies = 16;      // copies of a block's level counts (spread over the lanes)
 
-template <typename K>
-__global__ __launch_bounds__(kBlock) void k_reach_thread(const Ctrl* ctrl, const K* __restrict__ E, ReachArgs a) {
+__global__ __launch_bounds__(kBlock) void k_reach_thread(ReachArgs a) {
   constexpr int CAP = (int)kReachThreadCap;
-  __shared__ uint32_t s_q[CAP * kBlock];  // ids by (index, thread); then the tile's sorted ids
+  __shared__ uint32_t s_q[CAP * kBlock];  // starts to expand by (index, thread); then the sorted columns
+  __shared__ uint16_t s_stat[CAP * kBlock];  // by (level, thread): tuples | degrees << 8
   __shared__ unsigned long long s_cnt[kReachLevCopies][kReachThreadCap];  // level: tuples | degrees << 32
-  __shared__ uint32_t s_fail[2][kReachFailBuf];
-  __shared__ uint32_t s_fn[2];
+  __shared__ uint32_t s_fail[kReachFailBuf];
+  __shared__ uint32_t s_fn, s_flush;
   __shared__ uint32_t s_wave[kWavesPerBlock];
   __shared__ uint64_t s_pos;
-  __shared__ uint32_t s_flush[2];
   const uint32_t tid = threadIdx.x;
   for (uint32_t x = tid; x < (uint32_t)kReachLevCopies * CAP; x += kBlock) (&s_cnt[0][0])[x] = 0;
-  if (tid < 2) s_fn[tid] = 0;
-  const uint64_t n = ctrl->m_unique;
-  const uint32_t idm = a.w >= 32 ? 0xFFFFFFFFu : (1u << a.w) - 1u;
-  const uint32_t* __restrict__ R = a.R;
-  const uint32_t* __restrict__ Edst = a.Edst;
+  if (tid == 0) s_fn = 0;
+  const uint32_t n = a.rc->rows;
+  if (n < a.min_rows) {  // (uniform over the launch)
+    if (tid == 0 && blockIdx.x == 0) atomicOr(&a.rc->stop, (uint32_t)kReachUnsupported);
+    return;
+  }
+  const uint2* __restrict__ edge = a.g.edge;
   unsigned long long* const my = s_cnt[tid % kReachLevCopies];
   uint64_t chunk = 0;
   uint32_t left = 0;  // pool entries left of the block's chunk (uniform)
-  const uint64_t ntiles = (n + kBlock - 1) / kBlock;
+  const uint32_t ntiles = (n + kBlock - 1) / kBlock;
   __syncthreads();
-  for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const uint64_t i = tile * kBlock + tid;
-    uint32_t row = 0, fail = 0;  // fail: 1 to the next tier, 2 a hub
-    bool head = false;
-    if (i < n) {
-      row = head_row<K>(E[i], a.w);
-      head = i == 0 || head_row<K>(E[i - 1], a.w) != row;
-    }
+  for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const uint32_t row = tile * kBlock + tid;
     uint32_t q[CAP];
 #pragma unroll
-    for (int k = 0; k < CAP; ++k) q[k] = kReachNone;  // (no id: ids have at most 20 bits here)
-    uint32_t cnt = 0;
-    unsigned long long degs = 0;  // 4 bits per popped id
-    uint32_t starts = 1;          // bit f: id f opens a level
-    if (head) {
-      const uint32_t inst = row & ~idm;
-      const uint32_t d = R[(uint64_t)row + 1] - (uint32_t)i;
-      if (d > 15) {
-        fail = d >= a.hub ? 2u : 1u;
-      } else {
+    for (int k = 0; k < CAP; ++k) q[k] = kReachNone;  // (no column: columns have 31 bits)
+    uint32_t cnt = 0, pops = 0;
+    bool fail = false;
+    if (row < n) {
+      // the columns of the edges from e on that the row does not hold yet; returns the edges
+      auto expand = [&](uint32_t e) -> uint32_t {
+        uint32_t d = 0;
+        for (bool more = true; more && !fail; e += 4) {
+          uint2 x[4];
 #pragma unroll
-        for (int k = 0; k < 15; ++k)
-          if ((uint32_t)k < d) {
-            q[k] = Edst[i + k];
-            s_q[k * kBlock + tid] = q[k];
-          }
-        cnt = d;
-        uint32_t end = cnt;  // of the current level
-        for (uint32_t f = 0; f < cnt && !fail; ++f) {
-          if (f == end) {
-            starts |= 1u << f;
-            end = cnt;
-          }
-          const uint64_t v = inst | s_q[f * kBlock + tid];
-          const uint32_t e0 = R[v], e1 = R[v + 1];
-          const uint32_t dv = e1 - e0;
-          if (dv > 15) {
-            fail = dv >= a.hub ? 2u : 1u;
-            break;
-          }
-          degs |= (unsigned long long)dv << (4 * f);
-          for (uint32_t e = e0; e < e1; ++e) {
-            const uint32_t z = Edst[e];
+          for (int k = 0; k < 4; ++k) x[k] = edge[e + k];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            if (!more || fail) continue;
+            const uint32_t z = x[k].x & ~kReachLast;
+            more = (x[k].x & kReachLast) == 0;
+            if (++d > 15) fail = true;
             bool dup = false;
 #pragma unroll
-            for (int k = 0; k < CAP; ++k) dup |= q[k] == z;
+            for (int r = 0; r < CAP; ++r) dup |= q[r] == z;
             if (dup) continue;
             if (cnt == (uint32_t)CAP) {
-              fail = 1;
-              break;
+              fail = true;
+              continue;
             }
 #pragma unroll
-            for (int k = 0; k < CAP; ++k) q[k] = (uint32_t)k == cnt ? z : q[k];
-            s_q[cnt * kBlock + tid] = z;
+            for (int r = 0; r < CAP; ++r) q[r] = (uint32_t)r == cnt ? z : q[r];
             ++cnt;
+            if (x[k].y != kReachNone) s_q[pops++ * kBlock + tid] = x[k].y;
           }
         }
+        return d;
+      };
+      expand(a.g.rstart[row]);
+      uint32_t lv = 0, lo = 0, prev = 0;
+      while (!fail && cnt > prev) {
+        const uint32_t found = cnt - prev, hi = pops;
+        prev = cnt;
+        uint32_t d = 0;
+        for (uint32_t f = lo; f < hi && !fail; ++f) d += expand(s_q[f * kBlock + tid]);
+        lo = hi;
+        s_stat[lv++ * kBlock + tid] = (uint16_t)(found | (d << 8));
       }
       if (fail) {
         cnt = 0;
       } else {
-        uint32_t lv = 0, ln = 0, ld = 0;
-        for (uint32_t f = 0; f < cnt; ++f) {
-          if (f > 0 && ((starts >> f) & 1u)) {
-            atomicAdd(&my[lv], (unsigned long long)ln | ((unsigned long long)ld << 32));
-            ++lv;
-            ln = ld = 0;
-          }
-          ++ln;
-          ld += (uint32_t)(degs >> (4 * f)) & 15u;
+        for (uint32_t l = 0; l < lv; ++l) {
+          const uint32_t x = s_stat[l * kBlock + tid];
+          atomicAdd(&my[l], (unsigned long long)(x & 255u) | ((unsigned long long)(x >> 8) << 32));
         }
-        atomicAdd(&my[lv], (unsigned long long)ln | ((unsigned long long)ld << 32));
         sort_regs<CAP>(q);
       }
     }
@@ -203,57 +371,249 @@ __global__ __launch_bounds__(kBlock) void k_reach_thread(const Ctrl* ctrl, const
 #pragma unroll
     for (int k = 0; k < CAP; ++k)
       if ((uint32_t)k < cnt) s_q[at + k] = q[k];
-    if (fail) {
-      const int which = fail == 2 ? 1 : 0;
-      s_fail[which][atomicAdd(&s_fn[which], 1u)] = row;
-    }
-    if (i < n) {
-      a.cnt[i] = cnt;
-      a.seg[i] = (uint32_t)(chunk + at);
+    if (fail) s_fail[atomicAdd(&s_fn, 1u)] = row;
+    if (row < n) {
+      a.cnt[row] = cnt;
+      a.seg[row] = (uint32_t)(chunk + at);
     }
     __syncthreads();
     if (chunk + total <= a.pool_cap)
       for (uint32_t t = tid; t < total; t += kBlock) a.pool[chunk + t] = s_q[t];
     chunk += total;
     left -= total;
-    // queue buffers that a further tile could overfill go out
-    const bool last = tile + gridDim.x >= ntiles;
-#pragma unroll
-    for (int which = 0; which < 2; ++which) {
-      const uint32_t fn = s_fn[which];
-      const int tier = which ? a.hub_tier : a.tier_after[0];
-      if (fn > 0 && (last || fn > kReachFailBuf - kBlock)) {
-        if (tid == 0) {
-          if (tier < 0) atomicOr(&a.rc->stop, (uint32_t)kReachUnsupported);
-          else s_flush[which] = atomicAdd(&a.rc->queued[tier], fn);
-        }
-        __syncthreads();
-        if (tier >= 0)
-          for (uint32_t t = tid; t < fn; t += kBlock) a.queue[tier][s_flush[which] + t] = s_fail[which][t];
-        __syncthreads();
-        if (tid == 0) s_fn[which] = 0;
-      }
+    // a buffer that a further tile could overfill goes out
+    const uint32_t fn = s_fn;
+    if (fn > 0 && (tile + gridDim.x >= ntiles || fn > kReachFailBuf - kBlock)) {
+      if (tid == 0) s_flush = atomicAdd(&a.rc->queued[0], fn);
+      __syncthreads();
+      for (uint32_t t = tid; t < fn; t += kBlock) a.queue[0][s_flush + t] = s_fail[t];
+      __syncthreads();
+      if (tid == 0) s_fn = 0;
     }
     __syncthreads();
   }
-  __syncthreads();
   for (uint32_t lv = tid; lv < (uint32_t)CAP; lv += kBlock) {
     unsigned long long sn = 0, sd = 0;
     for (int c = 0; c < kReachLevCopies; ++c) {
       sn += s_cnt[c][lv] & 0xFFFFFFFFull;
       sd += s_cnt[c][lv] >> 32;
     }
-    if (sn) atomicAdd(&a.lev[lv].n, sn);
-    if (sd) atomicAdd(&a.lev[lv].d, sd);
+    if (sn) atomicAdd(&a.lev[lv].n[0], sn);
+    if (sd) atomicAdd(&a.lev[lv].d[0], sd);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Slabs.  A workgroup of 1,024 threads takes 32 (16) consecutive columns.  In LDS, for every row,
+// D = the columns found at the last level and acc = those of the row's successors at that level;
+// the columns found so far (S) are registers of the row's thread.  A level is two passes: each
+// thread ORs D of the successors of its stretch of edges (kept in registers) and adds each row's
+// part to acc with an LDS atomic; then every row takes acc & ~S as its new D.  The candidates are
+// the new columns' degrees, summed through a table per byte of columns.  No memory traffic within
+// a level; about 2 us per level at 30,000 edges, one workgroup per CU, every slab on its own.
+// R-MAT scale 15 (7,546 rows, 7,535 columns): 236 slabs of 13 levels where the bits tier ran
+// 180M candidates one by one.
+// ---------------------------------------------------------------------------
+// Whether the slabs take the rows (the same in every block of the launches before the tiers run).
+__device__ __forceinline__ bool slab_chosen(const ReachArgs& a) {
+  if (a.slab_mode == 0 || a.rc->rows > kSlabRows16) return false;
+  if (a.slab_mode == 1) return true;
+  return 2ull * a.rc->queued[0] >= a.rc->rows;
+}
+
+template <typename W, int RP>
+__device__ __forceinline__ void slab_run(const ReachArgs& a, uint32_t* s_mem, unsigned long long (*s_lev)[2],
+                                         uint32_t* s_tab, uint32_t* s_any) {
+  constexpr uint32_t B = 8 * sizeof(W);  // columns per slab
+  constexpr uint32_t TH = kSlabThreads;
+  constexpr int EREG = sizeof(W) == 4 ? (int)kSlabEdgeRegs : (int)kSlabEdgeRegs * 3 / 4;
+  const uint32_t tid = threadIdx.x;
+  const uint32_t rows = wave_uniform(a.rc->rows), cols = wave_uniform(a.rc->cols),
+                 edges = wave_uniform(a.rc->edges);
+  const uint32_t pitch = (rows / TH + 1) * TH;  // whole rounds of rows, an idle one among them
+  W* const D = (W*)s_mem;
+  W* const acc = D + pitch;
+  const uint32_t per = slab_per(edges);
+  const uint32_t* __restrict__ se = a.g.slab_edge;
+  const uint32_t* __restrict__ sc = a.g.slab_col;
+  W* const out = (W*)a.bits;
+  const auto add = [&](uint32_t x, uint32_t v) {
+    if constexpr (sizeof(W) == 4) atomicOr(&acc[x], v);
+    else atomicOr((uint32_t*)acc + (x >> 1), v << (16u * (x & 1u)));
+  };
+  // the thread's first edges stay in registers for every level of every slab
+  uint32_t er[EREG];
+#pragma unroll
+  for (int k = 0; k < EREG; ++k) {
+    er[k] = (uint32_t)k < per ? se[(uint32_t)k * TH + tid] : (rows << 16) | rows;  // (an idle row)
+    if (k % 4 == 3) WG_FENCE_LOADS;
+  }
+  const uint32_t slabs = (cols + B - 1) / B;
+  for (uint32_t slab = blockIdx.x; slab < slabs; slab += gridDim.x) {
+    // byte tables: s_tab[256 b + v] = degrees of the columns of byte b in v
+    for (uint32_t x = tid; x < 256u * sizeof(W); x += TH) {
+      uint32_t sum = 0;
+      for (uint32_t v = x & 255u; v; v &= v - 1) {
+        const uint32_t c = slab * B + (x >> 8) * 8u + (uint32_t)__ffs(v) - 1u;
+        const uint32_t st = c < cols ? a.g.cstart[c] : kReachNone;
+        if (st != kReachNone) {
+          // degree: the row's start is among rstart (its index by the column's key)
+          const uint32_t key = a.g.colkey[c];
+          const RankWord r = a.g.rank[key >> 5];
+          sum += a.g.rstart[r.rowpre + bits_below(r.rowbits, key) + 1] - st;
+        }
+      }
+      s_tab[x] = sum;
+    }
+    for (uint32_t x = tid; x < pitch; x += TH) {
+      D[x] = 0;
+      acc[x] = 0;
+    }
+    W S[RP];
+#pragma unroll
+    for (int k = 0; k < RP; ++k) S[k] = 0;
+    if (tid < 2) s_any[tid] = 0;
+    __syncthreads();
+    for (uint32_t k = 0; k < per; ++k) {
+      const uint32_t c = sc[k * TH + tid];
+      if (c / B == slab) add(se[k * TH + tid] >> 16, 1u << (c % B));
+    }
+    __syncthreads();
+    for (uint32_t lv = 0;; ++lv) {
+      uint32_t found = 0, deg = 0;
+#pragma unroll
+      for (int k = 0; k < RP; ++k) {
+        if ((uint32_t)k * TH >= rows) continue;  // (uniform; rows past the last have no bits)
+        const uint32_t x = (uint32_t)k * TH + tid;
+        const W v = acc[x];
+        const W nw = (W)(v & (W)~S[k]);
+        if (v) acc[x] = 0;
+        D[x] = nw;
+        if (nw) {
+          S[k] = (W)(S[k] | nw);
+          found += (uint32_t)__popc((uint32_t)nw);
+#pragma unroll
+          for (int q = 0; q < (int)sizeof(W); ++q) deg += s_tab[256 * q + (((uint32_t)nw >> (8 * q)) & 255u)];
+        }
+        WG_FENCE_LOADS;  // (registers: one row's loads at a time)
+      }
+      found = wave_sum<uint32_t>(found);
+      deg = wave_sum<uint32_t>(deg);
+      if (lane_id() == 0 && found) {
+        reach_count(s_lev, a, lv, found, deg);
+        s_any[lv & 1u] = 1;
+      }
+      if (tid == 0) s_any[(lv + 1) & 1u] = 0;
+      __syncthreads();
+      if (!s_any[lv & 1u]) break;
+      uint32_t cur = 0, v = 0;
+      auto edge = [&](uint32_t x, uint32_t dx) {
+        if (x != cur) {
+          if (v) add(cur, v);
+          v = 0;
+          cur = x;
+        }
+        v |= dx;
+      };
+#pragma unroll
+      for (int k = 0; k < EREG; k += 4) {  // four loads in flight
+        if ((uint32_t)k >= per) continue;  // (uniform)
+        uint32_t dv[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          WG_OPAQUE(er[k + q]);
+          dv[q] = (uint32_t)D[er[k + q] & 0xFFFFu];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) edge(er[k + q] >> 16, dv[q]);
+        WG_FENCE_LOADS;
+      }
+      for (uint32_t k = EREG; k < per; k += 4) {
+        uint32_t u[4], dv[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) u[q] = k + q < per ? se[(k + q) * TH + tid] : (rows << 16) | rows;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) dv[q] = (uint32_t)D[u[q] & 0xFFFFu];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) edge(u[q] >> 16, dv[q]);
+      }
+      if (v) add(cur, v);
+      __syncthreads();
+    }
+    uint32_t left = rows > tid ? rows - tid : 0u;  // rows from the thread's first on
+    WG_OPAQUE(left);
+    W* const o = out + (uint64_t)slab * rows + tid;
+#pragma unroll
+    for (int k = 0; k < RP; ++k) {
+      if ((uint32_t)k * TH < left) o[(uint32_t)k * TH] = S[k];
+      WG_FENCE_LOADS;
+    }
+    __syncthreads();
+  }
+}
+
+// (W: a slab's columns of a row; the launch of the other width returns)
+template <typename W>
+__global__ __launch_bounds__(kSlabThreads) void k_slab(ReachArgs a) {
+  __shared__ uint32_t s_mem[kSlabLdsWords];
+  __shared__ unsigned long long s_lev[kReachLdsLevels][2];
+  __shared__ uint32_t s_tab[256 * sizeof(W)];
+  __shared__ uint32_t s_any[2];
+  constexpr uint32_t B = 8 * sizeof(W);
+  constexpr uint32_t RMAX = B == 32 ? kSlabRows32 : kSlabRows16;
+  const uint32_t rows = a.rc->rows;
+  if (block_stop(!slab_chosen(a) || reach_halted(a.rc) || rows > RMAX || (B == 16 && rows <= kSlabRows32))) return;
+  if (rows < a.min_rows) {
+    if (threadIdx.x == 0 && blockIdx.x == 0) atomicOr(&a.rc->stop, (uint32_t)kReachUnsupported);
+    return;
+  }
+  const uint64_t need = (uint64_t)((a.rc->cols + B - 1) / B) * rows * sizeof(W);
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.rc->slab = B;  // read by later launches
+  if (need > 4 * a.bits_words) {
+    if (threadIdx.x == 0 && blockIdx.x == 0) atomicOr(&a.rc->stop, (uint32_t)kReachSlabFull);
+    return;
+  }
+  a.form = 1;
+  reach_levels_clear(s_lev);
+  __syncthreads();
+  slab_run<W, (int)((RMAX + kSlabThreads) / kSlabThreads)>(a, s_mem, s_lev, s_tab, s_any);
+  __syncthreads();
+  reach_levels_flush(s_lev, a);
+}
+
+// Tuples of each row over all slabs: 64 rows per block, its waves taking the slabs in turn.
+__global__ __launch_bounds__(kBlock) void k_slab_count(ReachArgs a) {
+  __shared__ uint32_t s_c[kWavesPerBlock][kWave];
+  if (block_stop(a.rc->slab == 0 || (a.rc->stop & (kReachHalt | kReachSlabFull)) != 0)) return;
+  const uint32_t rows = a.rc->rows, B = a.rc->slab, slabs = (a.rc->cols + B - 1) / B;
+  const uint32_t lane = (uint32_t)lane_id(), wid = threadIdx.x / kWave;
+  for (uint32_t x0 = blockIdx.x * kWave; x0 < rows; x0 += gridDim.x * kWave) {
+    const uint32_t x = x0 + lane;
+    uint32_t c = 0;
+    if (x < rows) {
+      if (B == 32)
+        for (uint32_t s = wid; s < slabs; s += kWavesPerBlock) c += (uint32_t)__popc(a.bits[(uint64_t)s * rows + x]);
+      else
+        for (uint32_t s = wid; s < slabs; s += kWavesPerBlock)
+          c += (uint32_t)__popc((uint32_t)((const uint16_t*)a.bits)[(uint64_t)s * rows + x]);
+    }
+    s_c[wid][lane] = c;
+    __syncthreads();
+    if (wid == 0 && x < rows) {
+      for (int q = 1; q < kWavesPerBlock; ++q) c += s_c[q][lane];
+      a.cnt[x] = c;
+    }
+    __syncthreads();
   }
 }
 
 // ---------------------------------------------------------------------------
 // Group tier: 16 lanes per row, four rows per wave in lockstep.  The set is a hash table of 256
-// slots (linear probing, at most half full), the ids in order of discovery are the queue whose
-// stretches are the levels.  A lane pops a vertex and walks its edges.  Rows of this tier are
-// narrow (a few vertices per level), so the lanes of 16 are about as many as a level can use, and
-// the rows in flight (96 per CU) hide the loads.
+// slots (linear probing, at most half full); the columns are kept in order of discovery, the
+// starts of the rows still to expand beside them.  A lane expands one row at a time, the next edge
+// record in flight while one is inserted.  Rows of this tier are narrow (a few vertices per
+// level), so 16 lanes are about as many as a level can use, and the rows in flight (64 per CU)
+// hide the loads.
 // ---------------------------------------------------------------------------
 constexpr int kReachGroup = 16;
 constexpr int kReachGroupsPerBlock = kBlock / kReachGroup;
@@ -263,11 +623,12 @@ __global__ __launch_bounds__(kBlock) void k_reach_group(ReachArgs a) {
   constexpr int G = kReachGroup;
   __shared__ uint32_t s_hash[kReachGroupsPerBlock][H];
   __shared__ uint32_t s_ids[kReachGroupsPerBlock][CAP];
-  __shared__ uint32_t s_buf[kWavesPerBlock][2][kWave];
+  __shared__ uint32_t s_todo[kReachGroupsPerBlock][CAP];
+  __shared__ uint32_t s_buf[kWavesPerBlock][kWave];
   __shared__ unsigned long long s_lev[kReachLdsLevels][2];
   const uint32_t n = a.rc->queued[0];
   const uint32_t tid = threadIdx.x;
-  if (block_stop(n == 0 || reach_halted(a.rc))) return;
+  if (block_stop(n == 0 || a.rc->slab != 0 || reach_halted(a.rc))) return;
   reach_levels_clear(s_lev);
   __syncthreads();
   const int lane = lane_id();
@@ -277,29 +638,23 @@ __global__ __launch_bounds__(kBlock) void k_reach_group(ReachArgs a) {
   const uint32_t grp = tid / G;
   uint32_t* const hash = s_hash[grp];
   uint32_t* const ids = s_ids[grp];
-  const uint32_t* __restrict__ R = a.R;
-  const uint32_t* __restrict__ Edst = a.Edst;
-  const uint32_t idm = a.w >= 32 ? 0xFFFFFFFFu : (1u << a.w) - 1u;
+  uint32_t* const todo = s_todo[grp];
+  const uint2* __restrict__ edge = a.g.edge;
   const uint32_t wave_id = blockIdx.x * kWavesPerBlock + tid / kWave;
   const uint32_t waves = gridDim.x * kWavesPerBlock;
   constexpr uint32_t PER = kWave / G;  // rows of a wave
   uint64_t chunk = 0;
   uint32_t left = 0;
-  uint32_t(*const buf)[kWave] = s_buf[tid / kWave];
-  uint32_t fn[2] = {0, 0};  // rows in the wave's buffers: outgrown, hub
-  auto flush = [&](int which) {  // (the whole wave)
-    if (fn[which] == 0) return;
+  uint32_t* const buf = s_buf[tid / kWave];
+  uint32_t fn = 0;          // rows in the wave's buffer
+  auto flush = [&]() {  // (the whole wave)
+    if (fn == 0) return;
     wave_lds_sync();
-    const int tier = which ? a.hub_tier : a.tier_after[1];
-    if (tier < 0) {
-      if (lane == 0) atomicOr(&a.rc->stop, (uint32_t)kReachUnsupported);
-    } else {
-      uint32_t at = 0;
-      if (lane == 0) at = atomicAdd(&a.rc->queued[tier], fn[which]);
-      at = __shfl(at, 0, kWave);
-      if ((uint32_t)lane < fn[which]) a.queue[tier][at + lane] = buf[which][lane];
-    }
-    fn[which] = 0;
+    uint32_t at = 0;
+    if (lane == 0) at = atomicAdd(&a.rc->queued[1], fn);
+    at = __shfl(at, 0, kWave);
+    if ((uint32_t)lane < fn) a.queue[1][at + lane] = buf[lane];
+    fn = 0;
     wave_lds_sync();
   };
   for (uint64_t base = (uint64_t)wave_id * PER; base < n; base += (uint64_t)waves * PER) {
@@ -307,85 +662,92 @@ __global__ __launch_bounds__(kBlock) void k_reach_group(ReachArgs a) {
     const uint64_t k = base + (uint32_t)lane / G;
     const bool have = k < n;
     const uint32_t row = have ? a.queue[0][k] : 0u;
-    const uint32_t inst = row & ~idm;
-    uint32_t first = 0, cnt = 0, fail = 0;
+    uint32_t cnt = 0, pops = 0;
+    bool fail = false;
     for (uint32_t x = gl; x < H; x += G) hash[x] = kReachNone;
     wave_lds_sync();
-    // adds the ids of edges [e0, e1) of every lane (empty: none) to the lane's row
-    auto expand = [&](uint32_t e0, uint32_t e1) {
-      while (__builtin_amdgcn_ballot_w64(e0 < e1 && !fail)) {
-        bool pending = e0 < e1 && !fail, fresh = false;
-        const uint32_t z = pending ? Edst[e0] : 0u;
-        ++e0;
-        uint32_t slot = (z * 0x9E3779B1u) >> 24;
-        while (__builtin_amdgcn_ballot_w64(pending)) {
-          if (pending) {
-            const uint32_t old = atomicCAS(&hash[slot], kReachNone, z);
-            fresh = old == kReachNone;
-            pending = !fresh && old != z;
-            slot = (slot + 1) % H;
-          }
+    // inserts the column of every lane with `on` into the lane's row
+    auto insert = [&](bool on, uint2 rec) {
+      const uint32_t z = rec.x & ~kReachLast;
+      bool pending = on, fresh = false;
+      uint32_t slot = (z * 0x9E3779B1u) >> 24;
+      while (__builtin_amdgcn_ballot_w64(pending)) {
+        if (pending) {
+          const uint32_t old = atomicCAS(&hash[slot], kReachNone, z);
+          fresh = old == kReachNone;
+          pending = !fresh && old != z;
+          slot = (slot + 1) % H;
         }
-        const uint64_t nb = __builtin_amdgcn_ballot_w64(fresh) & gmask;
-        const uint32_t at = cnt + (uint32_t)__popcll(nb & lt);
-        if (fresh && at < CAP) ids[at] = z;
-        cnt += (uint32_t)__popcll(nb);
-        if (cnt > CAP) fail = 1;
       }
+      const uint64_t nb = __builtin_amdgcn_ballot_w64(fresh) & gmask;
+      const uint64_t pb = __builtin_amdgcn_ballot_w64(fresh && rec.y != kReachNone) & gmask;
+      if (fresh) {
+        const uint32_t at = cnt + (uint32_t)__popcll(nb & lt), pt = pops + (uint32_t)__popcll(pb & lt);
+        if (at < CAP) ids[at] = z;
+        if (rec.y != kReachNone && pt < CAP) todo[pt] = rec.y;
+      }
+      cnt += (uint32_t)__popcll(nb);
+      pops += (uint32_t)__popcll(pb);
+      fail = fail || cnt > CAP;
     };
     {
-      uint32_t e1 = 0;
+      // the row's own edges: lane l takes edges l, l + G, ...
+      uint32_t e = 0, e1 = 0;
       if (have) {
-        first = R[row];
-        e1 = R[(uint64_t)row + 1];
-        if (e1 - first > CAP) fail = e1 - first >= a.hub ? 2u : 1u;
+        e = a.g.rstart[row];
+        e1 = a.g.rstart[row + 1];
+        fail = e1 - e > CAP;
       }
-      // the row's own edges are distinct: lane l takes edges l, l + G, ...
-      for (uint32_t e = first + gl; __builtin_amdgcn_ballot_w64(e < e1 && !fail); e += G)
-        expand(e, e < e1 ? e + 1 : e);
+      for (e += gl; __builtin_amdgcn_ballot_w64(e < e1 && !fail); e += G) {
+        const bool on = e < e1 && !fail;
+        uint2 rec;
+        rec.x = rec.y = kReachNone;
+        if (on) rec = edge[e];
+        insert(on, rec);
+      }
     }
     wave_lds_sync();
-    // level by level; the counts go out only once the row is done, so the levels' ends and
-    // degrees stay in registers of the lanes (level l in lane l % G's slot l / G)
-    uint32_t head = 0, end = cnt, levels = 0;
+    // level by level; the counts go out only once the row is done: until then level l's are in
+    // slot l / G of lane l % G
+    uint32_t lo = 0, prev = 0, levels = 0;
     constexpr int LREG = (int)(CAP / G);
     uint32_t lev_n[LREG], lev_d[LREG];
 #pragma unroll
     for (int r = 0; r < LREG; ++r) lev_n[r] = lev_d[r] = 0;
-    while (__builtin_amdgcn_ballot_w64(!fail && head < end)) {
-      uint32_t dsum = 0;
-      const bool act = !fail && head < end;
-      const uint32_t lo = act ? head : 0u, hi = act ? end : 0u;
-      for (uint32_t f = lo + gl; __builtin_amdgcn_ballot_w64(f < hi && !fail); f += G) {
-        uint32_t e0 = 0, e1 = 0;
-        if (f < hi && !fail) {
-          const uint64_t v = inst | ids[f];
-          e0 = R[v];
-          e1 = R[v + 1];
-          dsum += e1 - e0;
+    for (;;) {
+      const bool act = have && !fail && cnt > prev;
+      if (__builtin_amdgcn_ballot_w64(act) == 0) break;
+      const uint32_t found = cnt - prev, hi = pops;
+      if (act) prev = cnt;
+      uint32_t d = 0;
+      for (uint32_t f = lo + gl; __builtin_amdgcn_ballot_w64(act && f < hi && !fail); f += G) {
+        bool on = act && f < hi && !fail;
+        uint32_t e = on ? todo[f] : 0u;
+        uint2 cur;
+        cur.x = cur.y = kReachNone;
+        if (on) cur = edge[e];
+        while (__builtin_amdgcn_ballot_w64(on)) {
+          uint2 nxt = cur;
+          if (on) nxt = edge[++e];  // (readable past the last edge)
+          insert(on, cur);
+          d += on ? 1u : 0u;
+          on = on && (cur.x & kReachLast) == 0 && !fail;
+          cur = nxt;
         }
-        // a hub sends the whole row on (its edges alone outgrow the tier)
-        const uint64_t big = __builtin_amdgcn_ballot_w64(e1 - e0 > CAP) & gmask;
-        const uint64_t hub = __builtin_amdgcn_ballot_w64(e1 - e0 >= a.hub) & gmask;
-        if (big) fail = hub ? 2u : 1u;
-        expand(e0, e1);
         wave_lds_sync();
       }
+      if (act) lo = hi;
 #pragma unroll
-      for (int d = G / 2; d >= 1; d >>= 1) dsum += __shfl_xor(dsum, d, kWave);
+      for (int s = G / 2; s >= 1; s >>= 1) d += __shfl_xor(d, s, kWave);
       if (act && levels % G == gl) {
 #pragma unroll
         for (int r = 0; r < LREG; ++r)
           if ((uint32_t)r == levels / G) {
-            lev_n[r] = hi - lo;
-            lev_d[r] = dsum;
+            lev_n[r] = found;
+            lev_d[r] = d;
           }
       }
-      if (act) {
-        ++levels;
-        head = end;
-        end = cnt;
-      }
+      if (act) ++levels;
     }
     const bool good = have && !fail;
     if (good) {
@@ -409,7 +771,7 @@ __global__ __launch_bounds__(kBlock) void k_reach_group(ReachArgs a) {
       left = kReachChunk;
     }
     const bool fits = chunk + total <= a.pool_cap;
-    // sorted by counting the smaller ids: every lane ranks its ids against each id of the row
+    // sorted by counting the smaller columns: every lane ranks its own against each of the row
     {
       uint32_t v[LREG], rank[LREG];
 #pragma unroll
@@ -428,64 +790,97 @@ __global__ __launch_bounds__(kBlock) void k_reach_group(ReachArgs a) {
         if (fits && (uint32_t)r * G + gl < mine) a.pool[chunk + before + rank[r]] = v[r];
     }
     if (good && gl == 0) {
-      a.cnt[first] = cnt;
-      a.seg[first] = (uint32_t)(chunk + before);
+      a.cnt[row] = cnt;
+      a.seg[row] = (uint32_t)(chunk + before);
     }
     // rows sent on are buffered per wave (a same-address atomic costs 12 ns)
-#pragma unroll
-    for (int which = 0; which < 2; ++which) {
-      const bool out = have && gl == 0 && fail == (uint32_t)which + 1;
-      const uint64_t ob = __builtin_amdgcn_ballot_w64(out);
-      if (out) buf[which][fn[which] + (uint32_t)__popcll(ob & lt)] = row;
-      fn[which] += (uint32_t)__popcll(ob);
-      if (fn[which] > kWave - PER) flush(which);
-    }
+    const bool out = have && gl == 0 && fail;
+    const uint64_t ob = __builtin_amdgcn_ballot_w64(out);
+    if (out) buf[fn + (uint32_t)__popcll(ob & lt)] = row;
+    fn += (uint32_t)__popcll(ob);
+    if (fn > kWave - PER) flush();
     chunk += total;
     left -= total;
     wave_lds_sync();
   }
-  flush(0);
-  flush(1);
+  flush();
   __syncthreads();
   reach_levels_flush(s_lev, a);
 }
 
-// Edges of the vertices that the lanes of a wave hold, each id through `visit`: short lists by
-// their lane, long ones by the whole wave, one after the other.
-constexpr uint32_t kReachSerial = 8;
+// The edges of the rows that start at `start` in each lane of a wave (kReachNone: none), each record
+// through `visit(on, record)`: the first eight by their lane (four loads at a time), the rest of
+// a longer row by the whole wave.  Returns edges; their sum over the lanes is what was visited.
 template <typename Visit>
-__device__ __forceinline__ void wave_expand(const uint32_t* __restrict__ Edst, uint32_t e0, uint32_t deg, Visit visit) {
+__device__ __forceinline__ uint32_t wave_expand(const uint2* __restrict__ edge, uint32_t edges, uint32_t start,
+                                                Visit visit) {
   const uint32_t lane = (uint32_t)lane_id();
-  const uint32_t d = deg <= kReachSerial ? deg : 0u;
-  for (uint32_t j = 0; __builtin_amdgcn_ballot_w64(j < d); ++j) {
-    const uint32_t z = j < d ? Edst[e0 + j] : 0u;
-    visit(j < d, z);
+  bool on = start != kReachNone;
+  uint32_t e = on ? start : 0u, d = 0;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (__builtin_amdgcn_ballot_w64(on) == 0) return d;
+    uint2 x[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      x[k].x = x[k].y = kReachNone;
+      if (on) x[k] = edge[e + k];  // (readable past the last edge)
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (__builtin_amdgcn_ballot_w64(on) == 0) break;
+      visit(on, x[k]);
+      d += on ? 1u : 0u;
+      on = on && (x[k].x & kReachLast) == 0;
+    }
+    e += 4;
   }
-  for (uint64_t big = __builtin_amdgcn_ballot_w64(deg > kReachSerial); big; big &= big - 1) {
+  for (uint64_t big = __builtin_amdgcn_ballot_w64(on); big; big &= big - 1) {
     const int src = __ffsll((unsigned long long)big) - 1;
-    const uint32_t b0 = __shfl(e0, src, kWave), bd = __shfl(deg, src, kWave);
-    for (uint32_t j = 0; j < bd; j += kWave) {
-      const bool on = j + lane < bd;
-      const uint32_t z = on ? Edst[b0 + j + lane] : 0u;
-      visit(on, z);
+    uint32_t b = __shfl(e, src, kWave);
+    for (;;) {
+      uint2 x;
+      x.x = kReachLast;
+      x.y = kReachNone;
+      if (b + lane < edges) x = edge[b + lane];
+      const uint64_t ends = __builtin_amdgcn_ballot_w64((x.x & kReachLast) != 0);
+      // the row's edges: up to and including the first end
+      const bool in = ends == 0 || lane <= (uint32_t)(__ffsll((unsigned long long)ends) - 1);
+      visit(in, x);
+      d += in ? 1u : 0u;
+      if (ends) break;
+      b += kWave;
     }
   }
+  return d;
+}
+
+// The columns of a row's instance: [base, base + width).
+__device__ __forceinline__ void row_columns(const ReachArgs& a, uint32_t row, uint32_t& base, uint32_t& width) {
+  if (a.g.instances <= 1) {
+    base = 0;
+    width = a.rc->cols;
+    return;
+  }
+  const uint64_t first = a.g.rowkey[row] & ~id_mask(a.g.w);
+  const uint64_t end = first + (1ull << a.g.w);
+  base = rank_col(a.g.rank, first);
+  width = rank_col(a.g.rank, end < a.g.span ? end : a.g.span) - base;
 }
 
 // ---------------------------------------------------------------------------
-// Queue tier: one row per block of NW waves (one wave where the ids' bitmap is at most 8 KB).
-// The set is a bitmap of the id space in LDS; an id whose bit a lane sets first goes to the
-// next level's queue.  Thin, deep rows (a mesh: two hundred levels of a hundred vertices) pay
-// per level one index load, one edge load and one LDS round trip, and up to 32 of them run per
-// CU.  A level that outgrows the queue sends the row on.  The ids come out of the bitmap in
-// order.
+// Queue tier: one row per block of NW waves (one wave where the columns' bitmap is at most 8 KB).
+// The set is a bitmap of the instance's columns in LDS; a column whose bit a lane sets first is
+// found, and its row, if it has one, goes to the next level's queue.  Thin, deep rows pay per level
+// one edge load and one LDS round trip, and 16 to 32 of them run per CU.  A level that outgrows the
+// queue sends the row on.  The columns come out of the bitmap in order.
 // ---------------------------------------------------------------------------
-template <int NW, uint32_t WORDS, uint32_t QCAP, typename ID>
+template <int NW, uint32_t WORDS, uint32_t QCAP>
 __global__ __launch_bounds__(NW * kWave) void k_reach_queue(ReachArgs a) {
   constexpr uint32_t TH = NW * kWave;
   __shared__ uint32_t s_vis[WORDS];
-  __shared__ ID s_front[2][QCAP];
-  __shared__ uint32_t s_n[2];
+  __shared__ uint32_t s_front[2][QCAP];
+  __shared__ uint32_t s_n[2], s_f[2];  // queued, found
   __shared__ uint32_t s_row, s_d;
   __shared__ uint32_t s_wave[NW];
   __shared__ uint64_t s_pos;
@@ -493,108 +888,108 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_queue(ReachArgs a) {
   __shared__ uint32_t s_ln[kReachLdsLevels], s_ld[kReachLdsLevels];  // the row's levels so far
   const uint32_t tid = threadIdx.x;
   const uint32_t n = a.rc->queued[1];
-  if (block_stop(n == 0 || reach_halted(a.rc))) return;
+  if (block_stop(n == 0 || a.rc->slab != 0 || reach_halted(a.rc))) return;
   reach_levels_clear(s_lev);
-  const uint32_t words = a.words;
   const int wid = (int)(tid / kWave);
   const int lane = lane_id();
   const uint64_t lt = lanemask_lt();
-  const uint32_t* __restrict__ R = a.R;
-  const uint32_t* __restrict__ Edst = a.Edst;
-  const uint32_t idm = a.w >= 32 ? 0xFFFFFFFFu : (1u << a.w) - 1u;
+  const uint2* __restrict__ edge = a.g.edge;
+  const uint32_t edges = a.rc->edges;
   uint32_t share = 0;
-  for (uint32_t x = tid; x < words; x += TH) s_vis[x] = 0;
+  for (uint32_t x = tid; x < WORDS; x += TH) s_vis[x] = 0;
   __syncthreads();
   for (;;) {
     if (tid == 0) {
       const uint32_t at = reach_halted(a.rc) ? kReachNone : reach_claim(a.rc, 1, n, share);
       s_row = at == kReachNone ? kReachNone : a.queue[1][at];
-      s_n[0] = s_n[1] = 0;
+      s_n[0] = s_n[1] = s_f[0] = s_f[1] = 0;
     }
     __syncthreads();
     const uint32_t row = s_row;
     if (row == kReachNone) break;
-    const uint32_t inst = row & ~idm;
-    const uint32_t first = R[row], deg = R[(uint64_t)row + 1] - first;
-    // sets the bit of z; a lane that set it first appends z to queue `to`
+    uint32_t base, width;
+    row_columns(a, row, base, width);
+    const uint32_t words = (width + 31u) / 32u;
+    if (words > WORDS) {  // (the host sized WORDS for the widest instance)
+      if (tid == 0) atomicOr(&a.rc->stop, (uint32_t)kReachUnsupported);
+      break;
+    }
+    const uint32_t first = a.g.rstart[row], deg = a.g.rstart[row + 1] - first;
     int to = 0;
-    auto visit = [&](bool on, uint32_t z) {
+    auto visit = [&](bool on, uint2 rec) {
+      const uint32_t z = (rec.x & ~kReachLast) - base;
       bool fresh = false;
       if (on && !((s_vis[z >> 5] >> (z & 31u)) & 1u))
         fresh = !((atomicOr(&s_vis[z >> 5], 1u << (z & 31u)) >> (z & 31u)) & 1u);
       const uint64_t nb = __builtin_amdgcn_ballot_w64(fresh);
       if (nb) {  // (uniform in the wave)
+        const uint64_t pb = __builtin_amdgcn_ballot_w64(fresh && rec.y != kReachNone);
         uint32_t at = 0;
         if constexpr (NW == 1) {
           at = s_n[to];
           wave_lds_sync();
-          if (lane == 0) s_n[to] = at + (uint32_t)__popcll(nb);
+          if (lane == 0) {
+            s_n[to] = at + (uint32_t)__popcll(pb);
+            s_f[to] += (uint32_t)__popcll(nb);
+          }
           wave_lds_sync();
         } else {
-          if (lane == 0) at = atomicAdd(&s_n[to], (uint32_t)__popcll(nb));
+          if (lane == 0) {
+            at = atomicAdd(&s_n[to], (uint32_t)__popcll(pb));
+            atomicAdd(&s_f[to], (uint32_t)__popcll(nb));
+          }
           at = __shfl(at, 0, kWave);
         }
-        at += (uint32_t)__popcll(nb & lt);
-        if (fresh && at < QCAP) s_front[to][at] = (ID)z;
+        at += (uint32_t)__popcll(pb & lt);
+        if (fresh && rec.y != kReachNone && at < QCAP) s_front[to][at] = rec.y;
       }
     };
     for (uint32_t j = (uint32_t)wid * kWave; j < deg; j += TH) {
       const bool on = j + lane < deg;
-      visit(on, on ? Edst[first + j + lane] : 0u);
+      uint2 rec;
+      rec.x = rec.y = kReachNone;
+      if (on) rec = edge[first + j + lane];
+      visit(on, rec);
     }
     __syncthreads();
     uint32_t lv = 0, cnt = 0;
     bool fail = false;
     for (;;) {
       const int from = to;
-      const uint32_t fn = s_n[from];
-      cnt += fn;
-      if (fn == 0) break;
+      const uint32_t fn = s_n[from], found = s_f[from];
+      cnt += found;
+      if (found == 0) break;
       if (fn > QCAP) {
         fail = true;
         break;
       }
       to ^= 1;
       __syncthreads();
-      if (tid == 0) {
-        s_n[to] = 0;
-        s_d = 0;
-      }
+      if (tid == 0) s_n[to] = s_f[to] = s_d = 0;
       __syncthreads();
       uint32_t dsum = 0;
-      for (uint32_t f = (uint32_t)wid * kWave; f < fn; f += TH) {
-        uint32_t e0 = 0, d = 0;
-        if (f + lane < fn) {
-          const uint64_t v = inst | (uint32_t)s_front[from][f + lane];
-          e0 = R[v];
-          d = R[v + 1] - e0;
-        }
-        dsum += d;
-        wave_expand(Edst, e0, d, visit);
-      }
+      for (uint32_t f = (uint32_t)wid * kWave; f < fn; f += TH)
+        dsum += wave_expand(edge, edges, f + lane < fn ? s_front[from][f + lane] : kReachNone, visit);
       if (dsum) atomicAdd(&s_d, dsum);
       __syncthreads();
       // (the row's counts: kept until it is done, or straight to memory once it is deeper than
       // the table, from where on it can no longer be sent back)
       if (tid == 0) {
         if (lv < kReachLdsLevels) {
-          s_ln[lv] = fn;
+          s_ln[lv] = found;
           s_ld[lv] = s_d;
         } else {
-          reach_count(s_lev, a, lv, fn, s_d);
+          reach_count(s_lev, a, lv, found, s_d);
         }
       }
       ++lv;
     }
     __syncthreads();
-    if (fail && lv > kReachLdsLevels) {
-      // counted already: a row this deep whose level outgrows the queue goes to the general path
-      if (tid == 0) atomicOr(&a.rc->stop, (uint32_t)kReachUnsupported);
-    } else if (fail) {
+    if (fail) {
       if (tid == 0) {
-        const int tier = a.tier_after[2];
-        if (tier < 0) atomicOr(&a.rc->stop, (uint32_t)kReachUnsupported);
-        else a.queue[tier][atomicAdd(&a.rc->queued[tier], 1u)] = row;
+        // (counted already, or no tier for it: the general path)
+        if (lv > kReachLdsLevels || !a.bits_tier) atomicOr(&a.rc->stop, (uint32_t)kReachUnsupported);
+        else a.queue[2][atomicAdd(&a.rc->queued[2], 1u)] = row;
       }
       for (uint32_t x = tid; x < words; x += TH) s_vis[x] = 0;
     } else {
@@ -602,8 +997,8 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_queue(ReachArgs a) {
       if (tid == 0) {
         const uint64_t pos = reach_alloc(a, cnt);
         s_pos = pos + cnt > a.pool_cap ? ~0ull : pos;
-        a.cnt[first] = cnt;
-        a.seg[first] = (uint32_t)pos;
+        a.cnt[row] = cnt;
+        a.seg[row] = (uint32_t)pos;
       }
       __syncthreads();
       const uint64_t pos = s_pos;
@@ -619,7 +1014,7 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_queue(ReachArgs a) {
         uint32_t at = run + block_excl_scan<uint32_t, NW>((uint32_t)__popc(bits), s_wave, total);
         run += total;
         if (pos != ~0ull)
-          for (; bits; bits &= bits - 1) a.pool[pos + at++] = x * 32u + (uint32_t)__ffs(bits) - 1u;
+          for (; bits; bits &= bits - 1) a.pool[pos + at++] = base + x * 32u + (uint32_t)__ffs(bits) - 1u;
       }
     }
     __syncthreads();
@@ -631,19 +1026,18 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_queue(ReachArgs a) {
 // ---------------------------------------------------------------------------
 // Bits tier: one row per block of four waves, its set, its level and its next level three
 // bitmaps in LDS.  The waves scan the level's halfwords interleaved (a power-law graph's hubs sit
-// in few words), compact the ids they find into a list of their own and expand it with all
-// lanes; an id not in the set has its bit ORed into the next level, which therefore needs no
-// dedup at all (a repeated id costs an LDS read and an atomic without return).  Between levels
-// one pass joins the next level into the set.  Bound by LDS traffic and instruction issue per
-// candidate (a read of the set, an edge from L2); the bitmaps (12 KB at 15 bits) leave eight
-// blocks per CU.  The row goes out as its bitmap: 2^w / 8 bytes instead of 4 per tuple.
+// in few words), compact the columns they find into a list of their own and expand it with all
+// lanes; a column not in the set has its bit ORed into the next level, which therefore needs no
+// dedup at all (a repeat costs an LDS read and an atomic without return).  Between levels one
+// pass joins the next level into the set.  Bound by LDS traffic and instruction issue per
+// candidate.  The row goes out as its bitmap.
 // ---------------------------------------------------------------------------
 constexpr int kReachBitsWaves = 4;
 template <uint32_t WORDS, typename ID>
 __global__ __launch_bounds__(kReachBitsWaves * kWave) void k_reach_bits(ReachArgs a) {
   constexpr int NW = kReachBitsWaves;
   constexpr uint32_t TH = NW * kWave;
-  constexpr uint32_t LCAP = kWave * 16;  // ids of 64 halfwords
+  constexpr uint32_t LCAP = kWave * 16;  // columns of 64 halfwords
   __shared__ uint32_t s_vis[WORDS], s_cur[WORDS], s_nxt[WORDS];
   __shared__ ID s_list[NW][LCAP];
   __shared__ uint32_t s_n[NW];
@@ -651,21 +1045,20 @@ __global__ __launch_bounds__(kReachBitsWaves * kWave) void k_reach_bits(ReachArg
   __shared__ unsigned long long s_lev[kReachLdsLevels][2];
   const uint32_t tid = threadIdx.x;
   const uint32_t n = a.rc->queued[2];
-  if (block_stop(n == 0 || reach_halted(a.rc))) return;
+  if (block_stop(n == 0 || a.rc->slab != 0 || reach_halted(a.rc))) return;
   if (n > a.slots) {
     if (tid == 0 && blockIdx.x == 0) atomicOr(&a.rc->stop, (uint32_t)kReachSlotsFull);
     return;
   }
   reach_levels_clear(s_lev);
-  const uint32_t words = a.words, halves = words * 2;
   const int wid = (int)(tid / kWave);
   const int lane = lane_id();
-  const uint32_t* __restrict__ R = a.R;
-  const uint32_t* __restrict__ Edst = a.Edst;
-  const uint32_t idm = a.w >= 32 ? 0xFFFFFFFFu : (1u << a.w) - 1u;
+  const uint2* __restrict__ edge = a.g.edge;
+  const uint32_t edges = a.rc->edges;
   const uint16_t* const cur16 = (const uint16_t*)s_cur;
   ID* const list = s_list[wid];
   uint32_t share = 0;
+  for (uint32_t x = tid; x < WORDS; x += TH) s_vis[x] = s_cur[x] = s_nxt[x] = 0;
   __syncthreads();
   for (;;) {
     if (tid == 0) {
@@ -674,14 +1067,19 @@ __global__ __launch_bounds__(kReachBitsWaves * kWave) void k_reach_bits(ReachArg
       s_row = at == kReachNone ? kReachNone : a.queue[2][at];
       s_any[0] = 0;
     }
-    for (uint32_t x = tid; x < words; x += TH) s_vis[x] = s_cur[x] = s_nxt[x] = 0;
     __syncthreads();
     const uint32_t row = s_row, slot = s_at;
     if (row == kReachNone) break;
-    const uint32_t inst = row & ~idm;
-    const uint32_t first = R[row], deg = R[(uint64_t)row + 1] - first;
+    uint32_t base, width;
+    row_columns(a, row, base, width);
+    const uint32_t words = (width + 31u) / 32u, halves = words * 2;
+    if (words > WORDS) {
+      if (tid == 0) atomicOr(&a.rc->stop, (uint32_t)kReachUnsupported);
+      break;
+    }
+    const uint32_t first = a.g.rstart[row], deg = a.g.rstart[row + 1] - first;
     for (uint32_t j = tid; j < deg; j += TH) {
-      const uint32_t z = Edst[first + j];
+      const uint32_t z = (edge[first + j].x & ~kReachLast) - base;
       atomicOr(&s_nxt[z >> 5], 1u << (z & 31u));
     }
     __syncthreads();
@@ -721,14 +1119,9 @@ __global__ __launch_bounds__(kReachBitsWaves * kWave) void k_reach_bits(ReachArg
         wave_lds_sync();
         const uint32_t ln = s_n[wid];
         for (uint32_t f = 0; f < ln; f += kWave) {
-          uint32_t e0 = 0, d = 0;
-          if (f + lane < ln) {
-            const uint64_t v = inst | (uint32_t)list[f + lane];
-            e0 = R[v];
-            d = R[v + 1] - e0;
-          }
-          dsum += d;
-          wave_expand(Edst, e0, d, [&](bool on, uint32_t z) {
+          const uint32_t start = f + lane < ln ? a.g.cstart[base + (uint32_t)list[f + lane]] : kReachNone;
+          dsum += wave_expand(edge, edges, start, [&](bool on, uint2 rec) {
+            const uint32_t z = (rec.x & ~kReachLast) - base;
             if (on && !((s_vis[z >> 5] >> (z & 31u)) & 1u)) atomicOr(&s_nxt[z >> 5], 1u << (z & 31u));
           });
         }
@@ -737,11 +1130,15 @@ __global__ __launch_bounds__(kReachBitsWaves * kWave) void k_reach_bits(ReachArg
       if (dsum) reach_count(s_lev, a, lv, 0, dsum);
       __syncthreads();
     }
-    uint32_t* const out = a.bits + (uint64_t)slot * words;
-    for (uint32_t x = tid; x < words; x += TH) out[x] = s_vis[x];
+    uint32_t* const out = a.bits + (uint64_t)slot * a.words;
+    for (uint32_t x = tid; x < a.words; x += TH) {
+      const bool in = x < words;
+      out[x] = in ? s_vis[x] : 0u;
+      if (in) s_vis[x] = 0;
+    }
     if (tid == 0) {
-      a.cnt[first] = cnt | kReachBitRow;
-      a.seg[first] = slot;
+      a.cnt[row] = cnt | kReachBitRow;
+      a.seg[row] = slot;
     }
     __syncthreads();
   }
@@ -750,16 +1147,16 @@ __global__ __launch_bounds__(kReachBitsWaves * kWave) void k_reach_bits(ReachArg
 }
 
 // ---------------------------------------------------------------------------
-// Row offsets: off[i] = tuples of the rows before edge i (off[m] = all), from cnt in two
-// launches as every scan here.
+// Row offsets: off[r] = tuples of the rows before r (off[rows] = all), from cnt in two launches as
+// every scan here.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kReachScanTile = kBlock * 8;
 
-__global__ __launch_bounds__(kBlock) void k_reach_sum(const Ctrl* ctrl, ReachArgs a, uint64_t* __restrict__ part) {
+__global__ __launch_bounds__(kBlock) void k_reach_sum(ReachArgs a, uint64_t* __restrict__ part) {
   __shared__ uint64_t s_wave[kWavesPerBlock];
   if (block_stop(reach_halted(a.rc))) return;
   uint64_t lo, hi;
-  block_range(ctrl->m_unique, kReachScanTile, lo, hi);
+  block_range(a.rc->rows, kReachScanTile, lo, hi);
   uint64_t sum = 0;
   for (uint64_t i = lo + threadIdx.x; i < hi; i += kBlock) sum += a.cnt[i] & ~kReachBitRow;
   uint64_t total;
@@ -767,18 +1164,21 @@ __global__ __launch_bounds__(kBlock) void k_reach_sum(const Ctrl* ctrl, ReachArg
   if (threadIdx.x == 0) part[blockIdx.x] = total;
 }
 
+// (one block needs no totals: part nullptr)
 template <int SCAN_MAX>
-__global__ __launch_bounds__(kBlock) void k_reach_offsets(const Ctrl* ctrl, ReachArgs a,
-                                                          const uint64_t* __restrict__ part,
+__global__ __launch_bounds__(kBlock) void k_reach_offsets(ReachArgs a, const uint64_t* __restrict__ part,
                                                           uint32_t* __restrict__ off) {
   __shared__ uint64_t s_pre[SCAN_MAX];
   __shared__ uint64_t s_wave[kWavesPerBlock];
   if (block_stop(reach_halted(a.rc))) return;
-  const uint64_t n = ctrl->m_unique;
-  const uint64_t all = block_prefix<SCAN_MAX / kBlock>(part, (int)gridDim.x, s_pre, s_wave);
+  const uint32_t n = a.rc->rows;
+  uint64_t run = 0;
+  if (part) {
+    (void)block_prefix<SCAN_MAX / kBlock>(part, (int)gridDim.x, s_pre, s_wave);
+    run = s_pre[blockIdx.x];
+  }
   uint64_t lo, hi;
   block_range(n, kReachScanTile, lo, hi);
-  uint64_t run = s_pre[blockIdx.x];
   for (uint64_t base = lo; base < hi; base += kReachScanTile) {
     uint32_t c[8];
     uint64_t sum = 0;
@@ -798,101 +1198,159 @@ __global__ __launch_bounds__(kBlock) void k_reach_offsets(const Ctrl* ctrl, Reac
     }
     run += total;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    off[n] = (uint32_t)all;
-    a.rc->edges = n;
-  }
+  if (hi == n && lo < hi && threadIdx.x == 0) off[n] = (uint32_t)run;
 }
 
 // ---------------------------------------------------------------------------
-// Reading the result.  Rows with an id list: a tile of edges at a time, one output per thread and
-// step (its row found by bisection over the tile's list rows in LDS); the tile's ids are
-// mostly one stretch of the pool and its outputs one stretch of the result.  Rows with a bitmap:
-// a block per row expands 256 words at a time through LDS, so that the writes coalesce.
-// put(position, row, id) stores a tuple.
+// Reading the result.  put(position, row key, id) stores a tuple.
 // ---------------------------------------------------------------------------
-
-template <typename K, typename Put>
-__device__ __forceinline__ void reach_unpack_lists(const ReachResult& r, const K* __restrict__ E, uint32_t bid,
-                                                   uint32_t nblocks, Put put) {
-  __shared__ uint32_t s_start[kBlock], s_seg[kBlock], s_off[kBlock], s_row[kBlock];
-  __shared__ uint32_t s_wave[kWavesPerBlock];
-  const uint32_t tid = threadIdx.x;
-  const uint64_t ntiles = (r.m + kBlock - 1) / kBlock;
-  for (uint64_t tile = bid; tile < ntiles; tile += nblocks) {
-    const uint64_t i = tile * kBlock + tid;
-    uint32_t c = 0;
-    if (i < r.m) {
-      c = r.cnt[i];
-      if (c & kReachBitRow) c = 0;
-      s_seg[tid] = r.seg[i];
-      s_off[tid] = r.off[i];
-      s_row[tid] = head_row<K>(E[i], r.w);
-    }
-    uint32_t total;
-    s_start[tid] = block_excl_scan<uint32_t>(c, s_wave, total);
-    __syncthreads();
-    for (uint32_t t = tid; t < total; t += kBlock) {
-      // the last entry starting at or before t (rows without a list share the next start)
-      uint32_t lo = 0;
-#pragma unroll
-      for (uint32_t step = kBlock / 2; step >= 1; step >>= 1) lo = s_start[lo + step] <= t ? lo + step : lo;
-      const uint32_t q = t - s_start[lo];
-      put((uint64_t)s_off[lo] + q, s_row[lo], r.pool[(uint64_t)s_seg[lo] + q]);
-    }
-    __syncthreads();
-  }
-}
+// Rows with lists: tiles of outputs, so that rows of any length spread evenly; a tile's rows (at
+// most one per output: every row has a tuple) are staged in LDS and each output finds its own by
+// bisection.  Blocks take consecutive tiles, so only the first is searched over all rows.
+constexpr uint32_t kReachOutTile = 2048;
 
 template <typename Put>
+__device__ __forceinline__ void reach_unpack_lists(const ReachResult& r, uint32_t bid, uint32_t nblocks, Put put) {
+  constexpr uint32_t T = kReachOutTile;
+  __shared__ uint32_t s_off[T], s_seg[T], s_row[T];
+  __shared__ uint32_t s_r[2];
+  const uint32_t tid = threadIdx.x;
+  const uint32_t rows = r.rows;
+  const uint64_t F = r.off[rows];
+  const uint64_t ntiles = (F + T - 1) / T, per = (ntiles + nblocks - 1) / nblocks;
+  const uint64_t t0 = (uint64_t)bid * per, t1 = min(t0 + per, ntiles);
+  const int wid = (int)(tid / kWave);
+  uint64_t from = 0;  // a row at or before the next tile's first output
+  for (uint64_t tile = t0; tile < t1; ++tile) {
+    const uint64_t p0 = tile * T, p1 = min(p0 + T, F);
+    if (wid < 2) {
+      const uint64_t p = wid == 0 ? p0 : p1 - 1;
+      const uint64_t end = tile == t0 ? rows : min<uint64_t>(from + T + 1, rows);
+      const uint64_t v = wave_partition(from, end, [&](uint64_t i) { return r.off[i] <= p; }) - 1;
+      if (lane_id() == 0) s_r[wid] = (uint32_t)v;
+    }
+    __syncthreads();
+    const uint32_t r0 = s_r[0], span = s_r[1] - r0 + 1;  // span <= T
+    for (uint32_t x = tid; x < span; x += kBlock) {
+      s_off[x] = r.off[r0 + x];
+      s_seg[x] = r.seg[r0 + x];
+      s_row[x] = (r.cnt[r0 + x] & kReachBitRow) ? kReachNone : r0 + x;  // (the bitmaps' blocks write those)
+    }
+    __syncthreads();
+    for (uint32_t t = tid; t < (uint32_t)(p1 - p0); t += kBlock) {
+      const uint32_t p = (uint32_t)(p0 + t);
+      uint32_t lo = 0;
+      for (uint32_t len = span; len > 1;) {
+        const uint32_t half = len >> 1;
+        lo = s_off[lo + half] <= p ? lo + half : lo;
+        len -= half;
+      }
+      const uint32_t row = s_row[lo];
+      if (row != kReachNone) put(p, r.rowkey[row], r.colkey[r.pool[(uint64_t)s_seg[lo] + (p - s_off[lo])]]);
+    }
+    from = s_r[1];
+    __syncthreads();
+  }
+}
+
+// Rows with bitmaps: a block per row expands 256 words at a time through LDS, so that the writes
+// coalesce.
+template <typename Put>
 __device__ __forceinline__ void reach_unpack_bits(const ReachResult& r, uint32_t bid, uint32_t nblocks, Put put) {
-  __shared__ uint16_t s_id[kBlock * 32];  // ids relative to the 256 words' first
+  __shared__ uint16_t s_id[kBlock * 32];  // columns relative to the 256 words' first
   __shared__ uint32_t s_wave2[kWavesPerBlock];
   const uint32_t tid = threadIdx.x;
   for (uint64_t k = bid; k < r.n_bits; k += nblocks) {
-    const uint32_t row = r.bit_rows[k];
+    const uint32_t row = r.bit_rows[k], key = r.rowkey[row];
+    const uint32_t base = rank_col(r.rank, key & ~id_mask(r.w));
     const uint32_t* __restrict__ b = r.bits + k * r.words;
-    uint64_t out = r.off[r.R[row]];
+    uint64_t out = r.off[row];
     for (uint32_t x0 = 0; x0 < r.words; x0 += kBlock) {
       uint32_t v = x0 + tid < r.words ? b[x0 + tid] : 0u;
       uint32_t total;
       uint32_t at = block_excl_scan<uint32_t>((uint32_t)__popc(v), s_wave2, total);
       for (; v; v &= v - 1) s_id[at++] = (uint16_t)(tid * 32u + (uint32_t)__ffs(v) - 1u);
       __syncthreads();
-      for (uint32_t t = tid; t < total; t += kBlock) put(out + t, row, x0 * 32u + s_id[t]);
+      for (uint32_t t = tid; t < total; t += kBlock) put(out + t, key, r.colkey[base + x0 * 32u + s_id[t]]);
       out += total;
       __syncthreads();
     }
   }
 }
 
+// Slabs: a wave per row takes 64 slabs at a time (a lane each), lists their columns in LDS and writes
+// them out in order.  The eight waves of a block read neighbouring rows, that is the same lines of
+// every slab.
+constexpr int kSlabOutWaves = 8;
+template <typename Put>
+__device__ __forceinline__ void reach_unpack_slabs(const ReachResult& r, Put put) {
+  __shared__ uint16_t s_col[kSlabOutWaves][kWave * 32];
+  const int wid = (int)(threadIdx.x / kWave);
+  const uint32_t lane = (uint32_t)lane_id();
+  uint16_t* const mine = s_col[wid];
+  const uint32_t B = r.slab, slabs = (r.cols + B - 1) / B;
+  for (uint64_t row = (uint64_t)blockIdx.x * kSlabOutWaves + wid; row < r.rows;
+       row += (uint64_t)gridDim.x * kSlabOutWaves) {
+    const uint32_t key = r.rowkey[row];
+    uint64_t out = r.off[row];
+    for (uint32_t s0 = 0; s0 < slabs; s0 += kWave) {
+      uint32_t v = 0;
+      if (s0 + lane < slabs) {
+        const uint64_t at = (uint64_t)(s0 + lane) * r.rows + row;
+        v = B == 32 ? r.bits[at] : (uint32_t)((const uint16_t*)r.bits)[at];
+      }
+      const uint32_t c = (uint32_t)__popc(v);
+      const uint32_t incl = wave_incl_scan<uint32_t>(c);
+      const uint32_t total = __shfl(incl, kWave - 1, kWave);
+      for (uint32_t at = incl - c; v; v &= v - 1) mine[at++] = (uint16_t)(lane * B + (uint32_t)__ffs(v) - 1u);
+      wave_lds_sync();
+      for (uint32_t t = lane; t < total; t += kWave) put(out + t, key, r.colkey[s0 * B + mine[t]]);
+      out += total;
+      wave_lds_sync();
+    }
+  }
+}
+
+struct PutPairs {
+  uint32_t* src;
+  uint32_t* dst;
+  uint32_t mask;
+  __device__ __forceinline__ void operator()(uint64_t p, uint32_t row, uint32_t col) const {
+    src[p] = row & mask;
+    dst[p] = col & mask;
+  }
+};
+template <typename K>
+struct PutKeys {
+  K* keys;
+  int w;
+  uint32_t mask;
+  __device__ __forceinline__ void operator()(uint64_t p, uint32_t row, uint32_t col) const {
+    keys[p] = ((K)row << w) | (K)(col & mask);
+  }
+};
+
 // Blocks [0, list_blocks) take the rows with lists, the others the bitmaps.
-template <typename K>
-__global__ __launch_bounds__(kBlock) void k_reach_unpack(ReachResult r, const K* __restrict__ E, uint32_t list_blocks,
-                                                         uint32_t* __restrict__ src, uint32_t* __restrict__ dst) {
-  const uint32_t idm = r.w >= 32 ? 0xFFFFFFFFu : (1u << r.w) - 1u;
-  const auto put = [=](uint64_t p, uint32_t row, uint32_t id) {
-    src[p] = row & idm;
-    dst[p] = id;
-  };
-  if (blockIdx.x < list_blocks) reach_unpack_lists<K>(r, E, blockIdx.x, list_blocks, put);
+template <typename Put>
+__global__ __launch_bounds__(kBlock) void k_reach_unpack(ReachResult r, uint32_t list_blocks, Put put) {
+  if (blockIdx.x < list_blocks) reach_unpack_lists(r, blockIdx.x, list_blocks, put);
   else reach_unpack_bits(r, blockIdx.x - list_blocks, gridDim.x - list_blocks, put);
 }
-
-// The same into packed keys (a result that leaves its engine).
-template <typename K>
-__global__ __launch_bounds__(kBlock) void k_reach_keys(ReachResult r, const K* __restrict__ E, uint32_t list_blocks,
-                                                       K* __restrict__ keys) {
-  const int w = r.w;
-  const auto put = [=](uint64_t p, uint32_t row, uint32_t id) { keys[p] = ((K)row << w) | (K)id; };
-  if (blockIdx.x < list_blocks) reach_unpack_lists<K>(r, E, blockIdx.x, list_blocks, put);
-  else reach_unpack_bits(r, blockIdx.x - list_blocks, gridDim.x - list_blocks, put);
+template <typename Put>
+__global__ __launch_bounds__(kSlabOutWaves * kWave) void k_slab_unpack(ReachResult r, Put put) {
+  reach_unpack_slabs(r, put);
 }
 
-// First tuple of every instance: that of the first edge whose row is instance v's or later.
+// First tuple of every instance: that of its first row.
 __global__ __launch_bounds__(kBlock) void k_reach_instances(ReachResult r, uint32_t num, uint64_t* __restrict__ out) {
-  for (uint64_t v = (uint64_t)blockIdx.x * kBlock + threadIdx.x; v <= num; v += (uint64_t)gridDim.x * kBlock)
-    out[v] = v == num ? r.off[r.m] : r.off[r.R[v << r.w]];
+  for (uint64_t v = (uint64_t)blockIdx.x * kBlock + threadIdx.x; v <= num; v += (uint64_t)gridDim.x * kBlock) {
+    uint64_t row = r.rows;
+    if (v < num) {
+      const RankWord q = r.rank[(v << r.w) >> 5];
+      row = q.rowpre + bits_below(q.rowbits, (uint32_t)(v << r.w));
+    }
+    out[v] = r.off[row];
+  }
 }
 
 }  // namespace wg

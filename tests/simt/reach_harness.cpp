@@ -1,18 +1,22 @@
-// The row-at-a-time closure (the kernels of wg_reach_kernels.h, current text) on the CPU SIMT shim: every
-// tier, the row offsets and the unpacking, over one graph.
-//   reach_harness <in> <out> <grid> <workers> <pool entries> <bitmap slots> <start tier>
-// in:  u64 header (w, key bytes, instances, |E|, hub degree, level capacity), then the sorted
-//      distinct keys of E (u64).
-// out: u64 stop bits, pool entries used, rows queued for the three tiers; unless the stop bits
-//      are set: levels L, then (tuples, degrees) of each, the tuples' keys (u64, from the unpacked
-//      pairs), the keys as k_reach_keys writes them (u64) and the instances' offsets.
-// start tier 0: the thread tier first (its rows go on to the group tier); 1, 2: the thread tier
-//      sends every row it cannot hold to the queue or the bits tier directly.
+// The row-at-a-time closure (the kernels of wg_reach_kernels.h, current text) on the CPU SIMT shim:
+// the renumbering, every tier or the slabs, the row offsets and the unpacking, over one graph.
+//   reach_harness <in> <out> <grid> <workers> <pool entries> <bits words> <slab mode>
+// in:  u64 header (w, key bytes, instances, |E|, level capacity, span), then the sorted distinct
+//      keys of E (u64).
+// out: u64 stop bits, pool entries used, rows queued for the three tiers, columns per slab; unless
+//      the stop bits are set: levels L, then (tuples, degrees) of each, the tuples (src << 32 |
+//      dst, from the unpacked pairs), the keys as the key form writes them and the instances'
+//      offsets.
+// Odd grids take the ranking and the offsets through one block and the queue tier with one wave;
+// even ones through several blocks and four waves.
 #include <hip/hip_runtime.h>
+struct uint2 { uint32_t x, y; };
+struct uint4 { uint32_t x, y, z, w; };
 template <typename T> inline T atomicCAS(T* p, T c, T v) {
   __atomic_compare_exchange_n(p, &c, v, false, __ATOMIC_SEQ_CST, __ATOMIC_SEQ_CST);
   return c;
 }
+#define WG_OPAQUE(x) (void)0
 #define __builtin_amdgcn_wave_barrier simt::wave_sync
 #define __builtin_amdgcn_fence(...) (void)0
 #define __hip_atomic_load(p, ...) __atomic_load_n(p, __ATOMIC_SEQ_CST)
@@ -30,89 +34,127 @@ static void put(std::ofstream& f, const T& v) {
 
 template <typename K>
 int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigned workers, uint64_t pool_cap,
-        uint64_t slots, int start, const char* out_path) {
+        uint64_t bits_words, int slab_mode, const char* out_path) {
   const int w = (int)h[0];
-  const uint64_t m = E64.size(), num = h[2];
-  const K mask = (K)((K(1) << w) - 1);
+  const uint64_t m = E64.size(), num = h[2], span = h[5];
   std::vector<K> E(E64.begin(), E64.end());
-  const uint64_t dense = num << w;
-  std::vector<uint32_t> R(dense + 1), Edst(std::max<uint64_t>(m, 1));
-  for (uint64_t v = 0, i = 0; v <= dense; ++v) {
-    while (i < m && (uint64_t)(E[i] >> w) < v) ++i;
-    R[v] = (uint32_t)i;
-  }
-  for (uint64_t i = 0; i < m; ++i) Edst[i] = (uint32_t)(E[i] & mask);
   std::unique_ptr<Ctrl> ctrl(new Ctrl);
   std::memset(ctrl.get(), 0, sizeof(Ctrl));
   ctrl->m_unique = m;
   std::unique_ptr<ReachCtl> rc(new ReachCtl);
   std::memset(rc.get(), 0, sizeof(ReachCtl));
-  std::vector<ReachLevel> lev(h[5], ReachLevel{0, 0});
+  std::vector<ReachLevel> lev(h[4], ReachLevel{{0, 0}, {0, 0}});
   std::vector<uint32_t> cnt(m, 0xDEADu), seg(m, 0xBEEFu), off(m + 1), pool(std::max<uint64_t>(pool_cap, 1), 0x5A5A5A5Au);
   std::vector<uint32_t> queue[3];
   for (auto& q : queue) q.assign(m, 0x77777777u);
-  ReachArgs a;
-  a.R = R.data();
-  a.Edst = Edst.data();
-  a.w = w;
-  a.tier_after[0] = start;
-  a.tier_after[1] = 1;
-  a.tier_after[2] = w <= 18 ? 2 : -1;
-  a.hub = (uint32_t)h[4];
-  a.hub_tier = w <= 18 ? 2 : 1;
+  std::vector<uint32_t> rowkey(m), rstart(m + 1), colkey(m), cstart(m), se(m + kSlabThreads), sc(m + kSlabThreads);
+  std::vector<uint2> edge(m + kReachEdgePad);
+  std::vector<RankWord> rank(span / 32 + 1);
+  std::unique_ptr<uint8_t, void (*)(void*)> flags((uint8_t*)std::aligned_alloc(16, 2 * span), std::free);
+  std::memset(flags.get(), 0, 2 * span);
+  ReachArgs a{};
+  a.g.rowkey = rowkey.data();
+  a.g.rstart = rstart.data();
+  a.g.colkey = colkey.data();
+  a.g.cstart = cstart.data();
+  a.g.edge = edge.data();
+  a.g.slab_edge = se.data();
+  a.g.slab_col = sc.data();
+  a.g.rank = rank.data();
+  a.g.flags = flags.get();
+  a.g.span = span;
+  a.g.instances = (uint32_t)num;
+  a.g.w = w;
+  a.bits_tier = 1;
+  a.slab_mode = slab_mode;
+  a.min_rows = 1;
   a.cnt = cnt.data();
   a.seg = seg.data();
   for (int t = 0; t < 3; ++t) a.queue[t] = queue[t].data();
   a.pool = pool.data();
   a.pool_cap = pool_cap;
-  a.words = w > 5 ? 1u << (w - 5) : 1u;
-  std::vector<uint32_t> bits(std::max<uint64_t>(slots * a.words, 1), 0x33333333u);
+  a.words = 32;
+  std::vector<uint32_t> bits(std::max<uint64_t>(bits_words, 1), 0x33333333u);
   a.bits = bits.data();
-  a.slots = slots;
+  a.bits_words = bits_words;
+  a.slots = bits_words / a.words;
   a.rc = rc.get();
   a.lev = lev.data();
-  a.lev_cap = (uint32_t)h[5];
+  a.lev_cap = (uint32_t)h[4];
   std::vector<uint64_t> part(G);
-  if (w > 10) return 3;
-  simt::launch(G, kBlock, [&] { k_reach_thread<K>(ctrl.get(), E.data(), a); }, workers);
-  simt::launch(G, kBlock, [&] { k_reach_group(a); }, workers);
-  // (a queue of 96 ids, so that wide levels outgrow it; one wave, then the wide form)
-  if (G % 2) simt::launch(G, kWave, [&] { k_reach_queue<1, 32, 96, uint16_t>(a); }, workers);
-  else simt::launch(G, 4 * kWave, [&] { k_reach_queue<4, 32, 96, uint32_t>(a); }, workers);
-  simt::launch(G, kReachBitsWaves * kWave, [&] { k_reach_bits<32, uint16_t>(a); }, workers);
-  simt::launch(G, kBlock, [&] { k_reach_sum(ctrl.get(), a, part.data()); }, workers);
-  simt::launch(G, kBlock, [&] { k_reach_offsets<kScanBlocksMax>(ctrl.get(), a, part.data(), off.data()); }, workers);
+  const bool one = G % 2;
+  simt::launch(G, kBlock, [&] { k_reach_mark<K>(ctrl.get(), E.data(), a.g); }, workers);
+  if (one) {
+    simt::launch(1, kBlock, [&] { k_reach_rank(ctrl.get(), a.g, nullptr, a.rc); }, workers);
+  } else {
+    simt::launch(G, kBlock, [&] { k_reach_rank_sum(a.g, part.data()); }, workers);
+    simt::launch(G, kBlock, [&] { k_reach_rank(ctrl.get(), a.g, part.data(), a.rc); }, workers);
+  }
+  simt::launch(G, kBlock, [&] { k_reach_rows<K>(ctrl.get(), E.data(), a.g, a.rc); }, workers);
+  simt::launch(G, kBlock, [&] { k_reach_edges<K>(ctrl.get(), E.data(), a.g, a.rc, a.slab_mode); }, workers);
+  if (slab_mode != 1) simt::launch(G, kBlock, [&] { k_reach_thread(a); }, workers);
+  if (slab_mode != 0) {
+    simt::launch(G, kSlabThreads, [&] { k_slab<uint32_t>(a); }, workers);
+    simt::launch(G, kSlabThreads, [&] { k_slab<uint16_t>(a); }, workers);
+    simt::launch(G, kBlock, [&] { k_slab_count(a); }, workers);
+  }
+  if (slab_mode != 1) {
+    simt::launch(G, kBlock, [&] { k_reach_group(a); }, workers);
+    // (a queue of 96 rows, so that wide levels outgrow it)
+    if (one) simt::launch(G, kWave, [&] { k_reach_queue<1, 32, 96>(a); }, workers);
+    else simt::launch(G, 4 * kWave, [&] { k_reach_queue<4, 32, 96>(a); }, workers);
+    simt::launch(G, kReachBitsWaves * kWave, [&] { k_reach_bits<32, uint16_t>(a); }, workers);
+  }
+  if (one) {
+    simt::launch(1, kBlock, [&] { k_reach_offsets<kScanBlocksMax>(a, nullptr, off.data()); }, workers);
+  } else {
+    simt::launch(G, kBlock, [&] { k_reach_sum(a, part.data()); }, workers);
+    simt::launch(G, kBlock, [&] { k_reach_offsets<kScanBlocksMax>(a, part.data(), off.data()); }, workers);
+  }
   std::ofstream f(out_path, std::ios::binary);
   put(f, rc->stop);
   put(f, rc->cursor);
   for (int t = 0; t < 3; ++t) put(f, rc->queued[t]);
+  put(f, rc->slab);
   if (rc->stop) return 0;
+  const int form = rc->slab ? 1 : 0;
   uint64_t L = 0;
-  while (L < lev.size() && lev[L].n) ++L;
+  while (L < lev.size() && lev[L].n[form]) ++L;
   put(f, L);
   for (uint64_t i = 0; i < L; ++i) {
-    put(f, lev[i].n);
-    put(f, lev[i].d);
+    put(f, lev[i].n[form]);
+    put(f, lev[i].d[form]);
   }
-  const uint64_t F = off[m];
+  const uint64_t F = off[rc->rows];
   put(f, F);
-  ReachResult r;
+  ReachResult r{};
   r.cnt = cnt.data();
   r.seg = seg.data();
   r.off = off.data();
-  r.R = R.data();
+  r.rowkey = rowkey.data();
+  r.colkey = colkey.data();
   r.pool = pool.data();
   r.bits = bits.data();
   r.bit_rows = queue[2].data();
-  r.n_bits = rc->queued[2];
+  r.rank = rank.data();
+  r.n_bits = rc->slab ? 0 : rc->queued[2];
   r.words = a.words;
-  r.m = m;
+  r.rows = rc->rows;
+  r.cols = rc->cols;
+  r.slab = rc->slab;
   r.w = w;
   std::vector<uint32_t> src(F, 0x11111111u), dst(F, 0x22222222u);
   std::vector<K> keys(F, (K)0x44444444u);
+  const PutPairs pp{src.data(), dst.data(), id_mask(w)};
+  const PutKeys<K> pk{keys.data(), w, id_mask(w)};
   const uint32_t lb = 3, bb = r.n_bits ? 2 : 0;
-  simt::launch(lb + bb, kBlock, [&] { k_reach_unpack<K>(r, E.data(), lb, src.data(), dst.data()); }, workers);
-  simt::launch(lb + bb, kBlock, [&] { k_reach_keys<K>(r, E.data(), lb, keys.data()); }, workers);
+  if (r.slab) {
+    simt::launch(2, kSlabOutWaves * kWave, [&] { k_slab_unpack(r, pp); }, workers);
+    simt::launch(2, kSlabOutWaves * kWave, [&] { k_slab_unpack(r, pk); }, workers);
+  } else {
+    simt::launch(lb + bb, kBlock, [&] { k_reach_unpack(r, lb, pp); }, workers);
+    simt::launch(lb + bb, kBlock, [&] { k_reach_unpack(r, lb, pk); }, workers);
+  }
   std::vector<uint64_t> inst(num + 1);
   simt::launch(2, kBlock, [&] { k_reach_instances(r, (uint32_t)num, inst.data()); }, workers);
   for (uint64_t i = 0; i < F; ++i) put(f, ((uint64_t)src[i] << 32) | dst[i]);
@@ -129,8 +171,8 @@ int main(int argc, char** argv) {
   f.read((char*)E.data(), 8 * E.size());
   const uint32_t G = (uint32_t)atoi(argv[3]);
   const unsigned workers = (unsigned)atoi(argv[4]);
-  const uint64_t pool = strtoull(argv[5], nullptr, 10), slots = strtoull(argv[6], nullptr, 10);
-  const int start = atoi(argv[7]);
-  if (h[1] == 4) return run<uint32_t>(E, h, G, workers, pool, slots, start, argv[2]);
-  return run<uint64_t>(E, h, G, workers, pool, slots, start, argv[2]);
+  const uint64_t pool = strtoull(argv[5], nullptr, 10), bits = strtoull(argv[6], nullptr, 10);
+  const int mode = atoi(argv[7]);
+  if (h[1] == 4) return run<uint32_t>(E, h, G, workers, pool, bits, mode, argv[2]);
+  return run<uint64_t>(E, h, G, workers, pool, bits, mode, argv[2]);
 }

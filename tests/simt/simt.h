@@ -170,12 +170,12 @@ inline void run_block(uint32_t b, uint32_t block) {
       if (f.done) continue;
       cur = (int)t;
       threadIdx = {t, 0, 0};
-      const uint64_t g0 = bar_gen;
+      const uint64_t g0 = bar_gen, w0 = wbar_gen[t / 64];
       void* fake = nullptr;
       __sanitizer_start_switch_fiber(&fake, f.stack, kStack);
       simt_switch(&sched_sp, f.sp);
       __sanitizer_finish_switch_fiber(fake, &sched_bottom, &sched_size);
-      if (f.done || bar_gen != g0) ++progressed;
+      if (f.done || bar_gen != g0 || wbar_gen[t / 64] != w0) ++progressed;
       if (!f.done) ++alive;
     }
     if (alive && !progressed) {
