@@ -10,6 +10,7 @@
 
 #include <algorithm>
 #include <chrono>
+#include <cmath>
 #include <functional>
 #include <cstdio>
 #include <cstring>
@@ -20,6 +21,7 @@
 #include "wg_internal.h"
 #include "wg_launch.h"
 #include "wg_reach.h"
+#include "wg_sg.h"
 
 using namespace wg;
 
@@ -62,6 +64,12 @@ constexpr uint64_t kSlabAlways = 3u << 20;
 constexpr uint32_t kReachLevels = 4096;  // levels allotted at first (grown eightfold when passed)
 constexpr uint32_t kReachLevelsMax = 1u << 21;
 constexpr uint32_t kReachReadLevels = 126;  // levels read back with the control block
+// SG on the renumbered graph (wg_sg.h): rounds at most, and enqueued per host check
+constexpr uint32_t kSgLevels = 4096;
+constexpr uint32_t kSgMatrixRounds = 4;
+constexpr uint32_t kSgPairRounds = 4;
+constexpr size_t kReachHostBytes = std::max(sizeof(ReachCtl) + kReachReadLevels * sizeof(ReachLevel),
+                                            sizeof(ReachCtl) + sizeof(SgCtl) + kSgLevels * sizeof(SgLevel));
 // fixed arrays of an engine: control block, join and compaction block totals, radix counts
 // and totals (the triangle hits depend on the grid)
 constexpr size_t kFixedBytes[6] = {sizeof(Ctrl), sizeof(uint64_t) * kScanBlocksMax,
@@ -105,7 +113,7 @@ struct wg_engine {
   // the row-at-a-time closure: control block, levels and flags; the renumbered graph; the pool of
   // columns; bitmaps
   DevBuf rctl, rgraph, rpool, rbits;
-  uint8_t* h_reach = nullptr;  // pinned: ReachCtl and the first kReachReadLevels levels
+  uint8_t* h_reach = nullptr;  // pinned: the control blocks and the first levels, read back
   uint32_t reach_levels = kReachLevels;
   bool res_is_reach = false;   // the latest result is in that form
   ReachResult res_reach{};
@@ -730,6 +738,54 @@ uint64_t staged_growth(const wg_engine* e, uint64_t F, uint64_t C, uint64_t* can
          (std::max(*cand_cap, e->row_cap) - e->row_cap) * 12;
 }
 
+// Buffers of the renumbered graph of at most m edges (16-byte records first); returns `more` bytes
+// beside them.
+void* graph_buffers(wg_engine* e, ReachGraph& g, uint64_t m, int w, bool slabs, uint64_t more) {
+  g.span = (e->key_space + 31) & ~31ull;
+  g.instances = e->num_inst;
+  g.w = w;
+  const uint64_t slab_edges = slabs ? m + kSlabThreads : 0;
+  const uint64_t sizes[] = {(g.span / 32 + 1) * sizeof(RankWord), (m + kReachEdgePad) * sizeof(uint2), m * 4,
+                            (m + 1) * 4, m * 4, m * 4, slab_edges * 4, slab_edges * 4, more};
+  uint64_t at[9], total = 0;
+  for (int k = 0; k < 9; ++k) {
+    at[k] = total;
+    total += (sizes[k] + 15) & ~15ull;
+  }
+  ensure(e, e->rgraph, total);
+  uint8_t* const base = (uint8_t*)e->rgraph.p;
+  g.rank = (RankWord*)(base + at[0]);
+  g.edge = (uint2*)(base + at[1]);
+  g.rowkey = (uint32_t*)(base + at[2]);
+  g.rstart = (uint32_t*)(base + at[3]);
+  g.colkey = (uint32_t*)(base + at[4]);
+  g.cstart = (uint32_t*)(base + at[5]);
+  g.slab_edge = (uint32_t*)(base + at[6]);
+  g.slab_col = (uint32_t*)(base + at[7]);
+  return base + at[8];
+}
+
+// The growth for a fixpoint of F tuples and at most C candidates (or keys) per iteration: false when
+// a budget does not allow it.  The candidate buffers' contents are lost.
+bool grow_staged(wg_engine* e, uint64_t F, uint64_t C, uint64_t edges, bool* grown) {
+  uint64_t cand_cap, full_cap;
+  const uint64_t more = staged_growth(e, F, C, &cand_cap, &full_cap);
+  *grown = more != 0;
+  if (more == 0) return true;
+  if (e->budget && e->allocated + more > e->budget) {
+    const uint64_t granted = e->grow_hook ? e->grow_hook(e->allocated + more) : 0;
+    if (granted < e->allocated + more) return false;
+    e->budget = granted;
+  }
+  e->cand_cap = cand_cap;
+  e->full_cap = full_cap;
+  IterRec seed{};
+  seed.N = seed.F = seed.FA = edges;
+  size_buffers(e, true, 0, &seed);
+  launch_resume(e->stream, e->d_ctrl, e->cand_cap, e->full_cap, 0);
+  return true;
+}
+
 // TC one source row at a time (wg_reach.h), from the sorted distinct edges E and the seed.
 // Returns false where the iterations' launches have to take over (few rows, rows beyond the tiers,
 // no memory for the pool or the bitmaps): E and the seed are as they were.
@@ -739,9 +795,6 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
   ReachArgs a{};
   const uint64_t span = (e->key_space + 31) & ~31ull;
   const uint64_t cols = std::min<uint64_t>({m, e->num_inst > 1 ? 1ull << w : span, span});
-  a.g.span = span;
-  a.g.instances = e->num_inst;
-  a.g.w = w;
   a.words = (uint32_t)((cols + 31) / 32);
   a.bits_tier = cols <= kReachBitsCols;
   a.min_rows = kReachMinRows;
@@ -754,25 +807,7 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
   const ReachCtl* rc = (const ReachCtl*)e->h_reach;
   std::vector<ReachLevel> lev;
   try {
-    // the renumbered graph: 16-byte records first
-    const uint64_t slab_edges = a.slab_mode ? m + kSlabThreads : 0;
-    const uint64_t sizes[] = {(span / 32 + 1) * sizeof(RankWord), (m + kReachEdgePad) * sizeof(uint2), m * 4,
-                              (m + 1) * 4, m * 4, m * 4, slab_edges * 4, slab_edges * 4};
-    uint64_t at[8], total = 0;
-    for (int k = 0; k < 8; ++k) {
-      at[k] = total;
-      total += (sizes[k] + 15) & ~15ull;
-    }
-    ensure(e, e->rgraph, total);
-    uint8_t* const base = (uint8_t*)e->rgraph.p;
-    a.g.rank = (RankWord*)(base + at[0]);
-    a.g.edge = (uint2*)(base + at[1]);
-    a.g.rowkey = (uint32_t*)(base + at[2]);
-    a.g.rstart = (uint32_t*)(base + at[3]);
-    a.g.colkey = (uint32_t*)(base + at[4]);
-    a.g.cstart = (uint32_t*)(base + at[5]);
-    a.g.slab_edge = (uint32_t*)(base + at[6]);
-    a.g.slab_col = (uint32_t*)(base + at[7]);
+    graph_buffers(e, a.g, m, w, a.slab_mode != 0, 0);
     uint64_t F = 0, C = 0, cand_total = 0;
     for (int attempt = 0;; ++attempt) {
       b = make_bufs<K>(e);
@@ -840,25 +875,14 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
         cand_total += l.d[form];
       }
       if (F > kMaxKeys || C > kMaxKeys) return false;  // (the iterations' launches say so)
-      uint64_t cand_cap, full_cap;
-      const uint64_t more = staged_growth(e, F, C, &cand_cap, &full_cap);
-      if (more == 0) break;
-      if (e->budget && e->allocated + more > e->budget) {
-        const uint64_t granted = e->grow_hook ? e->grow_hook(e->allocated + more) : 0;
-        if (granted < e->allocated + more) {
-          free_buf(e, e->rpool);
-          free_buf(e, e->rbits);
-          return false;
-        }
-        e->budget = granted;
-      }
       // (once per size: the growth takes the buffers that hold the rows' counts along)
-      e->cand_cap = cand_cap;
-      e->full_cap = full_cap;
-      IterRec seed{};
-      seed.N = seed.F = seed.FA = rc->edges;
-      size_buffers(e, true, 0, &seed);
-      launch_resume(e->stream, e->d_ctrl, e->cand_cap, e->full_cap, 0);
+      bool grown = false;
+      if (!grow_staged(e, F, C, rc->edges, &grown)) {
+        free_buf(e, e->rpool);
+        free_buf(e, e->rbits);
+        return false;
+      }
+      if (!grown) break;
     }
     e->seen_cand.store(C, std::memory_order_relaxed);
     // round j of the loop joins level j - 1; the last round finds nothing
@@ -898,6 +922,178 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
   } catch (const Fail& f) {
     if (f.st != WG_ERR_CAPACITY && f.st != WG_ERR_OUT_OF_MEMORY) throw;
     // no memory for this form: the iterations' launches grow their own buffers
+    e->err.clear();
+    free_buf(e, e->rpool);
+    free_buf(e, e->rbits);
+    return false;
+  }
+}
+
+// SG on the renumbered graph (wg_sg.h), from the sorted distinct edges E: matrices or pairs.
+// Returns false where the iterations' launches have to take over (few rows, a graph neither form
+// takes, no memory for it): E is as it was.
+template <typename K>
+bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_options& o, wg_stats* st) {
+  Bufs<K> b = make_bufs<K>(e);
+  ReachArgs ra{};
+  ra.square = 1;
+  SgArgs a{};
+  const ReachCtl* rc = (const ReachCtl*)e->h_reach;
+  const SgCtl* sc = (const SgCtl*)(e->h_reach + sizeof(ReachCtl));
+  const SgLevel* lev = (const SgLevel*)(e->h_reach + sizeof(ReachCtl) + sizeof(SgCtl));
+  constexpr size_t head = sizeof(ReachCtl) + sizeof(SgCtl);
+  constexpr size_t level_bytes = kSgLevels * sizeof(SgLevel);
+  // reads the control blocks and the first `levels` levels
+  auto read = [&](uint32_t levels) {
+    hip_check(e, hipMemcpyAsync(e->h_reach, e->rctl.p, head + std::min(levels, kSgLevels) * sizeof(SgLevel),
+                                hipMemcpyDeviceToHost, e->stream), "readback");
+    sync_stream(e);
+    if (e->cancel && e->cancel->load()) fail(e, WG_ERR_CANCELLED, "cancelled");
+  };
+  try {
+    a.edge = (uint4*)graph_buffers(e, ra.g, m, w, true, m * sizeof(uint4));
+    ensure(e, e->rctl, head + level_bytes + 2 * ra.g.span);
+    ra.g.flags = (uint8_t*)e->rctl.p + head + level_bytes;
+    ra.rc = a.rc = (ReachCtl*)e->rctl.p;
+    a.sc = (SgCtl*)((uint8_t*)e->rctl.p + sizeof(ReachCtl));
+    a.lev = (SgLevel*)((uint8_t*)e->rctl.p + head);
+    a.lev_cap = kSgLevels;
+    a.g = ra.g;
+    hip_check(e, hipMemsetAsync(e->rctl.p, 0, head + level_bytes + 2 * ra.g.span, e->stream), "memset");
+    launch_reach_graph<K>(e->stream, e->grid, e->d_ctrl, b.E, m, ra, b.jtot);
+    launch_sg_edges<K>(e->stream, e->grid, e->d_ctrl, b.E, m, a);
+    read(0);
+    const uint64_t rows = rc->rows, cols = rc->cols, edges = rc->edges, base = sc->base;
+    if (rows < kReachMinRows || base > kMaxKeys) return false;
+    const bool fits = cols <= kSlabRows32 && rows + cols + 2 <= kSlabLdsWords && e->num_inst <= 1;
+    const bool matrices = fits && (base * kSgDense >= cols * cols || sc->wide);
+    if (!matrices && sc->wide) return false;
+    uint32_t rounds = 0;  // the fixpoint: the first round that finds nothing
+    auto at_fixpoint = [&](uint32_t known) {  // levels [0, known) are read back
+      while (rounds < known && (lev[rounds].n | lev[rounds].found)) ++rounds;
+      return rounds < known;
+    };
+    auto found = [&](uint32_t i) {  // tuples of level i
+      return matrices ? lev[i].n : 2ull * (uint32_t)lev[i].found - lev[i].diag;
+    };
+    uint64_t diagonal = 0;
+    const bool strict = (o.flags & WG_SG_IRREFLEXIVE) != 0;
+    const uint32_t slabs = (uint32_t)((cols + 31) / 32);
+    if (matrices) {
+      const uint64_t words = (uint64_t)slabs * cols;
+      ensure(e, e->rbits, words * 4);
+      ensure(e, e->rpool, 2 * words * 4);
+      a.S = (uint32_t*)e->rbits.p;
+      a.D = (uint32_t*)e->rpool.p;
+      a.M = a.D + words;
+      a.base_edge = a.g.slab_edge;
+      a.step_edge = a.g.slab_col;
+      a.cdeg = b.rowb;
+      launch_sg_matrix_base<K>(e->stream, e->grid, e->d_ctrl, b.E, m, a, slabs);
+      for (uint32_t j = 1;;) {
+        if (j + kSgMatrixRounds + 1 > kSgLevels) return false;
+        for (uint32_t k = 0; k < kSgMatrixRounds; ++k) launch_sg_matrix_round(e->stream, e->grid, a, j++, slabs);
+        read(j + 1);
+        if (at_fixpoint(j)) break;
+      }
+    } else {
+      // slots: eight times the base candidates at first (two of which are one pair)
+      uint64_t slots = 1024;
+      while (slots < 8 * base) slots <<= 1;
+      for (;; slots *= 4) {
+        if (slots > (1ull << 30)) return false;
+        // the table, then as many list entries as may fill half of it
+        ensure(e, e->rpool, slots * 20);
+        a.tab = (unsigned long long*)e->rpool.p;
+        a.mask = slots - 1;
+        a.keys = a.tab + slots;
+        a.key_cap = slots / 2;
+        a.front = (uint4*)(a.keys + slots / 2);
+        a.front_cap = slots / 2;
+        hip_check(e, hipMemsetAsync(a.tab, 0xFF, slots * 8, e->stream), "memset");
+        launch_sg_pairs_base(e->stream, e->grid, e->d_ctrl, m, a);
+        uint32_t j = 1;
+        rounds = 0;
+        for (uint32_t k = kSgPairRounds;;) {
+          for (; k > 0 && j + 1 < kSgLevels; --k) launch_sg_pairs_round(e->stream, e->grid, a, j++);
+          launch_sg_pairs_tail(e->stream, a, j);
+          read(j + kReachReadLevels);
+          if (sc->next > j + kReachReadLevels) read(sc->next);
+          j = sc->next;
+          if (sc->stop || at_fixpoint(j)) break;
+          if (j + 1 >= kSgLevels) return false;
+          // rounds until the pairs fit the tail, at their rate of change
+          const double f1 = (double)(lev[j - 1].found >> 32), f0 = (double)(lev[j - 2].found >> 32);
+          const double r = std::min(0.98, std::max(0.05, f1 / std::max(f0, 1.0)));
+          k = (uint32_t)std::min(16.0, std::max(1.0, std::ceil(std::log(kSgTail / f1) / std::log(r))));
+        }
+        if (sc->stop & kSgDeep) return false;
+        if (!sc->stop) break;
+        // too small: cleared and run again
+        hip_check(e, hipMemsetAsync(&a.sc->out, 0, sizeof(SgCtl) - offsetof(SgCtl, out) + level_bytes, e->stream), "memset");
+      }
+      for (uint32_t i = 0; i <= rounds; ++i) diagonal += lev[i].diag;
+    }
+    uint64_t F = 0, C = 0, cand_total = 0;
+    for (uint32_t i = 0; i <= rounds; ++i) {
+      F += found(i);
+      C = std::max<uint64_t>(C, lev[i].c);
+      if (i) cand_total += lev[i].c;
+    }
+    const uint64_t base_n = found(0);
+    if (F > kMaxKeys || std::max(C, base) > kMaxKeys) return false;  // (the iterations' launches say so)
+    if (o.max_iterations && rounds > o.max_iterations)
+      fail(e, WG_ERR_ITER_LIMIT, "max_iterations reached before the fixpoint");
+    if (st) {
+      st->iterations = rounds;
+      st->base_tuples = base_n;
+      st->join_candidates = cand_total;
+      if (st->delta_sizes)
+        for (uint64_t i = 0; i < std::min<uint64_t>(st->delta_sizes_cap, (uint64_t)rounds + 1); ++i)
+          st->delta_sizes[i] = found((uint32_t)i);
+    }
+    bool grown = false;
+    if (!grow_staged(e, F, std::max({C, base, matrices ? 0 : F}), edges, &grown)) {
+      free_buf(e, e->rpool);
+      free_buf(e, e->rbits);
+      return false;
+    }
+    b = make_bufs<K>(e);
+    e->seen_cand.store(C, std::memory_order_relaxed);
+    if (matrices) {
+      if (strict && F) {
+        launch_sg_matrix_diagonal(e->stream, e->grid, a, (uint32_t)cols);
+        read(0);
+        diagonal = sc->diagonal;
+      }
+      ra.bits = a.S;
+      ra.cnt = b.rowa;
+      ra.seg = b.rowb;
+      launch_slab_offsets(e->stream, e->grid, m, ra, b.jtot, b.off);
+      ReachResult& r = e->res_reach;
+      r = ReachResult{};
+      r.cnt = ra.cnt;
+      r.off = b.off;
+      r.rowkey = r.colkey = ra.g.colkey;
+      r.bits = a.S;
+      r.rank = ra.g.rank;
+      r.rows = r.cols = (uint32_t)cols;
+      r.slab = 32;
+      r.w = w;
+      e->res_is_reach = true;
+    } else if (F) {
+      uint64_t keys = 0;
+      for (uint32_t i = 0; i <= rounds; ++i) keys += (uint32_t)lev[i].found;
+      launch_sg_emit<K>(e->stream, e->grid, a, keys, strict ? 0 : 1, b.cand[0]);
+      enqueue_sort<K>(e, b, (const uint64_t*)&a.sc->out, F * sizeof(K) <= kSmallSortBytes ? 2 : 0);
+      e->res_keys = b.cand[passes & 1];
+    }
+    e->res_n = F - (strict ? diagonal : 0);
+    e->res_w = w;
+    if (st) st->result_tuples = e->res_n;
+    return true;
+  } catch (const Fail& f) {
+    if (f.st != WG_ERR_CAPACITY && f.st != WG_ERR_OUT_OF_MEMORY) throw;
     e->err.clear();
     free_buf(e, e->rpool);
     free_buf(e, e->rbits);
@@ -947,8 +1143,8 @@ wg_status run(wg_engine* e, int query, const uint32_t* src, const uint32_t* dst,
   const int mode = query == WG_QUERY_SG ? kModeEdges : (kModeEdges | kModeSeed);
   launch_compact<K>(e->stream, e->grid, mode, e->d_ctrl, &e->d_ctrl->m_in, b.cand[passes & 1],
                     b.cand[(passes & 1) ^ 1], b, w, 0, 0, stage(e, WG_STAGE_DEDUP_DIFF));
-  if (query == WG_QUERY_TC && e->row_wise) {
-    if (reach<K>(e, m, w, o, st)) {
+  if (e->row_wise) {
+    if (query == WG_QUERY_TC ? reach<K>(e, m, w, o, st) : same_generation<K>(e, m, w, passes, o, st)) {
       if (st) {
         st->field_bits = (uint32_t)w;
         st->key_bytes = (uint32_t)sizeof(K);
@@ -957,7 +1153,9 @@ wg_status run(wg_engine* e, int query, const uint32_t* src, const uint32_t* dst,
       }
       return WG_OK;
     }
-    if (st) st->resumes = 0;
+    if (st) {
+      st->iterations = st->base_tuples = st->join_candidates = st->resumes = 0;
+    }
     b = make_bufs<K>(e);
   }
   launch_edge_index<K>(e->stream, e->grid, e->d_ctrl, b, w, stage(e, WG_STAGE_PREPARE));
@@ -1452,14 +1650,16 @@ wg_status solve(wg_engine* e, int query, uint32_t num, const uint64_t* d_offsets
                        space <= 16 * m + (1u << 20))
                           ? space
                           : 0;
-      // The row-at-a-time closure: TC asked for without any of the options that describe the
-      // iterations' launches, over ids and columns the ranking and the tiers hold (kReachSpan,
-      // kReachColsMax; whether there are rows enough, kReachMinRows, shows on the device).
+      // The forms on the renumbered graph (wg_reach.h, wg_sg.h): a query without any of the options
+      // that describe the iterations' launches, over ids and columns the ranking and the tiers hold
+      // (kReachSpan, kReachColsMax; whether there are rows enough, kReachMinRows, shows on the
+      // device).
       e->key_space = space;
       const uint64_t widest = std::min<uint64_t>(m, num > 1 ? 1ull << w : space);
-      e->row_wise = query == WG_QUERY_TC && m >= kReachMinRows && space >= kReachMinRows &&
+      e->row_wise = query != WG_QUERY_TRIANGLES && m >= kReachMinRows && space >= kReachMinRows &&
                     (space <= kReachSpan || (space <= kDenseRowsMax && space <= 16 * m + (1u << 20))) &&
-                    widest <= kReachColsMax && o.flags == 0 && o.loop_mode == WG_LOOP_AUTO && o.batch_k == 0 &&
+                    (query == WG_QUERY_SG || widest <= kReachColsMax) &&
+                    (o.flags & ~(query == WG_QUERY_SG ? WG_SG_IRREFLEXIVE : 0u)) == 0 && o.loop_mode == WG_LOOP_AUTO && o.batch_k == 0 &&
                     o.force_overflow_at_iter == 0 && !e->trial;
       wg_status r = (ib + 2 * w <= 32) ? run<uint32_t>(e, query, d_src, d_dst, m, o, w, ib, st)
                                        : run<uint64_t>(e, query, d_src, d_dst, m, o, w, ib, st);
@@ -1722,8 +1922,7 @@ wg_status wg_engine_create_ex(int device, const wg_allocator* allocator, wg_engi
     fixed((void**)&e->d_hits, sizeof(uint64_t) * e->grid.stream);
     fixed((void**)&e->d_bstart, kFixedBytes[5]);
     hip_check(e, hipHostMalloc((void**)&e->h_rb, 3 * sizeof(Readback)), "hipHostMalloc");
-    hip_check(e, hipHostMalloc((void**)&e->h_reach, sizeof(ReachCtl) + kReachReadLevels * sizeof(ReachLevel)),
-              "hipHostMalloc");
+    hip_check(e, hipHostMalloc((void**)&e->h_reach, kReachHostBytes), "hipHostMalloc");
     hip_check(e, hipMemsetAsync(e->d_ctrl, 0, sizeof(Ctrl), nullptr), "hipMemsetAsync");
     for (int s = 0; s < 2; ++s)
       hip_check(e, hipEventCreateWithFlags(&e->ev_batch[s], hipEventDisableTiming), "hipEventCreate");

@@ -53,7 +53,7 @@ constexpr uint32_t kReachEdgePad = 8;       // edge records readable past the la
 // Fewer rows than this are left to the iterations' launches: a row's levels (and a slab's) are a
 // serial chain in one workgroup, so they leave most CUs idle where an iteration's launches spread
 // its candidates over the chip.
-constexpr uint32_t kReachMinRows = 512;
+constexpr uint32_t kReachMinRows = 128;
 
 // Slabs: LDS for two words per row (and one idle row).  32 columns per slab while the rows fit
 // at 4 bytes, else 16.
@@ -131,6 +131,7 @@ struct ReachArgs {
   ReachLevel* lev;
   uint32_t lev_cap;
   uint32_t min_rows;     // (kReachMinRows)
+  uint32_t square;       // the result's rows are the columns (same-generation)
   uint32_t form;         // which of a level's counts the kernel adds to
 };
 
@@ -158,6 +159,9 @@ void launch_reach_graph(hipStream_t s, const Grid& g, const Ctrl* ctrl, const K*
                         uint64_t* part);
 // The rows, then their offsets (off: rows + 1 entries; part: g.scan entries of scratch).
 void launch_reach(hipStream_t s, const Grid& g, uint64_t m, const ReachArgs& a, uint64_t* part, uint32_t* off);
+
+// The offsets of slabs alone (rows: at most m).
+void launch_slab_offsets(hipStream_t s, const Grid& g, uint64_t m, const ReachArgs& a, uint64_t* part, uint32_t* off);
 
 // The result (n tuples) as src / dst arrays, as packed keys, and the instances' first tuples (num + 1).
 void launch_reach_unpack(hipStream_t s, const Grid& g, const ReachResult& r, uint64_t n, uint32_t* src,

@@ -50,6 +50,18 @@ void unpack(hipStream_t s, const Grid& g, const ReachResult& r, uint64_t n, Put 
 constexpr uint64_t kRankOneBlock = 4096;
 constexpr uint64_t kOffsetsOneBlock = 16384;
 
+void offsets(hipStream_t s, const Grid& g, uint64_t m, const ReachArgs& a, uint64_t* part, uint32_t* off) {
+  if (m <= kOffsetsOneBlock) {
+    hipLaunchKernelGGL((k_reach_offsets<kScanBlocksMax>), dim3(1), dim3(kBlock), 0, s, a, (const uint64_t*)nullptr,
+                       off);
+  } else {
+    hipLaunchKernelGGL(k_reach_sum, dim3(g.scan), dim3(kBlock), 0, s, a, part);
+    hipLaunchKernelGGL((k_reach_offsets<kScanBlocksMax>), dim3(g.scan), dim3(kBlock), 0, s, a,
+                       (const uint64_t*)part, off);
+  }
+}
+
+
 }  // namespace
 
 template <typename K>
@@ -83,14 +95,12 @@ void launch_reach(hipStream_t s, const Grid& g, uint64_t m, const ReachArgs& a, 
     launch_queue(s, cu, a);
     if (a.bits_tier) launch_bits(s, cu, a);
   }
-  if (m <= kOffsetsOneBlock) {
-    hipLaunchKernelGGL((k_reach_offsets<kScanBlocksMax>), dim3(1), dim3(kBlock), 0, s, a, (const uint64_t*)nullptr,
-                       off);
-  } else {
-    hipLaunchKernelGGL(k_reach_sum, dim3(g.scan), dim3(kBlock), 0, s, a, part);
-    hipLaunchKernelGGL((k_reach_offsets<kScanBlocksMax>), dim3(g.scan), dim3(kBlock), 0, s, a,
-                       (const uint64_t*)part, off);
-  }
+  offsets(s, g, m, a, part, off);
+}
+
+void launch_slab_offsets(hipStream_t s, const Grid& g, uint64_t m, const ReachArgs& a, uint64_t* part, uint32_t* off) {
+  hipLaunchKernelGGL(k_slab_count, dim3(std::max<uint32_t>(1, blocks_for(g, 4 * m))), dim3(kBlock), 0, s, a);
+  offsets(s, g, m, a, part, off);
 }
 
 void launch_reach_unpack(hipStream_t s, const Grid& g, const ReachResult& r, uint64_t n, uint32_t* src,

@@ -1,0 +1,74 @@
+// Device-side pieces shared by the kernels on the renumbered graph (wg_reach.h, wg_sg.h).
+#pragma once
+
+#include "wg_device.h"
+#include "wg_reach.h"
+
+// Makes a register's value unknown to the compiler from here on (it would otherwise keep what it
+// derives from a loop's invariants in registers of their own).
+#ifndef WG_OPAQUE
+#define WG_OPAQUE(x) asm volatile("" : "+v"(x))
+#endif
+// Keeps loads on their side of this point (fewer of them, and of their registers, in flight).
+#define WG_FENCE_LOADS asm volatile("" ::: "memory")
+
+namespace wg {
+
+// LDS written by one lane of a wave, read by another: the wave's LDS instructions execute in
+// order, so only the compiler must keep them so.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A barrier for what the block's waves hand each other in LDS: loads and stores in flight to memory
+// are not waited for.
+__device__ __forceinline__ void block_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Inclusive prefix sum over the wave: six adds across lanes (row shifts and row broadcasts), where
+// shuffles through LDS take six round trips of over 100 cycles.
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t v) {
+#ifdef __HIP_DEVICE_COMPILE__
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);  // row_shr:1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);  // row_shr:2
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);  // row_shr:4
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);  // row_shr:8
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15 to rows 1, 3
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);  // row_bcast:31 to rows 2, 3
+  return v;
+#else
+  return wave_incl_scan<uint32_t>(v);
+#endif
+}
+
+// A value that every lane holds, in a scalar register.
+__device__ __forceinline__ uint32_t wave_uniform(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+
+__host__ __device__ __forceinline__ uint32_t id_mask(int w) { return w >= 32 ? 0xFFFFFFFFu : (1u << w) - 1u; }
+
+template <typename K>
+__device__ __forceinline__ uint32_t col_key(K k, int w) {  // instance << w | dst
+  const uint32_t m = id_mask(w);
+  return (head_row<K>(k, w) & ~m) | ((uint32_t)k & m);
+}
+
+__device__ __forceinline__ uint32_t bits_below(uint32_t v, uint32_t key) {
+  return (uint32_t)__popc(v & ((1u << (key & 31u)) - 1u));
+}
+__device__ __forceinline__ uint32_t rank_col(const RankWord* __restrict__ rank, uint64_t key) {
+  const RankWord r = rank[key >> 5];
+  return r.colpre + bits_below(r.colbits, (uint32_t)key);
+}
+
+// Edge i's place among the slabs' 1,024 stretches of `per` edges: thread i / per reads its k-th edge
+// at k * 1,024 + thread.
+__device__ __forceinline__ uint32_t slab_per(uint32_t edges) { return (edges + kSlabThreads - 1) / kSlabThreads; }
+
+}  // namespace wg

@@ -1,31 +1,9 @@
 // Kernels of the row-at-a-time closure (see wg_reach.h).
 #pragma once
 
-#include "wg_device.h"
-#include "wg_reach.h"
-
-// Makes a register's value unknown to the compiler from here on (it would otherwise keep what it
-// derives from a loop's invariants in registers of their own).
-#ifndef WG_OPAQUE
-#define WG_OPAQUE(x) asm volatile("" : "+v"(x))
-#endif
-// Keeps loads on their side of this point (fewer of them, and of their registers, in flight).
-#define WG_FENCE_LOADS asm volatile("" ::: "memory")
+#include "wg_reach_device.h"
 
 namespace wg {
-
-// LDS written by one lane of a wave, read by another: the wave's LDS instructions execute in
-// order, so only the compiler must keep them so.
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// A value that every lane holds, in a scalar register.
-__device__ __forceinline__ uint32_t wave_uniform(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
-}
 
 __device__ __forceinline__ bool reach_halted(const ReachCtl* rc) {
   return (__hip_atomic_load(&rc->stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kReachHalt) != 0;
@@ -83,22 +61,6 @@ __device__ __forceinline__ uint32_t reach_claim(ReachCtl* rc, int tier, uint32_t
 // a key's row or column number is one load; then the rows' starts, then the edge records.  A few
 // launches of streaming work over the edges and the id range.
 // ---------------------------------------------------------------------------
-__host__ __device__ __forceinline__ uint32_t id_mask(int w) { return w >= 32 ? 0xFFFFFFFFu : (1u << w) - 1u; }
-
-template <typename K>
-__device__ __forceinline__ uint32_t col_key(K k, int w) {  // instance << w | dst
-  const uint32_t m = id_mask(w);
-  return (head_row<K>(k, w) & ~m) | ((uint32_t)k & m);
-}
-
-__device__ __forceinline__ uint32_t bits_below(uint32_t v, uint32_t key) {
-  return (uint32_t)__popc(v & ((1u << (key & 31u)) - 1u));
-}
-__device__ __forceinline__ uint32_t rank_col(const RankWord* __restrict__ rank, uint64_t key) {
-  const RankWord r = rank[key >> 5];
-  return r.colpre + bits_below(r.colbits, (uint32_t)key);
-}
-
 template <typename K>
 __global__ __launch_bounds__(kBlock) void k_reach_mark(const Ctrl* ctrl, const K* __restrict__ E, ReachGraph g) {
   const uint64_t n = ctrl->m_unique;
@@ -206,10 +168,6 @@ __global__ __launch_bounds__(kBlock) void k_reach_rows(const Ctrl* ctrl, const K
     if (i + 1 == n) g.rstart[rc->rows] = (uint32_t)n;
   }
 }
-
-// Edge i's place among the slabs' 1,024 stretches of `per` edges: thread i / per reads its k-th edge
-// at k * 1,024 + thread.
-__device__ __forceinline__ uint32_t slab_per(uint32_t edges) { return (edges + kSlabThreads - 1) / kSlabThreads; }
 
 template <typename K>
 __global__ __launch_bounds__(kBlock) void k_reach_edges(const Ctrl* ctrl, const K* __restrict__ E, ReachGraph g,
@@ -581,11 +539,13 @@ __global__ __launch_bounds__(kSlabThreads) void k_slab(ReachArgs a) {
   reach_levels_flush(s_lev, a);
 }
 
+__device__ __forceinline__ uint32_t result_rows(const ReachArgs& a) { return a.square ? a.rc->cols : a.rc->rows; }
+
 // Tuples of each row over all slabs: 64 rows per block, its waves taking the slabs in turn.
 __global__ __launch_bounds__(kBlock) void k_slab_count(ReachArgs a) {
   __shared__ uint32_t s_c[kWavesPerBlock][kWave];
   if (block_stop(a.rc->slab == 0 || (a.rc->stop & (kReachHalt | kReachSlabFull)) != 0)) return;
-  const uint32_t rows = a.rc->rows, B = a.rc->slab, slabs = (a.rc->cols + B - 1) / B;
+  const uint32_t rows = result_rows(a), B = a.rc->slab, slabs = (a.rc->cols + B - 1) / B;
   const uint32_t lane = (uint32_t)lane_id(), wid = threadIdx.x / kWave;
   for (uint32_t x0 = blockIdx.x * kWave; x0 < rows; x0 += gridDim.x * kWave) {
     const uint32_t x = x0 + lane;
@@ -1156,7 +1116,7 @@ __global__ __launch_bounds__(kBlock) void k_reach_sum(ReachArgs a, uint64_t* __r
   __shared__ uint64_t s_wave[kWavesPerBlock];
   if (block_stop(reach_halted(a.rc))) return;
   uint64_t lo, hi;
-  block_range(a.rc->rows, kReachScanTile, lo, hi);
+  block_range(result_rows(a), kReachScanTile, lo, hi);
   uint64_t sum = 0;
   for (uint64_t i = lo + threadIdx.x; i < hi; i += kBlock) sum += a.cnt[i] & ~kReachBitRow;
   uint64_t total;
@@ -1171,7 +1131,7 @@ __global__ __launch_bounds__(kBlock) void k_reach_offsets(ReachArgs a, const uin
   __shared__ uint64_t s_pre[SCAN_MAX];
   __shared__ uint64_t s_wave[kWavesPerBlock];
   if (block_stop(reach_halted(a.rc))) return;
-  const uint32_t n = a.rc->rows;
+  const uint32_t n = result_rows(a);
   uint64_t run = 0;
   if (part) {
     (void)block_prefix<SCAN_MAX / kBlock>(part, (int)gridDim.x, s_pre, s_wave);
