@@ -22,6 +22,7 @@
 #include "wg_launch.h"
 #include "wg_reach.h"
 #include "wg_sg.h"
+#include "wg_tri.h"
 
 using namespace wg;
 
@@ -1101,6 +1102,72 @@ bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_optio
   }
 }
 
+int ceil_log2(uint64_t v) {
+  int b = 0;
+  while ((1ull << b) < v) ++b;
+  return b;
+}
+
+// Triangles on the renumbered graph (wg_tri.h), from the sorted distinct edges E: the count and the
+// two-paths.  Returns false where the join's launches have to take over (few rows, no memory, more
+// two-paths than they take): E is as it was.
+template <typename K>
+bool triangles(wg_engine* e, uint64_t m, int w, wg_stats* st) {
+  const Bufs<K> b = make_bufs<K>(e);
+  TriArgs a{};
+  try {
+    ReachArgs ra{};
+    a.edge = (uint4*)graph_buffers(e, ra.g, m, w, true, m * sizeof(uint4) + 2 * m * sizeof(uint2));
+    a.piece = (uint2*)(a.edge + m);
+    a.col = ra.g.slab_col;
+    // control blocks, rows' up edges and the ids' flags, cleared together
+    const uint64_t ctl = (sizeof(ReachCtl) + sizeof(TriCtl) + 15) & ~15ull, rows = (8 * m + 15) & ~15ull;
+    ensure(e, e->rctl, ctl + rows + 2 * ra.g.span);
+    uint8_t* const base = (uint8_t*)e->rctl.p;
+    ra.rc = a.rc = (ReachCtl*)base;
+    a.tc = (TriCtl*)(base + sizeof(ReachCtl));
+    a.ustart = (uint32_t*)(base + ctl);
+    a.uend = a.ustart + m;
+    ra.g.flags = base + ctl + rows;
+    a.g = ra.g;
+    a.w = ceil_log2(std::max<uint64_t>(2, std::min(m, e->key_space)));
+    hip_check(e, hipMemsetAsync(base, 0, ctl + rows + 2 * ra.g.span, e->stream), "memset");
+    launch_reach_graph<K>(e->stream, e->grid, e->d_ctrl, b.E, m, ra, b.jtot);
+    // the up edges sorted by their row: in one block, like E, or the digits of the row alone
+    const bool one_block = m * sizeof(K) <= kSmallSortBytes;
+    const int passes = sort_passes(2 * a.w, e->sort.rb), first = one_block ? 0 : a.w / e->sort.rb;
+    launch_tri_edges<K>(e->stream, e->grid, e->d_ctrl, b.E, m, a, b.cand[first & 1]);
+    const uint64_t* const up = (const uint64_t*)&a.tc->up;
+    if (one_block)
+      launch_small_sort<K>(e->stream, e->d_ctrl, up, b, passes, true);
+    for (int p = first; p < passes && !one_block; ++p) {
+      launch_sort_pass<K>(e->stream, e->d_ctrl, up, e->sort, b, p, false);
+      launch_sort_pass<K>(e->stream, e->d_ctrl, up, e->sort, b, p, true);
+    }
+    const uint64_t cols = std::min(m, e->key_space);
+    launch_tri_count<K>(e->stream, e->grid, m, a, b.cand[passes & 1], cols > 32ull * kTriWords);
+    hip_check(e, hipMemcpyAsync(e->h_reach, base, sizeof(ReachCtl) + sizeof(TriCtl), hipMemcpyDeviceToHost, e->stream),
+              "readback");
+    sync_stream(e);
+  } catch (const Fail& f) {
+    if (f.st != WG_ERR_CAPACITY && f.st != WG_ERR_OUT_OF_MEMORY) throw;
+    e->err.clear();
+    return false;
+  }
+  if (e->cancel && e->cancel->load()) fail(e, WG_ERR_CANCELLED, "cancelled");
+  const ReachCtl* rc = (const ReachCtl*)e->h_reach;
+  const TriCtl* tc = (const TriCtl*)(e->h_reach + sizeof(ReachCtl));
+  if (tc->two_paths > kMaxKeys) return false;  // (the join's launches say so)
+  e->tri_count = 3 * tc->hits + tc->loops;
+  e->res_w = w;
+  if (st) {
+    st->iterations = 1;
+    st->base_tuples = rc->edges;
+    st->join_candidates = tc->two_paths;
+  }
+  return true;
+}
+
 template <typename K>
 wg_status run(wg_engine* e, int query, const uint32_t* src, const uint32_t* dst, uint64_t m,
               const wg_options& o, int w, int ib, wg_stats* st) {
@@ -1144,7 +1211,10 @@ wg_status run(wg_engine* e, int query, const uint32_t* src, const uint32_t* dst,
   launch_compact<K>(e->stream, e->grid, mode, e->d_ctrl, &e->d_ctrl->m_in, b.cand[passes & 1],
                     b.cand[(passes & 1) ^ 1], b, w, 0, 0, stage(e, WG_STAGE_DEDUP_DIFF));
   if (e->row_wise) {
-    if (query == WG_QUERY_TC ? reach<K>(e, m, w, o, st) : same_generation<K>(e, m, w, passes, o, st)) {
+    const bool done = query == WG_QUERY_TC   ? reach<K>(e, m, w, o, st)
+                      : query == WG_QUERY_SG ? same_generation<K>(e, m, w, passes, o, st)
+                                             : triangles<K>(e, m, w, st);
+    if (done) {
       if (st) {
         st->field_bits = (uint32_t)w;
         st->key_bytes = (uint32_t)sizeof(K);
@@ -1510,12 +1580,6 @@ bool is_device_pointer(const void* p) {
   return a.type == hipMemoryTypeDevice;
 }
 
-int ceil_log2(uint64_t v) {
-  int b = 0;
-  while ((1ull << b) < v) ++b;
-  return b;
-}
-
 // num == 0: a single instance; else a batch of `num` instances with edge offsets.
 wg_status solve(wg_engine* e, int query, uint32_t num, const uint64_t* d_offsets,
                 const uint32_t* d_src, const uint32_t* d_dst, uint64_t m,
@@ -1656,7 +1720,7 @@ wg_status solve(wg_engine* e, int query, uint32_t num, const uint64_t* d_offsets
       // device).
       e->key_space = space;
       const uint64_t widest = std::min<uint64_t>(m, num > 1 ? 1ull << w : space);
-      e->row_wise = query != WG_QUERY_TRIANGLES && m >= kReachMinRows && space >= kReachMinRows &&
+      e->row_wise = m >= (query == WG_QUERY_TRIANGLES ? kTriMinEdges : kReachMinRows) && space >= kReachMinRows &&
                     (space <= kReachSpan || (space <= kDenseRowsMax && space <= 16 * m + (1u << 20))) &&
                     (query == WG_QUERY_SG || widest <= kReachColsMax) &&
                     (o.flags & ~(query == WG_QUERY_SG ? WG_SG_IRREFLEXIVE : 0u)) == 0 && o.loop_mode == WG_LOOP_AUTO && o.batch_k == 0 &&

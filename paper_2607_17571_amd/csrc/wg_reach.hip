@@ -46,8 +46,9 @@ void unpack(hipStream_t s, const Grid& g, const ReachResult& r, uint64_t n, Put 
   hipLaunchKernelGGL(k_reach_unpack<Put>, dim3(lb + bb), dim3(kBlock), 0, s, r, lb, put);
 }
 
-// id ranges of up to this many words are ranked by one block, without a launch for the totals
-constexpr uint64_t kRankOneBlock = 4096;
+// id ranges of up to this many words are ranked by one block, without a launch for the totals (one
+// block against two launches, us: 1,024 words 12 / 9, 2,048 27 / 9)
+constexpr uint64_t kRankOneBlock = 512;
 constexpr uint64_t kOffsetsOneBlock = 16384;
 
 void offsets(hipStream_t s, const Grid& g, uint64_t m, const ReachArgs& a, uint64_t* part, uint32_t* off) {

@@ -23,7 +23,7 @@ template <typename K>
 void launch_tri_count(hipStream_t s, const Grid& g, uint64_t m, const TriArgs& a, const K* up, bool wide) {
   const int cu = std::max(1, g.stream / 8);
   hipLaunchKernelGGL(k_tri_starts<K>, dim3(blocks_for(m, kBlock, g.stream)), dim3(kBlock), 0, s, a, up);
-  hipLaunchKernelGGL(k_tri_pairs<K>, dim3(blocks_for(m, kBlock, g.stream / 2)), dim3(kBlock), 0, s, a, up);
+  hipLaunchKernelGGL(k_tri_pairs<K>, dim3(blocks_for(m, kTriPairThreads, cu)), dim3(kTriPairThreads), 0, s, a, up);
   if (wide)
     hipLaunchKernelGGL((k_tri_bits<K, kTriWordsWide>), dim3(cu), dim3(kTriThreads), 0, s, a, up);
   else

@@ -7,6 +7,8 @@
 namespace wg {
 
 constexpr uint32_t kTriEdgeThreads = 1024;
+constexpr uint32_t kTriPairThreads = 1024;
+constexpr uint32_t kTriPairWaves = kTriPairThreads / kWave;
 
 // (large blocks: a few same-address atomics each)
 template <typename K>
@@ -48,7 +50,7 @@ __global__ __launch_bounds__(kTriEdgeThreads) void k_tri_edges(const Ctrl* ctrl,
         const bool before = e.z < deg || (e.z == deg && x.y <= first);  // b is not after a
         e.w = before ? 1 : 0;
         is_up = !before && ((q.colbits >> (row & 31u)) & 1u);
-        key = ((K)(q.colpre + bits_below(q.colbits, row)) << a.w) | (K)rb;
+        key = ((K)rb << a.w) | (K)(q.colpre + bits_below(q.colbits, row));
         two += e.z;
       }
       a.edge[i] = e;
@@ -74,23 +76,23 @@ __global__ __launch_bounds__(kTriEdgeThreads) void k_tri_edges(const Ctrl* ctrl,
 template <typename K>
 __global__ __launch_bounds__(kBlock) void k_tri_starts(TriArgs a, const K* __restrict__ up) {
   const uint64_t n = a.tc->up;
-  const uint32_t m = id_mask(a.w);
   for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (uint64_t)gridDim.x * kBlock) {
-    const uint32_t r = (uint32_t)up[i] & m;
-    if (i == 0 || ((uint32_t)up[i - 1] & m) != r) a.ustart[r] = (uint32_t)i;
-    if (i + 1 == n || ((uint32_t)up[i + 1] & m) != r) a.uend[r] = (uint32_t)i + 1;
+    const uint32_t r = (uint32_t)(up[i] >> a.w);
+    if (i == 0 || (uint32_t)(up[i - 1] >> a.w) != r) a.ustart[r] = (uint32_t)i;
+    if (i + 1 == n || (uint32_t)(up[i + 1] >> a.w) != r) a.uend[r] = (uint32_t)i + 1;
   }
 }
 
-// The lanes' counts n flattened: 64 units a step, each with its lane and its index there:
-// unit(lane, index) by the lanes that have one.
+// The lanes' counts n flattened: U x 64 units a step, each with its lane and its index there.  All of
+// a step's load(lane, index) come before its use(loaded): U loads in flight.
+template <int U>
 struct TriWave {
   uint32_t lane[kWave];  // the lanes that have units
   uint32_t pre[kWave];   // ... units before each
-  uint32_t mark[kWave];
+  uint32_t mark[U * kWave];
 };
-template <typename Unit>
-__device__ __forceinline__ void tri_flat(TriWave& w, uint32_t n, Unit unit) {
+template <int U, typename Load, typename Use>
+__device__ __forceinline__ void tri_flat(TriWave<U>& w, uint32_t n, Load load, Use use) {
   const uint32_t lane = (uint32_t)lane_id();
   const uint32_t incl = wave_prefix(n), pre = incl - n;
   const uint32_t total = __shfl(incl, kWave - 1, kWave);
@@ -102,18 +104,28 @@ __device__ __forceinline__ void tri_flat(TriWave& w, uint32_t n, Unit unit) {
     w.pre[at] = pre;
   }
   uint32_t before = 0;  // starts before this step
-  for (uint32_t k0 = 0; k0 < total; k0 += kWave) {
+  for (uint32_t k0 = 0; k0 < total; k0 += U * kWave) {
     wave_lds_sync();
-    w.mark[lane] = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) w.mark[u * kWave + lane] = 0;
     wave_lds_sync();
-    if (n && pre >= k0 && pre < k0 + kWave) w.mark[pre - k0] = 1;
+    if (n && pre >= k0 && pre < k0 + U * kWave) w.mark[pre - k0] = 1;
     wave_lds_sync();
-    const uint64_t starts = __builtin_amdgcn_ballot_w64(w.mark[lane] != 0);
-    if (k0 + lane < total) {
-      const uint32_t p = before + (uint32_t)__popcll(starts & ((2ull << lane) - 1ull)) - 1u;
-      unit(w.lane[p], k0 + lane - w.pre[p]);
+    uint32_t v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint64_t starts = __builtin_amdgcn_ballot_w64(w.mark[u * kWave + lane] != 0);
+      const uint32_t k = k0 + u * kWave + lane;
+      v[u] = 0;
+      if (k < total) {
+        const uint32_t p = before + (uint32_t)__popcll(starts & ((2ull << lane) - 1ull)) - 1u;
+        v[u] = load(w.lane[p], k - w.pre[p]);
+      }
+      before += (uint32_t)__popcll(starts);
     }
-    before += (uint32_t)__popcll(starts);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (k0 + u * kWave + lane < total) use(v[u]);
   }
   wave_lds_sync();
 }
@@ -129,20 +141,25 @@ __device__ __forceinline__ void tri_add(const TriArgs& a, uint64_t hits, unsigne
 // Every row, a lane each: its pairs (b, c) flattened over the wave, c looked up in b's out-edges;
 // rows with more pairs are queued in pieces for k_tri_bits.
 template <typename K>
-__global__ __launch_bounds__(kBlock) void k_tri_pairs(TriArgs a, const K* __restrict__ up) {
+__global__ __launch_bounds__(kTriPairThreads) void k_tri_pairs(TriArgs a, const K* __restrict__ up) {
   struct Row {
     uint32_t first, ustart, u;
   };
-  __shared__ TriWave s_flat[kWavesPerBlock];
-  __shared__ Row s_row[kWavesPerBlock][kWave];
+  __shared__ TriWave<1> s_flat[kTriPairWaves];
+  __shared__ Row s_row[kTriPairWaves][kWave];
+  __shared__ uint32_t s_pieces, s_piece0;
   __shared__ unsigned long long s_hits;
   const uint32_t rows = a.rc->rows, lane = (uint32_t)lane_id(), wid = threadIdx.x / kWave;
   if (threadIdx.x == 0) s_hits = 0;
   __syncthreads();
   uint32_t hits = 0;
-  for (uint32_t base = blockIdx.x * kBlock; base < rows; base += gridDim.x * kBlock) {
-    const uint32_t r = base + threadIdx.x;
-    uint32_t n = 0;
+  // (a wave's rows are far apart: the rows of hubs may be next to each other)
+  const uint32_t waves = gridDim.x * kTriPairWaves;
+  for (uint32_t base = blockIdx.x * kTriPairWaves; base < rows; base += waves * kWave) {
+    const uint32_t r = base + wid + lane * waves;
+    uint32_t n = 0, pieces = 0, at = 0, first = 0;
+    if (threadIdx.x == 0) s_pieces = 0;
+    __syncthreads();
     if (r < rows) {
       Row q;
       q.first = a.g.rstart[r];
@@ -150,33 +167,38 @@ __global__ __launch_bounds__(kBlock) void k_tri_pairs(TriArgs a, const K* __rest
       q.u = a.uend[r] - q.ustart;
       const uint32_t deg = a.g.rstart[r + 1] - q.first;
       if (q.u && (uint64_t)q.u * deg > kTriPairs) {
-        const uint32_t pieces = (deg + kTriPiece - 1) / kTriPiece;
-        const uint32_t at = atomicAdd(&a.tc->pieces, pieces);
-        for (uint32_t k = 0; k < pieces; ++k) {
-          uint2 p;
-          p.x = r;
-          p.y = q.first + k * kTriPiece;
-          a.piece[at + k] = p;
-        }
+        pieces = (deg + kTriPiece - 1) / kTriPiece;
+        first = q.first;
+        at = atomicAdd(&s_pieces, pieces);
       } else {
         n = q.u * deg;
         s_row[wid][lane] = q;
       }
     }
-    tri_flat(s_flat[wid], n, [&](uint32_t from, uint32_t k) {
+    __syncthreads();
+    if (threadIdx.x == 0 && s_pieces) s_piece0 = atomicAdd(&a.tc->pieces, s_pieces);
+    __syncthreads();
+    for (uint32_t k = 0; k < pieces; ++k) {
+      uint2 p;
+      p.x = r;
+      p.y = first + k * kTriPiece;
+      a.piece[s_piece0 + at + k] = p;
+    }
+    tri_flat<1>(s_flat[wid], n, [&](uint32_t from, uint32_t k) {
       const Row q = s_row[wid][from];
       const uint32_t i = k / q.u, j = k - i * q.u;
       const uint4 e = a.edge[q.first + i];
-      if (e.w == 0) return;
-      const uint32_t c = (uint32_t)(up[q.ustart + j] >> a.w);
+      if (e.w == 0) return 0u;
+      const uint32_t c = (uint32_t)up[q.ustart + j] & id_mask(a.w);
       uint32_t lo = e.y, len = e.z;
       while (len > 1) {
         const uint32_t half = len / 2;
         if (a.col[lo + half] <= c) lo += half;
         len -= half;
       }
-      hits += a.col[lo] == c ? 1u : 0u;
-    });
+      return a.col[lo] == c ? 1u : 0u;
+    }, [&](uint32_t v) { hits += v; });
+    __syncthreads();
   }
   tri_add(a, hits, &s_hits);
 }
@@ -187,7 +209,7 @@ template <typename K, uint32_t WORDS>
 __global__ __launch_bounds__(kTriThreads) void k_tri_bits(TriArgs a, const K* __restrict__ up) {
   constexpr uint32_t kWaves = kTriThreads / kWave;
   __shared__ uint32_t s_bits[WORDS];
-  __shared__ TriWave s_flat[kWaves];
+  __shared__ TriWave<4> s_flat[kWaves];
   __shared__ uint32_t s_first[kWaves][kWave];
   __shared__ unsigned long long s_hits;
   const uint32_t tid = threadIdx.x, lane = (uint32_t)lane_id(), wid = tid / kWave;
@@ -199,9 +221,13 @@ __global__ __launch_bounds__(kTriThreads) void k_tri_bits(TriArgs a, const K* __
   for (uint32_t p = blockIdx.x; p < pieces; p += gridDim.x) {
     const uint2 q = a.piece[p];
     const uint32_t u0 = a.ustart[q.x], u1 = a.uend[q.x], end = min(a.g.rstart[q.x + 1], q.y + kTriPiece);
-    for (uint32_t u = u0 + tid; u < u1; u += kTriThreads) {
-      const uint32_t c = (uint32_t)(up[u] >> a.w);
-      atomicOr(&s_bits[c >> 5], 1u << (c & 31u));
+    for (uint32_t u = u0 + tid; u < u1; u += 4 * kTriThreads) {
+      uint32_t c[4];
+#pragma unroll
+      for (uint32_t k = 0; k < 4; ++k) c[k] = u + k * kTriThreads < u1 ? (uint32_t)up[u + k * kTriThreads] & id_mask(a.w) : kReachNone;
+#pragma unroll
+      for (uint32_t k = 0; k < 4; ++k)
+        if (c[k] != kReachNone) atomicOr(&s_bits[c[k] >> 5], 1u << (c[k] & 31u));
     }
     __syncthreads();
     // (each wave takes every kWaves-th edge: neighbours' degrees differ most by wave otherwise)
@@ -213,13 +239,16 @@ __global__ __launch_bounds__(kTriThreads) void k_tri_bits(TriArgs a, const K* __
       s_first[wid][lane] = e.y;
     }
     uint32_t h = 0;
-    tri_flat(s_flat[wid], n, [&](uint32_t from, uint32_t k) {
-      const uint32_t c = a.col[s_first[wid][from] + k];
-      h += (s_bits[c >> 5] >> (c & 31u)) & 1u;
-    });
+    tri_flat<4>(s_flat[wid], n, [&](uint32_t from, uint32_t k) { return a.col[s_first[wid][from] + k]; },
+                [&](uint32_t c) { h += (s_bits[c >> 5] >> (c & 31u)) & 1u; });
     hits += h;
     __syncthreads();
-    for (uint32_t u = u0 + tid; u < u1; u += kTriThreads) s_bits[(uint32_t)(up[u] >> a.w) >> 5] = 0;
+    // (few: word by word; else all of them)
+    if (u1 - u0 <= kTriThreads) {
+      if (u0 + tid < u1) s_bits[((uint32_t)up[u0 + tid] & id_mask(a.w)) >> 5] = 0;
+    } else {
+      for (uint32_t x = tid; x < WORDS; x += kTriThreads) s_bits[x] = 0;
+    }
     __syncthreads();
   }
   tri_add(a, hits, &s_hits);

@@ -1,0 +1,44 @@
+"""The forms on the renumbered graph at the edges of their rules, through the C ABI, against the
+oracle: same-generation as matrices and as pairs, triangles beyond 65,536 columns."""
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2607_17571_amd import inputs, wg
+from tests.gpu_util import assert_same, run, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+SG = {
+    "matrices": lambda: inputs.rmat(12, 3600, *inputs.RMAT_ABCD, seed=12),
+    "matrices_by_degree": lambda: [np.concatenate(p) for p in zip(inputs.erdos_renyi(9_000, 5_000, seed=9), inputs.out_star(100))],
+    "pairs": lambda: inputs.erdos_renyi(60_000, 48_000, seed=5),
+    "pairs_table_grown": lambda: inputs.binary_tree(9),
+    "pairs_wide": lambda: inputs.scatter_ids(*inputs.erdos_renyi(5_000, 4_500, seed=6), 23, seed=1),
+    "grid": lambda: inputs.grid_dag(30),
+}
+
+
+@pytest.fixture(scope="module")
+def engine():
+    return wg.Engine(0)
+
+
+@pytest.mark.parametrize("irreflexive", [False, True])
+@pytest.mark.parametrize("graph", sorted(SG))
+def test_same_generation(engine, graph, irreflexive):
+    src, dst = SG[graph]()
+    opts = wg.make_options(flags=wg.WG_SG_IRREFLEXIVE if irreflexive else 0)
+    assert_same(*run(engine, "sg", src, dst, opts), oracle.sg(src, dst, irreflexive=irreflexive))
+
+
+@pytest.mark.parametrize("scale,m", [(12, 40_000), (15, 100_000), (17, 60_000)])
+def test_triangles(engine, scale, m):
+    src, dst = inputs.rmat(scale, m, *inputs.RMAT_ABCD, seed=scale)
+    src, dst = np.concatenate([src, src[:64]]), np.concatenate([dst, src[:64]])  # self-loops
+    if scale == 17:  # a column for every vertex
+        ids = np.arange(1 << scale, dtype=np.uint32)
+        src, dst = np.concatenate([src, ids[:-1]]), np.concatenate([dst, ids[1:]])
+    count, st = engine.triangles(to_gpu(src), to_gpu(dst))
+    assert (count, st["join_candidates"]) == oracle.triangles(src, dst)
