@@ -818,6 +818,7 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
       a.queue[0] = (uint32_t*)b.cand[0];
       a.queue[1] = (uint32_t*)b.cand[0] + m;
       a.queue[2] = (uint32_t*)b.cand[1];
+      a.queue[3] = (uint32_t*)b.cand[1] + m;
       const size_t head_bytes = sizeof(ReachCtl) + (size_t)e->reach_levels * sizeof(ReachLevel);
       ensure(e, e->rctl, head_bytes + 2 * span);
       ensure(e, e->rpool, pool * 4);
@@ -848,7 +849,7 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
           e->reach_levels *= 8;
         }
         if (rc->stop & kReachPoolFull) pool = std::max<uint64_t>(pool, rc->cursor + rc->cursor / 8);
-        if (rc->stop & kReachSlotsFull) bits = ((uint64_t)rc->queued[2] + rc->queued[2] / 8) * a.words;
+        if (rc->stop & kReachSlotsFull) bits = ((uint64_t)rc->queued[kBitsTier] + rc->queued[kBitsTier] / 8) * a.words;
         if (rc->stop & kReachSlabFull)
           bits = (uint64_t)((rc->cols + rc->slab - 1) / rc->slab) * rc->rows * rc->slab / 32 + 4;
         if (pool > kMaxKeys) return false;
@@ -897,9 +898,9 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
     r.colkey = a.g.colkey;
     r.pool = a.pool;
     r.bits = a.bits;
-    r.bit_rows = a.queue[2];
+    r.bit_rows = a.queue[kBitsTier];
     r.rank = a.g.rank;
-    r.n_bits = rc->slab ? 0 : rc->queued[2];
+    r.n_bits = rc->slab ? 0 : rc->queued[kBitsTier];
     r.words = a.words;
     r.rows = rc->rows;
     r.cols = rc->cols;

@@ -23,7 +23,7 @@
 // Tiers, where rows are short and differ by orders of magnitude: a row that outgrows a tier is
 // queued for the next one and starts over there (nothing of it has been counted yet):
 //   thread  <= 16 tuples: the set in registers                         k_reach_thread
-//   group   <= 128 tuples: 16 lanes, a hash set in LDS                 k_reach_group
+//   groups  <= 64 tuples (4 lanes) and <= 256 (8): a hash set in LDS   k_reach_group
 //   queue   any size, thin levels: a bitmap of the columns and two
 //           frontier queues in LDS (one wave, or a block for wide ones) k_reach_queue
 //   bits    any size, wide levels: three bitmaps in LDS                k_reach_bits
@@ -38,16 +38,20 @@
 
 namespace wg {
 
-constexpr int kReachTiers = 3;              // queues between the tiers: group, queue, bits
+constexpr int kReachTiers = 4;              // queues between the tiers: two groups, queue, bits
+constexpr int kQueueTier = 2, kBitsTier = 3;
 constexpr uint32_t kReachThreadCap = 16;    // tuples a thread's row holds
-constexpr uint32_t kReachGroupCap = 128;    // ... a 16-lane group's
-constexpr uint32_t kReachGroupSlots = 256;  // hash slots of a group (load at most 1/2)
 constexpr uint32_t kReachChunk = 4096;      // pool entries a block or wave reserves at a time
 constexpr uint32_t kReachLdsLevels = 128;   // levels counted in LDS (deeper ones in memory)
 constexpr uint32_t kReachBitRow = 0x80000000u;  // flag in cnt[]: the row is a bitmap
 constexpr uint32_t kReachNone = 0xFFFFFFFFu;
 constexpr uint32_t kReachLast = 0x80000000u;  // flag in an edge's column: the last of its row
 constexpr int kReachXcds = 8;
+// Tiles of 256 rows that go to one XCD together: the instances of a batch lie one after the other, so
+// that an XCD's L2 then holds the edges its rows share (256 random graphs, 18 MB of edges: the
+// small group tier 400 -> 361 us with it, the thread tier 351 -> 331).
+constexpr uint32_t kReachTileStretch = 64;
+constexpr uint32_t kReachQueueStretch = 512;  // queued rows likewise
 constexpr uint32_t kReachEdgePad = 8;       // edge records readable past the last
 
 // Fewer rows than this are left to the iterations' launches: a row's levels (and a slab's) are a

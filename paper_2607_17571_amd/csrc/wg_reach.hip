@@ -92,7 +92,8 @@ void launch_reach(hipStream_t s, const Grid& g, uint64_t m, const ReachArgs& a, 
     hipLaunchKernelGGL(k_slab_count, dim3(std::max<uint32_t>(1, blocks_for(g, 4 * m))), dim3(kBlock), 0, s, a);
   }
   if (a.slab_mode != 1) {
-    hipLaunchKernelGGL(k_reach_group, dim3(cu * 4), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL((k_reach_group<0, 4, 64, 128, 32, 32, 2>), dim3(cu * 6), dim3(2 * kWave), 0, s, a);
+    hipLaunchKernelGGL((k_reach_group<1, 8, 256, 512, 128, 64, 1>), dim3(cu * 6), dim3(kWave), 0, s, a);
     launch_queue(s, cu, a);
     if (a.bits_tier) launch_bits(s, cu, a);
   }

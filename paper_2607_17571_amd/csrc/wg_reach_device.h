@@ -1,6 +1,8 @@
 // Device-side pieces shared by the kernels on the renumbered graph (wg_reach.h, wg_sg.h).
 #pragma once
 
+#include <type_traits>
+
 #include "wg_device.h"
 #include "wg_reach.h"
 
@@ -44,6 +46,24 @@ __device__ __forceinline__ uint32_t wave_prefix(uint32_t v) {
 #else
   return wave_incl_scan<uint32_t>(v);
 #endif
+}
+
+// v of lane ^ D, D a power of two below 8.
+template <int D>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+#ifdef __HIP_DEVICE_COMPILE__
+  if constexpr (D == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);  // quads 1 0 3 2
+  if constexpr (D == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);  // quads 2 3 0 1
+#endif
+  return __shfl_xor(v, D, kWave);
+}
+
+// Tile `v` of this block's XCD (blocks go to the XCDs in turn, each with an L2 of its own): stretches of
+// C tiles go to the XCDs in turn, so that what neighbouring tiles share is read into one L2.
+__device__ __forceinline__ uint32_t xcd_tile(uint32_t iter, uint32_t C) {
+  if (gridDim.x % kReachXcds) return blockIdx.x + iter * gridDim.x;
+  const uint32_t x = blockIdx.x % kReachXcds, v = blockIdx.x / kReachXcds + iter * (gridDim.x / kReachXcds);
+  return (v / C) * (C * kReachXcds) + x * C + v % C;
 }
 
 // A value that every lane holds, in a scalar register.

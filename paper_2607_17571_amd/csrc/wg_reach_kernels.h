@@ -210,13 +210,18 @@ __global__ __launch_bounds__(kBlock) void k_reach_edges(const Ctrl* ctrl, const 
 
 // ---------------------------------------------------------------------------
 // Thread tier: thread t takes row t, holds its columns in 16 registers (a membership test is 16
-// compares) and the starts of the rows still to expand in LDS, and sorts the columns with a network
-// over the registers at the end.  A block's rows are consecutive, so their sorted columns are
-// packed into one stretch of the pool.  Bound by one dependent load per expansion (four edge
-// records at a time); 64 rows advance per wave.
+// compares, an insertion a shift) and the starts of the rows still to expand in LDS, and sorts the
+// columns with a network over the registers at the end.  Every row steps through its edge lists and
+// levels by itself, two edge records a step: level by level in lockstep, a wave took the widest of
+// its 64 rows at every level.  A block's rows are consecutive, so their sorted columns are packed
+// into one stretch of the pool.  Bound by instruction issue (about 40 per record).  1.65 million
+// rows of 256 random graphs: in lockstep 364 us, so 144.
 // ---------------------------------------------------------------------------
+// (flip all ones: descending)
 template <int N>
-__device__ __forceinline__ void sort_regs(uint32_t (&v)[N]) {
+__device__ __forceinline__ void sort_regs(uint32_t (&v)[N], uint32_t flip = 0) {
+#pragma unroll
+  for (int r = 0; r < N; ++r) v[r] ^= flip;
 #pragma unroll
   for (int k = 2; k <= N; k <<= 1) {
 #pragma unroll
@@ -232,6 +237,8 @@ __device__ __forceinline__ void sort_regs(uint32_t (&v)[N]) {
       }
     }
   }
+#pragma unroll
+  for (int r = 0; r < N; ++r) v[r] ^= flip;
 }
 
 constexpr uint32_t kReachFailBuf = 512;  // rows a block buffers before it appends them to a queue
@@ -260,52 +267,58 @@ __global__ __launch_bounds__(kBlock) void k_reach_thread(ReachArgs a) {
   uint32_t left = 0;  // pool entries left of the block's chunk (uniform)
   const uint32_t ntiles = (n + kBlock - 1) / kBlock;
   __syncthreads();
-  for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+  for (uint32_t iter = 0;; ++iter) {
+    const uint32_t tile = xcd_tile(iter, kReachTileStretch), next = xcd_tile(iter + 1, kReachTileStretch);
+    if (tile >= ntiles) break;
     const uint32_t row = tile * kBlock + tid;
     uint32_t q[CAP];
 #pragma unroll
     for (int k = 0; k < CAP; ++k) q[k] = kReachNone;  // (no column: columns have 31 bits)
-    uint32_t cnt = 0, pops = 0;
+    uint32_t cnt = 0, pops = 0, lv = 0;
     bool fail = false;
     if (row < n) {
-      // the columns of the edges from e on that the row does not hold yet; returns the edges
-      auto expand = [&](uint32_t e) -> uint32_t {
-        uint32_t d = 0;
-        for (bool more = true; more && !fail; e += 4) {
-          uint2 x[4];
-#pragma unroll
-          for (int k = 0; k < 4; ++k) x[k] = edge[e + k];
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            if (!more || fail) continue;
-            const uint32_t z = x[k].x & ~kReachLast;
-            more = (x[k].x & kReachLast) == 0;
-            if (++d > 15) fail = true;
-            bool dup = false;
-#pragma unroll
-            for (int r = 0; r < CAP; ++r) dup |= q[r] == z;
-            if (dup) continue;
-            if (cnt == (uint32_t)CAP) {
-              fail = true;
-              continue;
+      uint32_t e = a.g.rstart[row], f = 0, hi = 0, prev = 0, found = 0, d = 0;
+      bool on = true, first = true;
+      for (;;) {
+        if (!on) {
+          if (f == hi) {
+            // the level is expanded: its counts, then the level found
+            if (!first) s_stat[lv++ * kBlock + tid] = (uint16_t)(found | (d << 8));
+            first = false;
+            found = cnt - prev;
+            if (found == 0) break;
+            prev = cnt;
+            d = 0;
+            hi = pops;
+            if (f == hi) {
+              s_stat[lv++ * kBlock + tid] = (uint16_t)found;
+              break;
             }
-#pragma unroll
-            for (int r = 0; r < CAP; ++r) q[r] = (uint32_t)r == cnt ? z : q[r];
-            ++cnt;
-            if (x[k].y != kReachNone) s_q[pops++ * kBlock + tid] = x[k].y;
           }
+          e = s_q[f++ * kBlock + tid];
+          on = true;
         }
-        return d;
-      };
-      expand(a.g.rstart[row]);
-      uint32_t lv = 0, lo = 0, prev = 0;
-      while (!fail && cnt > prev) {
-        const uint32_t found = cnt - prev, hi = pops;
-        prev = cnt;
-        uint32_t d = 0;
-        for (uint32_t f = lo; f < hi && !fail; ++f) d += expand(s_q[f * kBlock + tid]);
-        lo = hi;
-        s_stat[lv++ * kBlock + tid] = (uint16_t)(found | (d << 8));
+        uint2 x[2];  // (readable past the last edge)
+        x[0] = edge[e];
+        x[1] = edge[e + 1];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          if (!on) continue;
+          const uint32_t z = x[k].x & ~kReachLast;
+          on = (x[k].x & kReachLast) == 0;
+          ++d;
+          bool dup = false;
+#pragma unroll
+          for (int r = 0; r < CAP; ++r) dup |= q[r] == z;
+          if (dup) continue;
+#pragma unroll
+          for (int r = CAP - 1; r > 0; --r) q[r] = q[r - 1];
+          q[0] = z;
+          if (++cnt <= (uint32_t)CAP && x[k].y != kReachNone) s_q[pops++ * kBlock + tid] = x[k].y;
+        }
+        e += 2;
+        fail = cnt > (uint32_t)CAP || d > 255u;
+        if (fail) break;
       }
       if (fail) {
         cnt = 0;
@@ -341,7 +354,7 @@ __global__ __launch_bounds__(kBlock) void k_reach_thread(ReachArgs a) {
     left -= total;
     // a buffer that a further tile could overfill goes out
     const uint32_t fn = s_fn;
-    if (fn > 0 && (tile + gridDim.x >= ntiles || fn > kReachFailBuf - kBlock)) {
+    if (fn > 0 && (next >= ntiles || fn > kReachFailBuf - kBlock)) {
       if (tid == 0) s_flush = atomicAdd(&a.rc->queued[0], fn);
       __syncthreads();
       for (uint32_t t = tid; t < fn; t += kBlock) a.queue[0][s_flush + t] = s_fail[t];
@@ -567,163 +580,184 @@ __global__ __launch_bounds__(kBlock) void k_slab_count(ReachArgs a) {
   }
 }
 
-// ---------------------------------------------------------------------------
-// Group tier: 16 lanes per row, four rows per wave in lockstep.  The set is a hash table of 256
-// slots (linear probing, at most half full); the columns are kept in order of discovery, the
-// starts of the rows still to expand beside them.  A lane expands one row at a time, the next edge
-// record in flight while one is inserted.  Rows of this tier are narrow (a few vertices per
-// level), so 16 lanes are about as many as a level can use, and the rows in flight (64 per CU)
-// hide the loads.
-// ---------------------------------------------------------------------------
-constexpr int kReachGroup = 16;
-constexpr int kReachGroupsPerBlock = kBlock / kReachGroup;
+// Sorts the N x G values of G neighbouring lanes (lane gl holds values gl * N ...), a bitonic network: the
+// steps within a lane are minima and maxima of registers, the few across lanes exchange them.
+template <int N, int G>
+__device__ __forceinline__ void sort_group(uint32_t (&v)[N], uint32_t gl) {
+  sort_regs<N>(v, (gl & 1u) ? 0xFFFFFFFFu : 0u);
+  auto across = [&](auto dist) {
+    constexpr int D = decltype(dist)::value;
+    // (down: this lane keeps the larger values; descending stretches are flipped)
+    const bool up = (gl & D) != 0;
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+      const uint32_t o = lane_xor<D>(v[r]);
+      v[r] = (v[r] < o) != up ? v[r] : o;
+    }
+  };
+#pragma unroll
+  for (int k = 2; k <= G; k <<= 1) {
+    const uint32_t flip = (gl & (uint32_t)k) && k < G ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+    for (int r = 0; r < N; ++r) v[r] ^= flip;
+    if (k > 4) across(std::integral_constant<int, 4>{});
+    if (k > 2) across(std::integral_constant<int, 2>{});
+    across(std::integral_constant<int, 1>{});
+#pragma unroll
+    for (int j = N / 2; j > 0; j >>= 1) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const int l = i ^ j;
+        if (l > i) {
+          const uint32_t lo = v[i] < v[l] ? v[i] : v[l], hi = v[i] < v[l] ? v[l] : v[i];
+          v[i] = lo;
+          v[l] = hi;
+        }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < N; ++r) v[r] ^= flip;
+  }
+}
 
-__global__ __launch_bounds__(kBlock) void k_reach_group(ReachArgs a) {
-  constexpr uint32_t CAP = kReachGroupCap, H = kReachGroupSlots;
-  constexpr int G = kReachGroup;
-  __shared__ uint32_t s_hash[kReachGroupsPerBlock][H];
-  __shared__ uint32_t s_ids[kReachGroupsPerBlock][CAP];
-  __shared__ uint32_t s_todo[kReachGroupsPerBlock][CAP];
-  __shared__ uint32_t s_buf[kWavesPerBlock][kWave];
+// ---------------------------------------------------------------------------
+// Group tiers: G lanes take a row, 64 / G rows a wave.  The set is a hash table in LDS, beside it the
+// starts of the rows still to expand (a ring) and the levels' counts.  Rows of these tiers are
+// narrow (one to four vertices per level), so few lanes can work on one; every lane steps
+// through an edge list of its own, takes the next from the ring when that ends, and a row moves to
+// its next level by itself: a wave's rows wait for each other only at their end.  Bound by the
+// steps' latency (a dependent load and an LDS compare-and-swap) over the rows in flight, which
+// their LDS limits (192 of the small tier per CU, 48 of the large).  140,000 rows of 17 to some
+// thousand tuples: one tier of 16 lanes and 128 tuples took 780 us and left 720 to the queue
+// tier; 361, 286 and 327 so.
+// ---------------------------------------------------------------------------
+template <uint32_t H, uint32_t RING, uint32_t LMAX>
+struct ReachRow {
+  uint32_t hash[H];    // columns; then those alone
+  uint32_t ring[RING];
+  uint32_t lev[LMAX];  // tuples | degrees << 16
+  uint32_t pad;        // (an odd stride: rows at the same place sit in different banks)
+};
+
+template <int TIER, int G, uint32_t CAP, uint32_t H, uint32_t RING, uint32_t LMAX, int NW>
+__global__ __launch_bounds__(NW * kWave) void k_reach_group(ReachArgs a) {
+  constexpr uint32_t PER = kWave / G;  // rows of a wave
+  constexpr uint32_t kHashShift = 32 - __builtin_ctz(H);
+  static_assert(H >= 2 * CAP && (H & (H - 1)) == 0 && (RING & (RING - 1)) == 0 && PER * CAP <= kReachChunk, "");
+  __shared__ ReachRow<H, RING, LMAX> s_row[NW * PER];
+  __shared__ uint32_t s_buf[NW][kWave];
   __shared__ unsigned long long s_lev[kReachLdsLevels][2];
-  const uint32_t n = a.rc->queued[0];
+  const uint32_t n = a.rc->queued[TIER];
   const uint32_t tid = threadIdx.x;
   if (block_stop(n == 0 || a.rc->slab != 0 || reach_halted(a.rc))) return;
   reach_levels_clear(s_lev);
   __syncthreads();
   const int lane = lane_id();
   const uint32_t gl = (uint32_t)lane % G;
-  const uint64_t gmask = 0xFFFFull << (lane & ~(G - 1));
+  const uint64_t gmask = ((1ull << G) - 1ull) << (lane & ~(G - 1));
   const uint64_t lt = lanemask_lt();
-  const uint32_t grp = tid / G;
-  uint32_t* const hash = s_hash[grp];
-  uint32_t* const ids = s_ids[grp];
-  uint32_t* const todo = s_todo[grp];
+  ReachRow<H, RING, LMAX>& q = s_row[tid / G];
   const uint2* __restrict__ edge = a.g.edge;
-  const uint32_t wave_id = blockIdx.x * kWavesPerBlock + tid / kWave;
-  const uint32_t waves = gridDim.x * kWavesPerBlock;
-  constexpr uint32_t PER = kWave / G;  // rows of a wave
   uint64_t chunk = 0;
   uint32_t left = 0;
   uint32_t* const buf = s_buf[tid / kWave];
-  uint32_t fn = 0;          // rows in the wave's buffer
+  uint32_t fn = 0;      // rows in the wave's buffer
   auto flush = [&]() {  // (the whole wave)
     if (fn == 0) return;
     wave_lds_sync();
     uint32_t at = 0;
-    if (lane == 0) at = atomicAdd(&a.rc->queued[1], fn);
+    if (lane == 0) at = atomicAdd(&a.rc->queued[TIER + 1], fn);
     at = __shfl(at, 0, kWave);
-    if ((uint32_t)lane < fn) a.queue[1][at + lane] = buf[lane];
+    if ((uint32_t)lane < fn) a.queue[TIER + 1][at + lane] = buf[lane];
     fn = 0;
     wave_lds_sync();
   };
-  for (uint64_t base = (uint64_t)wave_id * PER; base < n; base += (uint64_t)waves * PER) {
+  for (uint32_t iter = 0;; ++iter) {
+    const uint64_t tile = (uint64_t)xcd_tile(iter, kReachQueueStretch / (NW * PER)) * (NW * PER);
+    if (tile >= n) break;
+    const uint64_t base = tile + (tid / kWave) * PER;
     if (__builtin_amdgcn_readfirstlane((int)reach_halted(a.rc))) break;
     const uint64_t k = base + (uint32_t)lane / G;
     const bool have = k < n;
-    const uint32_t row = have ? a.queue[0][k] : 0u;
-    uint32_t cnt = 0, pops = 0;
-    bool fail = false;
-    for (uint32_t x = gl; x < H; x += G) hash[x] = kReachNone;
+    const uint32_t row = have ? a.queue[TIER][k] : 0u;
+    for (uint32_t x = gl; x < H; x += G) q.hash[x] = kReachNone;
+    // the row's own edges: one list, as if its vertex had been found before the first level
+    uint32_t cnt = 0, prev = 0, pops = have ? 1u : 0u, lo = 0, hi = pops, f = gl + G, level = 0, found = 0, d = 0;
+    bool fail = false, done = !have, first = true;
+    bool on = have && gl == 0;
+    uint32_t e = on ? a.g.rstart[row] : 0u;
     wave_lds_sync();
-    // inserts the column of every lane with `on` into the lane's row
-    auto insert = [&](bool on, uint2 rec) {
-      const uint32_t z = rec.x & ~kReachLast;
-      bool pending = on, fresh = false;
-      uint32_t slot = (z * 0x9E3779B1u) >> 24;
-      while (__builtin_amdgcn_ballot_w64(pending)) {
-        if (pending) {
-          const uint32_t old = atomicCAS(&hash[slot], kReachNone, z);
-          fresh = old == kReachNone;
-          pending = !fresh && old != z;
-          slot = (slot + 1) % H;
-        }
-      }
-      const uint64_t nb = __builtin_amdgcn_ballot_w64(fresh) & gmask;
-      const uint64_t pb = __builtin_amdgcn_ballot_w64(fresh && rec.y != kReachNone) & gmask;
-      if (fresh) {
-        const uint32_t at = cnt + (uint32_t)__popcll(nb & lt), pt = pops + (uint32_t)__popcll(pb & lt);
-        if (at < CAP) ids[at] = z;
-        if (rec.y != kReachNone && pt < CAP) todo[pt] = rec.y;
-      }
-      cnt += (uint32_t)__popcll(nb);
-      pops += (uint32_t)__popcll(pb);
-      fail = fail || cnt > CAP;
-    };
-    {
-      // the row's own edges: lane l takes edges l, l + G, ...
-      uint32_t e = 0, e1 = 0;
-      if (have) {
-        e = a.g.rstart[row];
-        e1 = a.g.rstart[row + 1];
-        fail = e1 - e > CAP;
-      }
-      for (e += gl; __builtin_amdgcn_ballot_w64(e < e1 && !fail); e += G) {
-        const bool on = e < e1 && !fail;
-        uint2 rec;
-        rec.x = rec.y = kReachNone;
-        if (on) rec = edge[e];
-        insert(on, rec);
-      }
-    }
-    wave_lds_sync();
-    // level by level; the counts go out only once the row is done: until then level l's are in
-    // slot l / G of lane l % G
-    uint32_t lo = 0, prev = 0, levels = 0;
-    constexpr int LREG = (int)(CAP / G);
-    uint32_t lev_n[LREG], lev_d[LREG];
-#pragma unroll
-    for (int r = 0; r < LREG; ++r) lev_n[r] = lev_d[r] = 0;
     for (;;) {
-      const bool act = have && !fail && cnt > prev;
-      if (__builtin_amdgcn_ballot_w64(act) == 0) break;
-      const uint32_t found = cnt - prev, hi = pops;
-      if (act) prev = cnt;
-      uint32_t d = 0;
-      for (uint32_t f = lo + gl; __builtin_amdgcn_ballot_w64(act && f < hi && !fail); f += G) {
-        bool on = act && f < hi && !fail;
-        uint32_t e = on ? todo[f] : 0u;
-        uint2 cur;
-        cur.x = cur.y = kReachNone;
-        if (on) cur = edge[e];
-        while (__builtin_amdgcn_ballot_w64(on)) {
-          uint2 nxt = cur;
-          if (on) nxt = edge[++e];  // (readable past the last edge)
-          insert(on, cur);
-          d += on ? 1u : 0u;
-          on = on && (cur.x & kReachLast) == 0 && !fail;
-          cur = nxt;
-        }
-        wave_lds_sync();
-      }
-      if (act) lo = hi;
-#pragma unroll
-      for (int s = G / 2; s >= 1; s >>= 1) d += __shfl_xor(d, s, kWave);
-      if (act && levels % G == gl) {
-#pragma unroll
-        for (int r = 0; r < LREG; ++r)
-          if ((uint32_t)r == levels / G) {
-            lev_n[r] = found;
-            lev_d[r] = d;
+      const uint64_t busy = __builtin_amdgcn_ballot_w64(on) & gmask;
+      const bool idle = busy == 0 && !done;
+      if (__builtin_amdgcn_ballot_w64(idle)) {
+        if (idle) {
+          // the row's level is expanded: its counts, then the level found
+          if (!first && gl == 0) q.lev[level] = found | (d << 16);
+          if (!first) ++level;
+          first = false;
+          found = cnt - prev;
+          fail = fail || (found != 0 && level >= LMAX);
+          done = fail || found == 0;
+          prev = cnt;
+          d = 0;
+          lo = hi;
+          hi = pops;
+          f = lo + gl;
+          if (!done && f < hi) {
+            e = q.ring[f % RING];
+            on = true;
+            f += G;
           }
+        }
       }
-      if (act) ++levels;
-    }
-    const bool good = have && !fail;
-    if (good) {
+      if (__builtin_amdgcn_ballot_w64(!done) == 0) break;
+      uint2 rec[2];  // (readable past the last edge)
+      rec[0].x = rec[0].y = rec[1].x = rec[1].y = kReachNone;
+      if (on) {
+        rec[0] = edge[e];
+        rec[1] = edge[e + 1];
+      }
 #pragma unroll
-      for (int r = 0; r < LREG; ++r)
-        if ((uint32_t)r * G + gl < levels) reach_count(s_lev, a, (uint32_t)r * G + gl, lev_n[r], lev_d[r]);
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t z = rec[h].x & ~kReachLast;
+        bool fresh = false;
+        if (on) {
+          uint32_t slot = (z * 0x9E3779B1u) >> kHashShift;
+          for (;;) {
+            const uint32_t old = atomicCAS(&q.hash[slot], kReachNone, z);
+            fresh = old == kReachNone;
+            if (fresh || old == z) break;
+            slot = (slot + 1) % H;
+          }
+        }
+        const uint64_t ob = __builtin_amdgcn_ballot_w64(on) & gmask;
+        const uint64_t nb = __builtin_amdgcn_ballot_w64(fresh) & gmask;
+        const uint64_t pb = __builtin_amdgcn_ballot_w64(fresh && rec[h].y != kReachNone) & gmask;
+        if (fresh && rec[h].y != kReachNone) q.ring[(pops + (uint32_t)__popcll(pb & lt)) % RING] = rec[h].y;
+        cnt += (uint32_t)__popcll(nb);
+        pops += (uint32_t)__popcll(pb);
+        d += (uint32_t)__popcll(ob);
+        fail = fail || cnt > CAP || pops - lo > RING || d > 0xFFFFu;
+        on = on && (rec[h].x & kReachLast) == 0 && !fail;
+      }
+      e += 2;
+      wave_lds_sync();
+      if (!on && !done && !fail && f < hi) {
+        e = q.ring[f % RING];
+        on = true;
+        f += G;
+      }
     }
+    wave_lds_sync();
+    const bool good = have && !fail;
+    if (good)
+      for (uint32_t x = gl; x < level; x += G) reach_count(s_lev, a, x, q.lev[x] & 0xFFFFu, q.lev[x] >> 16);
     // pool entries of the wave's rows, side by side
     const uint32_t mine = good ? cnt : 0u;
-    uint32_t before = 0, total = 0;
-#pragma unroll
-    for (int q = 0; q < (int)PER; ++q) {
-      const uint32_t c = __shfl(mine, q * G, kWave);
-      before += q < lane / G ? c : 0u;
-      total += c;
-    }
+    const uint32_t incl = wave_prefix(gl == 0 ? mine : 0u);
+    const uint32_t total = __shfl(incl, kWave - 1, kWave);
+    const uint32_t before = __shfl(incl, lane & ~(G - 1), kWave) - mine;
     if (total > left) {
       uint64_t pos = 0;
       if (lane == 0) pos = reach_alloc(a, kReachChunk);
@@ -731,23 +765,37 @@ __global__ __launch_bounds__(kBlock) void k_reach_group(ReachArgs a) {
       left = kReachChunk;
     }
     const bool fits = chunk + total <= a.pool_cap;
-    // sorted by counting the smaller columns: every lane ranks its own against each of the row
+    // the columns alone
     {
-      uint32_t v[LREG], rank[LREG];
+      constexpr int SLOTS = (int)(H / G);
+      uint32_t v[SLOTS], c = 0;
 #pragma unroll
-      for (int r = 0; r < LREG; ++r) {
-        const uint32_t x = (uint32_t)r * G + gl;
-        v[r] = x < mine ? ids[x] : kReachNone;
-        rank[r] = 0;
+      for (int r = 0; r < SLOTS; ++r) {
+        v[r] = q.hash[(uint32_t)r * G + gl];
+        c += v[r] != kReachNone ? 1u : 0u;
       }
-      for (uint32_t t = 0; t < mine; ++t) {
-        const uint32_t y = ids[t];
+      const uint32_t ends = wave_prefix(c);
+      uint32_t at = ends - c;
+      at -= __shfl(at, lane & ~(G - 1), kWave);
+      wave_lds_sync();
 #pragma unroll
-        for (int r = 0; r < LREG; ++r) rank[r] += y < v[r] ? 1u : 0u;
-      }
+      for (int r = 0; r < SLOTS; ++r)
+        if (v[r] != kReachNone) q.hash[at++] = v[r];
+      wave_lds_sync();
+    }
+    // sorted in registers
+    {
+      constexpr int N = (int)(CAP / G);
+      uint32_t v[N];
 #pragma unroll
-      for (int r = 0; r < LREG; ++r)
-        if (fits && (uint32_t)r * G + gl < mine) a.pool[chunk + before + rank[r]] = v[r];
+      for (int r = 0; r < N; ++r) v[r] = gl * N + r < mine ? q.hash[gl * N + r] : kReachNone;
+      sort_group<N, G>(v, gl);
+      wave_lds_sync();
+#pragma unroll
+      for (int r = 0; r < N; ++r) q.hash[gl * N + r] = v[r];
+      wave_lds_sync();
+      if (fits)
+        for (uint32_t x = gl; x < mine; x += G) a.pool[chunk + before + x] = q.hash[x];
     }
     if (good && gl == 0) {
       a.cnt[row] = cnt;
@@ -755,9 +803,9 @@ __global__ __launch_bounds__(kBlock) void k_reach_group(ReachArgs a) {
     }
     // rows sent on are buffered per wave (a same-address atomic costs 12 ns)
     const bool out = have && gl == 0 && fail;
-    const uint64_t ob = __builtin_amdgcn_ballot_w64(out);
-    if (out) buf[fn + (uint32_t)__popcll(ob & lt)] = row;
-    fn += (uint32_t)__popcll(ob);
+    const uint64_t sent = __builtin_amdgcn_ballot_w64(out);
+    if (out) buf[fn + (uint32_t)__popcll(sent & lt)] = row;
+    fn += (uint32_t)__popcll(sent);
     if (fn > kWave - PER) flush();
     chunk += total;
     left -= total;
@@ -847,7 +895,7 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_queue(ReachArgs a) {
   __shared__ unsigned long long s_lev[kReachLdsLevels][2];
   __shared__ uint32_t s_ln[kReachLdsLevels], s_ld[kReachLdsLevels];  // the row's levels so far
   const uint32_t tid = threadIdx.x;
-  const uint32_t n = a.rc->queued[1];
+  const uint32_t n = a.rc->queued[kQueueTier];
   if (block_stop(n == 0 || a.rc->slab != 0 || reach_halted(a.rc))) return;
   reach_levels_clear(s_lev);
   const int wid = (int)(tid / kWave);
@@ -860,8 +908,8 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_queue(ReachArgs a) {
   __syncthreads();
   for (;;) {
     if (tid == 0) {
-      const uint32_t at = reach_halted(a.rc) ? kReachNone : reach_claim(a.rc, 1, n, share);
-      s_row = at == kReachNone ? kReachNone : a.queue[1][at];
+      const uint32_t at = reach_halted(a.rc) ? kReachNone : reach_claim(a.rc, kQueueTier, n, share);
+      s_row = at == kReachNone ? kReachNone : a.queue[kQueueTier][at];
       s_n[0] = s_n[1] = s_f[0] = s_f[1] = 0;
     }
     __syncthreads();
@@ -949,7 +997,7 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_queue(ReachArgs a) {
       if (tid == 0) {
         // (counted already, or no tier for it: the general path)
         if (lv > kReachLdsLevels || !a.bits_tier) atomicOr(&a.rc->stop, (uint32_t)kReachUnsupported);
-        else a.queue[2][atomicAdd(&a.rc->queued[2], 1u)] = row;
+        else a.queue[kBitsTier][atomicAdd(&a.rc->queued[kBitsTier], 1u)] = row;
       }
       for (uint32_t x = tid; x < words; x += TH) s_vis[x] = 0;
     } else {
@@ -1004,7 +1052,7 @@ __global__ __launch_bounds__(kReachBitsWaves * kWave) void k_reach_bits(ReachArg
   __shared__ uint32_t s_row, s_at, s_any[2];
   __shared__ unsigned long long s_lev[kReachLdsLevels][2];
   const uint32_t tid = threadIdx.x;
-  const uint32_t n = a.rc->queued[2];
+  const uint32_t n = a.rc->queued[kBitsTier];
   if (block_stop(n == 0 || a.rc->slab != 0 || reach_halted(a.rc))) return;
   if (n > a.slots) {
     if (tid == 0 && blockIdx.x == 0) atomicOr(&a.rc->stop, (uint32_t)kReachSlotsFull);
@@ -1022,9 +1070,9 @@ __global__ __launch_bounds__(kReachBitsWaves * kWave) void k_reach_bits(ReachArg
   __syncthreads();
   for (;;) {
     if (tid == 0) {
-      const uint32_t at = reach_halted(a.rc) ? kReachNone : reach_claim(a.rc, 2, n, share);
+      const uint32_t at = reach_halted(a.rc) ? kReachNone : reach_claim(a.rc, kBitsTier, n, share);
       s_at = at;
-      s_row = at == kReachNone ? kReachNone : a.queue[2][at];
+      s_row = at == kReachNone ? kReachNone : a.queue[kBitsTier][at];
       s_any[0] = 0;
     }
     __syncthreads();

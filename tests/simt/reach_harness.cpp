@@ -16,6 +16,7 @@ template <typename T> inline T atomicCAS(T* p, T c, T v) {
   __atomic_compare_exchange_n(p, &c, v, false, __ATOMIC_SEQ_CST, __ATOMIC_SEQ_CST);
   return c;
 }
+#define __builtin_amdgcn_s_barrier __syncthreads
 #define WG_OPAQUE(x) (void)0
 #define __builtin_amdgcn_wave_barrier simt::wave_sync
 #define __builtin_amdgcn_fence(...) (void)0
@@ -45,7 +46,7 @@ int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigne
   std::memset(rc.get(), 0, sizeof(ReachCtl));
   std::vector<ReachLevel> lev(h[4], ReachLevel{{0, 0}, {0, 0}});
   std::vector<uint32_t> cnt(m, 0xDEADu), seg(m, 0xBEEFu), off(m + 1), pool(std::max<uint64_t>(pool_cap, 1), 0x5A5A5A5Au);
-  std::vector<uint32_t> queue[3];
+  std::vector<uint32_t> queue[kReachTiers];
   for (auto& q : queue) q.assign(m, 0x77777777u);
   std::vector<uint32_t> rowkey(m), rstart(m + 1), colkey(m), cstart(m), se(m + kSlabThreads), sc(m + kSlabThreads);
   std::vector<uint2> edge(m + kReachEdgePad);
@@ -70,7 +71,7 @@ int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigne
   a.min_rows = 1;
   a.cnt = cnt.data();
   a.seg = seg.data();
-  for (int t = 0; t < 3; ++t) a.queue[t] = queue[t].data();
+  for (int t = 0; t < kReachTiers; ++t) a.queue[t] = queue[t].data();
   a.pool = pool.data();
   a.pool_cap = pool_cap;
   a.words = 32;
@@ -99,7 +100,8 @@ int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigne
     simt::launch(G, kBlock, [&] { k_slab_count(a); }, workers);
   }
   if (slab_mode != 1) {
-    simt::launch(G, kBlock, [&] { k_reach_group(a); }, workers);
+    simt::launch(G, 2 * kWave, [&] { k_reach_group<0, 4, 64, 128, 32, 32, 2>(a); }, workers);
+    simt::launch(G, kWave, [&] { k_reach_group<1, 8, 256, 512, 128, 64, 1>(a); }, workers);
     // (a queue of 96 rows, so that wide levels outgrow it)
     if (one) simt::launch(G, kWave, [&] { k_reach_queue<1, 32, 96>(a); }, workers);
     else simt::launch(G, 4 * kWave, [&] { k_reach_queue<4, 32, 96>(a); }, workers);
@@ -114,7 +116,7 @@ int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigne
   std::ofstream f(out_path, std::ios::binary);
   put(f, rc->stop);
   put(f, rc->cursor);
-  for (int t = 0; t < 3; ++t) put(f, rc->queued[t]);
+  for (int t = 0; t < kReachTiers; ++t) put(f, rc->queued[t]);
   put(f, rc->slab);
   if (rc->stop) return 0;
   const int form = rc->slab ? 1 : 0;
@@ -135,9 +137,9 @@ int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigne
   r.colkey = colkey.data();
   r.pool = pool.data();
   r.bits = bits.data();
-  r.bit_rows = queue[2].data();
+  r.bit_rows = queue[kBitsTier].data();
   r.rank = rank.data();
-  r.n_bits = rc->slab ? 0 : rc->queued[2];
+  r.n_bits = rc->slab ? 0 : rc->queued[kBitsTier];
   r.words = a.words;
   r.rows = rc->rows;
   r.cols = rc->cols;
