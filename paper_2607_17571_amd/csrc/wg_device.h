@@ -8,6 +8,8 @@
 // the key fits, which halves the bytes every stage streams.
 #pragma once
 
+#include <type_traits>
+
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -169,22 +171,55 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
   return (1ull << lane_id()) - 1ull;
 }
 
+#ifdef __HIP_DEVICE_COMPILE__
+// v of another lane by a cross-lane move of the vector ALU (0 where the lane has no source).
+template <int CTRL, int ROWS, typename T>
+__device__ __forceinline__ T wave_move(T v) {
+  if constexpr (sizeof(T) == 4) {
+    return (T)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+  } else {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROWS, 0xF, false);
+    return (T)(((uint64_t)hi << 32) | lo);
+  }
+}
+#endif
+
+// Inclusive sums over the wave's 64 lanes: four shifts within the rows of 16 lanes, then the last
+// lanes of rows to the rows after them.  Six adds; shuffles through LDS took six round trips of
+// over 100 cycles.
 template <typename T>
 __device__ __forceinline__ T wave_incl_scan(T v) {
+  static_assert(std::is_integral<T>::value && (sizeof(T) == 4 || sizeof(T) == 8), "");
+#ifdef __HIP_DEVICE_COMPILE__
+  v += wave_move<0x111, 0xF>(v);  // row_shr:1
+  v += wave_move<0x112, 0xF>(v);
+  v += wave_move<0x114, 0xF>(v);
+  v += wave_move<0x118, 0xF>(v);
+  v += wave_move<0x142, 0xA>(v);  // row_bcast:15, to rows 1 and 3
+  v += wave_move<0x143, 0xC>(v);  // row_bcast:31, to rows 2 and 3
+#else
   const int lane = lane_id();
-#pragma unroll
   for (int d = 1; d < kWave; d <<= 1) {
     T t = __shfl_up(v, d, kWave);
     if (lane >= d) v += t;
   }
+#endif
   return v;
 }
 
+// The wave's sum, in every lane.
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
+#ifdef __HIP_DEVICE_COMPILE__
+  v = wave_incl_scan<T>(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, kWave - 1);
+  if constexpr (sizeof(T) == 4) return (T)lo;
+  else return (T)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), kWave - 1) << 32) | lo);
+#else
   for (int d = kWave / 2; d >= 1; d >>= 1) v += __shfl_xor(v, d, kWave);
   return v;
+#endif
 }
 
 // Exclusive scan over the block; `total` receives the block sum.  `s_wave` needs

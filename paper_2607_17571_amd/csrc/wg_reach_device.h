@@ -32,22 +32,6 @@ __device__ __forceinline__ void block_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Inclusive prefix sum over the wave: six adds across lanes (row shifts and row broadcasts), where
-// shuffles through LDS take six round trips of over 100 cycles.
-__device__ __forceinline__ uint32_t wave_prefix(uint32_t v) {
-#ifdef __HIP_DEVICE_COMPILE__
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);  // row_shr:1
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);  // row_shr:2
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);  // row_shr:4
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);  // row_shr:8
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15 to rows 1, 3
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);  // row_bcast:31 to rows 2, 3
-  return v;
-#else
-  return wave_incl_scan<uint32_t>(v);
-#endif
-}
-
 // v of lane ^ D, D a power of two below 8.
 template <int D>
 __device__ __forceinline__ uint32_t lane_xor(uint32_t v) {

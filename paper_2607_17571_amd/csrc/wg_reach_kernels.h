@@ -755,7 +755,7 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_group(ReachArgs a) {
       for (uint32_t x = gl; x < level; x += G) reach_count(s_lev, a, x, q.lev[x] & 0xFFFFu, q.lev[x] >> 16);
     // pool entries of the wave's rows, side by side
     const uint32_t mine = good ? cnt : 0u;
-    const uint32_t incl = wave_prefix(gl == 0 ? mine : 0u);
+    const uint32_t incl = wave_incl_scan<uint32_t>(gl == 0 ? mine : 0u);
     const uint32_t total = __shfl(incl, kWave - 1, kWave);
     const uint32_t before = __shfl(incl, lane & ~(G - 1), kWave) - mine;
     if (total > left) {
@@ -774,7 +774,7 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_group(ReachArgs a) {
         v[r] = q.hash[(uint32_t)r * G + gl];
         c += v[r] != kReachNone ? 1u : 0u;
       }
-      const uint32_t ends = wave_prefix(c);
+      const uint32_t ends = wave_incl_scan<uint32_t>(c);
       uint32_t at = ends - c;
       at -= __shfl(at, lane & ~(G - 1), kWave);
       wave_lds_sync();

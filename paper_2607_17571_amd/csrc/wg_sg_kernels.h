@@ -109,7 +109,7 @@ struct SgWave {
 template <bool Solo, typename Step>
 __device__ __forceinline__ uint32_t sg_expand(const SgArgs& a, SgWave& w, uint4 f, Step step) {
   const uint32_t lane = (uint32_t)lane_id();
-  const uint32_t n = f.z * f.w, incl = wave_prefix(n), pre = incl - n;
+  const uint32_t n = f.z * f.w, incl = wave_incl_scan<uint32_t>(n), pre = incl - n;
   const uint32_t total = __shfl(incl, kWave - 1, kWave);
   const uint64_t some = __builtin_amdgcn_ballot_w64(n != 0);
   wave_lds_sync();

@@ -94,7 +94,7 @@ struct TriWave {
 template <int U, typename Load, typename Use>
 __device__ __forceinline__ void tri_flat(TriWave<U>& w, uint32_t n, Load load, Use use) {
   const uint32_t lane = (uint32_t)lane_id();
-  const uint32_t incl = wave_prefix(n), pre = incl - n;
+  const uint32_t incl = wave_incl_scan<uint32_t>(n), pre = incl - n;
   const uint32_t total = __shfl(incl, kWave - 1, kWave);
   const uint64_t some = __builtin_amdgcn_ballot_w64(n != 0);
   wave_lds_sync();
