@@ -19,6 +19,7 @@ void launch_queue(hipStream_t s, int cu, const ReachArgs& a) {
   else if (a.words <= 512) hipLaunchKernelGGL((k_reach_queue<1, 512, 512>), dim3(cu * 20), B, 0, s, a);
   else if (a.words <= 1024) hipLaunchKernelGGL((k_reach_queue<1, 1024, 512>), dim3(cu * 16), B, 0, s, a);
   else if (a.words <= 2048) hipLaunchKernelGGL((k_reach_queue<1, 2048, 512>), dim3(cu * 12), B, 0, s, a);
+  else if (a.words <= 4096) hipLaunchKernelGGL((k_reach_queue<1, 4096, 1024>), dim3(cu * 5), B, 0, s, a);
   else if (a.words <= 8192) hipLaunchKernelGGL((k_reach_queue<4, 8192, 3072>), dim3(cu * 2), dim3(4 * kWave), 0, s, a);
   else hipLaunchKernelGGL((k_reach_queue<16, 32768, 3072>), dim3(cu), dim3(16 * kWave), 0, s, a);
 }

@@ -880,7 +880,8 @@ __device__ __forceinline__ void row_columns(const ReachArgs& a, uint32_t row, ui
 // Queue tier: one row per block of NW waves (one wave where the columns' bitmap is at most 8 KB).
 // The set is a bitmap of the instance's columns in LDS; a column whose bit a lane sets first is
 // found, and its row, if it has one, goes to the next level's queue.  Thin, deep rows pay per level
-// one edge load and one LDS round trip, and 16 to 32 of them run per CU.  A level that outgrows the
+// one edge load and a few LDS round trips (one wave keeps its counts in registers: 327 -> 293 us for
+// the rows past 256 tuples of 256 random graphs), and 5 to 24 of them run per CU.  A level that outgrows the
 // queue sends the row on.  The columns come out of the bitmap in order.
 // ---------------------------------------------------------------------------
 template <int NW, uint32_t WORDS, uint32_t QCAP>
@@ -924,23 +925,20 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_queue(ReachArgs a) {
     }
     const uint32_t first = a.g.rstart[row], deg = a.g.rstart[row + 1] - first;
     int to = 0;
+    // (one wave: its counts are in registers)
+    uint32_t nq = 0, nf = 0;
     auto visit = [&](bool on, uint2 rec) {
       const uint32_t z = (rec.x & ~kReachLast) - base;
       bool fresh = false;
-      if (on && !((s_vis[z >> 5] >> (z & 31u)) & 1u))
-        fresh = !((atomicOr(&s_vis[z >> 5], 1u << (z & 31u)) >> (z & 31u)) & 1u);
+      if (on) fresh = !((atomicOr(&s_vis[z >> 5], 1u << (z & 31u)) >> (z & 31u)) & 1u);
       const uint64_t nb = __builtin_amdgcn_ballot_w64(fresh);
       if (nb) {  // (uniform in the wave)
         const uint64_t pb = __builtin_amdgcn_ballot_w64(fresh && rec.y != kReachNone);
         uint32_t at = 0;
         if constexpr (NW == 1) {
-          at = s_n[to];
-          wave_lds_sync();
-          if (lane == 0) {
-            s_n[to] = at + (uint32_t)__popcll(pb);
-            s_f[to] += (uint32_t)__popcll(nb);
-          }
-          wave_lds_sync();
+          at = nq;
+          nq += (uint32_t)__popcll(pb);
+          nf += (uint32_t)__popcll(nb);
         } else {
           if (lane == 0) {
             at = atomicAdd(&s_n[to], (uint32_t)__popcll(pb));
@@ -964,7 +962,7 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_queue(ReachArgs a) {
     bool fail = false;
     for (;;) {
       const int from = to;
-      const uint32_t fn = s_n[from], found = s_f[from];
+      const uint32_t fn = NW == 1 ? nq : s_n[from], found = NW == 1 ? nf : s_f[from];
       cnt += found;
       if (found == 0) break;
       if (fn > QCAP) {
@@ -972,22 +970,33 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_queue(ReachArgs a) {
         break;
       }
       to ^= 1;
-      __syncthreads();
-      if (tid == 0) s_n[to] = s_f[to] = s_d = 0;
-      __syncthreads();
+      if constexpr (NW == 1) {
+        nq = nf = 0;
+        wave_lds_sync();
+      } else {
+        __syncthreads();
+        if (tid == 0) s_n[to] = s_f[to] = s_d = 0;
+        __syncthreads();
+      }
       uint32_t dsum = 0;
       for (uint32_t f = (uint32_t)wid * kWave; f < fn; f += TH)
         dsum += wave_expand(edge, edges, f + lane < fn ? s_front[from][f + lane] : kReachNone, visit);
-      if (dsum) atomicAdd(&s_d, dsum);
-      __syncthreads();
+      dsum = wave_sum<uint32_t>(dsum);
+      if constexpr (NW == 1) {
+        wave_lds_sync();
+      } else {
+        if (lane == 0 && dsum) atomicAdd(&s_d, dsum);
+        __syncthreads();
+        dsum = s_d;
+      }
       // (the row's counts: kept until it is done, or straight to memory once it is deeper than
       // the table, from where on it can no longer be sent back)
       if (tid == 0) {
         if (lv < kReachLdsLevels) {
           s_ln[lv] = found;
-          s_ld[lv] = s_d;
+          s_ld[lv] = dsum;
         } else {
-          reach_count(s_lev, a, lv, found, s_d);
+          reach_count(s_lev, a, lv, found, dsum);
         }
       }
       ++lv;
