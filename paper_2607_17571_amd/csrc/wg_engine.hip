@@ -71,6 +71,7 @@ constexpr uint32_t kSgMatrixRounds = 4;
 constexpr uint32_t kSgPairRounds = 4;
 constexpr size_t kReachHostBytes = std::max(sizeof(ReachCtl) + kReachReadLevels * sizeof(ReachLevel),
                                             sizeof(ReachCtl) + sizeof(SgCtl) + kSgLevels * sizeof(SgLevel));
+constexpr std::chrono::microseconds kFetchSpin{2000};  // a fetch polls this long
 // fixed arrays of an engine: control block, join and compaction block totals, radix counts
 // and totals (the triangle hits depend on the grid)
 constexpr size_t kFixedBytes[6] = {sizeof(Ctrl), sizeof(uint64_t) * kScanBlocksMax,
@@ -114,6 +115,8 @@ struct wg_engine {
   // the row-at-a-time closure: control block, levels and flags; the renumbered graph; the pool of
   // columns; bitmaps
   DevBuf rctl, rgraph, rpool, rbits;
+  uint32_t* h_flag = nullptr;  // pinned: the latest fetch() that has arrived
+  uint32_t fetch_seq = 0;
   uint8_t* h_reach = nullptr;  // pinned: the control blocks and the first levels, read back
   uint32_t reach_levels = kReachLevels;
   bool res_is_reach = false;   // the latest result is in that form
@@ -280,6 +283,24 @@ void ensure(wg_engine* e, DevBuf& b, size_t bytes) {
 
 void sync_stream(wg_engine* e) {
   hip_check(e, hipStreamSynchronize(e->stream), "hipStreamSynchronize");
+  ++e->syncs;
+}
+
+// Reads a few device words (a multiple of 4 bytes) into pinned memory and waits for them: a kernel
+// stores them there and the host polls for its last word (a copy and a stream synchronisation took
+// about 10 us more).  A read that is long in coming is waited for by the stream.
+void fetch(wg_engine* e, void* dst, const void* src, size_t bytes) {
+  const uint32_t seq = ++e->fetch_seq;
+  launch_fetch(e->stream, dst, src, bytes, e->h_flag, seq);
+  hip_check(e, hipGetLastError(), "readback");
+  const auto t0 = std::chrono::steady_clock::now();
+  for (uint32_t spin = 1; __atomic_load_n(e->h_flag, __ATOMIC_ACQUIRE) != seq; ++spin) {
+    if (spin % 256 == 0 && std::chrono::steady_clock::now() - t0 > kFetchSpin) {
+      hip_check(e, hipStreamSynchronize(e->stream), "hipStreamSynchronize");
+      break;
+    }
+    __builtin_ia32_pause();
+  }
   ++e->syncs;
 }
 
@@ -835,10 +856,7 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
       hip_check(e, hipMemsetAsync(e->rctl.p, 0, head_bytes + 2 * span, e->stream), "memset");
       launch_reach_graph<K>(e->stream, e->grid, e->d_ctrl, b.E, m, a, b.jtot);
       launch_reach(e->stream, e->grid, m, a, b.jtot, b.off);
-      hip_check(e, hipMemcpyAsync(e->h_reach, e->rctl.p,
-                                  sizeof(ReachCtl) + kReachReadLevels * sizeof(ReachLevel), hipMemcpyDeviceToHost,
-                                  e->stream), "readback");
-      sync_stream(e);
+      fetch(e, e->h_reach, e->rctl.p, sizeof(ReachCtl) + kReachReadLevels * sizeof(ReachLevel));
       if (e->cancel && e->cancel->load()) fail(e, WG_ERR_CANCELLED, "cancelled");
       if (rc->stop & (kReachUnsupported | kReachTooLarge)) return false;
       if (attempt == 12) return false;
@@ -947,9 +965,7 @@ bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_optio
   constexpr size_t level_bytes = kSgLevels * sizeof(SgLevel);
   // reads the control blocks and the first `levels` levels
   auto read = [&](uint32_t levels) {
-    hip_check(e, hipMemcpyAsync(e->h_reach, e->rctl.p, head + std::min(levels, kSgLevels) * sizeof(SgLevel),
-                                hipMemcpyDeviceToHost, e->stream), "readback");
-    sync_stream(e);
+    fetch(e, e->h_reach, e->rctl.p, head + std::min(levels, kSgLevels) * sizeof(SgLevel));
     if (e->cancel && e->cancel->load()) fail(e, WG_ERR_CANCELLED, "cancelled");
   };
   try {
@@ -1147,9 +1163,7 @@ bool triangles(wg_engine* e, uint64_t m, int w, wg_stats* st) {
     }
     const uint64_t cols = std::min(m, e->key_space);
     launch_tri_count<K>(e->stream, e->grid, m, a, b.cand[passes & 1], cols > 32ull * kTriWords);
-    hip_check(e, hipMemcpyAsync(e->h_reach, base, sizeof(ReachCtl) + sizeof(TriCtl), hipMemcpyDeviceToHost, e->stream),
-              "readback");
-    sync_stream(e);
+    fetch(e, e->h_reach, base, sizeof(ReachCtl) + sizeof(TriCtl));
   } catch (const Fail& f) {
     if (f.st != WG_ERR_CAPACITY && f.st != WG_ERR_OUT_OF_MEMORY) throw;
     e->err.clear();
@@ -1686,9 +1700,7 @@ wg_status solve(wg_engine* e, int query, uint32_t num, const uint64_t* d_offsets
       launch_ctrl_set(e->stream, e->d_ctrl, zero);
       launch_max_id(e->stream, e->grid, e->d_ctrl, d_src, d_dst, m);
       if (num) launch_check_offsets(e->stream, e->grid, e->d_ctrl, d_offsets, num, m);
-      hip_check(e, hipMemcpyAsync(&e->h_rb[0].c, e->d_ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, e->stream),
-                "readback");
-      sync_stream(e);
+      fetch(e, &e->h_rb[0].c, e->d_ctrl, sizeof(Ctrl));
       if (e->h_rb[0].c.bad_input) {
         e->err = "batch offsets must start at 0, not decrease and end at m";
         return WG_ERR_INVALID_ARG;
@@ -1988,6 +2000,8 @@ wg_status wg_engine_create_ex(int device, const wg_allocator* allocator, wg_engi
     fixed((void**)&e->d_bstart, kFixedBytes[5]);
     hip_check(e, hipHostMalloc((void**)&e->h_rb, 3 * sizeof(Readback)), "hipHostMalloc");
     hip_check(e, hipHostMalloc((void**)&e->h_reach, kReachHostBytes), "hipHostMalloc");
+    hip_check(e, hipHostMalloc((void**)&e->h_flag, 64), "hipHostMalloc");
+    *e->h_flag = 0;
     hip_check(e, hipMemsetAsync(e->d_ctrl, 0, sizeof(Ctrl), nullptr), "hipMemsetAsync");
     for (int s = 0; s < 2; ++s)
       hip_check(e, hipEventCreateWithFlags(&e->ev_batch[s], hipEventDisableTiming), "hipEventCreate");
@@ -2041,6 +2055,7 @@ void wg_engine_destroy(wg_engine* e) {
   if (e->h_rb) (void)hipHostFree(e->h_rb);
   if (e->h_rec) (void)hipHostFree(e->h_rec);
   if (e->h_reach) (void)hipHostFree(e->h_reach);
+  if (e->h_flag) (void)hipHostFree(e->h_flag);
   for (int s = 0; s < 2; ++s)
     if (e->ev_batch[s]) (void)hipEventDestroy(e->ev_batch[s]);
   if (e->ev_done) (void)hipEventDestroy(e->ev_done);

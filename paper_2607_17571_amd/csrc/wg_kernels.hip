@@ -2905,6 +2905,15 @@ __global__ __launch_bounds__(kBlock) void k_offsets2(const K* __restrict__ A, ui
 
 // The control block written from a kernel argument (captured when the launch is enqueued, so
 // no host staging buffer has to outlive the call that queues it).
+// Device memory into pinned host memory, then `seq` into the word the host polls.
+__global__ __launch_bounds__(kBlock) void k_fetch(uint32_t* __restrict__ dst, const uint32_t* __restrict__ src,
+                                                  uint32_t words, uint32_t* flag, uint32_t seq) {
+  for (uint32_t i = threadIdx.x; i < words; i += kBlock) dst[i] = src[i];
+  __threadfence_system();  // (every thread's words are out before the flag)
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __global__ void k_ctrl_set(Ctrl* ctrl, Ctrl v) {
   if (threadIdx.x == 0) *ctrl = v;
 }
@@ -3215,6 +3224,11 @@ void launch_unpack(hipStream_t s, const Grid& g, const K* keys, uint64_t n, cons
 
 void launch_ctrl_set(hipStream_t s, Ctrl* ctrl, const Ctrl& v) {
   hipLaunchKernelGGL(k_ctrl_set, dim3(1), dim3(kWave), 0, s, ctrl, v);
+}
+
+void launch_fetch(hipStream_t s, void* dst, const void* src, size_t bytes, uint32_t* flag, uint32_t seq) {
+  hipLaunchKernelGGL(k_fetch, dim3(1), dim3(kBlock), 0, s, (uint32_t*)dst, (const uint32_t*)src,
+                     (uint32_t)(bytes / sizeof(uint32_t)), flag, seq);
 }
 
 void launch_resume(hipStream_t s, Ctrl* ctrl, uint64_t cand_cap, uint64_t full_cap, uint32_t clear_hook) {

@@ -248,6 +248,9 @@ template <typename K>
 void launch_unpack(hipStream_t s, const Grid& g, const K* keys, uint64_t n, const K* keys2, uint64_t n2, int w,
                    uint32_t* src, uint32_t* dst);
 
+// Copies `bytes` (a multiple of 4) into pinned host memory and then stores `seq` in *flag (pinned).
+void launch_fetch(hipStream_t s, void* dst, const void* src, size_t bytes, uint32_t* flag, uint32_t seq);
+
 void launch_resume(hipStream_t s, Ctrl* ctrl, uint64_t cand_cap, uint64_t full_cap,
                    uint32_t clear_hook);
 
