@@ -345,7 +345,7 @@ void size_buffers(wg_engine* e, bool keep, uint32_t iter, const IterRec* last) {
 
 // Free every relation buffer (the engine stays usable; the next solve starts small).
 void release_relations(wg_engine* e) {
-  if (e->stream) hip_check(e, hipStreamSynchronize(e->stream), "hipStreamSynchronize");
+  hip_check(e, hipStreamSynchronize(e->stream), "hipStreamSynchronize");  // (the null stream's too)
   for (int s = 0; s < 2; ++s) {
     free_buf(e, e->cand[s]);
     free_buf(e, e->full[s]);
@@ -2342,8 +2342,8 @@ wg_status wg_result_offsets(const wg_result* r, uint64_t* offsets_out, uint64_t 
   if (err == hipSuccess) err = mark_engine_use(r, s);
   if (host) {
     if (err == hipSuccess) err = hipMemcpyAsync(offsets_out, dst, bytes, hipMemcpyDeviceToHost, s);
-    (void)hipFreeAsync(dst, s);
     if (err == hipSuccess) err = hipStreamSynchronize(s);
+    (void)hipFreeAsync(dst, s);
   }
   return err == hipSuccess ? WG_OK : device_error(r, "result offsets");
 }
@@ -2385,8 +2385,8 @@ wg_status wg_result_copy(const wg_result* r, uint32_t* src_out, uint32_t* dst_ou
   if (host) {
     if (err == hipSuccess) err = hipMemcpyAsync(src_out, tmp, r->n * 4, hipMemcpyDeviceToHost, s);
     if (err == hipSuccess) err = hipMemcpyAsync(dst_out, tmp + r->n, r->n * 4, hipMemcpyDeviceToHost, s);
-    (void)hipFreeAsync(tmp, s);
     if (err == hipSuccess) err = hipStreamSynchronize(s);
+    (void)hipFreeAsync(tmp, s);
   }
   return err == hipSuccess ? WG_OK : device_error(r, "result copy");
 }
@@ -2394,10 +2394,11 @@ wg_status wg_result_copy(const wg_result* r, uint32_t* src_out, uint32_t* dst_ou
 void wg_result_free(wg_result* r) {
   if (!r) return;
   if (r->owned) {
-    // stream-ordered on the null stream, after every read enqueued on any stream (each
-    // copy recorded an event), without waiting for the whole device
+    // after every read enqueued on any stream (each copy recorded an event), waited for here: memory
+    // freed on the null stream behind a wait went to another stream's allocation while a copy was
+    // still to read it (a server's next result, with the GPU busy).  No wait for the whole device.
     (void)hipSetDevice(r->device);
-    for (hipEvent_t ev : r->uses) (void)hipStreamWaitEvent(nullptr, ev, 0);
+    for (hipEvent_t ev : r->uses) (void)hipEventSynchronize(ev);
     (void)hipFreeAsync(r->owned, nullptr);
     if (r->release) r->release(r->owned_bytes);
   }
