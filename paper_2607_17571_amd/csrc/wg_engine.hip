@@ -72,6 +72,7 @@ constexpr uint32_t kSgPairRounds = 4;
 constexpr size_t kReachHostBytes = std::max(sizeof(ReachCtl) + kReachReadLevels * sizeof(ReachLevel),
                                             sizeof(ReachCtl) + sizeof(SgCtl) + kSgLevels * sizeof(SgLevel));
 constexpr std::chrono::microseconds kFetchSpin{2000};  // a fetch polls this long
+constexpr uint32_t kReachHostLevels = (uint32_t)((kReachHostBytes - sizeof(ReachCtl)) / sizeof(ReachLevel));
 // fixed arrays of an engine: control block, join and compaction block totals, radix counts
 // and totals (the triangle hits depend on the grid)
 constexpr size_t kFixedBytes[6] = {sizeof(Ctrl), sizeof(uint64_t) * kScanBlocksMax,
@@ -878,15 +879,22 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
       uint32_t n = 0;
       while (n < kReachReadLevels && first[n].n[form]) ++n;
       lev.assign(first, first + n);
-      if (n == kReachReadLevels) {
-        lev.resize(e->reach_levels);
-        hip_check(e, hipMemcpyAsync(lev.data(), a.lev, lev.size() * sizeof(ReachLevel), hipMemcpyDeviceToHost,
-                                    e->stream), "readback");
-        sync_stream(e);
-        n = 0;
-        while (n < lev.size() && lev[n].n[form]) ++n;
-        lev.resize(n);
+      for (uint32_t have = kReachReadLevels; n == have && have < e->reach_levels;) {
+        // deeper: eight times as many, while they fit the pinned memory
+        const uint32_t more = std::min(8 * have, e->reach_levels);
+        lev.resize(more);
+        if (more <= kReachHostLevels) {
+          fetch(e, e->h_reach + sizeof(ReachCtl), a.lev, more * sizeof(ReachLevel));
+          lev.assign(first, first + more);
+        } else {
+          hip_check(e, hipMemcpyAsync(lev.data(), a.lev, more * sizeof(ReachLevel), hipMemcpyDeviceToHost, e->stream),
+                    "readback");
+          sync_stream(e);
+        }
+        while (n < more && lev[n].n[form]) ++n;
+        have = more;
       }
+      lev.resize(n);
       F = C = cand_total = 0;
       for (ReachLevel& l : lev) {
         l.n[0] = l.n[form];
