@@ -18,10 +18,12 @@ its own input, outside the timed region (--no-autotune skips it).  Batched workl
 (tc_batch_er_4096: 4,096 ER instances in one solve) then also time the plain path: the
 same instances solved one at a time with wg_tc.
 
-The JSON line also carries the roofline of the dominant kernel: its algorithmic bytes
-(include/wg.h, wg_stats.stage_bytes) over the HIP-event time of its launches, taken in a
-second run of the same K solves with events around that kernel only (events cost launch
-overlap, so the throughput figure comes from the run without them), against 8 TB/s of
+The JSON line also carries "solve_hbm", the bytes a solve cannot do without (8 per input edge and
+per result tuple) over its time, against 8 TB/s of HBM; the roofline of the dominant kernel of
+the iterations' launches (join, sort, difference, merge), which solves with per-launch events
+take (WG_STAGE_TIMING) where the timed ones run on the renumbered graph and have no stages: its
+algorithmic bytes (include/wg.h, wg_stats.stage_bytes) over the HIP-event time of its launches,
+taken in a second run of K solves with events around that kernel only, against 8 TB/s of
 HBM; and the CPU oracle timed on the host (test infrastructure, used only for this
 baseline), with the CPU model and core counts.  The oracle is single-threaded; a batch
 also gets an all-core figure, its instances spread over worker processes.
@@ -153,6 +155,13 @@ def parse():
     if a.workload is None:
         a.workload = "tc_rmat_s15"
     return a
+
+
+def solve_hbm(edges: int, tuples: int, ms: float) -> dict:
+    """The bytes a solve cannot do without (each edge read once, each tuple written once) over its time."""
+    nbytes = 8 * (edges + tuples)
+    return {"bytes": nbytes, "achieved": round(nbytes / (ms * 1e6), 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            "frac": round(nbytes / (ms * 1e6) / HBM_PEAK_GBS, 4)}
 
 
 SG_EXTRA = "sg_er_500k"
@@ -751,8 +760,9 @@ def measure(args, name: str) -> dict:
     for _ in range(args.warmup):
         solve(wg.make_options(flags=base_flags, **sort_opts))
     torch.cuda.synchronize()
-    # Untimed probe with events on every kernel kind: per-stage breakdown and the dominant
-    # kernel kind, which the instrumented run after the timed region measures alone.
+    # Untimed probe with events on every kernel kind: per-stage breakdown of the iterations'
+    # launches and their dominant kernel kind, which the instrumented run after the timed region
+    # measures alone.
     if args.dominant:
         if args.dominant not in wg.STAGES:
             raise SystemExit(f"--dominant must be one of {wg.STAGES}")
@@ -809,6 +819,7 @@ def measure(args, name: str) -> dict:
                                    else eng.sort_config(st["key_bytes"])["tile_items"])
         tr = measured_traffic(STAGE_KERNELS[dom], name, st["digit_bits"], tile)
         roofline = {"bound": "hbm", "kernel": STAGE_KERNELS[dom], "stage": dom,
+                    "path": "the iterations' launches (WG_STAGE_TIMING)",
                     "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": round(achieved / HBM_PEAK_GBS, 4),
                     "traffic": tr["traffic_bytes_per_launch"] if tr else None,
@@ -855,6 +866,7 @@ def measure(args, name: str) -> dict:
         "stage_algorithmic_gb": probe_gb,
         "stage_hbm_frac": probe_frac,
         "roofline": roofline,
+        "solve_hbm": solve_hbm(edges, st["result_tuples"], ms_per_step),
         "cpu_baseline": None,
     }
     if args.roofline_only:

@@ -58,7 +58,8 @@ typedef enum { WG_QUERY_TC = 0, WG_QUERY_SG = 1, WG_QUERY_TRIANGLES = 2 } wg_que
 
 /* wg_options.flags */
 #define WG_SG_IRREFLEXIVE 0x1u /* SG: drop (x,x) from the final relation */
-#define WG_STAGE_TIMING 0x2u   /* time every kernel launch with HIP events (fills stage_ms) */
+#define WG_STAGE_TIMING 0x2u   /* time every kernel launch with HIP events (fills stage_ms); the
+                                  solve then takes the iterations' launches (WG_LOOP_AUTO) */
 #define WG_NO_SPECULATION 0x4u /* enqueue nothing behind a batch while the host checks it */
 #define WG_JOIN_HASH 0x8u      /* TC and triangles: join through a linear-probing hash table of
                                   E (thread per tuple) instead of the binary-search join of
@@ -88,7 +89,13 @@ typedef enum { WG_QUERY_TC = 0, WG_QUERY_SG = 1, WG_QUERY_TRIANGLES = 2 } wg_que
                                   host-enqueued multi-block launches (ablation) */
 
 /* wg_options.loop_mode */
-#define WG_LOOP_AUTO 0u     /* the default: device-resident loop checked by the host every 2
+#define WG_LOOP_AUTO 0u     /* the default.  A query without any flag but WG_SG_IRREFLEXIVE, with
+                               batch_k = 0 and no test hook runs on the renumbered graph where
+                               its size allows -- TC one source row at a time or as slabs of
+                               columns, SG as pairs or bit matrices, triangles one rotation
+                               each -- with the same result, iterations, delta sizes and
+                               candidates.  Everything else takes the iterations' launches: a
+                               device-resident loop checked by the host every 2
                                iterations (batch_k overrides), with a speculative batch
                                enqueued behind every check; and once the delta (at most
                                1,024-4,096 tuples by key width and query) and an
@@ -161,13 +168,15 @@ typedef struct {
   uint64_t base_tuples;     /* |Delta^0| */
   uint64_t join_candidates; /* candidates summed over iterations, with multiplicity */
   uint64_t host_syncs;      /* host waits on the device during the call */
-  uint64_t resumes;         /* grow-and-resume cycles after a capacity overflow */
+  uint64_t resumes;         /* grow-and-resume cycles after a capacity overflow; TC by rows:
+                               tiers that rows outgrew */
   uint32_t field_bits;      /* radix field width used (bits per id) */
   uint32_t key_bytes;       /* bytes per packed key (4 or 8) */
   double solve_ms;          /* host wall clock of the call */
   double stage_ms[WG_NUM_STAGES];        /* with WG_STAGE_TIMING: summed kernel time */
   uint64_t stage_launches[WG_NUM_STAGES];
-  uint64_t stage_bytes[WG_NUM_STAGES];   /* algorithmic HBM bytes of each kernel kind */
+  uint64_t stage_bytes[WG_NUM_STAGES];   /* algorithmic HBM bytes of each kernel kind (the
+                                            iterations' launches; else 0) */
   uint64_t* delta_sizes;    /* optional caller HOST buffer: |Delta^0| .. |Delta^iterations| */
   uint64_t delta_sizes_cap; /* its capacity in entries (filled up to the capacity) */
   uint32_t digit_bits;      /* radix digit bits per LSD pass used */
