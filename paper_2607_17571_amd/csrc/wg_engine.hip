@@ -57,6 +57,11 @@ constexpr uint64_t kDenseRowsMax = 1ull << 28;  // largest dense edge index (1 G
 // The row-at-a-time closure (wg_reach.h).  Ids are ranked through flags by id: spans of up to
 // 2^24 ids, or not much wider than the graph (as for the dense index).
 constexpr uint64_t kReachSpan = 1ull << 24;
+// Ids further apart go by their rank (us a pass, on their own keys through the iterations / by rank):
+// R-MAT scale 15 with 28-bit ids 15,379 / 498, scale 12 30-bit 1,876 / 263, scale 10 (600 edges) 768 /
+// 205; SG scale 14 26-bit 7,488 / 431.  The sort of the 2 m ids costs what the edges' wider keys would.
+// Fewer edges than this seldom have the rows (kReachMinRows) that make it pay.
+constexpr uint64_t kByRankMinEdges = 512, kByRankMaxEdges = 1ull << 28;
 constexpr uint64_t kReachColsMax = 1ull << 20;  // columns of one instance: a bitmap fits one CU's LDS
 constexpr uint64_t kReachBitsCols = 1ull << 18; // ... three bitmaps
 // Slabs at once, without the tiers' thread launch first, while a level over all slabs is at most
@@ -116,6 +121,7 @@ struct wg_engine {
   // the row-at-a-time closure: control block, levels and flags; the renumbered graph; the pool of
   // columns; bitmaps
   DevBuf rctl, rgraph, rpool, rbits;
+  DevBuf rids, rkeys;  // ids by rank; result keys mapped back
   uint32_t* h_flag = nullptr;  // pinned: the latest fetch() that has arrived
   uint32_t fetch_seq = 0;
   uint8_t* h_reach = nullptr;  // pinned: the control blocks and the first levels, read back
@@ -354,7 +360,7 @@ void release_relations(wg_engine* e) {
     free_buf(e, e->delta[s]);
   }
   for (DevBuf* b : {&e->E, &e->U, &e->R, &e->Edst, &e->rowa, &e->rowb, &e->off, &e->rec, &e->htab, &e->tailrun,
-                    &e->rctl, &e->rgraph, &e->rpool, &e->rbits})
+                    &e->rctl, &e->rgraph, &e->rpool, &e->rbits, &e->rids, &e->rkeys})
     free_buf(e, *b);
   e->cand_cap = e->full_cap = e->edge_cap = e->row_cap = e->rec_cap = 0;
 }
@@ -1191,16 +1197,19 @@ bool triangles(wg_engine* e, uint64_t m, int w, wg_stats* st) {
   return true;
 }
 
+constexpr wg_status kNotByRank = WG_ERR_STALE;  // (within the engine) the ids' own keys have to do
+
 template <typename K>
 wg_status run(wg_engine* e, int query, const uint32_t* src, const uint32_t* dst, uint64_t m,
-              const wg_options& o, int w, int ib, wg_stats* st) {
+              const wg_options& o, int w, int ib, wg_stats* st, bool by_rank = false) {
   e->key_bits = ib + 2 * w;
   e->seen_cand.store(0, std::memory_order_relaxed);
   e->sort = e->trial ? *e->trial : e->tune[sizeof(K) == 8];
   if (o.radix_digit_bits) e->sort.rb = (int)o.radix_digit_bits;
   if (o.tile_items) e->sort.items = (int)o.tile_items;
   const int passes = sort_passes(e->key_bits, e->sort.rb);
-  e->key_bytes = sizeof(K);
+  // (edges by rank stand for wider ones: the buffers are sized for those)
+  e->key_bytes = by_rank ? sizeof(uint64_t) : sizeof(K);
   e->edge_cap = std::max<uint64_t>(e->edge_cap, m);
   e->cand_cap = std::min(std::max<uint64_t>({e->cand_cap, 2 * m, 1u << 20}), kMaxKeys);
   e->full_cap = std::min(std::max<uint64_t>({e->full_cap, 2 * m, 1u << 20}), kMaxKeys);
@@ -1249,6 +1258,7 @@ wg_status run(wg_engine* e, int query, const uint32_t* src, const uint32_t* dst,
     if (st) {
       st->iterations = st->base_tuples = st->join_candidates = st->resumes = 0;
     }
+    if (by_rank) return kNotByRank;
     b = make_bufs<K>(e);
   }
   launch_edge_index<K>(e->stream, e->grid, e->d_ctrl, b, w, stage(e, WG_STAGE_PREPARE));
@@ -1603,6 +1613,77 @@ bool is_device_pointer(const void* p) {
   return a.type == hipMemoryTypeDevice;
 }
 
+// A query whose ids are too far apart for the renumbering (w bits): on their ranks among the graph's
+// ids, of at most 2 m, and its result back in ids.  kNotByRank where the forms on the renumbered
+// graph do not take it, or no memory for it.
+wg_status run_by_rank(wg_engine* e, int query, const uint32_t* src, const uint32_t* dst, uint64_t m, const wg_options& o,
+                      int w, wg_stats* st) {
+  const int rank_w = std::max(1, ceil_log2(2 * m));
+  const uint64_t space = e->key_space, dense = e->dense_rows;
+  try {
+    // the ids, sorted in the candidate buffers
+    e->key_bytes = sizeof(uint64_t);
+    e->key_bits = w;
+    e->sort = e->tune[0];
+    e->edge_cap = std::max<uint64_t>(e->edge_cap, m);
+    e->cand_cap = std::min(std::max<uint64_t>({e->cand_cap, 2 * m, 1u << 20}), kMaxKeys);
+    e->full_cap = std::min(std::max<uint64_t>({e->full_cap, 2 * m, 1u << 20}), kMaxKeys);
+    size_buffers(e, false, 0, nullptr);
+    ensure(e, e->rids, (4 * m + 4) * sizeof(uint32_t));
+    uint32_t* const ids = (uint32_t*)e->rids.p;
+    uint32_t* const by_rank = ids + 2 * m;  // sources, then destinations, then how many ids
+    Ctrl c0;
+    std::memset(&c0, 0, sizeof(Ctrl));
+    c0.m_in = 2 * m;
+    launch_ctrl_set(e->stream, e->d_ctrl, c0);
+    Bufs<uint32_t> b = make_bufs<uint32_t>(e);
+    launch_ids_gather(e->stream, e->grid, src, dst, m, b.cand[0]);
+    enqueue_sort<uint32_t>(e, b, &e->d_ctrl->m_in, 2 * m * sizeof(uint32_t) <= kSmallSortBytes ? 2 : 0);
+    const uint32_t* const sorted = b.cand[sort_passes(w, e->sort.rb) & 1];
+    launch_ids(e->stream, e->grid, sorted, src, dst, m, b.jtot, ids, by_rank + 2 * m, by_rank, by_rank + m);
+    e->key_space = 2 * m;
+    e->dense_rows = 0;
+    e->row_wise = true;
+    wg_status r = 2 * rank_w <= 32 ? run<uint32_t>(e, query, by_rank, by_rank + m, m, o, rank_w, 0, st, true)
+                                   : run<uint64_t>(e, query, by_rank, by_rank + m, m, o, rank_w, 0, st, true);
+    if (r != WG_OK) throw Fail{r == kNotByRank ? WG_ERR_CAPACITY : r};
+    if (e->res_is_reach) {
+      ReachResult& q = e->res_reach;
+      launch_ids_back(e->stream, e->grid, ids, (uint32_t*)q.colkey, q.cols);
+      if (q.rowkey != q.colkey) launch_ids_back(e->stream, e->grid, ids, (uint32_t*)q.rowkey, q.rows);
+      q.w = w;
+    } else if (query != WG_QUERY_TRIANGLES && e->res_n) {
+      ensure(e, e->rkeys, e->res_n * sizeof(uint64_t));
+      if (2 * rank_w <= 32)
+        launch_ids_keys<uint32_t>(e->stream, e->grid, ids, (const uint32_t*)e->res_keys, e->res_n, rank_w, w, (uint64_t*)e->rkeys.p);
+      else
+        launch_ids_keys<uint64_t>(e->stream, e->grid, ids, (const uint64_t*)e->res_keys, e->res_n, rank_w, w, (uint64_t*)e->rkeys.p);
+      e->res_keys = e->rkeys.p;
+    }
+    e->res_w = w;
+    e->key_bits = 2 * w;
+    if (st) {
+      st->field_bits = (uint32_t)w;
+      st->key_bytes = (uint32_t)sizeof(uint64_t);
+      st->digit_bits = (uint32_t)e->tune[1].rb;
+      st->sort_passes = (uint32_t)sort_passes(2 * w, e->tune[1].rb);
+    }
+    return WG_OK;
+  } catch (const Fail& f) {
+    if (f.st != WG_ERR_CAPACITY && f.st != WG_ERR_OUT_OF_MEMORY) throw;
+    e->err.clear();
+    free_buf(e, e->rids);
+    free_buf(e, e->rkeys);
+    e->key_space = space;
+    e->dense_rows = dense;
+    e->row_wise = false;
+    e->res_is_reach = false;
+    e->res_keys = nullptr;
+    e->res_n = 0;
+    return kNotByRank;
+  }
+}
+
 // num == 0: a single instance; else a batch of `num` instances with edge offsets.
 wg_status solve(wg_engine* e, int query, uint32_t num, const uint64_t* d_offsets,
                 const uint32_t* d_src, const uint32_t* d_dst, uint64_t m,
@@ -1741,13 +1822,17 @@ wg_status solve(wg_engine* e, int query, uint32_t num, const uint64_t* d_offsets
       // device).
       e->key_space = space;
       const uint64_t widest = std::min<uint64_t>(m, num > 1 ? 1ull << w : space);
-      e->row_wise = m >= (query == WG_QUERY_TRIANGLES ? kTriMinEdges : kReachMinRows) && space >= kReachMinRows &&
-                    (space <= kReachSpan || (space <= kDenseRowsMax && space <= 16 * m + (1u << 20))) &&
-                    (query == WG_QUERY_SG || widest <= kReachColsMax) &&
-                    (o.flags & ~(query == WG_QUERY_SG ? WG_SG_IRREFLEXIVE : 0u)) == 0 && o.loop_mode == WG_LOOP_AUTO && o.batch_k == 0 &&
-                    o.force_overflow_at_iter == 0 && !e->trial;
-      wg_status r = (ib + 2 * w <= 32) ? run<uint32_t>(e, query, d_src, d_dst, m, o, w, ib, st)
-                                       : run<uint64_t>(e, query, d_src, d_dst, m, o, w, ib, st);
+      const bool forms = m >= (query == WG_QUERY_TRIANGLES ? kTriMinEdges : kReachMinRows) && space >= kReachMinRows &&
+                         (query == WG_QUERY_SG || widest <= kReachColsMax) &&
+                         (o.flags & ~(query == WG_QUERY_SG ? WG_SG_IRREFLEXIVE : 0u)) == 0 &&
+                         o.loop_mode == WG_LOOP_AUTO && o.batch_k == 0 && o.force_overflow_at_iter == 0 && !e->trial;
+      e->row_wise = forms && (space <= kReachSpan || (space <= kDenseRowsMax && space <= 16 * m + (1u << 20)));
+      wg_status r = kNotByRank;
+      if (forms && !e->row_wise && num == 0 && 2 * w > 32 && m >= kByRankMinEdges && m <= kByRankMaxEdges)
+        r = run_by_rank(e, query, d_src, d_dst, m, o, w, st);
+      if (r == kNotByRank)
+        r = (ib + 2 * w <= 32) ? run<uint32_t>(e, query, d_src, d_dst, m, o, w, ib, st)
+                               : run<uint64_t>(e, query, d_src, d_dst, m, o, w, ib, st);
       if (r != WG_OK) return r;
       hip_check(e, hipEventRecord(e->ev_done, e->stream), "hipEventRecord");
       e->done_pending = true;
@@ -2053,6 +2138,8 @@ void wg_engine_destroy(wg_engine* e) {
   release(e->rgraph);
   release(e->rpool);
   release(e->rbits);
+  release(e->rids);
+  release(e->rkeys);
   dev_free(e, e->d_ctrl, kFixedBytes[0], nullptr);
   dev_free(e, e->d_jtot, kFixedBytes[1], nullptr);
   dev_free(e, e->d_bcnt, kFixedBytes[2], nullptr);

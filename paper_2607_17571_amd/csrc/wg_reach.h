@@ -161,6 +161,18 @@ struct ReachResult {
 template <typename K>
 void launch_reach_graph(hipStream_t s, const Grid& g, const Ctrl* ctrl, const K* E, uint64_t m, const ReachArgs& a,
                         uint64_t* part);
+// Ids too far apart to rank by their value: replaced by their rank among the graph's ids, which keeps
+// their order.  keys: the 2 m ids, gathered; sorted by the caller (count: where their number is);
+// then the distinct ones into ids (n_ids: how many), and the edges by rank.
+void launch_ids_gather(hipStream_t s, const Grid& g, const uint32_t* src, const uint32_t* dst, uint64_t m, uint32_t* keys);
+void launch_ids(hipStream_t s, const Grid& g, const uint32_t* sorted, const uint32_t* src, const uint32_t* dst, uint64_t m,
+                uint64_t* part, uint32_t* ids, uint32_t* n_ids, uint32_t* src_out, uint32_t* dst_out);
+// Back: n ranks in place, and n packed keys of w-bit ranks as keys of ids.
+void launch_ids_back(hipStream_t s, const Grid& g, const uint32_t* ids, uint32_t* ranks, uint64_t n);
+template <typename K>
+void launch_ids_keys(hipStream_t s, const Grid& g, const uint32_t* ids, const K* keys, uint64_t n, int w, int out_w,
+                     uint64_t* out);
+
 // The rows, then their offsets (off: rows + 1 entries; part: g.scan entries of scratch).
 void launch_reach(hipStream_t s, const Grid& g, uint64_t m, const ReachArgs& a, uint64_t* part, uint32_t* off);
 

@@ -120,10 +120,33 @@ void launch_reach_instances(hipStream_t s, const Grid& g, const ReachResult& r, 
   hipLaunchKernelGGL(k_reach_instances, dim3(blocks_for(g, (uint64_t)num + 1)), dim3(kBlock), 0, s, r, num, out);
 }
 
+void launch_ids_gather(hipStream_t s, const Grid& g, const uint32_t* src, const uint32_t* dst, uint64_t m, uint32_t* keys) {
+  hipLaunchKernelGGL(k_ids_gather, dim3(blocks_for(g, m)), dim3(kBlock), 0, s, src, dst, m, keys);
+}
+
+void launch_ids(hipStream_t s, const Grid& g, const uint32_t* sorted, const uint32_t* src, const uint32_t* dst, uint64_t m,
+                uint64_t* part, uint32_t* ids, uint32_t* n_ids, uint32_t* src_out, uint32_t* dst_out) {
+  hipLaunchKernelGGL(k_ids_count, dim3(g.scan), dim3(kBlock), 0, s, sorted, 2 * m, part);
+  hipLaunchKernelGGL(k_ids_write, dim3(g.scan), dim3(kBlock), 0, s, sorted, 2 * m, (const uint64_t*)part, ids, n_ids);
+  hipLaunchKernelGGL(k_ids_map, dim3(blocks_for(g, m)), dim3(kBlock), 0, s, (const uint32_t*)ids, (const uint32_t*)n_ids, src,
+                     dst, m, src_out, dst_out);
+}
+
+void launch_ids_back(hipStream_t s, const Grid& g, const uint32_t* ids, uint32_t* ranks, uint64_t n) {
+  hipLaunchKernelGGL(k_ids_back, dim3(blocks_for(g, n)), dim3(kBlock), 0, s, ids, ranks, n);
+}
+
+template <typename K>
+void launch_ids_keys(hipStream_t s, const Grid& g, const uint32_t* ids, const K* keys, uint64_t n, int w, int out_w,
+                     uint64_t* out) {
+  hipLaunchKernelGGL(k_ids_keys<K>, dim3(blocks_for(g, n)), dim3(kBlock), 0, s, ids, keys, n, w, out_w, out);
+}
+
 #define WG_REACH_INSTANTIATE(K)                                                                              \
   template void launch_reach_graph<K>(hipStream_t, const Grid&, const Ctrl*, const K*, uint64_t, const ReachArgs&, \
                                       uint64_t*);                                                            \
-  template void launch_reach_keys<K>(hipStream_t, const Grid&, const ReachResult&, uint64_t, K*);
+  template void launch_reach_keys<K>(hipStream_t, const Grid&, const ReachResult&, uint64_t, K*);            \
+  template void launch_ids_keys<K>(hipStream_t, const Grid&, const uint32_t*, const K*, uint64_t, int, int, uint64_t*);
 WG_REACH_INSTANTIATE(uint32_t)
 WG_REACH_INSTANTIATE(uint64_t)
 

@@ -56,6 +56,77 @@ __device__ __forceinline__ uint32_t reach_claim(ReachCtl* rc, int tier, uint32_t
 }
 
 // ---------------------------------------------------------------------------
+// Ids by rank (wg_reach.h): the distinct ids of a sorted run, a static range of it per block, and each
+// edge's two ids found among them by bisection.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kBlock) void k_ids_gather(const uint32_t* __restrict__ src, const uint32_t* __restrict__ dst,
+                                                       uint64_t m, uint32_t* __restrict__ keys) {
+  for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < m; i += (uint64_t)gridDim.x * kBlock) {
+    keys[i] = src[i];
+    keys[m + i] = dst[i];
+  }
+}
+
+constexpr uint32_t kIdsTile = kBlock;
+__global__ __launch_bounds__(kBlock) void k_ids_count(const uint32_t* __restrict__ v, uint64_t n, uint64_t* __restrict__ part) {
+  __shared__ uint64_t s_wave[kWavesPerBlock];
+  uint64_t lo, hi, c = 0, total;
+  block_range(n, kIdsTile, lo, hi);
+  for (uint64_t i = lo + threadIdx.x; i < hi; i += kBlock) c += i == 0 || v[i - 1] != v[i] ? 1 : 0;
+  (void)block_excl_scan<uint64_t>(c, s_wave, total);
+  if (threadIdx.x == 0) part[blockIdx.x] = total;
+}
+__global__ __launch_bounds__(kBlock) void k_ids_write(const uint32_t* __restrict__ v, uint64_t n, const uint64_t* __restrict__ part,
+                                                      uint32_t* __restrict__ ids, uint32_t* __restrict__ n_ids) {
+  __shared__ uint64_t s_wave[kWavesPerBlock];
+  uint64_t before = 0, run;
+  for (uint32_t x = threadIdx.x; x < blockIdx.x; x += kBlock) before += part[x];
+  (void)block_excl_scan<uint64_t>(before, s_wave, run);
+  uint64_t lo, hi;
+  block_range(n, kIdsTile, lo, hi);
+  for (uint64_t i0 = lo; i0 < hi; i0 += kBlock) {
+    const uint64_t i = i0 + threadIdx.x;
+    const bool head = i < hi && (i == 0 || v[i - 1] != v[i]);
+    uint64_t total;
+    const uint64_t at = run + block_excl_scan<uint64_t>(head ? 1 : 0, s_wave, total);
+    if (head) ids[at] = v[i];
+    run += total;
+  }
+  if (hi == n && lo < hi && threadIdx.x == 0) *n_ids = (uint32_t)run;
+}
+
+__device__ __forceinline__ uint32_t id_rank(const uint32_t* __restrict__ ids, uint32_t n, uint32_t id) {
+  uint32_t lo = 0;
+  for (uint32_t len = n; len > 1;) {
+    const uint32_t half = len / 2;
+    if (ids[lo + half] <= id) lo += half;
+    len -= half;
+  }
+  return lo;
+}
+__global__ __launch_bounds__(kBlock) void k_ids_map(const uint32_t* __restrict__ ids, const uint32_t* __restrict__ n_ids,
+                                                    const uint32_t* __restrict__ src, const uint32_t* __restrict__ dst,
+                                                    uint64_t m, uint32_t* __restrict__ src_out, uint32_t* __restrict__ dst_out) {
+  const uint32_t n = *n_ids;
+  for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < m; i += (uint64_t)gridDim.x * kBlock) {
+    src_out[i] = id_rank(ids, n, src[i]);
+    dst_out[i] = id_rank(ids, n, dst[i]);
+  }
+}
+__global__ __launch_bounds__(kBlock) void k_ids_back(const uint32_t* __restrict__ ids, uint32_t* ranks, uint64_t n) {
+  for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (uint64_t)gridDim.x * kBlock)
+    ranks[i] = ids[ranks[i]];
+}
+template <typename K>
+__global__ __launch_bounds__(kBlock) void k_ids_keys(const uint32_t* __restrict__ ids, const K* __restrict__ keys, uint64_t n,
+                                                     int w, int out_w, uint64_t* __restrict__ out) {
+  for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (uint64_t)gridDim.x * kBlock) {
+    const K k = keys[i];
+    out[i] = ((uint64_t)ids[(uint32_t)(k >> w)] << out_w) | ids[(uint32_t)k & id_mask(w)];
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Renumbering.  Every edge flags its row's and its column's key (plain byte stores: no atomics);
 // the flags become one 16-byte word per 32 keys with the bits and the ranks before them, so that
 // a key's row or column number is one load; then the rows' starts, then the edge records.  A few

@@ -33,6 +33,29 @@ def test_same_generation(engine, graph, irreflexive):
     assert_same(*run(engine, "sg", src, dst, opts), oracle.sg(src, dst, irreflexive=irreflexive))
 
 
+WIDE = {  # ids over 32 bits: by rank
+    "tc_slabs": ("tc", lambda: inputs.rmat(12, 3_600, *inputs.RMAT_ABCD, seed=12)),
+    "tc_tiers": ("tc", lambda: inputs.erdos_renyi(60_000, 50_000, seed=5)),
+    "sg_pairs": ("sg", lambda: inputs.erdos_renyi(20_000, 16_000, seed=6)),
+    "sg_pairs_wide_keys": ("sg", lambda: inputs.erdos_renyi(90_000, 70_000, seed=7)),
+    "sg_matrices": ("sg", lambda: inputs.rmat(11, 1_800, *inputs.RMAT_ABCD, seed=12)),
+    "few_rows": ("tc", lambda: inputs.complete_dag(60)),
+}
+
+
+@pytest.mark.parametrize("bits", [25, 32])
+@pytest.mark.parametrize("graph", sorted(WIDE))
+def test_ids_by_rank(engine, graph, bits):
+    query, make = WIDE[graph]
+    src, dst = inputs.scatter_ids(*make(), bits, seed=bits)
+    if bits == 32:  # the largest id there is
+        top = np.uint32(0xFFFFFFFF)
+        src, dst = np.where(src == src.max(), top, src), np.where(dst == src.max(), top, dst)
+    s, d, st = run(engine, query, src, dst)
+    assert_same(s, d, st, getattr(oracle, query)(src, dst))
+    assert st["key_bytes"] == 8
+
+
 @pytest.mark.parametrize("scale,m", [(12, 40_000), (15, 100_000), (17, 60_000)])
 def test_triangles(engine, scale, m):
     src, dst = inputs.rmat(scale, m, *inputs.RMAT_ABCD, seed=scale)
