@@ -65,7 +65,9 @@ constexpr uint64_t kByRankMinEdges = 512, kByRankMaxEdges = 1ull << 28;
 constexpr uint64_t kReachColsMax = 1ull << 20;  // columns of one instance: a bitmap fits one CU's LDS
 constexpr uint64_t kReachBitsCols = 1ull << 18; // ... three bitmaps
 // Slabs at once, without the tiers' thread launch first, while a level over all slabs is at most
-// this many word operations (edges x columns / 32): a few microseconds
+// this many word operations (edges x columns / 32): a few microseconds (us with no such line, here, at
+// 24M: random graphs of 2,000 vertices 331 / 194 / 209, 8,000 499 / 299 / 319, 20,000 339 / 319 /
+// 403; R-MAT scale 12 230 / 186 / 203)
 constexpr uint64_t kSlabAlways = 3u << 20;
 constexpr uint32_t kReachLevels = 4096;  // levels allotted at first (grown eightfold when passed)
 constexpr uint32_t kReachLevelsMax = 1u << 21;

@@ -23,14 +23,21 @@
 
 namespace wg {
 
-constexpr uint32_t kSgDense = 256;       // matrices from one base candidate per this many pairs on
-constexpr uint32_t kSgPairDegree = 64;   // largest out-degree the pair form takes (a wave
-                                         // expands up to 64 pairs by itself)
+// Matrices from one base candidate per this many pairs of columns on (us with the line at 1/16, here,
+// 1/4,096: random graph of 6,000 vertices 397 / 400 / 601; R-MAT scale 10 565 / 236 / 230, scale 14
+// 337 / 347 / 323).
+constexpr uint32_t kSgDense = 256;
+// Largest out-degree the pair form takes: a wave expands up to 64 pairs, of at most 4,096 candidates
+// each, by itself.
+constexpr uint32_t kSgPairDegree = 64;
+// Pairs to expand in a round that one workgroup takes alone (6 us for a thin one, 10 us as a launch of
+// its own; us a pass on 500,000 vertices / a batch of 256 graphs: 128 pairs 894 / 598, 256 885 / 590,
+// 512 876 / 574, 1,024 888 / 584, 2,048 930 / 613).
+constexpr uint32_t kSgTail = 512;
+constexpr uint32_t kSgProbes = 128;      // buckets of 4 slots probed before the table counts as full
 constexpr uint32_t kSgThreads = 1024;
 constexpr uint32_t kSgBuf = 2048;        // new pairs a block buffers
 constexpr uint32_t kSgEdgeThreads = 1024;
-constexpr uint32_t kSgTail = 2048;       // pairs to expand in a round that one workgroup takes alone
-constexpr uint32_t kSgProbes = 128;      // buckets of 4 slots probed before the table counts as full
 
 enum : uint32_t { kSgTableFull = 1, kSgListFull = 2, kSgDeep = 4 };
 
