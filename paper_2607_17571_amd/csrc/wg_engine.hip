@@ -12,6 +12,7 @@
 #include <chrono>
 #include <cmath>
 #include <functional>
+#include <mutex>
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -1934,10 +1935,52 @@ void engine_trim(wg_engine* e) {
   e->res_n = e->res_n2 = 0;
 }
 
+// Memory of results that were freed while copies out of it were still queued: given back once those
+// have run (looked at whenever a result is detached or freed).  Freed stream-ordered behind the copies
+// it went to another stream's allocation before a copy had read it.
+namespace {
+struct PendingFree {
+  void* p;
+  int device;
+  std::vector<hipEvent_t> uses;
+};
+std::mutex pending_mu;
+std::vector<PendingFree> pending;
+
+void free_pending() {
+  std::lock_guard<std::mutex> lock(pending_mu);
+  for (size_t i = 0; i < pending.size();) {
+    PendingFree& f = pending[i];
+    while (!f.uses.empty() && hipEventQuery(f.uses.back()) == hipSuccess) {
+      (void)hipEventDestroy(f.uses.back());
+      f.uses.pop_back();
+    }
+    if (!f.uses.empty()) {
+      ++i;
+      continue;
+    }
+    (void)hipSetDevice(f.device);
+    (void)hipFreeAsync(f.p, nullptr);
+    pending[i] = std::move(pending.back());
+    pending.pop_back();
+  }
+  (void)hipGetLastError();  // ("not ready" is no error)
+}
+
+void free_after(void* p, int device, std::vector<hipEvent_t> uses) {
+  {
+    std::lock_guard<std::mutex> lock(pending_mu);
+    pending.push_back(PendingFree{p, device, std::move(uses)});
+  }
+  free_pending();
+}
+}  // namespace
+
 wg_status result_detach(const wg_result* r, hipStream_t s, std::function<void(uint64_t)> release,
                         wg_result** out, uint64_t* bytes) {
   const wg_status v = check_result(r);
   if (v != WG_OK) return v;
+  free_pending();
   wg_result* c = new wg_result(*r);
   c->engine = nullptr;
   c->device = result_device(r);
@@ -2491,12 +2534,10 @@ wg_status wg_result_copy(const wg_result* r, uint32_t* src_out, uint32_t* dst_ou
 void wg_result_free(wg_result* r) {
   if (!r) return;
   if (r->owned) {
-    // after every read enqueued on any stream (each copy recorded an event), waited for here: memory
-    // freed on the null stream behind a wait went to another stream's allocation while a copy was
-    // still to read it (a server's next result, with the GPU busy).  No wait for the whole device.
-    (void)hipSetDevice(r->device);
-    for (hipEvent_t ev : r->uses) (void)hipEventSynchronize(ev);
-    (void)hipFreeAsync(r->owned, nullptr);
+    // once every read enqueued on any stream (each copy recorded an event) has run, without waiting
+    // for any of them
+    free_after(r->owned, r->device, std::move(r->uses));
+    r->uses.clear();
     if (r->release) r->release(r->owned_bytes);
   }
   for (hipEvent_t ev : r->uses) (void)hipEventDestroy(ev);

@@ -26,7 +26,7 @@ def test_copy_queued_behind_other_work():
         job = server.submit("tc", to_gpu(src), to_gpu(dst))
         time.sleep(0.2)  # (solved before the stream of the copy is busy)
         torch.cuda._sleep(50_000_000)  # some tens of milliseconds on the current stream
-        s, d, _, _ = job.wait()  # copies behind that, then frees the result
+        s, d, _, _ = job.wait()  # copies behind that, and frees the result without waiting for it
         jobs = [server.submit(q, a, b) for q, a, b in with_inputs]
         for j in jobs:
             j.wait(want_result=False)
