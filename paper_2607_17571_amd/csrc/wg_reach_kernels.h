@@ -19,13 +19,13 @@ __device__ __forceinline__ uint64_t reach_alloc(const ReachArgs& a, uint32_t n) 
 
 // Adds a level's counts to the block's LDS table (levels below kReachLdsLevels) or to memory.
 __device__ __forceinline__ void reach_count(unsigned long long (*s_lev)[2], const ReachArgs& a, uint32_t lv,
-                                            uint32_t n, uint32_t d) {
+                                            uint32_t n, unsigned long long d) {
   if (lv < kReachLdsLevels) {
     if (n) atomicAdd(&s_lev[lv][0], (unsigned long long)n);
-    if (d) atomicAdd(&s_lev[lv][1], (unsigned long long)d);
+    if (d) atomicAdd(&s_lev[lv][1], d);
   } else if (lv < a.lev_cap) {
     if (n) atomicAdd(&a.lev[lv].n[a.form], (unsigned long long)n);
-    if (d) atomicAdd(&a.lev[lv].d[a.form], (unsigned long long)d);
+    if (d) atomicAdd(&a.lev[lv].d[a.form], d);
   } else {
     atomicOr(&a.rc->stop, (uint32_t)kReachDeep);
   }
@@ -522,7 +522,7 @@ __device__ __forceinline__ void slab_run(const ReachArgs& a, uint32_t* s_mem, un
     }
     __syncthreads();
     for (uint32_t lv = 0;; ++lv) {
-      uint32_t found = 0, deg = 0;
+      uint32_t found = 0, deg = 0;  // (a thread's columns, 576 at most, have at most 2^20 edges each)
 #pragma unroll
       for (int k = 0; k < RP; ++k) {
         if ((uint32_t)k * TH >= rows) continue;  // (uniform; rows past the last have no bits)
@@ -540,9 +540,10 @@ __device__ __forceinline__ void slab_run(const ReachArgs& a, uint32_t* s_mem, un
         WG_FENCE_LOADS;  // (registers: one row's loads at a time)
       }
       found = wave_sum<uint32_t>(found);
-      deg = wave_sum<uint32_t>(deg);
+      unsigned long long sum = wave_sum<uint32_t>(deg);
+      if (__builtin_amdgcn_ballot_w64(deg >> 26 != 0)) sum = wave_sum<uint64_t>(deg);  // (else below 2^32)
       if (lane_id() == 0 && found) {
-        reach_count(s_lev, a, lv, found, deg);
+        reach_count(s_lev, a, lv, found, sum);
         s_any[lv & 1u] = 1;
       }
       if (tid == 0) s_any[(lv + 1) & 1u] = 0;

@@ -1,6 +1,8 @@
 // The row-at-a-time closure (the kernels of wg_reach_kernels.h, current text) on the CPU SIMT shim:
 // the renumbering, every tier or the slabs, the row offsets and the unpacking, over one graph.
-//   reach_harness <in> <out> <grid> <workers> <pool entries> <bits words> <slab mode>
+//   reach_harness <in> <out> <grid> <workers> <pool entries> <bits words> <slab mode> <rows> <degree>
+// The first <rows> rows get <degree> further edges each as far as the slabs' sums of degrees can tell
+// (the starts of the rows after them move on; no edge is there).
 // in:  u64 header (w, key bytes, instances, |E|, level capacity, span), then the sorted distinct
 //      keys of E (u64).
 // out: u64 stop bits, pool entries used, rows queued for the three tiers, columns per slab; unless
@@ -35,7 +37,7 @@ static void put(std::ofstream& f, const T& v) {
 
 template <typename K>
 int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigned workers, uint64_t pool_cap,
-        uint64_t bits_words, int slab_mode, const char* out_path) {
+        uint64_t bits_words, int slab_mode, uint32_t more_rows, uint32_t more, const char* out_path) {
   const int w = (int)h[0];
   const uint64_t m = E64.size(), num = h[2], span = h[5];
   std::vector<K> E(E64.begin(), E64.end());
@@ -94,6 +96,15 @@ int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigne
   simt::launch(G, kBlock, [&] { k_reach_rows<K>(ctrl.get(), E.data(), a.g, a.rc); }, workers);
   simt::launch(G, kBlock, [&] { k_reach_edges<K>(ctrl.get(), E.data(), a.g, a.rc, a.slab_mode); }, workers);
   if (slab_mode != 1) simt::launch(G, kBlock, [&] { k_reach_thread(a); }, workers);
+  if (more) {
+    std::vector<uint32_t> start(rstart.begin(), rstart.begin() + rc->rows + 1);
+    for (uint32_t c = 0; c < rc->cols; ++c)
+      if (cstart[c] != kReachNone) {
+        const uint32_t r = (uint32_t)(std::lower_bound(start.begin(), start.end(), cstart[c]) - start.begin());
+        cstart[c] += std::min(r, more_rows) * more;
+      }
+    for (uint32_t r = 0; r <= rc->rows; ++r) rstart[r] += std::min(r, more_rows) * more;
+  }
   if (slab_mode != 0) {
     simt::launch(G, kSlabThreads, [&] { k_slab<uint32_t>(a); }, workers);
     simt::launch(G, kSlabThreads, [&] { k_slab<uint16_t>(a); }, workers);
@@ -175,6 +186,7 @@ int main(int argc, char** argv) {
   const unsigned workers = (unsigned)atoi(argv[4]);
   const uint64_t pool = strtoull(argv[5], nullptr, 10), bits = strtoull(argv[6], nullptr, 10);
   const int mode = atoi(argv[7]);
-  if (h[1] == 4) return run<uint32_t>(E, h, G, workers, pool, bits, mode, argv[2]);
-  return run<uint64_t>(E, h, G, workers, pool, bits, mode, argv[2]);
+  const uint32_t rows = (uint32_t)strtoul(argv[8], nullptr, 10), more = (uint32_t)strtoul(argv[9], nullptr, 10);
+  if (h[1] == 4) return run<uint32_t>(E, h, G, workers, pool, bits, mode, rows, more, argv[2]);
+  return run<uint64_t>(E, h, G, workers, pool, bits, mode, rows, more, argv[2]);
 }

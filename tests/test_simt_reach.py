@@ -35,9 +35,10 @@ def harness(tmp_path_factory):
     return exe
 
 
-def _run(harness, tmp_path, graphs, w=None, kb=4, grid=3, pool=1 << 20, bits=1 << 18, slab=0, levels=4096):
+def _run(harness, tmp_path, graphs, w=None, kb=4, grid=3, pool=1 << 20, bits=1 << 18, slab=0, levels=4096, more=(0, 0)):
     """Closure of one graph or a batch; returns the stop bits, the pool used, the queued rows and the
-    columns per slab, after comparing everything else with the oracle (when nothing stopped it)."""
+    columns per slab, after comparing everything else with the oracle (when nothing stopped it).  more:
+    rows whose vertices count as having that many further out-edges in the slabs' candidates."""
     w = w or max(1, max(int(max(s.max(), d.max())).bit_length() for s, d in graphs if len(s)))
     keys = [np.unique((np.uint64(i) << np.uint64(2 * w)) | (s.astype(np.uint64) << np.uint64(w)) | d.astype(np.uint64))
             for i, (s, d) in enumerate(graphs)]
@@ -47,7 +48,8 @@ def _run(harness, tmp_path, graphs, w=None, kb=4, grid=3, pool=1 << 20, bits=1 <
     with open(inp, "wb") as f:
         np.array([w, kb, len(graphs), E.size, levels, span], dtype=np.uint64).tofile(f)
         E.tofile(f)
-    r = subprocess.run([str(harness), str(inp), str(out), str(grid), "4", str(pool), str(bits), str(slab)],
+    r = subprocess.run([str(harness), str(inp), str(out), str(grid), "4", str(pool), str(bits), str(slab),
+                        str(more[0]), str(more[1])],
                        capture_output=True, text=True, timeout=300, env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0"))
     assert r.returncode == 0, r.stdout + r.stderr[-3000:]
     got = np.fromfile(out, dtype=np.uint64)
@@ -64,7 +66,9 @@ def _run(harness, tmp_path, graphs, w=None, kb=4, grid=3, pool=1 << 20, bits=1 <
     for x in refs:
         want[:len(x.delta_sizes)] += np.asarray(x.delta_sizes, dtype=np.int64)
     assert lev[:, 0].tolist() == want[:L].tolist()
-    assert int(lev[:, 1].sum()) == sum(x.candidates for x in refs)
+    rows = np.unique(E >> np.uint64(w)) if more[0] else []
+    extra = int(np.isin(refs[0].dst, rows[:more[0]]).sum()) * more[1] if more[0] else 0
+    assert int(lev[:, 1].sum()) == sum(x.candidates for x in refs) + extra
     ref_pairs = np.concatenate([(x.src.astype(np.uint64) << np.uint64(32)) | x.dst for x in refs])
     np.testing.assert_array_equal(pairs, ref_pairs)
     ref_keys = np.concatenate([(np.uint64(i) << np.uint64(2 * w)) | (x.src.astype(np.uint64) << np.uint64(w))
@@ -145,6 +149,16 @@ def test_slabs_of_many_rows(harness, tmp_path, rows):
     dst = dst.astype(np.uint32)
     assert np.unique(src).size == rows
     assert _run(harness, tmp_path, [(src, dst)], kb=8, slab=1)[3] == (32 if rows == 18431 else 16)
+
+
+@pytest.mark.parametrize("rows", [18431, 18432])
+def test_slabs_of_large_degrees(harness, tmp_path, rows):
+    """A level's candidates beyond 2^32 in one wave of one slab: every row reaches 16 vertices of 2^20
+    out-edges each (a wave takes 1,152 rows: 2^34 candidates), in slabs of both widths."""
+    top = np.repeat(np.arange(17, 17 + rows - 16, dtype=np.uint32), 16)
+    hubs = np.arange(16, dtype=np.uint32)
+    src, dst = np.concatenate([hubs, top]), np.concatenate([np.full(16, 16, np.uint32), np.tile(hubs, rows - 16)])
+    assert _run(harness, tmp_path, [(src, dst)], kb=8, slab=1, more=(16, 1 << 20))[3] == (32 if rows < 18432 else 16)
 
 
 def test_batches(harness, tmp_path):
