@@ -1668,8 +1668,9 @@ wg_status run_by_rank(wg_engine* e, int query, const uint32_t* src, const uint32
     if (st) {
       st->field_bits = (uint32_t)w;
       st->key_bytes = (uint32_t)sizeof(uint64_t);
-      st->digit_bits = (uint32_t)e->tune[1].rb;
-      st->sort_passes = (uint32_t)sort_passes(2 * w, e->tune[1].rb);
+      // (of the ids' own keys, as without the ranks)
+      st->digit_bits = o.radix_digit_bits ? o.radix_digit_bits : (uint32_t)e->tune[1].rb;
+      st->sort_passes = (uint32_t)sort_passes(2 * w, (int)st->digit_bits);
     }
     return WG_OK;
   } catch (const Fail& f) {

@@ -56,6 +56,15 @@ def test_ids_by_rank(engine, graph, bits):
     assert st["key_bytes"] == 8
 
 
+@pytest.mark.parametrize("digit_bits", [0, 10])
+def test_sort_configuration_reported_by_rank(engine, digit_bits):
+    """The digits reported are those of the ids' own keys, as the iterations (batch_k) report them."""
+    src, dst = inputs.scatter_ids(*inputs.rmat(11, 1_800, *inputs.RMAT_ABCD, seed=12), 28, seed=3)
+    st, ref = (run(engine, "tc", src, dst, wg.make_options(radix_digit_bits=digit_bits, batch_k=k))[2] for k in (0, 2))
+    for key in ("field_bits", "key_bytes", "digit_bits", "sort_passes"):
+        assert st[key] == ref[key], key
+
+
 @pytest.mark.parametrize("scale,m", [(12, 40_000), (15, 100_000), (17, 60_000)])
 def test_triangles(engine, scale, m):
     src, dst = inputs.rmat(scale, m, *inputs.RMAT_ABCD, seed=scale)
