@@ -97,6 +97,8 @@ double now_ms() {
 
 }  // namespace
 
+enum : int { kFormNone = 0, kFormIds = 1, kFormAll = 2 };
+
 struct wg_engine {
   int device = 0;
   Grid grid{};
@@ -125,6 +127,9 @@ struct wg_engine {
   // columns; bitmaps
   DevBuf rctl, rgraph, rpool, rbits;
   DevBuf rids, rkeys;  // ids by rank; result keys mapped back
+  // which of those six the solve is using: kFormNone of them (an allocation that does not fit beside
+  // them gives them back first), kFormIds all but the ids' ranks so, kFormAll: all in use
+  int forms_used = kFormNone;
   uint32_t* h_flag = nullptr;  // pinned: the latest fetch() that has arrived
   uint32_t fetch_seq = 0;
   uint8_t* h_reach = nullptr;  // pinned: the control blocks and the first levels, read back
@@ -268,15 +273,28 @@ void free_buf(wg_engine* e, DevBuf& b) {
   b.bytes = 0;
 }
 
+// Gives back what the solve does not use of the renumbered graph's buffers (kept from an earlier solve,
+// or by a form that left the solve to the iterations' launches), so that a budget, a server's
+// reservation or the device holds what the iterations' launches alone need.
+bool release_forms(wg_engine* e) {
+  if (e->forms_used == kFormAll) return false;
+  const size_t before = e->allocated;
+  for (DevBuf* b : {&e->rctl, &e->rgraph, &e->rpool, &e->rbits, &e->rkeys}) free_buf(e, *b);
+  if (e->forms_used == kFormNone) free_buf(e, e->rids);
+  return e->allocated < before;
+}
+
 void alloc_buf(wg_engine* e, DevBuf& b, size_t bytes) {
   bytes = (bytes + 255) & ~size_t(255);
   if (bytes == 0) bytes = 256;
+  if (e->budget && e->allocated + bytes > e->budget) release_forms(e);
   if (e->budget && e->allocated + bytes > e->budget) {
     const uint64_t granted = e->grow_hook ? e->grow_hook(e->allocated + bytes) : 0;
     if (granted < e->allocated + bytes) fail(e, WG_ERR_CAPACITY, "device memory budget exceeded");
     e->budget = granted;
   }
   void* p = dev_alloc(e, bytes, e->stream);
+  if (!p && release_forms(e)) p = dev_alloc(e, bytes, e->stream);
   if (!p) fail(e, WG_ERR_OUT_OF_MEMORY, "device allocation of " + std::to_string(bytes) + " bytes failed");
   b.p = p;
   b.bytes = bytes;
@@ -1246,6 +1264,7 @@ wg_status run(wg_engine* e, int query, const uint32_t* src, const uint32_t* dst,
   launch_compact<K>(e->stream, e->grid, mode, e->d_ctrl, &e->d_ctrl->m_in, b.cand[passes & 1],
                     b.cand[(passes & 1) ^ 1], b, w, 0, 0, stage(e, WG_STAGE_DEDUP_DIFF));
   if (e->row_wise) {
+    e->forms_used = kFormAll;
     const bool done = query == WG_QUERY_TC   ? reach<K>(e, m, w, o, st)
                       : query == WG_QUERY_SG ? same_generation<K>(e, m, w, passes, o, st)
                                              : triangles<K>(e, m, w, st);
@@ -1258,6 +1277,7 @@ wg_status run(wg_engine* e, int query, const uint32_t* src, const uint32_t* dst,
       }
       return WG_OK;
     }
+    e->forms_used = by_rank ? kFormIds : kFormNone;
     if (st) {
       st->iterations = st->base_tuples = st->join_candidates = st->resumes = 0;
     }
@@ -1633,6 +1653,7 @@ wg_status run_by_rank(wg_engine* e, int query, const uint32_t* src, const uint32
     e->full_cap = std::min(std::max<uint64_t>({e->full_cap, 2 * m, 1u << 20}), kMaxKeys);
     size_buffers(e, false, 0, nullptr);
     ensure(e, e->rids, (4 * m + 4) * sizeof(uint32_t));
+    e->forms_used = kFormIds;
     uint32_t* const ids = (uint32_t*)e->rids.p;
     uint32_t* const by_rank = ids + 2 * m;  // sources, then destinations, then how many ids
     Ctrl c0;
@@ -1676,6 +1697,7 @@ wg_status run_by_rank(wg_engine* e, int query, const uint32_t* src, const uint32
   } catch (const Fail& f) {
     if (f.st != WG_ERR_CAPACITY && f.st != WG_ERR_OUT_OF_MEMORY) throw;
     e->err.clear();
+    e->forms_used = kFormNone;
     free_buf(e, e->rids);
     free_buf(e, e->rkeys);
     e->key_space = space;
@@ -1772,6 +1794,7 @@ wg_status solve(wg_engine* e, int query, uint32_t num, const uint64_t* d_offsets
     e->res_keys = e->res_keys2 = nullptr;
     e->res_n = e->res_n2 = 0;
     e->res_is_reach = false;
+    e->forms_used = kFormNone;
     e->syncs = 0;
     e->budget = o.mem_budget_bytes;
     // the budget bounds everything the engine holds: buffers kept from earlier solves
