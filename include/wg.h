@@ -352,8 +352,8 @@ wg_status wg_result_copy(const wg_result* result, uint32_t* src_out, uint32_t* d
                          uint64_t capacity, void* stream);
 
 /* Release a result handle.  An engine's result lives in the engine's buffers until its
- * next solve; a served result owns a device copy, freed in order on the null stream
- * (after copies enqueued on blocking streams). */
+ * next solve; a served result owns a device copy, given back (and credited to the server)
+ * once every copy out of it, on whatever stream, has run.  The call does not wait. */
 void wg_result_free(wg_result* result);
 
 /* ----- Sort configuration and the autotuner (radix digit width and tile size).

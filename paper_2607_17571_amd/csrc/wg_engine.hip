@@ -16,6 +16,7 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/wg.h"
@@ -294,6 +295,7 @@ void alloc_buf(wg_engine* e, DevBuf& b, size_t bytes) {
     e->budget = granted;
   }
   void* p = dev_alloc(e, bytes, e->stream);
+  if (!p && wait_pending()) p = dev_alloc(e, bytes, e->stream);
   if (!p && release_forms(e)) p = dev_alloc(e, bytes, e->stream);
   if (!p) fail(e, WG_ERR_OUT_OF_MEMORY, "device allocation of " + std::to_string(bytes) + " bytes failed");
   b.p = p;
@@ -1952,6 +1954,7 @@ void engine_trim(wg_engine* e) {
   try {
     hip_check(e, hipSetDevice(e->device), "hipSetDevice");
     release_relations(e);
+    (void)free_pending();
   } catch (const Fail&) {
   }
   e->generation++;
@@ -1959,44 +1962,81 @@ void engine_trim(wg_engine* e) {
   e->res_n = e->res_n2 = 0;
 }
 
-// Memory of results that were freed while copies out of it were still queued: given back once those
-// have run (looked at whenever a result is detached or freed).  Freed stream-ordered behind the copies
-// it went to another stream's allocation before a copy had read it.
+// Memory of results that were freed while copies out of it were still queued: given back, and
+// credited to its server, once those have run.  (Freed stream-ordered behind the copies it went to
+// another stream's allocation before a copy had read it.)  A server's idle workers look after the
+// list, as do the calls that free or detach a result, and an allocation that fails waits for it.
 namespace {
 struct PendingFree {
   void* p;
   int device;
+  uint64_t bytes;
+  std::function<void(uint64_t)> release;
   std::vector<hipEvent_t> uses;
 };
 std::mutex pending_mu;
 std::vector<PendingFree> pending;
+std::atomic<size_t> pending_count{0};
+constexpr std::chrono::milliseconds kPendingWait{1000};
 
-void free_pending() {
-  std::lock_guard<std::mutex> lock(pending_mu);
-  for (size_t i = 0; i < pending.size();) {
-    PendingFree& f = pending[i];
-    while (!f.uses.empty() && hipEventQuery(f.uses.back()) == hipSuccess) {
-      (void)hipEventDestroy(f.uses.back());
-      f.uses.pop_back();
-    }
-    if (!f.uses.empty()) {
-      ++i;
-      continue;
-    }
-    (void)hipSetDevice(f.device);
-    (void)hipFreeAsync(f.p, nullptr);
-    pending[i] = std::move(pending.back());
-    pending.pop_back();
-  }
-  (void)hipGetLastError();  // ("not ready" is no error)
+// (the caller's current device stays what it was)
+void give_back(PendingFree& f) {
+  int device = -1;
+  (void)hipGetDevice(&device);
+  if (device != f.device) (void)hipSetDevice(f.device);
+  (void)hipFreeAsync(f.p, nullptr);
+  if (device != f.device && device >= 0) (void)hipSetDevice(device);
+  if (f.release) f.release(f.bytes);
 }
+}  // namespace
 
-void free_after(void* p, int device, std::vector<hipEvent_t> uses) {
+bool have_pending() { return pending_count.load() != 0; }
+
+bool free_pending() {
+  if (pending_count.load() == 0) return false;
+  const bool had_error = hipPeekAtLastError() != hipSuccess;
+  std::vector<PendingFree> done;  // (their servers' locks are taken with the list's released)
   {
     std::lock_guard<std::mutex> lock(pending_mu);
-    pending.push_back(PendingFree{p, device, std::move(uses)});
+    for (size_t i = 0; i < pending.size();) {
+      PendingFree& f = pending[i];
+      // (an event in error will never be reached: its copy has ended as well as it can)
+      while (!f.uses.empty() && hipEventQuery(f.uses.back()) != hipErrorNotReady) {
+        (void)hipEventDestroy(f.uses.back());
+        f.uses.pop_back();
+      }
+      if (!f.uses.empty()) {
+        ++i;
+        continue;
+      }
+      done.push_back(std::move(f));
+      if (i + 1 < pending.size()) pending[i] = std::move(pending.back());
+      pending.pop_back();
+    }
+    pending_count.store(pending.size());
   }
-  free_pending();
+  for (PendingFree& f : done) give_back(f);
+  if (!had_error) (void)hipGetLastError();  // ("not ready" is no error)
+  return pending_count.load() != 0;
+}
+
+bool wait_pending() {
+  if (pending_count.load() == 0) return false;
+  const auto t0 = std::chrono::steady_clock::now();
+  while (free_pending() && std::chrono::steady_clock::now() - t0 < kPendingWait)
+    std::this_thread::sleep_for(std::chrono::microseconds(100));
+  return true;
+}
+
+namespace {
+void free_after(PendingFree f) {
+  std::function<void(uint64_t)> release = f.release;
+  {
+    std::lock_guard<std::mutex> lock(pending_mu);
+    pending.push_back(std::move(f));
+    pending_count.store(pending.size());
+  }
+  if (free_pending() && release) release(0);  // (wakes the workers, which look again)
 }
 }  // namespace
 
@@ -2010,7 +2050,8 @@ wg_status result_detach(const wg_result* r, hipStream_t s, std::function<void(ui
   c->device = result_device(r);
   c->grid = result_grid(r);
   c->owned_bytes = std::max<uint64_t>(r->n * r->key_bytes, 256);
-  if (hipSetDevice(c->device) != hipSuccess || hipMallocAsync(&c->owned, c->owned_bytes, s) != hipSuccess) {
+  auto alloc = [&] { return hipMallocAsync(&c->owned, c->owned_bytes, s) == hipSuccess; };
+  if (hipSetDevice(c->device) != hipSuccess || !(alloc() || (wait_pending() && alloc()))) {
     (void)hipGetLastError();
     delete c;
     return WG_ERR_OUT_OF_MEMORY;
@@ -2018,7 +2059,7 @@ wg_status result_detach(const wg_result* r, hipStream_t s, std::function<void(ui
   // both runs, back to back
   const uint64_t na = r->is_reach ? 0 : r->n - r->n2;
   hipError_t err = wait_engine(r, s);
-  if (r->is_reach) {
+  if (r->is_reach && err == hipSuccess) {
     if (r->key_bytes == 4)
       launch_reach_keys<uint32_t>(s, c->grid, r->reach, r->n, (uint32_t*)c->owned);
     else
@@ -2026,7 +2067,7 @@ wg_status result_detach(const wg_result* r, hipStream_t s, std::function<void(ui
     err = hipGetLastError();
     c->is_reach = false;
   }
-  if (na) err = hipMemcpyAsync(c->owned, r->keys, na * r->key_bytes, hipMemcpyDeviceToDevice, s);
+  if (na && err == hipSuccess) err = hipMemcpyAsync(c->owned, r->keys, na * r->key_bytes, hipMemcpyDeviceToDevice, s);
   if (err == hipSuccess && r->n2)
     err = hipMemcpyAsync((uint8_t*)c->owned + na * r->key_bytes, r->keys2, r->n2 * r->key_bytes,
                          hipMemcpyDeviceToDevice, s);
@@ -2560,9 +2601,8 @@ void wg_result_free(wg_result* r) {
   if (r->owned) {
     // once every read enqueued on any stream (each copy recorded an event) has run, without waiting
     // for any of them
-    free_after(r->owned, r->device, std::move(r->uses));
+    free_after(PendingFree{r->owned, r->device, r->owned_bytes, std::move(r->release), std::move(r->uses)});
     r->uses.clear();
-    if (r->release) r->release(r->owned_bytes);
   }
   for (hipEvent_t ev : r->uses) (void)hipEventDestroy(ev);
   delete r;

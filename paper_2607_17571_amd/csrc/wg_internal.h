@@ -33,8 +33,15 @@ uint64_t engine_seen_candidates(const wg_engine* e);
 // the engine a new job reads engine_seen_candidates of that job from then on).
 void engine_clear_seen(wg_engine* e);
 
+// Memory of freed results whose last copies had not run: gives back what can be now; true while some
+// is left.  wait_pending waits for the rest (a second at most); false if there was none.
+bool have_pending();
+bool free_pending();
+bool wait_pending();
+
 // Copy a result's keys (stream-ordered, then waits) into a device buffer owned by a new
-// handle.  `release(bytes)` runs when that handle is freed.
+// handle.  `release(bytes)` runs when that memory is given back
+// (and `release(0)` when the handle is freed before it can be).
 wg_status result_detach(const wg_result* r, hipStream_t s, std::function<void(uint64_t)> release,
                         wg_result** out, uint64_t* bytes);
 

@@ -43,6 +43,7 @@ enum JobPhase : int { kQueued = 0, kRunning = 1, kDone = 2 };
 constexpr uint64_t kMinReservation = 64ull << 20;
 constexpr uint32_t kMaxPassOver = 16;  // later requests may pass a waiting one this often
 constexpr uint64_t kHoldCandidates = 1ull << 21;  // an iteration this large marks a long solve
+constexpr std::chrono::milliseconds kPendingPoll{1};  // between looks at freed results still being copied
 constexpr double kMaxMemoryWaitMs = 5000.0;  // a growing solve waits this long for memory
 
 struct JobState {
@@ -65,6 +66,7 @@ struct JobState {
   std::vector<uint64_t> deltas;
   std::string error;
   double t_submit = 0, t_start = 0, t_end = 0;
+  double t_alone = 0;  // first found waiting alone for freed results
   uint64_t peak_bytes = 0;
 };
 
@@ -187,6 +189,11 @@ std::shared_ptr<JobState> pick(wg_server* sv, size_t i, uint64_t* grant) {
       for (size_t k = 0; k < sv->slots.size(); ++k)
         if (k != i && sv->slots[k]->trim_requested) pending = true;
       if (pending) return nullptr;
+      // (it gets one try: freed results that are still being copied come back first)
+      if (wg::have_pending()) {
+        if (j.t_alone == 0) j.t_alone = now;
+        if (now - j.t_alone < kMaxMemoryWaitMs) return nullptr;
+      }
       *grant = sv->budget > others ? sv->budget - others : 0;
     } else {
       const uint64_t need = j.reservation;
@@ -243,11 +250,19 @@ void worker(wg_server* sv, size_t i) {
       sv->core->cv.notify_all();
       continue;
     }
+    if (wg::have_pending()) {
+      lk.unlock();
+      wg::free_pending();
+      lk.lock();
+    }
     if (sv->stop && sv->queue.empty()) break;
     uint64_t grant = 0;
     std::shared_ptr<JobState> job = pick(sv, i, &grant);
     if (!job) {
-      if (!me.trim_requested) sv->core->cv.wait(lk);
+      if (me.trim_requested) continue;
+      // (freed results whose copies are still queued: nothing notifies when those have run)
+      if (wg::have_pending()) sv->core->cv.wait_for(lk, kPendingPoll);
+      else sv->core->cv.wait(lk);
       continue;
     }
     JobState& j = *job;
@@ -354,10 +369,16 @@ uint64_t grow(wg_server* sv, size_t i, uint64_t need) {
       return grant;
     }
     if (me.job && me.job->cancel) return 0;
+    if (wg::have_pending()) {  // (freed results: this solve may be all that is running)
+      lk.unlock();
+      wg::free_pending();
+      lk.lock();
+    }
     // can anything still free memory?  another solve that is not itself waiting, or an
     // idle slot whose buffers are (about to be) trimmed
     request_trims(sv, i);
-    bool progress = false;
+    const bool pending = wg::have_pending();
+    bool progress = pending;
     for (size_t k = 0; k < sv->slots.size(); ++k) {
       const Slot& o = *sv->slots[k];
       if (k != i && ((o.job && !o.waiting_memory) || (!o.job && o.resident > 0))) progress = true;
@@ -367,7 +388,7 @@ uint64_t grow(wg_server* sv, size_t i, uint64_t need) {
       return 0;
     }
     me.waiting_memory = true;
-    sv->core->cv.wait_for(lk, std::chrono::milliseconds(50));
+    sv->core->cv.wait_for(lk, pending ? kPendingPoll : std::chrono::milliseconds(50));
     me.waiting_memory = false;
   }
 }
@@ -448,6 +469,7 @@ void wg_server_destroy(wg_server* sv) {
   }
   (void)hipStreamSynchronize(sv->copy_stream);
   (void)hipStreamDestroy(sv->copy_stream);
+  (void)wg::wait_pending();  // (no worker is left to look after freed results)
   {
     std::lock_guard<std::mutex> g(sv->core->mu);
     sv->core->alive = false;
@@ -468,7 +490,8 @@ wg_status wg_submit(wg_server* sv, int query, const uint32_t* src, const uint32_
   j->m = m;
   j->input_bytes = std::max<uint64_t>(8 * m, 256);
   if (hipSetDevice(sv->device) != hipSuccess) return WG_ERR_DEVICE;
-  if (hipMallocAsync((void**)&j->d_edges, j->input_bytes, sv->copy_stream) != hipSuccess) {
+  auto alloc = [&] { return hipMallocAsync((void**)&j->d_edges, j->input_bytes, sv->copy_stream) == hipSuccess; };
+  if (!alloc() && !(wg::wait_pending() && alloc())) {
     (void)hipGetLastError();
     return WG_ERR_OUT_OF_MEMORY;
   }
@@ -600,6 +623,7 @@ void wg_job_free(wg_job* job) {
 
 wg_status wg_server_get_stats(const wg_server* sv, wg_server_stats* out) {
   if (!sv || !out) return WG_ERR_INVALID_ARG;
+  (void)wg::free_pending();  // (held_bytes: what is resident now)
   std::lock_guard<std::mutex> g(sv->core->mu);
   *out = sv->st;
   out->held_bytes = (uint64_t)std::max<int64_t>(sv->core->held, 0);
