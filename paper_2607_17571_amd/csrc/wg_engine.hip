@@ -876,7 +876,8 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
       if (bits) ensure(e, e->rbits, bits * 4);
       a.rc = (ReachCtl*)e->rctl.p;
       a.lev = (ReachLevel*)((uint8_t*)e->rctl.p + sizeof(ReachCtl));
-      a.lev_cap = e->reach_levels;
+      // (a row or slab that passes max_iterations ends the closure)
+      a.lev_cap = (uint32_t)(o.max_iterations ? std::min<uint64_t>(o.max_iterations, e->reach_levels) : e->reach_levels);
       a.g.flags = (uint8_t*)e->rctl.p + head_bytes;
       a.pool = (uint32_t*)e->rpool.p;
       a.pool_cap = std::min<uint64_t>(e->rpool.bytes / 4, kMaxKeys);
@@ -893,6 +894,8 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
       if (rc->stop) {
         // more room, and the rows again
         if (rc->stop & kReachDeep) {
+          if (o.max_iterations && a.lev_cap == o.max_iterations)
+            fail(e, WG_ERR_ITER_LIMIT, "max_iterations reached before the fixpoint");
           if (e->reach_levels >= kReachLevelsMax) return false;
           e->reach_levels *= 8;
         }
@@ -1012,7 +1015,12 @@ bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_optio
     ra.rc = a.rc = (ReachCtl*)e->rctl.p;
     a.sc = (SgCtl*)((uint8_t*)e->rctl.p + sizeof(ReachCtl));
     a.lev = (SgLevel*)((uint8_t*)e->rctl.p + head);
-    a.lev_cap = kSgLevels;
+    // (rounds up to max_iterations show whether the fixpoint is among them)
+    a.lev_cap = (uint32_t)(o.max_iterations ? std::min<uint64_t>(o.max_iterations, kSgLevels - 1) + 1 : kSgLevels);
+    auto check_limit = [&](uint64_t known) {  // all of levels [0, known) found something
+      if (o.max_iterations && known > o.max_iterations)
+        fail(e, WG_ERR_ITER_LIMIT, "max_iterations reached before the fixpoint");
+    };
     a.g = ra.g;
     hip_check(e, hipMemsetAsync(e->rctl.p, 0, head + level_bytes + 2 * ra.g.span, e->stream), "memset");
     launch_reach_graph<K>(e->stream, e->grid, e->d_ctrl, b.E, m, ra, b.jtot);
@@ -1050,6 +1058,7 @@ bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_optio
         for (uint32_t k = 0; k < kSgMatrixRounds; ++k) launch_sg_matrix_round(e->stream, e->grid, a, j++, slabs);
         read(j + 1);
         if (at_fixpoint(j)) break;
+        check_limit(j);
       }
     } else {
       // slots: eight times the base candidates at first (two of which are one pair)
@@ -1076,13 +1085,17 @@ bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_optio
           if (sc->next > j + kReachReadLevels) read(sc->next);
           j = sc->next;
           if (sc->stop || at_fixpoint(j)) break;
+          check_limit(j);
           if (j + 1 >= kSgLevels) return false;
           // rounds until the pairs fit the tail, at their rate of change
           const double f1 = (double)(lev[j - 1].found >> 32), f0 = (double)(lev[j - 2].found >> 32);
           const double r = std::min(0.98, std::max(0.05, f1 / std::max(f0, 1.0)));
           k = (uint32_t)std::min(16.0, std::max(1.0, std::ceil(std::log(kSgTail / f1) / std::log(r))));
         }
-        if (sc->stop & kSgDeep) return false;
+        if (sc->stop & kSgDeep) {
+          check_limit(a.lev_cap);
+          return false;
+        }
         if (!sc->stop) break;
         // too small: cleared and run again
         hip_check(e, hipMemsetAsync(&a.sc->out, 0, sizeof(SgCtl) - offsetof(SgCtl, out) + level_bytes, e->stream), "memset");
@@ -1097,8 +1110,7 @@ bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_optio
     }
     const uint64_t base_n = found(0);
     if (F > kMaxKeys || std::max(C, base) > kMaxKeys) return false;  // (the iterations' launches say so)
-    if (o.max_iterations && rounds > o.max_iterations)
-      fail(e, WG_ERR_ITER_LIMIT, "max_iterations reached before the fixpoint");
+    check_limit(rounds);
     if (st) {
       st->iterations = rounds;
       st->base_tuples = base_n;

@@ -17,17 +17,18 @@ __device__ __forceinline__ uint64_t reach_alloc(const ReachArgs& a, uint32_t n) 
   return at;
 }
 
-// Adds a level's counts to the block's LDS table (levels below kReachLdsLevels) or to memory.
+// Adds a level's counts to the block's LDS table (levels below kReachLdsLevels) or to memory.  (A row or
+// slab that gets to lev_cap ends there.)
 __device__ __forceinline__ void reach_count(unsigned long long (*s_lev)[2], const ReachArgs& a, uint32_t lv,
                                             uint32_t n, unsigned long long d) {
-  if (lv < kReachLdsLevels) {
+  if (lv >= a.lev_cap) {
+    atomicOr(&a.rc->stop, (uint32_t)kReachDeep);
+  } else if (lv < kReachLdsLevels) {
     if (n) atomicAdd(&s_lev[lv][0], (unsigned long long)n);
     if (d) atomicAdd(&s_lev[lv][1], d);
-  } else if (lv < a.lev_cap) {
+  } else {
     if (n) atomicAdd(&a.lev[lv].n[a.form], (unsigned long long)n);
     if (d) atomicAdd(&a.lev[lv].d[a.form], d);
-  } else {
-    atomicOr(&a.rc->stop, (uint32_t)kReachDeep);
   }
 }
 
@@ -548,7 +549,7 @@ __device__ __forceinline__ void slab_run(const ReachArgs& a, uint32_t* s_mem, un
       }
       if (tid == 0) s_any[(lv + 1) & 1u] = 0;
       __syncthreads();
-      if (!s_any[lv & 1u]) break;
+      if (!s_any[lv & 1u] || lv >= a.lev_cap) break;
       uint32_t cur = 0, v = 0;
       auto edge = [&](uint32_t x, uint32_t dx) {
         if (x != cur) {
@@ -1037,6 +1038,10 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_queue(ReachArgs a) {
       const uint32_t fn = NW == 1 ? nq : s_n[from], found = NW == 1 ? nf : s_f[from];
       cnt += found;
       if (found == 0) break;
+      if (lv >= a.lev_cap) {
+        if (tid == 0) atomicOr(&a.rc->stop, (uint32_t)kReachDeep);
+        break;
+      }
       if (fn > QCAP) {
         fail = true;
         break;
@@ -1192,7 +1197,7 @@ __global__ __launch_bounds__(kReachBitsWaves * kWave) void k_reach_bits(ReachArg
       if (tid == 0) s_any[(lv + 1) & 1u] = 0;
       __syncthreads();
       const uint32_t found = s_any[lv & 1u];
-      if (found == 0) break;
+      if (found == 0 || lv >= a.lev_cap) break;
       cnt += found;
       uint32_t dsum = 0;
       for (uint32_t h0 = 0; h0 < halves; h0 += TH) {

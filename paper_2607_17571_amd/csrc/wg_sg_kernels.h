@@ -266,11 +266,11 @@ __global__ __launch_bounds__(kSgThreads) void k_sg_pairs_round(SgArgs a, uint32_
   __shared__ SgOut o;
   __shared__ SgWave s_wave[kWaves];
   const uint32_t tid = threadIdx.x, lane = (uint32_t)lane_id(), wid = tid / kWave;
-  if (j >= a.lev_cap) {
-    if (tid == 0 && blockIdx.x == 0) atomicOr(&a.sc->stop, (uint32_t)kSgDeep);
+  const SgLevel prev = a.lev[j - 1];
+  if (j >= a.lev_cap) {  // (enqueued behind the last round counted; nothing to do after the fixpoint)
+    if (tid == 0 && blockIdx.x == 0 && prev.found != 0) atomicOr(&a.sc->stop, (uint32_t)kSgDeep);
     return;
   }
-  const SgLevel prev = a.lev[j - 1];
   if (block_stop(a.sc->stop != 0)) return;
   const uint32_t fn = (uint32_t)(prev.found >> 32);
   const uint32_t kstart = prev.kstart + (uint32_t)prev.found, fstart = prev.fstart + fn;

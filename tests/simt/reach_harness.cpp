@@ -46,7 +46,7 @@ int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigne
   ctrl->m_unique = m;
   std::unique_ptr<ReachCtl> rc(new ReachCtl);
   std::memset(rc.get(), 0, sizeof(ReachCtl));
-  std::vector<ReachLevel> lev(h[4], ReachLevel{{0, 0}, {0, 0}});
+  std::vector<ReachLevel> lev(std::max<uint64_t>(h[4], kReachThreadCap), ReachLevel{{0, 0}, {0, 0}});
   std::vector<uint32_t> cnt(m, 0xDEADu), seg(m, 0xBEEFu), off(m + 1), pool(std::max<uint64_t>(pool_cap, 1), 0x5A5A5A5Au);
   std::vector<uint32_t> queue[kReachTiers];
   for (auto& q : queue) q.assign(m, 0x77777777u);

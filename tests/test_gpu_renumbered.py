@@ -1,6 +1,8 @@
 """The forms on the renumbered graph at the edges of their rules, through the C ABI, against the
 oracle: same-generation as matrices and as pairs, triangles beyond 65,536 columns."""
 
+import time
+
 import numpy as np
 import pytest
 
@@ -63,6 +65,53 @@ def test_sort_configuration_reported_by_rank(engine, digit_bits):
     st, ref = (run(engine, "tc", src, dst, wg.make_options(radix_digit_bits=digit_bits, batch_k=k))[2] for k in (0, 2))
     for key in ("field_bits", "key_bytes", "digit_bits", "sort_passes"):
         assert st[key] == ref[key], key
+
+
+DEEP = {
+    "tc_slabs": ("tc", lambda: inputs.chain(30_000)),
+    "tc_tiers": ("tc", lambda: inputs.chain(60_000)),
+    "sg_pairs": ("sg", lambda: _two_chains(4_000)),
+}
+
+
+def _two_chains(n):
+    """One root over two chains of n vertices: n rounds of one pair each."""
+    s = np.arange(2 * n, dtype=np.uint32)
+    s, d = np.delete(s, [n - 1, 2 * n - 1]), np.delete(s, [0, n])
+    return np.append(s, np.uint32([2 * n, 2 * n])), np.append(d, np.uint32([0, n]))
+
+
+@pytest.mark.parametrize("graph", sorted(DEEP))
+def test_iteration_limit_bounds_the_work(engine, graph):
+    """A limit far below the fixpoint's depth ends the solve after that many iterations, not at the
+    fixpoint (the closures: 4.5e8 and 1.8e9 tuples, half a second and more)."""
+    query, make = DEEP[graph]
+    s, d = map(to_gpu, make())
+    opts = wg.make_options(max_iterations=12)
+    times = []
+    for _ in range(3):
+        t = time.perf_counter()
+        with pytest.raises(wg.WgError) as ei:
+            engine.solve(query, s, d, opts)
+        times.append(time.perf_counter() - t)
+        assert ei.value.status == wg.WG_ERR_ITER_LIMIT
+    assert min(times) < 0.015
+
+
+@pytest.mark.parametrize("limit", [0, 1, 2])
+@pytest.mark.parametrize("graph", sorted(SG))
+def test_iteration_limit_at_the_fixpoint(engine, graph, limit):
+    """The last iteration that is enough, and one fewer."""
+    src, dst = SG[graph]()
+    ref = oracle.sg(src, dst)
+    if limit == 2:
+        assert_same(*run(engine, "sg", src, dst, wg.make_options(max_iterations=2**64 - 1)), ref)
+    elif limit == 1:
+        assert_same(*run(engine, "sg", src, dst, wg.make_options(max_iterations=ref.iterations)), ref)
+    elif ref.iterations > 1:
+        with pytest.raises(wg.WgError) as ei:
+            run(engine, "sg", src, dst, wg.make_options(max_iterations=ref.iterations - 1))
+        assert ei.value.status == wg.WG_ERR_ITER_LIMIT
 
 
 @pytest.mark.parametrize("scale,m", [(12, 40_000), (15, 100_000), (17, 60_000)])

@@ -183,5 +183,15 @@ def test_too_small_buffers_are_reported(harness, tmp_path):
     src, dst = inputs.erdos_renyi(300, 1500, seed=4)
     stop, _, queued, _ = _run(harness, tmp_path, [(src, dst)], bits=5 * 32)
     assert stop & 2 and queued[3] > 5
+
+
+@pytest.mark.parametrize("levels", [1, 20, 40, 100, 300])
+def test_too_many_levels_are_reported(harness, tmp_path, levels):
+    """Rows and slabs deeper than the levels allotted, in the group tiers, the queue tier above and below
+    the table in LDS, the bits tier and the slabs."""
     for slab in (0, 1):
-        assert _run(harness, tmp_path, [inputs.chain(400)], levels=300, slab=slab)[0] == 8
+        assert _run(harness, tmp_path, [inputs.chain(400)], levels=levels, slab=slab)[0] == 8
+    s, d = inputs.erdos_renyi(300, 1500, seed=4)  # the bits tier, whose rows all lead into the chain
+    deep = np.arange(300, 300 + levels, dtype=np.uint32)
+    s, d = np.concatenate([s, [0], deep]).astype(np.uint32), np.concatenate([d, [300], deep + 1]).astype(np.uint32)
+    assert _run(harness, tmp_path, [(s, d)], levels=levels)[0] & 8
