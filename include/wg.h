@@ -459,7 +459,8 @@ wg_status wg_poll(wg_job* job, int* done);
  * the result, which the caller frees with wg_result_free (once per job). */
 wg_status wg_wait(wg_job* job, wg_result** out, wg_stats* stats);
 /* A queued request ends at once with WG_ERR_CANCELLED; a running one at its next host
- * check. */
+ * check, or (the closure and the thin rounds of SG on the renumbered graph) when its
+ * launches next look. */
 wg_status wg_cancel(wg_job* job);
 wg_status wg_job_get_info(const wg_job* job, wg_job_info* info);
 /* Release the handle (cancels the request if it has not finished). */

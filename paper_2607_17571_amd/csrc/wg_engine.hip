@@ -132,6 +132,7 @@ struct wg_engine {
   // them gives them back first), kFormIds all but the ids' ranks so, kFormAll: all in use
   int forms_used = kFormNone;
   uint32_t* h_flag = nullptr;  // pinned: the latest fetch() that has arrived
+  uint32_t* h_cancel = nullptr;  // ... and whether the solve is cancelled, for launches that are running
   uint32_t fetch_seq = 0;
   uint8_t* h_reach = nullptr;  // pinned: the control blocks and the first levels, read back
   uint32_t reach_levels = kReachLevels;
@@ -318,16 +319,30 @@ void sync_stream(wg_engine* e) {
 
 // Reads a few device words (a multiple of 4 bytes) into pinned memory and waits for them: a kernel
 // stores them there and the host polls for its last word (a copy and a stream synchronisation took
-// about 10 us more).  A read that is long in coming is waited for by the stream.
+// about 10 us more).  A read that is long in coming is waited for by the stream; where a request may
+// be cancelled meanwhile, by looking at both every 50 us; the launches ahead of the read are told.
 void fetch(wg_engine* e, void* dst, const void* src, size_t bytes) {
   const uint32_t seq = ++e->fetch_seq;
   launch_fetch(e->stream, dst, src, bytes, e->h_flag, seq);
   hip_check(e, hipGetLastError(), "readback");
   const auto t0 = std::chrono::steady_clock::now();
+  bool may_stop = e->cancel != nullptr;
   for (uint32_t spin = 1; __atomic_load_n(e->h_flag, __ATOMIC_ACQUIRE) != seq; ++spin) {
-    if (spin % 256 == 0 && std::chrono::steady_clock::now() - t0 > kFetchSpin) {
-      hip_check(e, hipStreamSynchronize(e->stream), "hipStreamSynchronize");
-      break;
+    if (spin % 256 == 0) {
+      if (may_stop && e->cancel->load()) {
+        __atomic_store_n(e->h_cancel, 1u, __ATOMIC_RELEASE);
+        may_stop = false;
+      }
+      if (std::chrono::steady_clock::now() - t0 > kFetchSpin) {
+        hipError_t done = hipErrorNotReady;
+        if (!may_stop) done = hipStreamSynchronize(e->stream);
+        else if ((done = hipStreamQuery(e->stream)) == hipErrorNotReady) (void)hipGetLastError();
+        if (done != hipErrorNotReady) {
+          hip_check(e, done, "readback");
+          break;
+        }
+        std::this_thread::sleep_for(std::chrono::microseconds(50));
+      }
     }
     __builtin_ia32_pause();
   }
@@ -877,6 +892,7 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
       a.rc = (ReachCtl*)e->rctl.p;
       a.lev = (ReachLevel*)((uint8_t*)e->rctl.p + sizeof(ReachCtl));
       // (a row or slab that passes max_iterations ends the closure)
+      a.cancel = e->cancel ? e->h_cancel : nullptr;
       a.lev_cap = (uint32_t)(o.max_iterations ? std::min<uint64_t>(o.max_iterations, e->reach_levels) : e->reach_levels);
       a.g.flags = (uint8_t*)e->rctl.p + head_bytes;
       a.pool = (uint32_t*)e->rpool.p;
@@ -1015,6 +1031,7 @@ bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_optio
     ra.rc = a.rc = (ReachCtl*)e->rctl.p;
     a.sc = (SgCtl*)((uint8_t*)e->rctl.p + sizeof(ReachCtl));
     a.lev = (SgLevel*)((uint8_t*)e->rctl.p + head);
+    a.cancel = e->cancel ? e->h_cancel : nullptr;
     // (rounds up to max_iterations show whether the fixpoint is among them)
     a.lev_cap = (uint32_t)(o.max_iterations ? std::min<uint64_t>(o.max_iterations, kSgLevels - 1) + 1 : kSgLevels);
     auto check_limit = [&](uint64_t known) {  // all of levels [0, known) found something
@@ -1809,6 +1826,7 @@ wg_status solve(wg_engine* e, int query, uint32_t num, const uint64_t* d_offsets
     e->res_n = e->res_n2 = 0;
     e->res_is_reach = false;
     e->forms_used = kFormNone;
+    __atomic_store_n(e->h_cancel, 0u, __ATOMIC_RELEASE);  // (no launch of an earlier solve is running)
     e->syncs = 0;
     e->budget = o.mem_budget_bytes;
     // the budget bounds everything the engine holds: buffers kept from earlier solves
@@ -2216,7 +2234,8 @@ wg_status wg_engine_create_ex(int device, const wg_allocator* allocator, wg_engi
     hip_check(e, hipHostMalloc((void**)&e->h_rb, 3 * sizeof(Readback)), "hipHostMalloc");
     hip_check(e, hipHostMalloc((void**)&e->h_reach, kReachHostBytes), "hipHostMalloc");
     hip_check(e, hipHostMalloc((void**)&e->h_flag, 64), "hipHostMalloc");
-    *e->h_flag = 0;
+    e->h_cancel = e->h_flag + 8;
+    *e->h_flag = *e->h_cancel = 0;
     hip_check(e, hipMemsetAsync(e->d_ctrl, 0, sizeof(Ctrl), nullptr), "hipMemsetAsync");
     for (int s = 0; s < 2; ++s)
       hip_check(e, hipEventCreateWithFlags(&e->ev_batch[s], hipEventDisableTiming), "hipEventCreate");

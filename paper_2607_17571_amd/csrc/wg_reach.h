@@ -76,8 +76,13 @@ enum : uint32_t {
   kReachDeep = 8,         // more levels than the host allotted
   kReachTooLarge = 16,    // more than 2^32 - 16 tuples
   kReachSlabFull = 32,    // the slabs' bits do not fit their buffer: the slabs did not run
-  kReachHalt = kReachUnsupported | kReachDeep | kReachTooLarge,
+  kReachCancelled = 64,   // the host's word said so (ReachArgs::cancel); so for SgCtl::stop
+  kReachHalt = kReachUnsupported | kReachDeep | kReachTooLarge | kReachCancelled,
 };
+// Rows and slabs, and the tail of same-generation, look at `stop` and the host's word every so many levels
+// (a load of 1 to 3 us every 64 levels of 1 us and more), queued rows at the host's word every so many rows.
+constexpr uint32_t kStopLevels = 64;
+constexpr uint32_t kStopRows = 16;
 constexpr unsigned long long kReachMaxTuples = 0xFFFFFFF0ull;
 
 struct ReachLevel {          // [0]: by the tiers, [1]: by the slabs
@@ -136,6 +141,8 @@ struct ReachArgs {
   uint32_t lev_cap;
   uint32_t min_rows;     // (kReachMinRows)
   uint32_t square;       // the result's rows are the columns (same-generation)
+  const uint32_t* cancel;  // pinned: not 0 once the caller gives up (nullptr: never).  (A kernel on a
+                           // stream of its own may be queued behind the very launches it is to end.)
   uint32_t form;         // which of a level's counts the kernel adds to
 };
 

@@ -71,6 +71,13 @@ __device__ __forceinline__ uint32_t rank_col(const RankWord* __restrict__ rank, 
   return r.colpre + bits_below(r.colbits, (uint32_t)key);
 }
 
+// Whether the caller has given up (one thread; then `stop` says so to the others).
+__device__ __forceinline__ bool cancelled(const uint32_t* cancel, uint32_t* stop) {
+  if (!cancel || __hip_atomic_load(cancel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == 0) return false;
+  atomicOr(stop, (uint32_t)kReachCancelled);
+  return true;
+}
+
 // Edge i's place among the slabs' 1,024 stretches of `per` edges: thread i / per reads its k-th edge
 // at k * 1,024 + thread.
 __device__ __forceinline__ uint32_t slab_per(uint32_t edges) { return (edges + kSlabThreads - 1) / kSlabThreads; }

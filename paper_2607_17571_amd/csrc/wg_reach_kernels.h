@@ -9,6 +9,9 @@ __device__ __forceinline__ bool reach_halted(const ReachCtl* rc) {
   return (__hip_atomic_load(&rc->stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kReachHalt) != 0;
 }
 
+// ... or cancelled, from within a long row or slab (one thread)
+__device__ __forceinline__ bool reach_look(const ReachArgs& a) { return reach_halted(a.rc) || cancelled(a.cancel, &a.rc->stop); }
+
 // `n` pool entries (one thread); past the pool's end they are counted but not to be written.
 __device__ __forceinline__ uint64_t reach_alloc(const ReachArgs& a, uint32_t n) {
   const unsigned long long at = atomicAdd(&a.rc->cursor, (unsigned long long)n);
@@ -466,7 +469,7 @@ __device__ __forceinline__ bool slab_chosen(const ReachArgs& a) {
 
 template <typename W, int RP>
 __device__ __forceinline__ void slab_run(const ReachArgs& a, uint32_t* s_mem, unsigned long long (*s_lev)[2],
-                                         uint32_t* s_tab, uint32_t* s_any) {
+                                         uint32_t* s_tab, uint32_t* s_any, uint32_t* s_halt) {
   constexpr uint32_t B = 8 * sizeof(W);  // columns per slab
   constexpr uint32_t TH = kSlabThreads;
   constexpr int EREG = sizeof(W) == 4 ? (int)kSlabEdgeRegs : (int)kSlabEdgeRegs * 3 / 4;
@@ -516,12 +519,15 @@ __device__ __forceinline__ void slab_run(const ReachArgs& a, uint32_t* s_mem, un
 #pragma unroll
     for (int k = 0; k < RP; ++k) S[k] = 0;
     if (tid < 2) s_any[tid] = 0;
+    if (tid == 0) *s_halt = reach_halted(a.rc);
     __syncthreads();
+    if (*s_halt) break;
     for (uint32_t k = 0; k < per; ++k) {
       const uint32_t c = sc[k * TH + tid];
       if (c / B == slab) add(se[k * TH + tid] >> 16, 1u << (c % B));
     }
     __syncthreads();
+    uint32_t look = min(kStopLevels, a.lev_cap);  // the next level to stop at, if need be
     for (uint32_t lv = 0;; ++lv) {
       uint32_t found = 0, deg = 0;  // (a thread's columns, 576 at most, have at most 2^20 edges each)
 #pragma unroll
@@ -542,14 +548,21 @@ __device__ __forceinline__ void slab_run(const ReachArgs& a, uint32_t* s_mem, un
       }
       found = wave_sum<uint32_t>(found);
       unsigned long long sum = wave_sum<uint32_t>(deg);
-      if (__builtin_amdgcn_ballot_w64(deg >> 26 != 0)) sum = wave_sum<uint64_t>(deg);  // (else below 2^32)
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(deg >> 26 != 0) != 0, 0)) sum = wave_sum<uint64_t>(deg);  // (else below 2^32)
       if (lane_id() == 0 && found) {
         reach_count(s_lev, a, lv, found, sum);
         s_any[lv & 1u] = 1;
       }
       if (tid == 0) s_any[(lv + 1) & 1u] = 0;
       __syncthreads();
-      if (!s_any[lv & 1u] || lv >= a.lev_cap) break;
+      if (!s_any[lv & 1u]) break;
+      if (__builtin_expect(lv >= look, 0)) {
+        if (lv >= a.lev_cap) break;
+        if (tid == 0) *s_halt = reach_look(a);
+        __syncthreads();
+        if (*s_halt) break;
+        look = min(lv + kStopLevels, a.lev_cap);
+      }
       uint32_t cur = 0, v = 0;
       auto edge = [&](uint32_t x, uint32_t dx) {
         if (x != cur) {
@@ -602,7 +615,7 @@ __global__ __launch_bounds__(kSlabThreads) void k_slab(ReachArgs a) {
   __shared__ uint32_t s_mem[kSlabLdsWords];
   __shared__ unsigned long long s_lev[kReachLdsLevels][2];
   __shared__ uint32_t s_tab[256 * sizeof(W)];
-  __shared__ uint32_t s_any[2];
+  __shared__ uint32_t s_any[2], s_halt;
   constexpr uint32_t B = 8 * sizeof(W);
   constexpr uint32_t RMAX = B == 32 ? kSlabRows32 : kSlabRows16;
   const uint32_t rows = a.rc->rows;
@@ -620,7 +633,7 @@ __global__ __launch_bounds__(kSlabThreads) void k_slab(ReachArgs a) {
   a.form = 1;
   reach_levels_clear(s_lev);
   __syncthreads();
-  slab_run<W, (int)((RMAX + kSlabThreads) / kSlabThreads)>(a, s_mem, s_lev, s_tab, s_any);
+  slab_run<W, (int)((RMAX + kSlabThreads) / kSlabThreads)>(a, s_mem, s_lev, s_tab, s_any, &s_halt);
   __syncthreads();
   reach_levels_flush(s_lev, a);
 }
@@ -963,7 +976,7 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_queue(ReachArgs a) {
   __shared__ uint32_t s_vis[WORDS];
   __shared__ uint32_t s_front[2][QCAP];
   __shared__ uint32_t s_n[2], s_f[2];  // queued, found
-  __shared__ uint32_t s_row, s_d;
+  __shared__ uint32_t s_row, s_d, s_halt;
   __shared__ uint32_t s_wave[NW];
   __shared__ uint64_t s_pos;
   __shared__ unsigned long long s_lev[kReachLdsLevels][2];
@@ -977,12 +990,13 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_queue(ReachArgs a) {
   const uint64_t lt = lanemask_lt();
   const uint2* __restrict__ edge = a.g.edge;
   const uint32_t edges = a.rc->edges;
-  uint32_t share = 0;
+  uint32_t share = 0, claims = 0;
   for (uint32_t x = tid; x < WORDS; x += TH) s_vis[x] = 0;
   __syncthreads();
   for (;;) {
     if (tid == 0) {
-      const uint32_t at = reach_halted(a.rc) ? kReachNone : reach_claim(a.rc, kQueueTier, n, share);
+      const bool over = reach_halted(a.rc) || (++claims % kStopRows == 0 && cancelled(a.cancel, &a.rc->stop));
+      const uint32_t at = over ? kReachNone : reach_claim(a.rc, kQueueTier, n, share);
       s_row = at == kReachNone ? kReachNone : a.queue[kQueueTier][at];
       s_n[0] = s_n[1] = s_f[0] = s_f[1] = 0;
     }
@@ -1047,13 +1061,19 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_queue(ReachArgs a) {
         break;
       }
       to ^= 1;
+      const bool look = lv % kStopLevels == kStopLevels - 1;
       if constexpr (NW == 1) {
+        if (look && wave_uniform(tid == 0 && reach_look(a))) break;
         nq = nf = 0;
         wave_lds_sync();
       } else {
         __syncthreads();
-        if (tid == 0) s_n[to] = s_f[to] = s_d = 0;
+        if (tid == 0) {
+          s_n[to] = s_f[to] = s_d = 0;
+          s_halt = look && reach_look(a);
+        }
         __syncthreads();
+        if (s_halt) break;
       }
       uint32_t dsum = 0;
       for (uint32_t f = (uint32_t)wid * kWave; f < fn; f += TH)
@@ -1135,7 +1155,7 @@ __global__ __launch_bounds__(kReachBitsWaves * kWave) void k_reach_bits(ReachArg
   __shared__ uint32_t s_vis[WORDS], s_cur[WORDS], s_nxt[WORDS];
   __shared__ ID s_list[NW][LCAP];
   __shared__ uint32_t s_n[NW];
-  __shared__ uint32_t s_row, s_at, s_any[2];
+  __shared__ uint32_t s_row, s_at, s_any[2], s_halt;
   __shared__ unsigned long long s_lev[kReachLdsLevels][2];
   const uint32_t tid = threadIdx.x;
   const uint32_t n = a.rc->queued[kBitsTier];
@@ -1151,12 +1171,13 @@ __global__ __launch_bounds__(kReachBitsWaves * kWave) void k_reach_bits(ReachArg
   const uint32_t edges = a.rc->edges;
   const uint16_t* const cur16 = (const uint16_t*)s_cur;
   ID* const list = s_list[wid];
-  uint32_t share = 0;
+  uint32_t share = 0, claims = 0;
   for (uint32_t x = tid; x < WORDS; x += TH) s_vis[x] = s_cur[x] = s_nxt[x] = 0;
   __syncthreads();
   for (;;) {
     if (tid == 0) {
-      const uint32_t at = reach_halted(a.rc) ? kReachNone : reach_claim(a.rc, kBitsTier, n, share);
+      const bool over = reach_halted(a.rc) || (++claims % kStopRows == 0 && cancelled(a.cancel, &a.rc->stop));
+      const uint32_t at = over ? kReachNone : reach_claim(a.rc, kBitsTier, n, share);
       s_at = at;
       s_row = at == kReachNone ? kReachNone : a.queue[kBitsTier][at];
       s_any[0] = 0;
@@ -1194,10 +1215,13 @@ __global__ __launch_bounds__(kReachBitsWaves * kWave) void k_reach_bits(ReachArg
         reach_count(s_lev, a, lv, mine, 0);
         atomicAdd(&s_any[lv & 1u], mine);
       }
-      if (tid == 0) s_any[(lv + 1) & 1u] = 0;
+      if (tid == 0) {
+        s_any[(lv + 1) & 1u] = 0;
+        s_halt = lv % kStopLevels == kStopLevels - 1 && reach_look(a);
+      }
       __syncthreads();
       const uint32_t found = s_any[lv & 1u];
-      if (found == 0 || lv >= a.lev_cap) break;
+      if (found == 0 || lv >= a.lev_cap || s_halt) break;
       cnt += found;
       uint32_t dsum = 0;
       for (uint32_t h0 = 0; h0 < halves; h0 += TH) {

@@ -67,6 +67,7 @@ struct SgArgs {
   SgCtl* sc;
   SgLevel* lev;
   uint32_t lev_cap;
+  const uint32_t* cancel;    // (as for ReachArgs)
   uint4* edge;               // {column, first edge of its row, edges of its row, edges from this one
                              // to the end of its own row}
   // pairs: columns x <= y as x << 32 | y

@@ -313,6 +313,7 @@ __global__ __launch_bounds__(kSgThreads) void k_sg_pairs_tail(SgArgs a, uint32_t
   __shared__ uint4 s_front[2][kSgTail];
   __shared__ SgWave s_wave[kWaves];
   __shared__ Counts s_cnt[3];  // (this round's; the next one's, cleared; the last one's, being read)
+  __shared__ uint32_t s_stop;
   const uint32_t tid = threadIdx.x, lane = (uint32_t)lane_id(), wid = tid / kWave;
   const SgLevel first = a.lev[j - 1];
   uint32_t fn = (uint32_t)(first.found >> 32);
@@ -322,14 +323,20 @@ __global__ __launch_bounds__(kSgThreads) void k_sg_pairs_tail(SgArgs a, uint32_t
   }
   uint32_t kstart = first.kstart + (uint32_t)first.found, fstart = first.fstart + fn;
   for (uint32_t t = tid; t < fn; t += kSgThreads) s_front[(j - 1) & 1u][t] = a.front[first.fstart + t];
-  if (tid == 0) s_cnt[j % 3] = Counts{0, 0, 0};
+  if (tid == 0) {
+    s_cnt[j % 3] = Counts{0, 0, 0};
+    s_stop = 0;
+  }
   block_lds_sync();
   for (;; ++j) {
     if (j >= a.lev_cap) {
       if (tid == 0) atomicOr(&a.sc->stop, (uint32_t)kSgDeep);
       break;
     }
-    if (tid == 0) s_cnt[(j + 1) % 3] = Counts{0, 0, 0};
+    if (tid == 0) {
+      s_cnt[(j + 1) % 3] = Counts{0, 0, 0};
+      if (j % kStopLevels == 0) s_stop = cancelled(a.cancel, &a.sc->stop);
+    }
     Counts& cnt = s_cnt[j % 3];
     const uint32_t per = min(max((fn + kWaves - 1) / kWaves, 1u), (uint32_t)kWave);
     for (uint32_t base = wid * per; base < fn; base += kWaves * per) {
@@ -365,7 +372,7 @@ __global__ __launch_bounds__(kSgThreads) void k_sg_pairs_tail(SgArgs a, uint32_t
     kstart += nk;
     fstart += nf;
     fn = nf;
-    if (nk == 0 || nf > kSgTail) {
+    if (nk == 0 || nf > kSgTail || s_stop) {
       ++j;
       break;
     }

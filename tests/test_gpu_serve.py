@@ -138,6 +138,42 @@ def test_cancel_queued_request(engine):
     assert stats["cancelled"] == 1
 
 
+CANCELLED = {  # closures of 1.8e9, 6.5e8 and 6.4e8 tuples, half a second and more of launches
+    "tiers": ("tc", lambda: inputs.chain(60_000)),
+    "slabs": ("tc", lambda: inputs.chain(36_000)),
+    "slabs_cycle": ("tc", lambda: inputs.cycle(25_000)),
+}
+
+
+@pytest.mark.parametrize("graph", sorted(CANCELLED))
+def test_cancel_running_request(engine, graph):
+    """A running closure ends soon after it is cancelled, not at its fixpoint, and the slot takes the
+    next request."""
+    query, make = CANCELLED[graph]
+    s, d = map(to_gpu, make())
+    srv = wg.Server(0, slots=1)
+    try:
+        for _ in range(2):
+            job = srv.submit(query, s, d)
+            end = time.time() + 10
+            while job.info()["phase"] == 0 and time.time() < end:
+                time.sleep(0.001)
+            time.sleep(0.02)
+            assert job.info()["phase"] == 1
+            t = time.perf_counter()
+            job.cancel()
+            with pytest.raises(wg.WgError) as ei:
+                job.wait()
+            t = time.perf_counter() - t
+            assert ei.value.status == wg.WG_ERR_CANCELLED
+            small = inputs.grid_dag(20)
+            assert srv.submit("tc", *map(to_gpu, small)).wait()[2]["result_tuples"] == oracle.tc(*small).src.size
+            print(f"[gpu] cancelled after {t * 1e3:.1f} ms", flush=True, file=sys.stderr)
+        assert t < 0.05
+    finally:
+        srv.close()
+
+
 def test_host_pointer_inputs_and_empty_request(engine):
     reqs = inputs.served_requests(6, seed=22, n_lo=50, n_hi=500)
     srv = wg.Server(0, slots=2, mem_budget_bytes=2 << 30)
