@@ -127,6 +127,7 @@ struct wg_engine {
   // the row-at-a-time closure: control block, levels and flags; the renumbered graph; the pool of
   // columns; bitmaps
   DevBuf rctl, rgraph, rpool, rbits;
+  DevBuf rvis;         // bitmaps of the thin tier, all zeros between launches
   DevBuf rids, rkeys;  // ids by rank; result keys mapped back
   // which of those six the solve is using: kFormNone of them (an allocation that does not fit beside
   // them gives them back first), kFormIds all but the ids' ranks so, kFormAll: all in use
@@ -281,7 +282,7 @@ void free_buf(wg_engine* e, DevBuf& b) {
 bool release_forms(wg_engine* e) {
   if (e->forms_used == kFormAll) return false;
   const size_t before = e->allocated;
-  for (DevBuf* b : {&e->rctl, &e->rgraph, &e->rpool, &e->rbits, &e->rkeys}) free_buf(e, *b);
+  for (DevBuf* b : {&e->rctl, &e->rgraph, &e->rpool, &e->rbits, &e->rvis, &e->rkeys}) free_buf(e, *b);
   if (e->forms_used == kFormNone) free_buf(e, e->rids);
   return e->allocated < before;
 }
@@ -398,7 +399,7 @@ void release_relations(wg_engine* e) {
     free_buf(e, e->delta[s]);
   }
   for (DevBuf* b : {&e->E, &e->U, &e->R, &e->Edst, &e->rowa, &e->rowb, &e->off, &e->rec, &e->htab, &e->tailrun,
-                    &e->rctl, &e->rgraph, &e->rpool, &e->rbits, &e->rids, &e->rkeys})
+                    &e->rctl, &e->rgraph, &e->rpool, &e->rbits, &e->rvis, &e->rids, &e->rkeys})
     free_buf(e, *b);
   e->cand_cap = e->full_cap = e->edge_cap = e->row_cap = e->rec_cap = 0;
 }
@@ -865,6 +866,9 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
   a.words = (uint32_t)((cols + 31) / 32);
   a.bits_tier = cols <= kReachBitsCols;
   a.min_rows = kReachMinRows;
+  a.after_groups = sizeof(K) == 8 && a.words >= kThinWords ? kThinTier : kQueueTier;
+  a.vis_words = (a.words + 31u) & ~31u;
+  a.thin_rows = thin_rows(e->grid, a.words);
   const uint64_t level_ops = m * ((cols + 31) / 32);
   a.slab_mode = e->num_inst > 1 ? 0 : (level_ops <= kSlabAlways ? 1 : 2);
   uint64_t pool = std::max<uint64_t>(e->rpool.bytes / 4, std::max<uint64_t>(4 * m, 1u << 20));
@@ -880,11 +884,27 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
       b = make_bufs<K>(e);
       a.cnt = b.rowa;
       a.seg = b.rowb;
-      // queues of at most m rows each, in the candidate buffers (free once E is sorted)
+      // queues of at most m rows each, in the candidate buffers (2 m keys each, free once E is sorted);
+      // the thin tier's columns have 17 bits, so that its keys have 64
       a.queue[0] = (uint32_t*)b.cand[0];
       a.queue[1] = (uint32_t*)b.cand[0] + m;
-      a.queue[2] = (uint32_t*)b.cand[1];
-      a.queue[3] = (uint32_t*)b.cand[1] + m;
+      a.queue[kThinTier] = sizeof(K) == 8 ? (uint32_t*)b.cand[0] + 2 * m : nullptr;
+      a.queue[kQueueTier] = (uint32_t*)b.cand[1];
+      a.queue[kBitsTier] = (uint32_t*)b.cand[1] + m;
+      if (a.after_groups == kThinTier) {
+        const size_t bytes = (size_t)thin_blocks(e->grid, a.vis_words) * a.vis_words * 4;
+        try {
+          if (e->rvis.bytes < bytes) {
+            ensure(e, e->rvis, bytes);
+            hip_check(e, hipMemsetAsync(e->rvis.p, 0, e->rvis.bytes, e->stream), "memset");
+          }
+          a.vis = (uint32_t*)e->rvis.p;
+        } catch (const Fail& f) {
+          if (f.st != WG_ERR_CAPACITY && f.st != WG_ERR_OUT_OF_MEMORY) throw;
+          e->err.clear();
+          a.after_groups = kQueueTier;  // (no memory for it: the queue tier takes them all)
+        }
+      }
       const size_t head_bytes = sizeof(ReachCtl) + (size_t)e->reach_levels * sizeof(ReachLevel);
       ensure(e, e->rctl, head_bytes + 2 * span);
       ensure(e, e->rpool, pool * 4);
@@ -2279,6 +2299,7 @@ void wg_engine_destroy(wg_engine* e) {
   release(e->rgraph);
   release(e->rpool);
   release(e->rbits);
+  release(e->rvis);
   release(e->rids);
   release(e->rkeys);
   dev_free(e, e->d_ctrl, kFixedBytes[0], nullptr);

@@ -24,10 +24,12 @@
 // queued for the next one and starts over there (nothing of it has been counted yet):
 //   thread  <= 16 tuples: the set in registers                         k_reach_thread
 //   groups  <= 64 tuples (4 lanes) and <= 256 (8): a hash set in LDS   k_reach_group
+//   thin    (past 131,072 columns) any size, thin levels: two frontier
+//           queues in LDS, a bitmap of the columns in memory          k_reach_thin
 //   queue   any size, thin levels: a bitmap of the columns and two
 //           frontier queues in LDS (one wave, or a block for wide ones) k_reach_queue
 //   bits    any size, wide levels: three bitmaps in LDS                k_reach_bits
-// The first three write a row's sorted columns to a pool of 32-bit entries, the last writes the
+// All but the last write a row's sorted columns to a pool of 32-bit entries, the last writes the
 // row's bitmap.  The result stays in its form; reading it unpacks it.
 #pragma once
 
@@ -38,8 +40,20 @@
 
 namespace wg {
 
-constexpr int kReachTiers = 4;              // queues between the tiers: two groups, queue, bits
-constexpr int kQueueTier = 2, kBitsTier = 3;
+constexpr int kReachTiers = 5;              // queues between the tiers: two groups, thin, queue, bits
+constexpr int kThinTier = 2, kQueueTier = 3, kBitsTier = 4;
+// The queue tier holds a row's bitmap of all columns in LDS: from this many words on one or two rows
+// per CU.  The thin tier then takes the rows first, 20 per CU (ms a closure by the iterations' launches /
+// with the queue tier alone / with the thin tier: 1,000 chains of 300 vertices 37.7 / 171 / 26.6, 800 of
+// 300 36.2 / 69.5 / 21.0, 100 of 3,000 678 / 1,816 / 127; random graphs of 1,000,000 vertices with
+// 950,000 edges 13.6 / 6.0 / 3.2, of 700,000 with 630,000 6.6 / 1.45 / 1.21).  Up to kThinRounds rows
+// for each that the queue tier has in flight stay there: a binary tree of 2^18 vertices has 1,023, wide
+// ones among them, 1.45 ms so and 1.54 through both.
+constexpr uint32_t kThinWords = 4097;
+constexpr uint32_t kThinQueue = 512;         // rows queued per level (256 and 1,024 alike)
+constexpr uint32_t kThinRounds = 4;
+constexpr uint32_t kThinGroups = 1024;       // of 1,024 columns each, 2^20 at most
+constexpr uint64_t kThinBytes = 256u << 20;  // bitmaps of all rows in flight, at most
 constexpr uint32_t kReachThreadCap = 16;    // tuples a thread's row holds
 constexpr uint32_t kReachChunk = 4096;      // pool entries a block or wave reserves at a time
 constexpr uint32_t kReachLdsLevels = 128;   // levels counted in LDS (deeper ones in memory)
@@ -133,6 +147,10 @@ struct ReachArgs {
   uint32_t* pool;
   uint64_t pool_cap;
   uint32_t* bits;        // bitmap slots of `words` words, or the slabs' bits
+  int after_groups;      // the tier the groups send rows on to: kThinTier or kQueueTier
+  uint32_t* vis;         // thin tier: a bitmap per block, all zeros between launches
+  uint32_t vis_words;    // ... its words (a multiple of 32)
+  uint32_t thin_rows;    // rows up to which it leaves all of them to the queue tier
   uint32_t words;        // words of a row's bitmap: the columns of the widest instance (at most)
   uint64_t slots;
   uint64_t bits_words;   // words of `bits`
@@ -179,6 +197,10 @@ void launch_ids_back(hipStream_t s, const Grid& g, const uint32_t* ids, uint32_t
 template <typename K>
 void launch_ids_keys(hipStream_t s, const Grid& g, const uint32_t* ids, const K* keys, uint64_t n, int w, int out_w,
                      uint64_t* out);
+
+// Blocks of the thin tier, for the bitmaps of `words` words, and the rows up to which it does nothing.
+uint32_t thin_blocks(const Grid& g, uint32_t words);
+uint32_t thin_rows(const Grid& g, uint32_t words);
 
 // The rows, then their offsets (off: rows + 1 entries; part: g.scan entries of scratch).
 void launch_reach(hipStream_t s, const Grid& g, uint64_t m, const ReachArgs& a, uint64_t* part, uint32_t* off);

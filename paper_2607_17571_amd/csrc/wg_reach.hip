@@ -10,6 +10,9 @@ namespace wg {
 
 namespace {
 
+// Blocks of the queue tier past kThinWords.
+uint32_t wide_queue_blocks(int cu, uint32_t words) { return (uint32_t)cu * (words <= 8192 ? 2 : 1); }
+
 // Rows of the queue tier by the widest instance's columns: one wave per row up to 65,536 (bitmaps
 // of at most 8 KB, as many rows per CU as their LDS allows), wider blocks above, where one bitmap
 // takes much of a CU's LDS.
@@ -20,9 +23,11 @@ void launch_queue(hipStream_t s, int cu, const ReachArgs& a) {
   else if (a.words <= 1024) hipLaunchKernelGGL((k_reach_queue<1, 1024, 512>), dim3(cu * 16), B, 0, s, a);
   else if (a.words <= 2048) hipLaunchKernelGGL((k_reach_queue<1, 2048, 512>), dim3(cu * 12), B, 0, s, a);
   else if (a.words <= 4096) hipLaunchKernelGGL((k_reach_queue<1, 4096, 1024>), dim3(cu * 5), B, 0, s, a);
-  else if (a.words <= 8192) hipLaunchKernelGGL((k_reach_queue<4, 8192, 3072>), dim3(cu * 2), dim3(4 * kWave), 0, s, a);
-  else hipLaunchKernelGGL((k_reach_queue<16, 32768, 3072>), dim3(cu), dim3(16 * kWave), 0, s, a);
+  else if (a.words <= 8192) hipLaunchKernelGGL((k_reach_queue<4, 8192, 3072>), dim3(wide_queue_blocks(cu, a.words)), dim3(4 * kWave), 0, s, a);
+  else hipLaunchKernelGGL((k_reach_queue<16, 32768, 3072>), dim3(wide_queue_blocks(cu, a.words)), dim3(16 * kWave), 0, s, a);
 }
+
+constexpr int kThinPerCu = 20;  // (7 KB of LDS each)
 
 void launch_bits(hipStream_t s, int cu, const ReachArgs& a) {
   const dim3 B(kReachBitsWaves * kWave);
@@ -84,6 +89,15 @@ void launch_reach_graph(hipStream_t s, const Grid& g, const Ctrl* ctrl, const K*
                      a.slab_mode);
 }
 
+uint32_t thin_blocks(const Grid& g, uint32_t words) {
+  const uint64_t cu = (uint64_t)std::max(1, g.stream / 8);
+  return (uint32_t)std::min<uint64_t>(cu * kThinPerCu, kThinBytes / 4 / words / kReachXcds * kReachXcds);
+}
+
+uint32_t thin_rows(const Grid& g, uint32_t words) {
+  return kThinRounds * wide_queue_blocks(std::max(1, g.stream / 8), words);
+}
+
 void launch_reach(hipStream_t s, const Grid& g, uint64_t m, const ReachArgs& a, uint64_t* part, uint32_t* off) {
   const int cu = std::max(1, g.stream / 8);
   if (a.slab_mode != 1) hipLaunchKernelGGL(k_reach_thread, dim3(blocks_for(g, m)), dim3(kBlock), 0, s, a);
@@ -95,6 +109,8 @@ void launch_reach(hipStream_t s, const Grid& g, uint64_t m, const ReachArgs& a, 
   if (a.slab_mode != 1) {
     hipLaunchKernelGGL((k_reach_group<0, 4, 64, 128, 32, 32, 2>), dim3(cu * 6), dim3(2 * kWave), 0, s, a);
     hipLaunchKernelGGL((k_reach_group<1, 8, 256, 512, 128, 64, 1>), dim3(cu * 6), dim3(kWave), 0, s, a);
+    if (a.after_groups == kThinTier)
+      hipLaunchKernelGGL((k_reach_thin<kThinQueue, kThinGroups>), dim3(thin_blocks(g, a.vis_words)), dim3(kWave), 0, s, a);
     launch_queue(s, cu, a);
     if (a.bits_tier) launch_bits(s, cu, a);
   }

@@ -20,16 +20,16 @@ __device__ __forceinline__ uint64_t reach_alloc(const ReachArgs& a, uint32_t n) 
   return at;
 }
 
-// Adds a level's counts to the block's LDS table (levels below kReachLdsLevels) or to memory.  (A row or
-// slab that gets to lev_cap ends there.)
+// A row or slab with columns at a level past the last one allotted: the closure ends.
+__device__ __forceinline__ void reach_deep(const ReachArgs& a) { atomicOr(&a.rc->stop, (uint32_t)kReachDeep); }
+
+// Adds a level's counts to the block's LDS table (levels below kReachLdsLevels) or to memory.
 __device__ __forceinline__ void reach_count(unsigned long long (*s_lev)[2], const ReachArgs& a, uint32_t lv,
                                             uint32_t n, unsigned long long d) {
-  if (lv >= a.lev_cap) {
-    atomicOr(&a.rc->stop, (uint32_t)kReachDeep);
-  } else if (lv < kReachLdsLevels) {
+  if (lv < kReachLdsLevels) {
     if (n) atomicAdd(&s_lev[lv][0], (unsigned long long)n);
     if (d) atomicAdd(&s_lev[lv][1], d);
-  } else {
+  } else if (lv < a.lev_cap) {
     if (n) atomicAdd(&a.lev[lv].n[a.form], (unsigned long long)n);
     if (d) atomicAdd(&a.lev[lv].d[a.form], d);
   }
@@ -557,7 +557,10 @@ __device__ __forceinline__ void slab_run(const ReachArgs& a, uint32_t* s_mem, un
       __syncthreads();
       if (!s_any[lv & 1u]) break;
       if (__builtin_expect(lv >= look, 0)) {
-        if (lv >= a.lev_cap) break;
+        if (lv >= a.lev_cap) {
+          if (tid == 0) reach_deep(a);
+          break;
+        }
         if (tid == 0) *s_halt = reach_look(a);
         __syncthreads();
         if (*s_halt) break;
@@ -747,14 +750,16 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_group(ReachArgs a) {
   uint64_t chunk = 0;
   uint32_t left = 0;
   uint32_t* const buf = s_buf[tid / kWave];
+  uint32_t* const next = TIER == 0 ? a.queue[1] : (a.after_groups == kThinTier ? a.queue[kThinTier] : a.queue[kQueueTier]);
+  uint32_t* const queued = &a.rc->queued[TIER == 0 ? 1 : a.after_groups];
   uint32_t fn = 0;      // rows in the wave's buffer
   auto flush = [&]() {  // (the whole wave)
     if (fn == 0) return;
     wave_lds_sync();
     uint32_t at = 0;
-    if (lane == 0) at = atomicAdd(&a.rc->queued[TIER + 1], fn);
+    if (lane == 0) at = atomicAdd(queued, fn);
     at = __shfl(at, 0, kWave);
-    if ((uint32_t)lane < fn) a.queue[TIER + 1][at + lane] = buf[lane];
+    if ((uint32_t)lane < fn) next[at + lane] = buf[lane];
     fn = 0;
     wave_lds_sync();
   };
@@ -837,6 +842,7 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_group(ReachArgs a) {
     }
     wave_lds_sync();
     const bool good = have && !fail;
+    if (good && gl == 0 && level > a.lev_cap) reach_deep(a);
     if (good)
       for (uint32_t x = gl; x < level; x += G) reach_count(s_lev, a, x, q.lev[x] & 0xFFFFu, q.lev[x] >> 16);
     // pool entries of the wave's rows, side by side
@@ -963,6 +969,166 @@ __device__ __forceinline__ void row_columns(const ReachArgs& a, uint32_t row, ui
 }
 
 // ---------------------------------------------------------------------------
+// Thin tier: one row per wave, the set a bitmap of the instance's columns in memory (the wave's own, in
+// its XCD's L2), beside it in LDS a bit per 1,024 columns that has any and the levels' queues.  A level
+// costs the latencies of an edge load and of an atomic in the L2, 1.2 us; what counts is how
+// many rows are in flight, 20 per CU where a bitmap in LDS leaves one or two.  Only the stretches
+// that have columns are read back and cleared.  A level that outgrows the queue sends the row on, and so
+// does one that is not thin by the last level whose counts can still be taken back.
+// ---------------------------------------------------------------------------
+template <uint32_t QCAP, uint32_t GROUPS>  // stretches of 1,024 columns
+__global__ __launch_bounds__(kWave) void k_reach_thin(ReachArgs a) {
+  static_assert(4 * QCAP >= GROUPS && GROUPS % 32 == 0 && GROUPS / 32 <= kWave, "");
+  __shared__ uint32_t s_front[2][QCAP];
+  __shared__ uint32_t s_any[GROUPS / 32];
+  __shared__ unsigned long long s_lev[kReachLdsLevels][2];
+  __shared__ uint32_t s_ln[kReachLdsLevels], s_ld[kReachLdsLevels];
+  const uint32_t lane = threadIdx.x;
+  const uint32_t n = a.rc->queued[kThinTier];
+  if (block_stop(n == 0 || a.rc->slab != 0 || reach_halted(a.rc))) return;
+  if (n <= a.thin_rows) {  // (uniform over the launch)
+    for (uint32_t i = blockIdx.x * kWave + lane; i < n; i += gridDim.x * kWave) a.queue[kQueueTier][i] = a.queue[kThinTier][i];
+    if (lane == 0 && blockIdx.x == 0) a.rc->queued[kQueueTier] = n;
+    return;
+  }
+  reach_levels_clear(s_lev);
+  if (lane < GROUPS / 32) s_any[lane] = 0;
+  __syncthreads();
+  const uint64_t lt = lanemask_lt();
+  const uint2* __restrict__ edge = a.g.edge;
+  const uint32_t edges = a.rc->edges;
+  uint32_t* const vis = a.vis + (uint64_t)blockIdx.x * a.vis_words;
+  uint32_t share = 0, claims = 0;
+  for (;;) {
+    uint32_t row = kReachNone;
+    if (lane == 0 && !reach_halted(a.rc) && !(++claims % kStopRows == 0 && cancelled(a.cancel, &a.rc->stop))) {
+      const uint32_t at = reach_claim(a.rc, kThinTier, n, share);
+      if (at != kReachNone) row = a.queue[kThinTier][at];
+    }
+    row = wave_uniform(row);
+    if (row == kReachNone) break;
+    uint32_t base, width;
+    row_columns(a, row, base, width);
+    if ((width + 31u) / 32u > min(a.vis_words, GROUPS * 32u)) {  // (the host sized it for the widest instance)
+      if (lane == 0) atomicOr(&a.rc->stop, (uint32_t)kReachUnsupported);
+      break;
+    }
+    const uint32_t first = a.g.rstart[row], deg = a.g.rstart[row + 1] - first;
+    int to = 0;
+    uint32_t nq = 0, nf = 0;
+    auto visit = [&](bool on, uint2 rec) {
+      const uint32_t z = (rec.x & ~kReachLast) - base;
+      bool fresh = false;
+      if (on) {
+        const uint32_t bit = 1u << (z & 31u);
+        fresh = (__hip_atomic_fetch_or(&vis[z >> 5], bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) & bit) == 0;
+        if (fresh) atomicOr(&s_any[z >> 15], 1u << ((z >> 10) & 31u));
+      }
+      const uint64_t nb = __builtin_amdgcn_ballot_w64(fresh);
+      if (nb) {  // (uniform)
+        const uint64_t pb = __builtin_amdgcn_ballot_w64(fresh && rec.y != kReachNone);
+        const uint32_t at = nq + (uint32_t)__popcll(pb & lt);
+        if (fresh && rec.y != kReachNone && at < QCAP) s_front[to][at] = rec.y;
+        nq += (uint32_t)__popcll(pb);
+        nf += (uint32_t)__popcll(nb);
+      }
+    };
+    for (uint32_t j = 0; j < deg; j += kWave) {
+      const bool on = j + lane < deg;
+      uint2 rec;
+      rec.x = rec.y = kReachNone;
+      if (on) rec = edge[first + j + lane];
+      visit(on, rec);
+    }
+    uint32_t lv = 0, cnt = 0, look = min(kStopLevels, a.lev_cap);
+    bool fail = false;
+    for (;;) {
+      const int from = to;
+      const uint32_t fn = nq, found = nf;
+      cnt += found;
+      if (found == 0) break;
+      if (__builtin_expect(lv >= look, 0)) {
+        if (lane == 0 && lv >= a.lev_cap) reach_deep(a);
+        if (wave_uniform(lane == 0 && (lv >= a.lev_cap || reach_look(a)))) break;
+        look = min(lv + kStopLevels, a.lev_cap);
+      }
+      if (fn > QCAP || (lv == kReachLdsLevels && fn > QCAP / 4)) {
+        fail = true;
+        break;
+      }
+      to ^= 1;
+      nq = nf = 0;
+      wave_lds_sync();
+      uint32_t dsum = 0;
+      for (uint32_t f = 0; f < fn; f += kWave)
+        dsum += wave_expand(edge, edges, f + lane < fn ? s_front[from][f + lane] : kReachNone, visit);
+      dsum = wave_sum<uint32_t>(dsum);
+      wave_lds_sync();
+      if (lane == 0) {
+        if (lv < kReachLdsLevels) {
+          s_ln[lv] = found;
+          s_ld[lv] = dsum;
+        } else {
+          reach_count(s_lev, a, lv, found, dsum);
+        }
+      }
+      ++lv;
+    }
+    wave_lds_sync();
+    uint64_t pos = ~0ull;
+    if (fail) {
+      if (lane == 0) {
+        if (lv > kReachLdsLevels) atomicOr(&a.rc->stop, (uint32_t)kReachUnsupported);  // (counted already)
+        else a.queue[kQueueTier][atomicAdd(&a.rc->queued[kQueueTier], 1u)] = row;
+      }
+    } else {
+      for (uint32_t x = lane; x < lv && x < kReachLdsLevels; x += kWave) reach_count(s_lev, a, x, s_ln[x], s_ld[x]);
+      if (lane == 0) {
+        pos = reach_alloc(a, cnt);
+        a.cnt[row] = cnt;
+        a.seg[row] = (uint32_t)pos;
+        if (pos + cnt > a.pool_cap) pos = ~0ull;
+      }
+      pos = __shfl(pos, 0, kWave);
+    }
+    // the stretches that have columns, in order (the queues are free)
+    uint16_t* const list = (uint16_t*)&s_front[0][0];
+    uint32_t v = lane < GROUPS / 32 ? s_any[lane] : 0u;
+    const uint32_t c = (uint32_t)__popc(v), incl = wave_incl_scan<uint32_t>(c);
+    const uint32_t groups = __shfl(incl, kWave - 1, kWave);
+    for (uint32_t at = incl - c; v; v &= v - 1) list[at++] = (uint16_t)(lane * 32u + (uint32_t)__ffs(v) - 1u);
+    if (lane < GROUPS / 32) s_any[lane] = 0;
+    wave_lds_sync();
+    // eight at a time, four words a lane
+    for (uint32_t g0 = 0; g0 < groups; g0 += 8) {
+      const uint32_t g = g0 + lane / 8;
+      const uint32_t x0 = g < groups ? (uint32_t)list[g] * 32u + lane % 8 * 4u : 0u;
+      uint32_t b[4], sum = 0;
+#pragma unroll
+      for (uint32_t q = 0; q < 4; ++q)
+        b[q] = g < groups ? __hip_atomic_load(&vis[x0 + q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : 0u;
+#pragma unroll
+      for (uint32_t q = 0; q < 4; ++q) {
+        if (b[q]) __hip_atomic_store(&vis[x0 + q], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        sum += (uint32_t)__popc(b[q]);
+      }
+      if (pos != ~0ull) {
+        const uint32_t ends = wave_incl_scan<uint32_t>(sum);
+        uint64_t at = pos + ends - sum;
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q)
+          for (; b[q]; b[q] &= b[q] - 1) a.pool[at++] = base + (x0 + q) * 32u + (uint32_t)__ffs(b[q]) - 1u;
+        pos += __shfl(ends, kWave - 1, kWave);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // (the words are zero before the next row's bits)
+    wave_lds_sync();
+  }
+  __syncthreads();
+  reach_levels_flush(s_lev, a);
+}
+
+// ---------------------------------------------------------------------------
 // Queue tier: one row per block of NW waves (one wave where the columns' bitmap is at most 8 KB).
 // The set is a bitmap of the instance's columns in LDS; a column whose bit a lane sets first is
 // found, and its row, if it has one, goes to the next level's queue.  Thin, deep rows pay per level
@@ -1045,35 +1211,33 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_queue(ReachArgs a) {
       visit(on, rec);
     }
     __syncthreads();
-    uint32_t lv = 0, cnt = 0;
+    uint32_t lv = 0, cnt = 0, look = min(kStopLevels, a.lev_cap);  // the next level to stop at, if need be
     bool fail = false;
     for (;;) {
       const int from = to;
       const uint32_t fn = NW == 1 ? nq : s_n[from], found = NW == 1 ? nf : s_f[from];
       cnt += found;
       if (found == 0) break;
-      if (lv >= a.lev_cap) {
-        if (tid == 0) atomicOr(&a.rc->stop, (uint32_t)kReachDeep);
-        break;
-      }
-      if (fn > QCAP) {
-        fail = true;
-        break;
+      if (__builtin_expect(fn > QCAP || lv >= look, 0)) {
+        fail = fn > QCAP;
+        if (fail) break;
+        if (tid == 0) {
+          s_halt = lv >= a.lev_cap || reach_look(a);
+          if (lv >= a.lev_cap) reach_deep(a);
+        }
+        if constexpr (NW == 1) wave_lds_sync();
+        else __syncthreads();
+        if (s_halt) break;
+        look = min(lv + kStopLevels, a.lev_cap);
       }
       to ^= 1;
-      const bool look = lv % kStopLevels == kStopLevels - 1;
       if constexpr (NW == 1) {
-        if (look && wave_uniform(tid == 0 && reach_look(a))) break;
         nq = nf = 0;
         wave_lds_sync();
       } else {
         __syncthreads();
-        if (tid == 0) {
-          s_n[to] = s_f[to] = s_d = 0;
-          s_halt = look && reach_look(a);
-        }
+        if (tid == 0) s_n[to] = s_f[to] = s_d = 0;
         __syncthreads();
-        if (s_halt) break;
       }
       uint32_t dsum = 0;
       for (uint32_t f = (uint32_t)wid * kWave; f < fn; f += TH)
@@ -1221,6 +1385,7 @@ __global__ __launch_bounds__(kReachBitsWaves * kWave) void k_reach_bits(ReachArg
       }
       __syncthreads();
       const uint32_t found = s_any[lv & 1u];
+      if (found != 0 && lv >= a.lev_cap && tid == 0) reach_deep(a);
       if (found == 0 || lv >= a.lev_cap || s_halt) break;
       cnt += found;
       uint32_t dsum = 0;

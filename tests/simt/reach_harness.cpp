@@ -1,11 +1,13 @@
 // The row-at-a-time closure (the kernels of wg_reach_kernels.h, current text) on the CPU SIMT shim:
 // the renumbering, every tier or the slabs, the row offsets and the unpacking, over one graph.
-//   reach_harness <in> <out> <grid> <workers> <pool entries> <bits words> <slab mode> <rows> <degree>
+//   reach_harness <in> <out> <grid> <workers> <pool entries> <bits words> <slab mode> <rows> <degree> <thin>
 // The first <rows> rows get <degree> further edges each as far as the slabs' sums of degrees can tell
 // (the starts of the rows after them move on; no edge is there).
 // in:  u64 header (w, key bytes, instances, |E|, level capacity, span), then the sorted distinct
 //      keys of E (u64).
-// out: u64 stop bits, pool entries used, rows queued for the three tiers, columns per slab; unless
+// thin: not 0: with the thin tier, for more than thin - 1 rows.
+// out: u64 stop bits, pool entries used, rows queued for the groups, the queue and the bits tier, columns
+//      per slab, rows queued for the thin tier; unless
 //      the stop bits are set: levels L, then (tuples, degrees) of each, the tuples (src << 32 |
 //      dst, from the unpacked pairs), the keys as the key form writes them and the instances'
 //      offsets.
@@ -23,6 +25,8 @@ template <typename T> inline T atomicCAS(T* p, T c, T v) {
 #define __builtin_amdgcn_wave_barrier simt::wave_sync
 #define __builtin_amdgcn_fence(...) (void)0
 #define __hip_atomic_load(p, ...) __atomic_load_n(p, __ATOMIC_SEQ_CST)
+#define __hip_atomic_store(p, v, ...) __atomic_store_n(p, v, __ATOMIC_SEQ_CST)
+#define __hip_atomic_fetch_or(p, v, ...) __atomic_fetch_or(p, v, __ATOMIC_SEQ_CST)
 #include "wg_launch.h"
 #include "wg_reach_kernels.h"
 #include <fstream>
@@ -37,7 +41,7 @@ static void put(std::ofstream& f, const T& v) {
 
 template <typename K>
 int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigned workers, uint64_t pool_cap,
-        uint64_t bits_words, int slab_mode, uint32_t more_rows, uint32_t more, const char* out_path) {
+        uint64_t bits_words, int slab_mode, uint32_t more_rows, uint32_t more, uint32_t thin, const char* out_path) {
   const int w = (int)h[0];
   const uint64_t m = E64.size(), num = h[2], span = h[5];
   std::vector<K> E(E64.begin(), E64.end());
@@ -77,6 +81,11 @@ int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigne
   a.pool = pool.data();
   a.pool_cap = pool_cap;
   a.words = 32;
+  a.after_groups = thin ? kThinTier : kQueueTier;
+  a.thin_rows = thin ? thin - 1 : 0;
+  a.vis_words = (((uint32_t)m + 31u) / 32u + 31u) & ~31u;
+  std::vector<uint32_t> vis(G * a.vis_words, 0u);
+  a.vis = vis.data();
   std::vector<uint32_t> bits(std::max<uint64_t>(bits_words, 1), 0x33333333u);
   a.bits = bits.data();
   a.bits_words = bits_words;
@@ -113,6 +122,9 @@ int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigne
   if (slab_mode != 1) {
     simt::launch(G, 2 * kWave, [&] { k_reach_group<0, 4, 64, 128, 32, 32, 2>(a); }, workers);
     simt::launch(G, kWave, [&] { k_reach_group<1, 8, 256, 512, 128, 64, 1>(a); }, workers);
+    if (thin) simt::launch(G, kWave, [&] { k_reach_thin<96, 32>(a); }, workers);
+    for (uint32_t x : vis)
+      if (x) return 3;  // (all zeros between launches)
     // (a queue of 96 rows, so that wide levels outgrow it)
     if (one) simt::launch(G, kWave, [&] { k_reach_queue<1, 32, 96>(a); }, workers);
     else simt::launch(G, 4 * kWave, [&] { k_reach_queue<4, 32, 96>(a); }, workers);
@@ -127,8 +139,9 @@ int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigne
   std::ofstream f(out_path, std::ios::binary);
   put(f, rc->stop);
   put(f, rc->cursor);
-  for (int t = 0; t < kReachTiers; ++t) put(f, rc->queued[t]);
+  for (int t : {0, 1, kQueueTier, kBitsTier}) put(f, rc->queued[t]);
   put(f, rc->slab);
+  put(f, rc->queued[kThinTier]);
   if (rc->stop) return 0;
   const int form = rc->slab ? 1 : 0;
   uint64_t L = 0;
@@ -187,6 +200,7 @@ int main(int argc, char** argv) {
   const uint64_t pool = strtoull(argv[5], nullptr, 10), bits = strtoull(argv[6], nullptr, 10);
   const int mode = atoi(argv[7]);
   const uint32_t rows = (uint32_t)strtoul(argv[8], nullptr, 10), more = (uint32_t)strtoul(argv[9], nullptr, 10);
-  if (h[1] == 4) return run<uint32_t>(E, h, G, workers, pool, bits, mode, rows, more, argv[2]);
-  return run<uint64_t>(E, h, G, workers, pool, bits, mode, rows, more, argv[2]);
+  const uint32_t thin = (uint32_t)atoi(argv[10]);
+  if (h[1] == 4) return run<uint32_t>(E, h, G, workers, pool, bits, mode, rows, more, thin, argv[2]);
+  return run<uint64_t>(E, h, G, workers, pool, bits, mode, rows, more, thin, argv[2]);
 }

@@ -67,6 +67,22 @@ def test_sort_configuration_reported_by_rank(engine, digit_bits):
         assert st[key] == ref[key], key
 
 
+@pytest.mark.parametrize("count,length", [(700, 200), (2_700, 100), (40, 3_400)])
+def test_thin_rows_of_wide_graphs(engine, count, length):
+    """Chains side by side, more than 131,072 columns in all: rows up to 64 levels deep, deeper, and past
+    the levels counted in LDS."""
+    v = np.arange(count * length, dtype=np.uint32).reshape(count, length)
+    order = np.random.default_rng(7).permutation(count * (length - 1))
+    src, dst = v[:, :-1].ravel()[order], v[:, 1:].ravel()[order]
+    s, d, st = run(engine, "tc", src, dst)
+    i, j = np.triu_indices(length, 1)
+    np.testing.assert_array_equal(s, v[:, i].ravel())
+    np.testing.assert_array_equal(d, v[:, j].ravel())
+    sizes = [count * (length - 1 - k) for k in range(length)]
+    assert st["iterations"] == length - 1 and st["delta_sizes"] == sizes
+    assert st["join_candidates"] == sum(sizes[1:]) and sum(st["stage_bytes"].values()) == 0
+
+
 DEEP = {
     "tc_slabs": ("tc", lambda: inputs.chain(30_000)),
     "tc_tiers": ("tc", lambda: inputs.chain(60_000)),

@@ -35,10 +35,11 @@ def harness(tmp_path_factory):
     return exe
 
 
-def _run(harness, tmp_path, graphs, w=None, kb=4, grid=3, pool=1 << 20, bits=1 << 18, slab=0, levels=4096, more=(0, 0)):
+def _run(harness, tmp_path, graphs, w=None, kb=4, grid=3, pool=1 << 20, bits=1 << 18, slab=0, levels=4096, more=(0, 0), thin=0):
     """Closure of one graph or a batch; returns the stop bits, the pool used, the queued rows and the
     columns per slab, after comparing everything else with the oracle (when nothing stopped it).  more:
-    rows whose vertices count as having that many further out-edges in the slabs' candidates."""
+    rows whose vertices count as having that many further out-edges in the slabs' candidates.  thin: the
+    thin tier between the groups and the queue tier, and its rows among those queued."""
     w = w or max(1, max(int(max(s.max(), d.max())).bit_length() for s, d in graphs if len(s)))
     keys = [np.unique((np.uint64(i) << np.uint64(2 * w)) | (s.astype(np.uint64) << np.uint64(w)) | d.astype(np.uint64))
             for i, (s, d) in enumerate(graphs)]
@@ -49,18 +50,20 @@ def _run(harness, tmp_path, graphs, w=None, kb=4, grid=3, pool=1 << 20, bits=1 <
         np.array([w, kb, len(graphs), E.size, levels, span], dtype=np.uint64).tofile(f)
         E.tofile(f)
     r = subprocess.run([str(harness), str(inp), str(out), str(grid), "4", str(pool), str(bits), str(slab),
-                        str(more[0]), str(more[1])],
+                        str(more[0]), str(more[1]), str(thin)],
                        capture_output=True, text=True, timeout=300, env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0"))
     assert r.returncode == 0, r.stdout + r.stderr[-3000:]
     got = np.fromfile(out, dtype=np.uint64)
     stop, used, queued, width = int(got[0]), int(got[1]), [int(x) for x in got[2:6]], int(got[6])
+    if thin:
+        queued.insert(2, int(got[7]))
     if stop:
         return stop, used, queued, width
     refs = [oracle.tc(s, d) for s, d in graphs]
-    L = int(got[7])
-    lev = got[8:8 + 2 * L].reshape(L, 2)
-    F = int(got[8 + 2 * L])
-    pairs, flat, inst = np.split(got[9 + 2 * L:], [F, 2 * F])
+    L = int(got[8])
+    lev = got[9:9 + 2 * L].reshape(L, 2)
+    F = int(got[9 + 2 * L])
+    pairs, flat, inst = np.split(got[10 + 2 * L:], [F, 2 * F])
     assert L == max(x.iterations for x in refs)
     want = np.zeros(L + 1, dtype=np.int64)
     for x in refs:
@@ -122,6 +125,48 @@ def test_tiers(harness, tmp_path, kb, grid, graph):
         assert queued[1] > 0
     if graph == "dense":
         assert queued[3] > 0
+
+
+def _ring(n, fans):
+    """A cycle of n vertices with fans of (vertex, leaves, whether they lead back into the cycle)."""
+    s = [np.arange(n)]
+    d = [(np.arange(n) + 1) % n]
+    for v, k, back in fans:
+        leaf = sum(x.size for x in s) + np.arange(k) + n
+        s += [np.full(k, v)] + ([leaf] if back else [])
+        d += [leaf] + ([np.full(k, v)] if back else [])
+    return np.concatenate(s).astype(np.uint32), np.concatenate(d).astype(np.uint32)
+
+
+# rows past the groups: thin ones of any size; levels at the thin tier's 96 queued rows; not thin (more
+# than 24 rows) at its 128th level
+@pytest.mark.parametrize("graph,want", [
+    (lambda: inputs.chain(400), [383, 367, 335, 0, 0]), (lambda: inputs.cycle(70), [70, 70, 70, 0, 0]),
+    (lambda: _star(257), [1, 1, 1, 0, 0]), (lambda: _star(2500), [1, 1, 1, 0, 0]), (lambda: _fan(96), [1, 1, 0, 0, 0]), (lambda: _fan(128), [1, 1, 1, 1, 1]),
+    (lambda: _ring(300, [(299, 24, True)]), [324, 324, 324, 1, 0]),
+    (lambda: _ring(129, [(5, 95, True)]), [224, 224, 224, 1, 0]),
+    (lambda: _ring(129, [(5, 96, True)]), [225, 225, 225, 225, 225])])
+@pytest.mark.parametrize("grid", [3, 4])
+def test_thin_rows(harness, tmp_path, graph, want, grid):
+    assert _run(harness, tmp_path, [graph()], grid=grid, kb=8, thin=1)[2] == want
+
+
+@pytest.mark.parametrize("kb,grid", [(8, 3), (8, 4)])
+@pytest.mark.parametrize("graph", sorted(GRAPHS))
+def test_tiers_with_thin(harness, tmp_path, kb, grid, graph):
+    _run(harness, tmp_path, [GRAPHS[graph]()], kb=kb, grid=grid, thin=1)
+    _run(harness, tmp_path, [GRAPHS[g]() for g in ("er", "grid", "dense")], kb=kb, grid=grid, thin=1)
+
+
+def test_few_thin_rows(harness, tmp_path):
+    """Up to a number of rows the thin tier sends all of them on; one more and it takes them."""
+    assert _run(harness, tmp_path, [inputs.chain(120)], kb=8, thin=56)[2] == [103, 87, 55, 55, 0]
+    assert _run(harness, tmp_path, [inputs.chain(120)], kb=8, thin=55, grid=4)[2] == [103, 87, 55, 0, 0]
+
+
+def test_thin_rows_too_wide_too_late(harness, tmp_path):
+    """A level that outgrows the queue past the levels that can be taken back: no tier holds the row."""
+    assert _run(harness, tmp_path, [_ring(300, [(0, 97, True)])], kb=8, thin=1)[0] == 4
 
 
 @pytest.mark.parametrize("kb,grid", [(4, 3), (8, 4)])
@@ -189,8 +234,8 @@ def test_too_small_buffers_are_reported(harness, tmp_path):
 def test_too_many_levels_are_reported(harness, tmp_path, levels):
     """Rows and slabs deeper than the levels allotted, in the group tiers, the queue tier above and below
     the table in LDS, the bits tier and the slabs."""
-    for slab in (0, 1):
-        assert _run(harness, tmp_path, [inputs.chain(400)], levels=levels, slab=slab)[0] == 8
+    for slab, thin in ((0, 0), (0, 1), (1, 0)):
+        assert _run(harness, tmp_path, [inputs.chain(400)], levels=levels, slab=slab, thin=thin)[0] == 8
     s, d = inputs.erdos_renyi(300, 1500, seed=4)  # the bits tier, whose rows all lead into the chain
     deep = np.arange(300, 300 + levels, dtype=np.uint32)
     s, d = np.concatenate([s, [0], deep]).astype(np.uint32), np.concatenate([d, [300], deep + 1]).astype(np.uint32)
