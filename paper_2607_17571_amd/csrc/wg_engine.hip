@@ -892,7 +892,7 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
       a.queue[kQueueTier] = (uint32_t*)b.cand[1];
       a.queue[kBitsTier] = (uint32_t*)b.cand[1] + m;
       if (a.after_groups == kThinTier) {
-        const size_t bytes = (size_t)thin_blocks(e->grid, a.vis_words) * a.vis_words * 4;
+        const size_t bytes = (size_t)thin_waves(e->grid, a.vis_words) * a.vis_words * 4;
         try {
           if (e->rvis.bytes < bytes) {
             ensure(e, e->rvis, bytes);

@@ -43,7 +43,7 @@ namespace wg {
 constexpr int kReachTiers = 5;              // queues between the tiers: two groups, thin, queue, bits
 constexpr int kThinTier = 2, kQueueTier = 3, kBitsTier = 4;
 // The queue tier holds a row's bitmap of all columns in LDS: from this many words on one or two rows
-// per CU.  The thin tier then takes the rows first, 20 per CU (ms a closure by the iterations' launches /
+// per CU.  The thin tier then takes the rows first, 24 per CU (ms a closure by the iterations' launches /
 // with the queue tier alone / with the thin tier: 1,000 chains of 300 vertices 37.7 / 171 / 26.6, 800 of
 // 300 36.2 / 69.5 / 21.0, 100 of 3,000 678 / 1,816 / 127; random graphs of 1,000,000 vertices with
 // 950,000 edges 13.6 / 6.0 / 3.2, of 700,000 with 630,000 6.6 / 1.45 / 1.21).  Up to kThinRounds rows
@@ -148,7 +148,7 @@ struct ReachArgs {
   uint64_t pool_cap;
   uint32_t* bits;        // bitmap slots of `words` words, or the slabs' bits
   int after_groups;      // the tier the groups send rows on to: kThinTier or kQueueTier
-  uint32_t* vis;         // thin tier: a bitmap per block, all zeros between launches
+  uint32_t* vis;         // thin tier: a bitmap per wave, all zeros between launches
   uint32_t vis_words;    // ... its words (a multiple of 32)
   uint32_t thin_rows;    // rows up to which it leaves all of them to the queue tier
   uint32_t words;        // words of a row's bitmap: the columns of the widest instance (at most)
@@ -198,8 +198,8 @@ template <typename K>
 void launch_ids_keys(hipStream_t s, const Grid& g, const uint32_t* ids, const K* keys, uint64_t n, int w, int out_w,
                      uint64_t* out);
 
-// Blocks of the thin tier, for the bitmaps of `words` words, and the rows up to which it does nothing.
-uint32_t thin_blocks(const Grid& g, uint32_t words);
+// Waves of the thin tier, for the bitmaps of `words` words, and the rows up to which it does nothing.
+uint32_t thin_waves(const Grid& g, uint32_t words);
 uint32_t thin_rows(const Grid& g, uint32_t words);
 
 // The rows, then their offsets (off: rows + 1 entries; part: g.scan entries of scratch).

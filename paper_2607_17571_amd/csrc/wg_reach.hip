@@ -27,7 +27,7 @@ void launch_queue(hipStream_t s, int cu, const ReachArgs& a) {
   else hipLaunchKernelGGL((k_reach_queue<16, 32768, 3072>), dim3(wide_queue_blocks(cu, a.words)), dim3(16 * kWave), 0, s, a);
 }
 
-constexpr int kThinPerCu = 20;  // (7 KB of LDS each)
+constexpr int kThinPerCu = 24;  // (waves; 23 KB of LDS for four)
 
 void launch_bits(hipStream_t s, int cu, const ReachArgs& a) {
   const dim3 B(kReachBitsWaves * kWave);
@@ -89,9 +89,9 @@ void launch_reach_graph(hipStream_t s, const Grid& g, const Ctrl* ctrl, const K*
                      a.slab_mode);
 }
 
-uint32_t thin_blocks(const Grid& g, uint32_t words) {
+uint32_t thin_waves(const Grid& g, uint32_t words) {
   const uint64_t cu = (uint64_t)std::max(1, g.stream / 8);
-  return (uint32_t)std::min<uint64_t>(cu * kThinPerCu, kThinBytes / 4 / words / kReachXcds * kReachXcds);
+  return (uint32_t)std::min<uint64_t>(cu * kThinPerCu, kThinBytes / 4 / words) / (kReachXcds * kThinWaves) * (kReachXcds * kThinWaves);
 }
 
 uint32_t thin_rows(const Grid& g, uint32_t words) {
@@ -102,15 +102,16 @@ void launch_reach(hipStream_t s, const Grid& g, uint64_t m, const ReachArgs& a, 
   const int cu = std::max(1, g.stream / 8);
   if (a.slab_mode != 1) hipLaunchKernelGGL(k_reach_thread, dim3(blocks_for(g, m)), dim3(kBlock), 0, s, a);
   if (a.slab_mode != 0) {
-    hipLaunchKernelGGL(k_slab<uint32_t>, dim3(cu), dim3(kSlabThreads), 0, s, a);
-    if (m > kSlabRows32) hipLaunchKernelGGL(k_slab<uint16_t>, dim3(cu), dim3(kSlabThreads), 0, s, a);
+    if (m > kSlabRows32) hipLaunchKernelGGL(k_slab<true>, dim3(cu), dim3(kSlabThreads), 0, s, a);
+    else hipLaunchKernelGGL(k_slab<false>, dim3(cu), dim3(kSlabThreads), 0, s, a);
     hipLaunchKernelGGL(k_slab_count, dim3(std::max<uint32_t>(1, blocks_for(g, 4 * m))), dim3(kBlock), 0, s, a);
   }
   if (a.slab_mode != 1) {
     hipLaunchKernelGGL((k_reach_group<0, 4, 64, 128, 32, 32, 2>), dim3(cu * 6), dim3(2 * kWave), 0, s, a);
     hipLaunchKernelGGL((k_reach_group<1, 8, 256, 512, 128, 64, 1>), dim3(cu * 6), dim3(kWave), 0, s, a);
     if (a.after_groups == kThinTier)
-      hipLaunchKernelGGL((k_reach_thin<kThinQueue, kThinGroups>), dim3(thin_blocks(g, a.vis_words)), dim3(kWave), 0, s, a);
+      hipLaunchKernelGGL((k_reach_thin<kThinQueue, kThinGroups>), dim3(thin_waves(g, a.vis_words) / kThinWaves),
+                         dim3(kThinWaves * kWave), 0, s, a);
     launch_queue(s, cu, a);
     if (a.bits_tier) launch_bits(s, cu, a);
   }

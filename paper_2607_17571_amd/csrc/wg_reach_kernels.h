@@ -612,22 +612,22 @@ __device__ __forceinline__ void slab_run(const ReachArgs& a, uint32_t* s_mem, un
   }
 }
 
-// (W: a slab's columns of a row; the launch of the other width returns)
-template <typename W>
+// One launch for both widths where there may be rows for the narrow one (a launch that finds nothing to do
+// takes 5 us of a closure by tiers).
+template <bool BOTH>
 __global__ __launch_bounds__(kSlabThreads) void k_slab(ReachArgs a) {
   __shared__ uint32_t s_mem[kSlabLdsWords];
   __shared__ unsigned long long s_lev[kReachLdsLevels][2];
-  __shared__ uint32_t s_tab[256 * sizeof(W)];
+  __shared__ uint32_t s_tab[1024];
   __shared__ uint32_t s_any[2], s_halt;
-  constexpr uint32_t B = 8 * sizeof(W);
-  constexpr uint32_t RMAX = B == 32 ? kSlabRows32 : kSlabRows16;
   const uint32_t rows = a.rc->rows;
-  if (block_stop(!slab_chosen(a) || reach_halted(a.rc) || rows > RMAX || (B == 16 && rows <= kSlabRows32))) return;
+  if (block_stop(!slab_chosen(a) || reach_halted(a.rc) || rows > (BOTH ? kSlabRows16 : kSlabRows32))) return;
   if (rows < a.min_rows) {
     if (threadIdx.x == 0 && blockIdx.x == 0) atomicOr(&a.rc->stop, (uint32_t)kReachUnsupported);
     return;
   }
-  const uint64_t need = (uint64_t)((a.rc->cols + B - 1) / B) * rows * sizeof(W);
+  const uint32_t B = BOTH && rows > kSlabRows32 ? 16 : 32;
+  const uint64_t need = (uint64_t)((a.rc->cols + B - 1) / B) * rows * (B / 8);
   if (blockIdx.x == 0 && threadIdx.x == 0) a.rc->slab = B;  // read by later launches
   if (need > 4 * a.bits_words) {
     if (threadIdx.x == 0 && blockIdx.x == 0) atomicOr(&a.rc->stop, (uint32_t)kReachSlabFull);
@@ -636,7 +636,10 @@ __global__ __launch_bounds__(kSlabThreads) void k_slab(ReachArgs a) {
   a.form = 1;
   reach_levels_clear(s_lev);
   __syncthreads();
-  slab_run<W, (int)((RMAX + kSlabThreads) / kSlabThreads)>(a, s_mem, s_lev, s_tab, s_any, &s_halt);
+  if (BOTH && rows > kSlabRows32)
+    slab_run<uint16_t, (int)((kSlabRows16 + kSlabThreads) / kSlabThreads)>(a, s_mem, s_lev, s_tab, s_any, &s_halt);
+  else
+    slab_run<uint32_t, (int)((kSlabRows32 + kSlabThreads) / kSlabThreads)>(a, s_mem, s_lev, s_tab, s_any, &s_halt);
   __syncthreads();
   reach_levels_flush(s_lev, a);
 }
@@ -972,32 +975,38 @@ __device__ __forceinline__ void row_columns(const ReachArgs& a, uint32_t row, ui
 // Thin tier: one row per wave, the set a bitmap of the instance's columns in memory (the wave's own, in
 // its XCD's L2), beside it in LDS a bit per 1,024 columns that has any and the levels' queues.  A level
 // costs the latencies of an edge load and of an atomic in the L2, 1.2 us; what counts is how
-// many rows are in flight, 20 per CU where a bitmap in LDS leaves one or two.  Only the stretches
+// many rows are in flight, 24 per CU where a bitmap in LDS leaves one or two.  Only the stretches
 // that have columns are read back and cleared.  A level that outgrows the queue sends the row on, and so
 // does one that is not thin by the last level whose counts can still be taken back.
 // ---------------------------------------------------------------------------
+constexpr uint32_t kThinWaves = 4;  // (each for itself: a quarter of the blocks to start)
 template <uint32_t QCAP, uint32_t GROUPS>  // stretches of 1,024 columns
-__global__ __launch_bounds__(kWave) void k_reach_thin(ReachArgs a) {
+__global__ __launch_bounds__(kThinWaves * kWave) void k_reach_thin(ReachArgs a) {
+  constexpr uint32_t TH = kThinWaves * kWave;
   static_assert(4 * QCAP >= GROUPS && GROUPS % 32 == 0 && GROUPS / 32 <= kWave, "");
-  __shared__ uint32_t s_front[2][QCAP];
-  __shared__ uint32_t s_any[GROUPS / 32];
+  struct Row {  // a wave's
+    uint32_t front[2][QCAP];
+    uint32_t any[GROUPS / 32];
+    uint32_t ln[kReachLdsLevels], ld[kReachLdsLevels];
+  };
+  __shared__ Row s_row[kThinWaves];
   __shared__ unsigned long long s_lev[kReachLdsLevels][2];
-  __shared__ uint32_t s_ln[kReachLdsLevels], s_ld[kReachLdsLevels];
-  const uint32_t lane = threadIdx.x;
+  const uint32_t lane = (uint32_t)lane_id(), wid = threadIdx.x / kWave;
+  Row& r = s_row[wid];
   const uint32_t n = a.rc->queued[kThinTier];
   if (block_stop(n == 0 || a.rc->slab != 0 || reach_halted(a.rc))) return;
   if (n <= a.thin_rows) {  // (uniform over the launch)
-    for (uint32_t i = blockIdx.x * kWave + lane; i < n; i += gridDim.x * kWave) a.queue[kQueueTier][i] = a.queue[kThinTier][i];
-    if (lane == 0 && blockIdx.x == 0) a.rc->queued[kQueueTier] = n;
+    for (uint32_t i = blockIdx.x * TH + threadIdx.x; i < n; i += gridDim.x * TH) a.queue[kQueueTier][i] = a.queue[kThinTier][i];
+    if (threadIdx.x == 0 && blockIdx.x == 0) a.rc->queued[kQueueTier] = n;
     return;
   }
   reach_levels_clear(s_lev);
-  if (lane < GROUPS / 32) s_any[lane] = 0;
+  if (lane < GROUPS / 32) r.any[lane] = 0;
   __syncthreads();
   const uint64_t lt = lanemask_lt();
   const uint2* __restrict__ edge = a.g.edge;
   const uint32_t edges = a.rc->edges;
-  uint32_t* const vis = a.vis + (uint64_t)blockIdx.x * a.vis_words;
+  uint32_t* const vis = a.vis + ((uint64_t)blockIdx.x * kThinWaves + wid) * a.vis_words;
   uint32_t share = 0, claims = 0;
   for (;;) {
     uint32_t row = kReachNone;
@@ -1022,13 +1031,13 @@ __global__ __launch_bounds__(kWave) void k_reach_thin(ReachArgs a) {
       if (on) {
         const uint32_t bit = 1u << (z & 31u);
         fresh = (__hip_atomic_fetch_or(&vis[z >> 5], bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) & bit) == 0;
-        if (fresh) atomicOr(&s_any[z >> 15], 1u << ((z >> 10) & 31u));
+        if (fresh) atomicOr(&r.any[z >> 15], 1u << ((z >> 10) & 31u));
       }
       const uint64_t nb = __builtin_amdgcn_ballot_w64(fresh);
       if (nb) {  // (uniform)
         const uint64_t pb = __builtin_amdgcn_ballot_w64(fresh && rec.y != kReachNone);
         const uint32_t at = nq + (uint32_t)__popcll(pb & lt);
-        if (fresh && rec.y != kReachNone && at < QCAP) s_front[to][at] = rec.y;
+        if (fresh && rec.y != kReachNone && at < QCAP) r.front[to][at] = rec.y;
         nq += (uint32_t)__popcll(pb);
         nf += (uint32_t)__popcll(nb);
       }
@@ -1061,13 +1070,13 @@ __global__ __launch_bounds__(kWave) void k_reach_thin(ReachArgs a) {
       wave_lds_sync();
       uint32_t dsum = 0;
       for (uint32_t f = 0; f < fn; f += kWave)
-        dsum += wave_expand(edge, edges, f + lane < fn ? s_front[from][f + lane] : kReachNone, visit);
+        dsum += wave_expand(edge, edges, f + lane < fn ? r.front[from][f + lane] : kReachNone, visit);
       dsum = wave_sum<uint32_t>(dsum);
       wave_lds_sync();
       if (lane == 0) {
         if (lv < kReachLdsLevels) {
-          s_ln[lv] = found;
-          s_ld[lv] = dsum;
+          r.ln[lv] = found;
+          r.ld[lv] = dsum;
         } else {
           reach_count(s_lev, a, lv, found, dsum);
         }
@@ -1082,7 +1091,7 @@ __global__ __launch_bounds__(kWave) void k_reach_thin(ReachArgs a) {
         else a.queue[kQueueTier][atomicAdd(&a.rc->queued[kQueueTier], 1u)] = row;
       }
     } else {
-      for (uint32_t x = lane; x < lv && x < kReachLdsLevels; x += kWave) reach_count(s_lev, a, x, s_ln[x], s_ld[x]);
+      for (uint32_t x = lane; x < lv && x < kReachLdsLevels; x += kWave) reach_count(s_lev, a, x, r.ln[x], r.ld[x]);
       if (lane == 0) {
         pos = reach_alloc(a, cnt);
         a.cnt[row] = cnt;
@@ -1092,12 +1101,12 @@ __global__ __launch_bounds__(kWave) void k_reach_thin(ReachArgs a) {
       pos = __shfl(pos, 0, kWave);
     }
     // the stretches that have columns, in order (the queues are free)
-    uint16_t* const list = (uint16_t*)&s_front[0][0];
-    uint32_t v = lane < GROUPS / 32 ? s_any[lane] : 0u;
+    uint16_t* const list = (uint16_t*)&r.front[0][0];
+    uint32_t v = lane < GROUPS / 32 ? r.any[lane] : 0u;
     const uint32_t c = (uint32_t)__popc(v), incl = wave_incl_scan<uint32_t>(c);
     const uint32_t groups = __shfl(incl, kWave - 1, kWave);
     for (uint32_t at = incl - c; v; v &= v - 1) list[at++] = (uint16_t)(lane * 32u + (uint32_t)__ffs(v) - 1u);
-    if (lane < GROUPS / 32) s_any[lane] = 0;
+    if (lane < GROUPS / 32) r.any[lane] = 0;
     wave_lds_sync();
     // eight at a time, four words a lane
     for (uint32_t g0 = 0; g0 < groups; g0 += 8) {

@@ -84,7 +84,7 @@ int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigne
   a.after_groups = thin ? kThinTier : kQueueTier;
   a.thin_rows = thin ? thin - 1 : 0;
   a.vis_words = (((uint32_t)m + 31u) / 32u + 31u) & ~31u;
-  std::vector<uint32_t> vis(G * a.vis_words, 0u);
+  std::vector<uint32_t> vis(G * kThinWaves * a.vis_words, 0u);
   a.vis = vis.data();
   std::vector<uint32_t> bits(std::max<uint64_t>(bits_words, 1), 0x33333333u);
   a.bits = bits.data();
@@ -115,14 +115,14 @@ int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigne
     for (uint32_t r = 0; r <= rc->rows; ++r) rstart[r] += std::min(r, more_rows) * more;
   }
   if (slab_mode != 0) {
-    simt::launch(G, kSlabThreads, [&] { k_slab<uint32_t>(a); }, workers);
-    simt::launch(G, kSlabThreads, [&] { k_slab<uint16_t>(a); }, workers);
+    if (m > kSlabRows32) simt::launch(G, kSlabThreads, [&] { k_slab<true>(a); }, workers);
+    else simt::launch(G, kSlabThreads, [&] { k_slab<false>(a); }, workers);
     simt::launch(G, kBlock, [&] { k_slab_count(a); }, workers);
   }
   if (slab_mode != 1) {
     simt::launch(G, 2 * kWave, [&] { k_reach_group<0, 4, 64, 128, 32, 32, 2>(a); }, workers);
     simt::launch(G, kWave, [&] { k_reach_group<1, 8, 256, 512, 128, 64, 1>(a); }, workers);
-    if (thin) simt::launch(G, kWave, [&] { k_reach_thin<96, 32>(a); }, workers);
+    if (thin) simt::launch(G, kThinWaves * kWave, [&] { k_reach_thin<96, 32>(a); }, workers);
     for (uint32_t x : vis)
       if (x) return 3;  // (all zeros between launches)
     // (a queue of 96 rows, so that wide levels outgrow it)

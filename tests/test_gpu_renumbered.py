@@ -83,6 +83,17 @@ def test_thin_rows_of_wide_graphs(engine, count, length):
     assert st["join_candidates"] == sum(sizes[1:]) and sum(st["stage_bytes"].values()) == 0
 
 
+@pytest.mark.parametrize("depth", [16, 17, 18])
+def test_wide_levels_of_wide_graphs(engine, depth):
+    """Binary trees, rows of some hundred thousand tuples among many short ones: three bitmaps in LDS, the
+    widest graph of those (262,142 columns), and levels too wide for the tiers of a wider one, which is
+    left to the iterations when the others have run."""
+    src, dst = inputs.binary_tree(depth)
+    s, d, st = run(engine, "tc", src, dst)
+    assert_same(s, d, st, oracle.tc(src, dst))
+    assert (sum(st["stage_bytes"].values()) == 0) == (depth < 18)
+
+
 DEEP = {
     "tc_slabs": ("tc", lambda: inputs.chain(30_000)),
     "tc_tiers": ("tc", lambda: inputs.chain(60_000)),

@@ -240,3 +240,4 @@ def test_too_many_levels_are_reported(harness, tmp_path, levels):
     deep = np.arange(300, 300 + levels, dtype=np.uint32)
     s, d = np.concatenate([s, [0], deep]).astype(np.uint32), np.concatenate([d, [300], deep + 1]).astype(np.uint32)
     assert _run(harness, tmp_path, [(s, d)], levels=levels)[0] & 8
+    assert _run(harness, tmp_path, [(s, d)], levels=levels, thin=1, kb=8, grid=4)[0] & 8
