@@ -42,6 +42,14 @@ __device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
   return __shfl_xor(v, D, kWave);
 }
 
+// The stretch in which n tiles go to the XCDs in turn: `most` tiles at most, as many stretches for each
+// (36,000 vertices, 18,256 edges: 63 tiles in stretches of 64, all of them one XCD's, took 326 us a closure,
+// 255 so).
+__device__ __forceinline__ uint32_t xcd_stretch(uint32_t n, uint32_t most) {
+  const uint32_t rounds = (n + kReachXcds * most - 1) / (kReachXcds * most);
+  return rounds ? (n + kReachXcds * rounds - 1) / (kReachXcds * rounds) : 1u;
+}
+
 // Tile `v` of this block's XCD (blocks go to the XCDs in turn, each with an L2 of its own): stretches of
 // C tiles go to the XCDs in turn, so that what neighbouring tiles share is read into one L2.
 __device__ __forceinline__ uint32_t xcd_tile(uint32_t iter, uint32_t C) {

@@ -340,10 +340,10 @@ __global__ __launch_bounds__(kBlock) void k_reach_thread(ReachArgs a) {
   unsigned long long* const my = s_cnt[tid % kReachLevCopies];
   uint64_t chunk = 0;
   uint32_t left = 0;  // pool entries left of the block's chunk (uniform)
-  const uint32_t ntiles = (n + kBlock - 1) / kBlock;
+  const uint32_t ntiles = (n + kBlock - 1) / kBlock, stretch = xcd_stretch(ntiles, kReachTileStretch);
   __syncthreads();
   for (uint32_t iter = 0;; ++iter) {
-    const uint32_t tile = xcd_tile(iter, kReachTileStretch), next = xcd_tile(iter + 1, kReachTileStretch);
+    const uint32_t tile = xcd_tile(iter, stretch), next = xcd_tile(iter + 1, stretch);
     if (tile >= ntiles) break;
     const uint32_t row = tile * kBlock + tid;
     uint32_t q[CAP];
@@ -766,8 +766,9 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_group(ReachArgs a) {
     fn = 0;
     wave_lds_sync();
   };
+  const uint32_t stretch = xcd_stretch((n + NW * PER - 1) / (NW * PER), kReachQueueStretch / (NW * PER));
   for (uint32_t iter = 0;; ++iter) {
-    const uint64_t tile = (uint64_t)xcd_tile(iter, kReachQueueStretch / (NW * PER)) * (NW * PER);
+    const uint64_t tile = (uint64_t)xcd_tile(iter, stretch) * (NW * PER);
     if (tile >= n) break;
     const uint64_t base = tile + (tid / kWave) * PER;
     if (__builtin_amdgcn_readfirstlane((int)reach_halted(a.rc))) break;

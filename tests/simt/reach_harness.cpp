@@ -189,7 +189,41 @@ int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigne
   return 0;
 }
 
+// The tiles' order over the blocks: every tile once, no block much past an even share, and
+// at least half of the blocks that an even share would keep busy.
+int tiles() {
+  for (uint32_t most : {16u, 64u})
+    for (uint32_t grid : {1u, 7u, 8u, 32u, 98u, 104u, 256u, 1536u, 2048u})
+      for (uint32_t n : {0u, 1u, 7u, 8u, 9u, 20u, 63u, 64u, 65u, 100u, 128u, 129u, 511u, 512u, 513u, 600u, 1025u, 6450u, 70000u}) {
+        std::vector<uint32_t> seen(n, 0);
+        uint32_t busiest = 0, busy = 0;
+        gridDim = {grid, 1, 1};
+        const uint32_t C = xcd_stretch(n, most);
+        if (C > most) return 5;
+        for (uint32_t b = 0; b < grid; ++b) {
+          blockIdx = {b, 0, 0};
+          uint32_t mine = 0;
+          for (uint32_t i = 0;; ++i, ++mine) {
+            const uint32_t t = xcd_tile(i, C);
+            if (t >= n) break;
+            ++seen[t];
+          }
+          busiest = std::max(busiest, mine);
+          busy += mine ? 1 : 0;
+        }
+        for (uint32_t x : seen)
+          if (x != 1) return 6;
+        const uint32_t even = (n + grid - 1) / grid;
+        if (busiest > even + 1 + even / 16 || 2 * busy < std::min(n, grid)) {
+          std::printf("grid %u tiles %u stretch %u: busiest %u busy %u\n", grid, n, C, busiest, busy);
+          return 7;
+        }
+      }
+  return 0;
+}
+
 int main(int argc, char** argv) {
+  if (argc == 1) return tiles();
   std::ifstream f(argv[1], std::ios::binary);
   uint64_t h[6];
   f.read((char*)h, sizeof(h));

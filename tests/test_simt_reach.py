@@ -81,6 +81,12 @@ def _run(harness, tmp_path, graphs, w=None, kb=4, grid=3, pool=1 << 20, bits=1 <
     return stop, used, queued, width
 
 
+def test_tiles_over_the_xcds(harness):
+    """Every tile goes to one block, and to nearly as many blocks as there are tiles."""
+    r = subprocess.run([str(harness)], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stdout
+
+
 def _star(deg):
     return np.zeros(deg, np.uint32), np.arange(1, deg + 1, dtype=np.uint32)
 
