@@ -20,6 +20,8 @@ template <typename T> inline T atomicCAS(T* p, T c, T v) {
 #define __builtin_amdgcn_wave_barrier simt::wave_sync
 #define __builtin_amdgcn_fence(...) (void)0
 #define __hip_atomic_load(p, ...) __atomic_load_n(p, __ATOMIC_SEQ_CST)
+#define __hip_atomic_store(p, v, ...) __atomic_store_n(p, v, __ATOMIC_SEQ_CST)
+#define __hip_atomic_fetch_or(p, v, ...) __atomic_fetch_or(p, v, __ATOMIC_SEQ_CST)
 #include "wg_launch.h"
 #include "wg_reach_kernels.h"
 #include "wg_sg_kernels.h"
