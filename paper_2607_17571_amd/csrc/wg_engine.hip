@@ -905,7 +905,7 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
           a.after_groups = kQueueTier;  // (no memory for it: the queue tier takes them all)
         }
       }
-      const size_t head_bytes = sizeof(ReachCtl) + (size_t)e->reach_levels * sizeof(ReachLevel);
+      const size_t head_bytes = reach_flags_at(sizeof(ReachCtl) + (size_t)e->reach_levels * sizeof(ReachLevel));
       ensure(e, e->rctl, head_bytes + 2 * span);
       ensure(e, e->rpool, pool * 4);
       if (bits) ensure(e, e->rbits, bits * 4);
@@ -1046,8 +1046,9 @@ bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_optio
   };
   try {
     a.edge = (uint4*)graph_buffers(e, ra.g, m, w, true, m * sizeof(uint4));
-    ensure(e, e->rctl, head + level_bytes + 2 * ra.g.span);
-    ra.g.flags = (uint8_t*)e->rctl.p + head + level_bytes;
+    const size_t flags_at = reach_flags_at(head + level_bytes);
+    ensure(e, e->rctl, flags_at + 2 * ra.g.span);
+    ra.g.flags = (uint8_t*)e->rctl.p + flags_at;
     ra.rc = a.rc = (ReachCtl*)e->rctl.p;
     a.sc = (SgCtl*)((uint8_t*)e->rctl.p + sizeof(ReachCtl));
     a.lev = (SgLevel*)((uint8_t*)e->rctl.p + head);
@@ -1059,7 +1060,7 @@ bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_optio
         fail(e, WG_ERR_ITER_LIMIT, "max_iterations reached before the fixpoint");
     };
     a.g = ra.g;
-    hip_check(e, hipMemsetAsync(e->rctl.p, 0, head + level_bytes + 2 * ra.g.span, e->stream), "memset");
+    hip_check(e, hipMemsetAsync(e->rctl.p, 0, flags_at + 2 * ra.g.span, e->stream), "memset");
     launch_reach_graph<K>(e->stream, e->grid, e->d_ctrl, b.E, m, ra, b.jtot);
     launch_sg_edges<K>(e->stream, e->grid, e->d_ctrl, b.E, m, a);
     read(0);
@@ -1224,7 +1225,7 @@ bool triangles(wg_engine* e, uint64_t m, int w, wg_stats* st) {
     a.piece = (uint2*)(a.edge + m);
     a.col = ra.g.slab_col;
     // control blocks, rows' up edges and the ids' flags, cleared together
-    const uint64_t ctl = (sizeof(ReachCtl) + sizeof(TriCtl) + 15) & ~15ull, rows = (8 * m + 15) & ~15ull;
+    const uint64_t ctl = reach_flags_at(sizeof(ReachCtl) + sizeof(TriCtl)), rows = reach_flags_at(8 * m);
     ensure(e, e->rctl, ctl + rows + 2 * ra.g.span);
     uint8_t* const base = (uint8_t*)e->rctl.p;
     ra.rc = a.rc = (ReachCtl*)base;

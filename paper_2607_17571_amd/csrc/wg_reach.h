@@ -34,6 +34,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "wg_launch.h"
@@ -104,17 +105,22 @@ struct ReachLevel {          // [0]: by the tiers, [1]: by the slabs
   unsigned long long d[2];  // their out-degrees: the candidates of the next iteration
 };
 
-struct ReachCtl {
+struct alignas(64) ReachCtl {
   uint32_t queued[kReachTiers];  // rows queued for each tier
   uint32_t stop;                 // kReach* bits
   unsigned long long cursor;     // pool entries handed out
   uint32_t rows, cols, edges;    // of the renumbered graph
   uint32_t slab;                 // the slabs took the rows: columns per slab (32 or 16), else 0
-  unsigned long long pad[3];
+  unsigned long long pad[2];
   uint32_t claim[kReachTiers][kReachXcds][16];  // rows handed out, one counter per XCD (a 64 B line
                                                 // each: same-address atomics of all XCDs serialise
                                                 // at 12 ns)
 };
+
+static_assert(offsetof(ReachCtl, claim) % 64 == 0 && sizeof(ReachCtl) % 64 == 0, "");
+
+// Where the flags go that are read 16 at a time, behind `head` bytes of control blocks and levels.
+constexpr size_t reach_flags_at(size_t head) { return (head + 15) & ~(size_t)15; }
 
 // Ranks of 32 consecutive ids: which are rows and columns, and how many come before them.
 struct RankWord {

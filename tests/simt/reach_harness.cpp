@@ -14,8 +14,8 @@
 // Odd grids take the ranking and the offsets through one block and the queue tier with one wave;
 // even ones through several blocks and four waves.
 #include <hip/hip_runtime.h>
-struct uint2 { uint32_t x, y; };
-struct uint4 { uint32_t x, y, z, w; };
+struct alignas(8) uint2 { uint32_t x, y; };
+struct alignas(16) uint4 { uint32_t x, y, z, w; };
 template <typename T> inline T atomicCAS(T* p, T c, T v) {
   __atomic_compare_exchange_n(p, &c, v, false, __ATOMIC_SEQ_CST, __ATOMIC_SEQ_CST);
   return c;
@@ -48,17 +48,18 @@ int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigne
   std::unique_ptr<Ctrl> ctrl(new Ctrl);
   std::memset(ctrl.get(), 0, sizeof(Ctrl));
   ctrl->m_unique = m;
-  std::unique_ptr<ReachCtl> rc(new ReachCtl);
-  std::memset(rc.get(), 0, sizeof(ReachCtl));
-  std::vector<ReachLevel> lev(std::max<uint64_t>(h[4], kReachThreadCap), ReachLevel{{0, 0}, {0, 0}});
+  // control block, levels and flags laid out as the engine's buffer is (with levels to spare)
+  const uint64_t levels = std::max<uint64_t>(h[4], kReachThreadCap), flags_at = reach_flags_at(sizeof(ReachCtl) + levels * sizeof(ReachLevel));
+  std::vector<uint8_t> ctl_mem(flags_at + 2 * span + 256, 0);
+  uint8_t* const ctl = (uint8_t*)(((uintptr_t)ctl_mem.data() + 255) & ~(uintptr_t)255);
+  ReachCtl* const rc = (ReachCtl*)ctl;
+  ReachLevel* const lev = (ReachLevel*)(ctl + sizeof(ReachCtl));
   std::vector<uint32_t> cnt(m, 0xDEADu), seg(m, 0xBEEFu), off(m + 1), pool(std::max<uint64_t>(pool_cap, 1), 0x5A5A5A5Au);
   std::vector<uint32_t> queue[kReachTiers];
   for (auto& q : queue) q.assign(m, 0x77777777u);
   std::vector<uint32_t> rowkey(m), rstart(m + 1), colkey(m), cstart(m), se(m + kSlabThreads), sc(m + kSlabThreads);
   std::vector<uint2> edge(m + kReachEdgePad);
   std::vector<RankWord> rank(span / 32 + 1);
-  std::unique_ptr<uint8_t, void (*)(void*)> flags((uint8_t*)std::aligned_alloc(16, 2 * span), std::free);
-  std::memset(flags.get(), 0, 2 * span);
   ReachArgs a{};
   a.g.rowkey = rowkey.data();
   a.g.rstart = rstart.data();
@@ -68,7 +69,7 @@ int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigne
   a.g.slab_edge = se.data();
   a.g.slab_col = sc.data();
   a.g.rank = rank.data();
-  a.g.flags = flags.get();
+  a.g.flags = ctl + flags_at;
   a.g.span = span;
   a.g.instances = (uint32_t)num;
   a.g.w = w;
@@ -90,8 +91,8 @@ int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigne
   a.bits = bits.data();
   a.bits_words = bits_words;
   a.slots = bits_words / a.words;
-  a.rc = rc.get();
-  a.lev = lev.data();
+  a.rc = rc;
+  a.lev = lev;
   a.lev_cap = (uint32_t)h[4];
   std::vector<uint64_t> part(G);
   const bool one = G % 2;
@@ -145,7 +146,7 @@ int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigne
   if (rc->stop) return 0;
   const int form = rc->slab ? 1 : 0;
   uint64_t L = 0;
-  while (L < lev.size() && lev[L].n[form]) ++L;
+  while (L < levels && lev[L].n[form]) ++L;
   put(f, L);
   for (uint64_t i = 0; i < L; ++i) {
     put(f, lev[i].n[form]);

@@ -7,8 +7,8 @@
 // out: u64 stop bits, base candidates, whether a degree is large; unless the stop bits are set: rounds R
 //      (levels 0 .. R, the last one empty), then (tuples, candidates) of each, |SG|, its sorted keys.
 #include <hip/hip_runtime.h>
-struct uint2 { uint32_t x, y; };
-struct uint4 { uint32_t x, y, z, w; };
+struct alignas(8) uint2 { uint32_t x, y; };
+struct alignas(16) uint4 { uint32_t x, y, z, w; };
 template <typename T> inline T atomicCAS(T* p, T c, T v) {
   __atomic_compare_exchange_n(p, &c, v, false, __ATOMIC_SEQ_CST, __ATOMIC_SEQ_CST);
   return c;
@@ -44,13 +44,14 @@ int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigne
   std::unique_ptr<Ctrl> ctrl(new Ctrl);
   std::memset(ctrl.get(), 0, sizeof(Ctrl));
   ctrl->m_unique = m;
-  std::unique_ptr<ReachCtl> rc(new ReachCtl);
-  std::memset(rc.get(), 0, sizeof(ReachCtl));
+  // control blocks, levels and flags laid out as the engine's buffer is
+  const uint64_t head = sizeof(ReachCtl) + sizeof(SgCtl), flags_at = reach_flags_at(head + h[4] * sizeof(SgLevel));
+  std::vector<uint8_t> ctl_mem(flags_at + 2 * span + 256, 0);
+  uint8_t* const base = (uint8_t*)(((uintptr_t)ctl_mem.data() + 255) & ~(uintptr_t)255);
+  ReachCtl* const rc = (ReachCtl*)base;
   std::vector<uint32_t> rowkey(m), rstart(m + 1), colkey(m), cstart(m), se(m + kSlabThreads), sc_(m + kSlabThreads), cdeg(m);
   std::vector<uint2> edge(m + kReachEdgePad);
   std::vector<RankWord> rank(span / 32 + 1);
-  std::unique_ptr<uint8_t, void (*)(void*)> flags((uint8_t*)std::aligned_alloc(16, 2 * span), std::free);
-  std::memset(flags.get(), 0, 2 * span);
   SgArgs a{};
   a.g.rowkey = rowkey.data();
   a.g.rstart = rstart.data();
@@ -60,16 +61,15 @@ int run(const std::vector<uint64_t>& E64, const uint64_t* h, uint32_t G, unsigne
   a.g.slab_edge = se.data();
   a.g.slab_col = sc_.data();
   a.g.rank = rank.data();
-  a.g.flags = flags.get();
+  a.g.flags = base + flags_at;
   a.g.span = span;
   a.g.instances = (uint32_t)h[2];
   a.g.w = w;
-  a.rc = rc.get();
-  SgCtl ctl;
-  std::memset(&ctl, 0, sizeof(ctl));
+  a.rc = rc;
+  SgCtl& ctl = *(SgCtl*)(base + sizeof(ReachCtl));
   a.sc = &ctl;
-  std::vector<SgLevel> lev(h[4], SgLevel{});
-  a.lev = lev.data();
+  SgLevel* const lev = (SgLevel*)(base + head);
+  a.lev = lev;
   a.lev_cap = (uint32_t)h[4];
   simt::launch(G, kBlock, [&] { k_reach_mark<K>(ctrl.get(), E.data(), a.g); }, workers);
   simt::launch(1, kBlock, [&] { k_reach_rank(ctrl.get(), a.g, nullptr, a.rc); }, workers);

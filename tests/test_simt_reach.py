@@ -28,7 +28,8 @@ pytestmark = pytest.mark.skipif(shutil.which("g++") is None or platform.machine(
 @pytest.fixture(scope="module")
 def harness(tmp_path_factory):
     exe = tmp_path_factory.mktemp("simt_reach") / "reach_harness"
-    subprocess.run(["g++", "-std=c++20", "-O1", "-g", "-DSIMT_STACK=131072", "-fsanitize=address",
+    subprocess.run(["g++", "-std=c++20", "-O1", "-g", "-DSIMT_STACK=131072", "-fsanitize=address,alignment",
+                    "-fno-sanitize-recover=alignment",
                     "-fno-omit-frame-pointer", f"-I{SIMT}", f"-I{CSRC}", f"-I{os.path.join(ROOT, 'include')}",
                     "-pthread", os.path.join(SIMT, "reach_harness.cpp"), "-o", str(exe)], check=True,
                    capture_output=True)

@@ -25,7 +25,8 @@ ROUNDS, TAIL, MATRICES = 0, 1, 2
 @pytest.fixture(scope="module")
 def harness(tmp_path_factory):
     exe = tmp_path_factory.mktemp("simt_sg") / "sg_harness"
-    subprocess.run(["g++", "-std=c++20", "-O1", "-g", "-DSIMT_STACK=131072", "-fsanitize=address",
+    subprocess.run(["g++", "-std=c++20", "-O1", "-g", "-DSIMT_STACK=131072", "-fsanitize=address,alignment",
+                    "-fno-sanitize-recover=alignment",
                     "-fno-omit-frame-pointer", f"-I{SIMT}", f"-I{CSRC}", f"-I{os.path.join(ROOT, 'include')}",
                     "-pthread", os.path.join(SIMT, "sg_harness.cpp"), "-o", str(exe)], check=True,
                    capture_output=True)
