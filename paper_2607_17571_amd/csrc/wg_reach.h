@@ -81,6 +81,14 @@ constexpr uint32_t kSlabLdsWords = 36864;                    // 147,456 bytes
 constexpr uint32_t kSlabRows32 = kSlabLdsWords / 2 - 1;      // rows at 32 columns per slab
 constexpr uint32_t kSlabRows16 = kSlabLdsWords - 1;          // ... at 16
 constexpr uint32_t kSlabEdgeRegs = 32;                       // edges a thread keeps in registers
+// Where the host leaves the choice to the device (slab_mode 2), slabs take the rows if half of them
+// outgrew the thread tier and the graph goes on: every second row at least has an edge to a vertex with
+// edges, and a level over all slabs is at most kSlabLevel word operations (edges x columns / 32, 1.1e12
+// a second), or rows reach further on average than to one other and the columns are not mostly leaves.
+// (us a closure by the iterations' launches / by slabs / by tiers: 1,000 vertices with 800 leaves each
+// 409 / 32,164 / 476, 20,000 with 20 349 / 21,174 / 277, 1,000 with 36 297 / 373 / 247, 30,000 with 17 of
+// 60,000 leaves 326 / 4,919 / 303.)
+constexpr uint64_t kSlabLevel = 128u << 20;
 
 // ReachCtl::stop.  A pool or slots too small leave the counting on (the host then knows what is
 // needed and runs the rows again); the others end every kernel at its next look.
@@ -112,6 +120,7 @@ struct alignas(64) ReachCtl {
   uint32_t rows, cols, edges;    // of the renumbered graph
   uint32_t slab;                 // the slabs took the rows: columns per slab (32 or 16), else 0
   unsigned long long pad[2];
+  uint32_t inner[kReachXcds][16];  // edges to a vertex that has edges, a counter on a line of its own per XCD
   uint32_t claim[kReachTiers][kReachXcds][16];  // rows handed out, one counter per XCD (a 64 B line
                                                 // each: same-address atomics of all XCDs serialise
                                                 // at 12 ns)
@@ -146,7 +155,7 @@ struct ReachGraph {
 struct ReachArgs {
   ReachGraph g;
   int bits_tier;         // rows that outgrow the queue tier go to the bits tier (else they stop)
-  int slab_mode;         // 0: no slabs; 1: slabs; 2: slabs where half the rows outgrew the thread tier
+  int slab_mode;         // 0: no slabs; 1: slabs; 2: slabs where slab_chosen says so (kSlabLevel)
   uint32_t* cnt;         // per row: its tuples (| kReachBitRow)
   uint32_t* seg;         // per row: pool position of its columns, or its bitmap's slot
   uint32_t* queue[kReachTiers];

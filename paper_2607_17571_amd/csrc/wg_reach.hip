@@ -85,8 +85,7 @@ void launch_reach_graph(hipStream_t s, const Grid& g, const Ctrl* ctrl, const K*
                        (const uint64_t*)part, a.rc);
   }
   hipLaunchKernelGGL(k_reach_rows<K>, dim3(b), dim3(kBlock), 0, s, ctrl, E, a.g, (const ReachCtl*)a.rc);
-  hipLaunchKernelGGL(k_reach_edges<K>, dim3(b), dim3(kBlock), 0, s, ctrl, E, a.g, (const ReachCtl*)a.rc,
-                     a.slab_mode);
+  hipLaunchKernelGGL(k_reach_edges<K>, dim3(b), dim3(kBlock), 0, s, ctrl, E, a.g, a.rc, a.slab_mode);
 }
 
 uint32_t thin_waves(const Grid& g, uint32_t words) {

@@ -246,9 +246,13 @@ __global__ __launch_bounds__(kBlock) void k_reach_rows(const Ctrl* ctrl, const K
 
 template <typename K>
 __global__ __launch_bounds__(kBlock) void k_reach_edges(const Ctrl* ctrl, const K* __restrict__ E, ReachGraph g,
-                                                        const ReachCtl* rc, int slabs) {
+                                                        ReachCtl* rc, int slabs) {
+  __shared__ uint32_t s_inner;
   const uint64_t n = ctrl->m_unique;
   const uint32_t rows = rc->rows;
+  if (threadIdx.x == 0) s_inner = 0;
+  __syncthreads();
+  uint32_t inner = 0;
   const bool slab = slabs && rows <= kSlabRows16;
   const uint32_t per = slab_per((uint32_t)n);
   const uint64_t end = slab ? (uint64_t)per * kSlabThreads : n;
@@ -264,6 +268,7 @@ __global__ __launch_bounds__(kBlock) void k_reach_edges(const Ctrl* ctrl, const 
       if ((r.rowbits >> (ck & 31u)) & 1u) {
         to = r.rowpre + bits_below(r.rowbits, ck);
         start = g.rstart[to];
+        ++inner;
       }
       uint2 rec;
       rec.x = c | (last ? kReachLast : 0u);
@@ -281,6 +286,11 @@ __global__ __launch_bounds__(kBlock) void k_reach_edges(const Ctrl* ctrl, const 
       g.slab_col[at] = c;
     }
   }
+  if (slabs != 2) return;
+  inner = wave_sum<uint32_t>(inner);
+  if (lane_id() == 0 && inner) atomicAdd(&s_inner, inner);
+  __syncthreads();
+  if (threadIdx.x == 0 && s_inner) atomicAdd(&rc->inner[blockIdx.x % kReachXcds][0], s_inner);
 }
 
 // ---------------------------------------------------------------------------
@@ -464,7 +474,12 @@ __global__ __launch_bounds__(kBlock) void k_reach_thread(ReachArgs a) {
 __device__ __forceinline__ bool slab_chosen(const ReachArgs& a) {
   if (a.slab_mode == 0 || a.rc->rows > kSlabRows16) return false;
   if (a.slab_mode == 1) return true;
-  return 2ull * a.rc->queued[0] >= a.rc->rows;
+  if (2ull * a.rc->queued[0] < a.rc->rows) return false;
+  const uint64_t rows = a.rc->rows, cols = a.rc->cols, level = (uint64_t)a.rc->edges * ((cols + 31) / 32);
+  uint64_t inner = 0;
+#pragma unroll
+  for (int x = 0; x < kReachXcds; ++x) inner += a.rc->inner[x][0];
+  return level <= kSlabLevel ? 2 * inner >= rows : cols <= 2 * rows && 2 * inner >= 3 * rows;
 }
 
 template <typename W, int RP>

@@ -94,6 +94,24 @@ def test_wide_levels_of_wide_graphs(engine, depth):
     assert (sum(st["stage_bytes"].values()) == 0) == (depth < 18)
 
 
+@pytest.mark.parametrize("rows,leaves", [(200, 4_000), (20_000, 20)])
+def test_fans_take_the_tiers(engine, rows, leaves):
+    """Rows that outgrow the thread tier and lead nowhere: as slabs, a pass over all edges for every 32
+    leaves, they took 32 and 21 ms."""
+    src = np.repeat(np.arange(rows, dtype=np.uint32), leaves)
+    dst = np.arange(rows, rows * (leaves + 1), dtype=np.uint32)
+    s, d = to_gpu(src), to_gpu(dst)
+    ms = []
+    for _ in range(4):
+        t = time.perf_counter()
+        out_s, out_d, st = engine.solve("tc", s, d)
+        ms.append((time.perf_counter() - t) * 1e3)
+    np.testing.assert_array_equal(out_s.cpu().numpy(), src)
+    np.testing.assert_array_equal(out_d.cpu().numpy(), dst)
+    assert (st["iterations"], st["delta_sizes"], st["join_candidates"]) == (1, [rows * leaves, 0], 0)
+    assert min(ms) < 5
+
+
 DEEP = {
     "tc_slabs": ("tc", lambda: inputs.chain(30_000)),
     "tc_tiers": ("tc", lambda: inputs.chain(60_000)),

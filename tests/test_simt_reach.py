@@ -188,6 +188,13 @@ def test_slabs_where_most_rows_are_long(harness, tmp_path):
     src, dst = inputs.erdos_renyi(400, 250, seed=3)
     _, _, queued, width = _run(harness, tmp_path, [(src, dst)], slab=2)
     assert width == 0 and queued[0] < np.unique(src).size / 2
+    # long rows that lead nowhere, and the same with an edge from every second row (and one fewer)
+    src, dst = np.repeat(np.arange(40, dtype=np.uint32), 20), np.arange(40, 840, dtype=np.uint32)
+    assert _run(harness, tmp_path, [(src, dst)], slab=2)[3] == 0
+    for more, width in ((20, 32), (19, 0)):
+        hop = np.arange(more, dtype=np.uint32)
+        graph = np.concatenate([src, hop]), np.concatenate([dst, hop + np.uint32(20)])
+        assert _run(harness, tmp_path, [graph], grid=4, kb=8, slab=2)[3] == width
 
 
 @pytest.mark.parametrize("rows", [18431, 18432])
