@@ -75,6 +75,8 @@ struct Ctrl {
   uint64_t tail_n;             // tail loop: size of its run T (0: nothing for the fold)
   uint32_t tail_b;             // ... B's side before the fold (the fold writes the other)
   uint32_t tail_exit;          // ... why it stopped (kTail*)
+  uint32_t sources;            // distinct sources among 2,048 of the edges, or a few fewer
+  uint32_t rows;               // distinct rows of E, where they were counted (launch_count_rows)
 };
 
 // Why a tail loop stopped: the fixpoint or the iteration limit; the next iteration does

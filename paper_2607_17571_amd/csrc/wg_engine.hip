@@ -62,8 +62,11 @@ constexpr uint64_t kReachSpan = 1ull << 24;
 // Ids further apart go by their rank (us a pass, on their own keys through the iterations / by rank):
 // R-MAT scale 15 with 28-bit ids 15,379 / 498, scale 12 30-bit 1,876 / 263, scale 10 (600 edges) 768 /
 // 205; SG scale 14 26-bit 7,488 / 431.  The sort of the 2 m ids costs what the edges' wider keys would.
-// Fewer edges than this seldom have the rows (kReachMinRows) that make it pay.
+// (Fewer edges than this were not measured.)
 constexpr uint64_t kByRankMinEdges = 512, kByRankMaxEdges = 1ull << 28;
+// A sample of all edges that shows fewer sources than this is of fewer than kReachMinRows (128 sources set
+// 126 of its 4,096 bits on average).
+constexpr uint32_t kSurelyFew = 112;
 constexpr uint64_t kReachColsMax = 1ull << 20;  // columns of one instance: a bitmap fits one CU's LDS
 constexpr uint64_t kReachBitsCols = 1ull << 18; // ... three bitmaps
 // Slabs at once, without the tiers' thread launch first, while a level over all slabs is at most
@@ -142,6 +145,7 @@ struct wg_engine {
   uint64_t hash_slots = 0;  // hash-join variant: table slots of the current solve (0: off)
   uint32_t hrows_mask = 0;  // fair hash variant: row-table slots - 1 (0: off)
   uint32_t hpairs_mask = 0; // ... and pair-set slots - 1 (triangles; 0: none)
+  uint32_t sources = 0;     // of the current solve: distinct sources among a sample of its edges
   uint64_t key_space = 0;   // row ids (instance << w | src) of the current solve are below this
   uint64_t dense_rows = 0;  // rows of the dense edge index of the current solve (0: U + search)
   // how the loop's iterations join and sort: 0 the LSD passes; 1 the one-block sort,
@@ -854,6 +858,19 @@ bool grow_staged(wg_engine* e, uint64_t F, uint64_t C, uint64_t edges, bool* gro
   return true;
 }
 
+// TC with too few rows for its forms.  The input's sample (Ctrl::sources) rules that out where it can, and
+// says so of a small graph by itself; else E's rows are counted (15 us, where a renumbering and a dozen
+// launches that then find too few rows took 30 to 90).
+template <typename K>
+bool few_rows(wg_engine* e, uint64_t m, int w) {
+  if (e->sources >= kReachMinRows) return false;
+  if (m <= kSampledEdges && e->num_inst <= 1 && e->sources < kSurelyFew) return true;
+  Bufs<K> b = make_bufs<K>(e);
+  launch_count_rows<K>(e->stream, e->grid, e->d_ctrl, b.E, m, w);
+  fetch(e, &e->h_rb[0].c, e->d_ctrl, sizeof(Ctrl));
+  return e->h_rb[0].c.rows < kReachMinRows;
+}
+
 // TC one source row at a time (wg_reach.h), from the sorted distinct edges E and the seed.
 // Returns false where the iterations' launches have to take over (few rows, rows beyond the tiers,
 // no memory for the pool or the bitmaps): E and the seed are as they were.
@@ -1065,7 +1082,7 @@ bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_optio
     launch_sg_edges<K>(e->stream, e->grid, e->d_ctrl, b.E, m, a);
     read(0);
     const uint64_t rows = rc->rows, cols = rc->cols, edges = rc->edges, base = sc->base;
-    if (rows < kReachMinRows || base > kMaxKeys) return false;
+    if (base > kMaxKeys) return false;
     const bool fits = cols <= kSlabRows32 && rows + cols + 2 <= kSlabLdsWords && e->num_inst <= 1;
     const bool matrices = fits && (base * kSgDense >= cols * cols || sc->wide);
     if (!matrices && sc->wide) return false;
@@ -1315,6 +1332,10 @@ wg_status run(wg_engine* e, int query, const uint32_t* src, const uint32_t* dst,
   const int mode = query == WG_QUERY_SG ? kModeEdges : (kModeEdges | kModeSeed);
   launch_compact<K>(e->stream, e->grid, mode, e->d_ctrl, &e->d_ctrl->m_in, b.cand[passes & 1],
                     b.cand[(passes & 1) ^ 1], b, w, 0, 0, stage(e, WG_STAGE_DEDUP_DIFF));
+  if (e->row_wise && query == WG_QUERY_TC && few_rows<K>(e, m, w)) {
+    if (by_rank) return kNotByRank;
+    e->row_wise = false;
+  }
   if (e->row_wise) {
     e->forms_used = kFormAll;
     const bool done = query == WG_QUERY_TC   ? reach<K>(e, m, w, o, st)
@@ -1874,6 +1895,7 @@ wg_status solve(wg_engine* e, int query, uint32_t num, const uint64_t* d_offsets
         e->err = "batch offsets must start at 0, not decrease and end at m";
         return WG_ERR_INVALID_ARG;
       }
+      e->sources = e->h_rb[0].c.sources;
       int w = field_bits(e->h_rb[0].c.maxid);
       if (o.radix_field_bits) {
         const uint32_t maxid = e->h_rb[0].c.maxid;

@@ -41,13 +41,39 @@ constexpr uint32_t kNoRow = 0xFFFFFFFFu;
 // wave, 6.4 us so.
 constexpr int kMaxIdItems = 8;
 constexpr uint32_t kMaxIdEdges = kBlock * kMaxIdItems;
+static_assert(kMaxIdEdges == kSampledEdges, "");
+// The last block samples the sources instead: how many bits of 4,096 those of 2,048 edges set (all of
+// them, where there are no more), spread over the whole input.
 __global__ __launch_bounds__(kBlock) void k_max_id(Ctrl* ctrl, const uint32_t* __restrict__ src,
                                                    const uint32_t* __restrict__ dst, uint64_t m) {
+  constexpr uint32_t kSampleWords = 128;
   __shared__ uint32_t s_max;
+  __shared__ uint32_t s_bits[kSampleWords];
   if (threadIdx.x == 0) s_max = 0;
+  if (threadIdx.x < kSampleWords) s_bits[threadIdx.x] = 0;
   __syncthreads();
+  const uint32_t last = gridDim.x - 1;
+  if (blockIdx.x == last) {
+    const uint64_t step = max<uint64_t>(m / kMaxIdEdges, 1);
+    uint32_t v[kMaxIdItems];
+#pragma unroll
+    for (int k = 0; k < kMaxIdItems; ++k) {
+      const uint64_t i = ((uint64_t)k * kBlock + threadIdx.x) * step;
+      v[k] = i < m ? src[i] : src[0];
+    }
+#pragma unroll
+    for (int k = 0; k < kMaxIdItems; ++k) {
+      const uint32_t h = (v[k] * 0x9E3779B1u) >> 20;  // (a multiplicative hash: 2^32 over the golden ratio)
+      atomicOr(&s_bits[h >> 5], 1u << (h & 31u));
+    }
+    __syncthreads();
+    if (threadIdx.x < kSampleWords) atomicAdd(&s_max, (uint32_t)__popc(s_bits[threadIdx.x]));
+    __syncthreads();
+    if (threadIdx.x == 0) ctrl->sources = s_max;
+    return;
+  }
   uint32_t mx = 0;
-  for (uint64_t base = (uint64_t)blockIdx.x * kMaxIdEdges; base < m; base += (uint64_t)gridDim.x * kMaxIdEdges) {
+  for (uint64_t base = (uint64_t)blockIdx.x * kMaxIdEdges; base < m; base += (uint64_t)last * kMaxIdEdges) {
 #pragma unroll
     for (int k = 0; k < kMaxIdItems; ++k) {
       const uint64_t i = base + (uint64_t)k * kBlock + threadIdx.x;
@@ -2959,7 +2985,8 @@ static inline int stream_blocks(const Grid& g, uint64_t n) {
 
 void launch_max_id(hipStream_t s, const Grid& g, Ctrl* ctrl, const uint32_t* src,
                    const uint32_t* dst, uint64_t m) {
-  hipLaunchKernelGGL(k_max_id, dim3(stream_blocks(g, (m + kMaxIdItems - 1) / kMaxIdItems)), dim3(kBlock), 0, s, ctrl, src, dst, m);
+  hipLaunchKernelGGL(k_max_id, dim3(stream_blocks(g, (m + kMaxIdItems - 1) / kMaxIdItems) + 1), dim3(kBlock), 0, s, ctrl, src,
+                     dst, m);
 }
 
 void launch_check_offsets(hipStream_t s, const Grid& g, Ctrl* ctrl, const uint64_t* offsets,

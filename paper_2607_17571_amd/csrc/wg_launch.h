@@ -122,6 +122,8 @@ struct Bufs {
   uint32_t hpairs; // ... and E's pair set htab[hrows + 1, hrows + 1 + hpairs], 0 = none
 };
 
+// The largest id, and a sample of the sources of at most kSampledEdges edges.
+constexpr uint64_t kSampledEdges = 2048;
 void launch_max_id(hipStream_t s, const Grid& g, Ctrl* ctrl, const uint32_t* src,
                    const uint32_t* dst, uint64_t m);
 

@@ -69,9 +69,10 @@ constexpr uint32_t kReachTileStretch = 64;
 constexpr uint32_t kReachQueueStretch = 512;  // queued rows likewise
 constexpr uint32_t kReachEdgePad = 8;       // edge records readable past the last
 
-// Fewer rows than this are left to the iterations' launches: a row's levels (and a slab's) are a
-// serial chain in one workgroup, so they leave most CUs idle where an iteration's launches spread
-// its candidates over the chip.  (Down to 180 rows the rows are ahead: 171 us against 256.)
+// Fewer rows than this are left to the iterations' launches (TC): a fat row is a serial chain in one
+// workgroup, where an iteration's launches spread its candidates over the chip (one vertex with 1,000,000
+// leaves 2,118 us against 448, four instances with one row of 100,000 1,177 against 345; down to 180 rows
+// the rows are ahead, 171 us against 256).
 constexpr uint32_t kReachMinRows = 128;
 
 // Slabs: LDS for two words per row (and one idle row).  32 columns per slab while the rows fit
@@ -197,6 +198,9 @@ struct ReachResult {
   int w;
 };
 
+// Counts the rows of the sorted distinct edges E (at most m) into ctrl->rows.
+template <typename K>
+void launch_count_rows(hipStream_t s, const Grid& g, Ctrl* ctrl, const K* E, uint64_t m, int w);
 // Renumbers the sorted distinct edges E (ctrl->m_unique of them, at most m).
 template <typename K>
 void launch_reach_graph(hipStream_t s, const Grid& g, const Ctrl* ctrl, const K* E, uint64_t m, const ReachArgs& a,

@@ -72,6 +72,13 @@ void offsets(hipStream_t s, const Grid& g, uint64_t m, const ReachArgs& a, uint6
 }  // namespace
 
 template <typename K>
+void launch_count_rows(hipStream_t s, const Grid& g, Ctrl* ctrl, const K* E, uint64_t m, int w) {
+  // (few blocks: one same-address atomic each)
+  hipLaunchKernelGGL(k_count_rows<K>, dim3(std::min<uint32_t>(blocks_for(g, m), std::max(1, g.stream / 8))), dim3(kBlock), 0, s,
+                     ctrl, E, w);
+}
+
+template <typename K>
 void launch_reach_graph(hipStream_t s, const Grid& g, const Ctrl* ctrl, const K* E, uint64_t m, const ReachArgs& a,
                         uint64_t* part) {
   const uint32_t b = blocks_for(g, m);
@@ -161,6 +168,7 @@ void launch_ids_keys(hipStream_t s, const Grid& g, const uint32_t* ids, const K*
 #define WG_REACH_INSTANTIATE(K)                                                                              \
   template void launch_reach_graph<K>(hipStream_t, const Grid&, const Ctrl*, const K*, uint64_t, const ReachArgs&, \
                                       uint64_t*);                                                            \
+  template void launch_count_rows<K>(hipStream_t, const Grid&, Ctrl*, const K*, uint64_t, int);             \
   template void launch_reach_keys<K>(hipStream_t, const Grid&, const ReachResult&, uint64_t, K*);            \
   template void launch_ids_keys<K>(hipStream_t, const Grid&, const uint32_t*, const K*, uint64_t, int, int, uint64_t*);
 WG_REACH_INSTANTIATE(uint32_t)

@@ -130,6 +130,21 @@ __global__ __launch_bounds__(kBlock) void k_ids_keys(const uint32_t* __restrict_
   }
 }
 
+template <typename K>
+__global__ __launch_bounds__(kBlock) void k_count_rows(Ctrl* ctrl, const K* __restrict__ E, int w) {
+  __shared__ uint32_t s_rows;
+  if (threadIdx.x == 0) s_rows = 0;
+  __syncthreads();
+  const uint64_t n = ctrl->m_unique;
+  uint32_t rows = 0;
+  for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (uint64_t)gridDim.x * kBlock)
+    rows += i == 0 || head_row<K>(E[i - 1], w) != head_row<K>(E[i], w) ? 1 : 0;
+  rows = wave_sum<uint32_t>(rows);
+  if (lane_id() == 0 && rows) atomicAdd(&s_rows, rows);
+  __syncthreads();
+  if (threadIdx.x == 0 && s_rows) atomicAdd(&ctrl->rows, s_rows);
+}
+
 // ---------------------------------------------------------------------------
 // Renumbering.  Every edge flags its row's and its column's key (plain byte stores: no atomics);
 // the flags become one 16-byte word per 32 keys with the bits and the ranks before them, so that

@@ -112,6 +112,53 @@ def test_fans_take_the_tiers(engine, rows, leaves):
     assert min(ms) < 5
 
 
+def _fan(rows, leaves, first=0):
+    ids = np.arange(first, first + rows * (leaves + 1), dtype=np.uint32)
+    return np.repeat(ids[:rows], leaves), ids[rows:]
+
+
+def _offset(graph, by=200):
+    return tuple(x + np.uint32(by) for x in graph)
+
+
+# (a sample of 2,048 edges that holds them all, or a part of them)
+FEW_ROWS = {
+    "one": ("tc", lambda: _fan(1, 200), False), "fans_111": ("tc", lambda: _fan(111, 10), False),
+    "fans_127": ("tc", lambda: _fan(127, 10), False), "fans_128": ("tc", lambda: _fan(128, 10), True),
+    "dense": ("tc", lambda: _offset(inputs.erdos_renyi(120, 3_000, seed=2)), False),
+    "chain": ("tc", lambda: _offset(inputs.chain(129)), True),
+    "fat_127": ("tc", lambda: _fan(127, 400), False), "fat_128": ("tc", lambda: _fan(128, 400), True),
+    "fat_one": ("tc", lambda: _fan(1, 60_000), False),
+    "fat_few_often": ("tc", lambda: [np.concatenate(p) for p in zip(_fan(20, 20_000), _fan(108, 2, first=500_000))], True),
+    "sg_one": ("sg", lambda: _fan(1, 200), True), "sg_fans": ("sg", lambda: _fan(100, 30), True),
+    "sg_dense": ("sg", lambda: _offset(inputs.erdos_renyi(120, 3_000, seed=2)), True),
+}
+
+
+@pytest.mark.parametrize("graph", sorted(FEW_ROWS))
+def test_few_rows(engine, graph):
+    """Closures of fewer than 128 rows are the iterations', however few of them the sample sees; SG's are not."""
+    query, make, forms = FEW_ROWS[graph]
+    src, dst = make()
+    s, d, st = run(engine, query, src, dst)
+    assert_same(s, d, st, getattr(oracle, query)(src, dst))
+    assert (sum(st["stage_bytes"].values()) == 0) == forms
+
+
+@pytest.mark.parametrize("rows,leaves,forms", [(20, 10, False), (20, 50, False), (31, 50, False), (32, 50, True)])
+def test_few_rows_of_a_batch(engine, rows, leaves, forms):
+    import torch
+
+    src, dst = _fan(rows, leaves)
+    n = src.size
+    s, d, offs, st = engine.solve_batch("tc", to_gpu(np.tile(src, 4)), to_gpu(np.tile(dst, 4)),
+                                        torch.arange(0, 5 * n, n, dtype=torch.int64, device="cuda"))
+    np.testing.assert_array_equal(s.cpu().numpy(), np.tile(src, 4))
+    np.testing.assert_array_equal(d.cpu().numpy(), np.tile(dst, 4))
+    assert offs.tolist() == list(range(0, 5 * n, n)) and st["iterations"] == 1
+    assert (sum(st["stage_bytes"].values()) == 0) == forms
+
+
 DEEP = {
     "tc_slabs": ("tc", lambda: inputs.chain(30_000)),
     "tc_tiers": ("tc", lambda: inputs.chain(60_000)),
