@@ -77,8 +77,10 @@ constexpr uint64_t kSlabAlways = 3u << 20;
 constexpr uint32_t kReachLevels = 4096;  // levels allotted at first (grown eightfold when passed)
 constexpr uint32_t kReachLevelsMax = 1u << 21;
 constexpr uint32_t kReachReadLevels = 126;  // levels read back with the control block
-// SG on the renumbered graph (wg_sg.h): rounds at most, and enqueued per host check
+// SG on the renumbered graph (wg_sg.h): rounds allotted at first (grown eightfold when passed, as the
+// closure's), and enqueued per host check
 constexpr uint32_t kSgLevels = 4096;
+constexpr uint32_t kSgLevelsMax = 1u << 21;
 constexpr uint32_t kSgMatrixRounds = 4;
 constexpr uint32_t kSgPairRounds = 4;
 constexpr size_t kReachHostBytes = std::max(sizeof(ReachCtl) + kReachReadLevels * sizeof(ReachLevel),
@@ -140,6 +142,7 @@ struct wg_engine {
   uint32_t fetch_seq = 0;
   uint8_t* h_reach = nullptr;  // pinned: the control blocks and the first levels, read back
   uint32_t reach_levels = kReachLevels;
+  uint32_t sg_levels = kSgLevels;
   bool res_is_reach = false;   // the latest result is in that form
   ReachResult res_reach{};
   uint64_t hash_slots = 0;  // hash-join variant: table slots of the current solve (0: off)
@@ -1043,8 +1046,8 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
 }
 
 // SG on the renumbered graph (wg_sg.h), from the sorted distinct edges E: matrices or pairs.
-// Returns false where the iterations' launches have to take over (few rows, a graph neither form
-// takes, no memory for it): E is as it was.
+// Returns false where the iterations' launches have to take over (a graph neither form takes, no
+// memory for it): E is as it was.  More rounds than allotted: run again with eight times as many.
 template <typename K>
 bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_options& o, wg_stats* st) {
   Bufs<K> b = make_bufs<K>(e);
@@ -1053,13 +1056,30 @@ bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_optio
   SgArgs a{};
   const ReachCtl* rc = (const ReachCtl*)e->h_reach;
   const SgCtl* sc = (const SgCtl*)(e->h_reach + sizeof(ReachCtl));
-  const SgLevel* lev = (const SgLevel*)(e->h_reach + sizeof(ReachCtl) + sizeof(SgCtl));
+  const SgLevel* const pinned = (const SgLevel*)(e->h_reach + sizeof(ReachCtl) + sizeof(SgCtl));
+  const SgLevel* lev = pinned;
   constexpr size_t head = sizeof(ReachCtl) + sizeof(SgCtl);
-  constexpr size_t level_bytes = kSgLevels * sizeof(SgLevel);
-  // reads the control blocks and the first `levels` levels
+  const uint32_t allotted = e->sg_levels;
+  const size_t level_bytes = allotted * sizeof(SgLevel);
+  uint32_t rounds = 0;         // the fixpoint: the first round that finds nothing
+  std::vector<SgLevel> deep;   // the levels, once they are more than the pinned memory holds
+  // reads the control blocks and the first `levels` levels (those before `rounds` are final)
   auto read = [&](uint32_t levels) {
+    levels = std::min(levels, allotted);
     fetch(e, e->h_reach, e->rctl.p, head + std::min(levels, kSgLevels) * sizeof(SgLevel));
     if (e->cancel && e->cancel->load()) fail(e, WG_ERR_CANCELLED, "cancelled");
+    if (levels <= kSgLevels) return;
+    const uint32_t from = deep.empty() ? 0 : rounds;
+    deep.resize(levels);
+    hip_check(e, hipMemcpyAsync(deep.data() + from, a.lev + from, (levels - from) * sizeof(SgLevel), hipMemcpyDeviceToHost,
+                                e->stream), "readback");
+    sync_stream(e);
+    lev = deep.data();
+  };
+  auto deeper = [&] {
+    if (allotted >= kSgLevelsMax) return false;
+    e->sg_levels = allotted * 8;
+    return same_generation<K>(e, m, w, passes, o, st);
   };
   try {
     a.edge = (uint4*)graph_buffers(e, ra.g, m, w, true, m * sizeof(uint4));
@@ -1071,7 +1091,7 @@ bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_optio
     a.lev = (SgLevel*)((uint8_t*)e->rctl.p + head);
     a.cancel = e->cancel ? e->h_cancel : nullptr;
     // (rounds up to max_iterations show whether the fixpoint is among them)
-    a.lev_cap = (uint32_t)(o.max_iterations ? std::min<uint64_t>(o.max_iterations, kSgLevels - 1) + 1 : kSgLevels);
+    a.lev_cap = (uint32_t)(o.max_iterations ? std::min<uint64_t>(o.max_iterations, allotted - 1) + 1 : allotted);
     auto check_limit = [&](uint64_t known) {  // all of levels [0, known) found something
       if (o.max_iterations && known > o.max_iterations)
         fail(e, WG_ERR_ITER_LIMIT, "max_iterations reached before the fixpoint");
@@ -1086,7 +1106,6 @@ bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_optio
     const bool fits = cols <= kSlabRows32 && rows + cols + 2 <= kSlabLdsWords && e->num_inst <= 1;
     const bool matrices = fits && (base * kSgDense >= cols * cols || sc->wide);
     if (!matrices && sc->wide) return false;
-    uint32_t rounds = 0;  // the fixpoint: the first round that finds nothing
     auto at_fixpoint = [&](uint32_t known) {  // levels [0, known) are read back
       while (rounds < known && (lev[rounds].n | lev[rounds].found)) ++rounds;
       return rounds < known;
@@ -1109,8 +1128,10 @@ bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_optio
       a.cdeg = b.rowb;
       launch_sg_matrix_base<K>(e->stream, e->grid, e->d_ctrl, b.E, m, a, slabs);
       for (uint32_t j = 1;;) {
-        if (j + kSgMatrixRounds + 1 > kSgLevels) return false;
-        for (uint32_t k = 0; k < kSgMatrixRounds; ++k) launch_sg_matrix_round(e->stream, e->grid, a, j++, slabs);
+        // (a read of levels beyond the pinned memory takes longer than four thin rounds)
+        const uint32_t more = j < kSgLevels ? kSgMatrixRounds : 16 * kSgMatrixRounds;
+        if (j + more + 1 > allotted) return deeper();
+        for (uint32_t k = 0; k < more; ++k) launch_sg_matrix_round(e->stream, e->grid, a, j++, slabs);
         read(j + 1);
         if (at_fixpoint(j)) break;
         check_limit(j);
@@ -1133,15 +1154,17 @@ bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_optio
         launch_sg_pairs_base(e->stream, e->grid, e->d_ctrl, m, a);
         uint32_t j = 1;
         rounds = 0;
+        deep.clear();
+        lev = pinned;
         for (uint32_t k = kSgPairRounds;;) {
-          for (; k > 0 && j + 1 < kSgLevels; --k) launch_sg_pairs_round(e->stream, e->grid, a, j++);
+          for (; k > 0 && j + 1 < allotted; --k) launch_sg_pairs_round(e->stream, e->grid, a, j++);
           launch_sg_pairs_tail(e->stream, a, j);
           read(j + kReachReadLevels);
           if (sc->next > j + kReachReadLevels) read(sc->next);
           j = sc->next;
           if (sc->stop || at_fixpoint(j)) break;
           check_limit(j);
-          if (j + 1 >= kSgLevels) return false;
+          if (j + 1 >= allotted) return deeper();
           // rounds until the pairs fit the tail, at their rate of change
           const double f1 = (double)(lev[j - 1].found >> 32), f0 = (double)(lev[j - 2].found >> 32);
           const double r = std::min(0.98, std::max(0.05, f1 / std::max(f0, 1.0)));
@@ -1149,7 +1172,7 @@ bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_optio
         }
         if (sc->stop & kSgDeep) {
           check_limit(a.lev_cap);
-          return false;
+          return deeper();
         }
         if (!sc->stop) break;
         // too small: cleared and run again

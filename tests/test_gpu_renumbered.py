@@ -166,6 +166,30 @@ DEEP = {
 }
 
 
+@pytest.mark.parametrize("n,hub", [(4_095, 0), (4_096, 0), (9_000, 0), (4_400, 70)])
+def test_same_generation_of_many_rounds(n, hub):
+    """More rounds than are allotted at first, as pairs and (beside a vertex of 70 out-edges) as
+    matrices: grown, and not left to the iterations."""
+    src, dst = _two_chains(n)
+    pairs = 2 * n
+    if hub:
+        leaf = np.arange(30_000, 30_000 + hub, dtype=np.uint32)
+        src, dst = np.append(src, np.full(hub, 29_999, np.uint32)), np.append(dst, leaf)
+        pairs += hub * (hub - 1)
+    eng = wg.Engine(0)
+    try:
+        for _ in range(2):
+            s, d, st = run(eng, "sg", src, dst)
+            assert (st["iterations"], st["result_tuples"]) == (n, pairs) and sum(st["stage_bytes"].values()) == 0
+            assert st["delta_sizes"] == [pairs - 2 * (n - 1)] + [2] * (n - 1) + [0]
+            assert st["join_candidates"] == 2 * (n - 1)
+            keep = s < 29_000
+            np.testing.assert_array_equal(s[keep], np.arange(2 * n))
+            np.testing.assert_array_equal(d[keep], np.roll(np.arange(2 * n), n))
+    finally:
+        eng.close()
+
+
 def _two_chains(n):
     """One root over two chains of n vertices: n rounds of one pair each."""
     s = np.arange(2 * n, dtype=np.uint32)
