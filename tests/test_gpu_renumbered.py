@@ -1,5 +1,7 @@
 """The forms on the renumbered graph at the edges of their rules, through the C ABI, against the
-oracle: same-generation as matrices and as pairs, triangles beyond 65,536 columns."""
+oracle: same-generation as matrices and as pairs, triangles beyond 65,536 columns, closures as slabs
+and by tiers, ids by rank.  Every form leaves to the iterations' launches what it does not take, with
+the same result, so each test says which of them it is for (stage_bytes are the iterations' alone)."""
 
 import time
 
@@ -27,12 +29,34 @@ def engine():
     return wg.Engine(0)
 
 
+def by_forms(st):
+    return sum(st["stage_bytes"].values()) == 0
+
+
+def sg_form(src, dst):
+    """The form of same-generation a graph takes, by the rule of the sizes."""
+    edges = np.unique((src.astype(np.uint64) << np.uint64(32)) | dst)
+    deg = np.unique(edges >> np.uint64(32), return_counts=True)[1].astype(np.int64)
+    cols, base, wide = np.unique(dst).size, int((deg * (deg - 1)).sum()), bool(deg.max() > 64)
+    if cols <= 18_431 and deg.size + cols + 2 <= 36_864 and (base * 256 >= cols * cols or wide):
+        return "matrices"
+    return "" if wide else "pairs"
+
+
 @pytest.mark.parametrize("irreflexive", [False, True])
 @pytest.mark.parametrize("graph", sorted(SG))
 def test_same_generation(engine, graph, irreflexive):
     src, dst = SG[graph]()
+    form = {"grid": "pairs"}.get(graph, graph.split("_")[0])
+    assert sg_form(src, dst) == form
     opts = wg.make_options(flags=wg.WG_SG_IRREFLEXIVE if irreflexive else 0)
-    assert_same(*run(engine, "sg", src, dst, opts), oracle.sg(src, dst, irreflexive=irreflexive))
+    ref = oracle.sg(src, dst, irreflexive=irreflexive)
+    s, d, st = run(engine, "sg", src, dst, opts)
+    assert_same(s, d, st, ref)
+    assert by_forms(st)
+    if graph == "pairs_table_grown":  # (more pairs than the first table's list holds)
+        base = 2 * np.unique(src).size
+        assert ref.src.size / 2 > max(1024, 1 << (8 * base - 1).bit_length()) / 2
 
 
 WIDE = {  # ids over 32 bits: by rank
@@ -55,7 +79,11 @@ def test_ids_by_rank(engine, graph, bits):
         src, dst = np.where(src == src.max(), top, src), np.where(dst == src.max(), top, dst)
     s, d, st = run(engine, query, src, dst)
     assert_same(s, d, st, getattr(oracle, query)(src, dst))
-    assert st["key_bytes"] == 8
+    assert st["key_bytes"] == 8 and by_forms(st) == (graph != "few_rows")
+    if query == "sg":
+        assert sg_form(src, dst) == graph.split("_")[1]
+    elif graph != "few_rows":
+        assert (st["resumes"] > 0) == (graph == "tc_tiers")  # (tiers that rows outgrew)
 
 
 @pytest.mark.parametrize("digit_bits", [0, 10])
@@ -80,7 +108,7 @@ def test_thin_rows_of_wide_graphs(engine, count, length):
     np.testing.assert_array_equal(d, v[:, j].ravel())
     sizes = [count * (length - 1 - k) for k in range(length)]
     assert st["iterations"] == length - 1 and st["delta_sizes"] == sizes
-    assert st["join_candidates"] == sum(sizes[1:]) and sum(st["stage_bytes"].values()) == 0
+    assert st["join_candidates"] == sum(sizes[1:]) and by_forms(st)
 
 
 @pytest.mark.parametrize("depth", [16, 17, 18])
@@ -91,7 +119,7 @@ def test_wide_levels_of_wide_graphs(engine, depth):
     src, dst = inputs.binary_tree(depth)
     s, d, st = run(engine, "tc", src, dst)
     assert_same(s, d, st, oracle.tc(src, dst))
-    assert (sum(st["stage_bytes"].values()) == 0) == (depth < 18)
+    assert by_forms(st) == (depth < 18)
 
 
 @pytest.mark.parametrize("rows,leaves", [(200, 4_000), (20_000, 20)])
@@ -142,7 +170,7 @@ def test_few_rows(engine, graph):
     src, dst = make()
     s, d, st = run(engine, query, src, dst)
     assert_same(s, d, st, getattr(oracle, query)(src, dst))
-    assert (sum(st["stage_bytes"].values()) == 0) == forms
+    assert by_forms(st) == forms
 
 
 @pytest.mark.parametrize("rows,leaves,forms", [(20, 10, False), (20, 50, False), (31, 50, False), (32, 50, True)])
@@ -156,7 +184,7 @@ def test_few_rows_of_a_batch(engine, rows, leaves, forms):
     np.testing.assert_array_equal(s.cpu().numpy(), np.tile(src, 4))
     np.testing.assert_array_equal(d.cpu().numpy(), np.tile(dst, 4))
     assert offs.tolist() == list(range(0, 5 * n, n)) and st["iterations"] == 1
-    assert (sum(st["stage_bytes"].values()) == 0) == forms
+    assert by_forms(st) == forms
 
 
 DEEP = {
@@ -180,7 +208,7 @@ def test_same_generation_of_many_rounds(n, hub):
     try:
         for _ in range(2):
             s, d, st = run(eng, "sg", src, dst)
-            assert (st["iterations"], st["result_tuples"]) == (n, pairs) and sum(st["stage_bytes"].values()) == 0
+            assert (st["iterations"], st["result_tuples"]) == (n, pairs) and by_forms(st)
             assert st["delta_sizes"] == [pairs - 2 * (n - 1)] + [2] * (n - 1) + [0]
             assert st["join_candidates"] == 2 * (n - 1)
             keep = s < 29_000
@@ -239,3 +267,21 @@ def test_triangles(engine, scale, m):
         src, dst = np.concatenate([src, ids[:-1]]), np.concatenate([dst, ids[1:]])
     count, st = engine.triangles(to_gpu(src), to_gpu(dst))
     assert (count, st["join_candidates"]) == oracle.triangles(src, dst)
+    assert by_forms(st)
+
+
+@pytest.mark.parametrize("make", [
+    lambda: inputs.grid_dag(150), lambda: inputs.erdos_renyi(200_000, 160_000, seed=5),
+    lambda: inputs.erdos_renyi(600_000, 480_000, seed=4), lambda: inputs.erdos_renyi(700_000, 630_000, seed=4)],
+    ids=["slabs_of_16", "queue_4_waves", "queue_16_waves", "thin_and_queue"])
+def test_large_closures_equal_the_iterations(engine, make):
+    """Routes whose graphs are too large for the oracle, against the iterations' launches."""
+    import torch
+
+    s, d = map(to_gpu, make())
+    a_s, a_d, a = engine.solve("tc", s, d)
+    b_s, b_d, b = engine.solve("tc", s, d, wg.make_options(batch_k=2))
+    assert by_forms(a) and not by_forms(b)
+    assert torch.equal(a_s.view(torch.int32), b_s.view(torch.int32)) and torch.equal(a_d.view(torch.int32), b_d.view(torch.int32))
+    for key in ("iterations", "delta_sizes", "join_candidates"):
+        assert a[key] == b[key], key
