@@ -852,13 +852,28 @@ bool grow_staged(wg_engine* e, uint64_t F, uint64_t C, uint64_t edges, bool* gro
     if (granted < e->allocated + more) return false;
     e->budget = granted;
   }
+  const uint64_t had_cand = e->cand_cap, had_full = e->full_cap;
   e->cand_cap = cand_cap;
   e->full_cap = full_cap;
-  IterRec seed{};
-  seed.N = seed.F = seed.FA = edges;
-  size_buffers(e, true, 0, &seed);
+  try {
+    IterRec seed{};
+    seed.N = seed.F = seed.FA = edges;
+    size_buffers(e, true, 0, &seed);
+  } catch (const Fail&) {
+    // (a buffer may be gone: staged_again)
+    e->cand_cap = had_cand;
+    e->full_cap = had_full;
+    throw;
+  }
   launch_resume(e->stream, e->d_ctrl, e->cand_cap, e->full_cap, 0);
   return true;
+}
+
+// The staged buffers at their capacities, E and the seed as they are, where a growth that failed half
+// way has left some without memory: the iterations' launches use all of them.
+void staged_again(wg_engine* e) {
+  const IterRec seed{};
+  size_buffers(e, true, 0, &seed);
 }
 
 // TC with too few rows for its forms.  The input's sample (Ctrl::sources) rules that out where it can, and
@@ -1378,6 +1393,7 @@ wg_status run(wg_engine* e, int query, const uint32_t* src, const uint32_t* dst,
       st->iterations = st->base_tuples = st->join_candidates = st->resumes = 0;
     }
     if (by_rank) return kNotByRank;
+    staged_again(e);
     b = make_bufs<K>(e);
   }
   launch_edge_index<K>(e->stream, e->grid, e->d_ctrl, b, w, stage(e, WG_STAGE_PREPARE));

@@ -77,6 +77,64 @@ def test_allocator_failure_is_out_of_memory_and_engine_stays_usable():
     assert hook.frees == hook.allocs
 
 
+class _RefusingAllocator(wg.TorchAllocator):
+    """Refuses one allocation, the one numbered `at`."""
+
+    def __init__(self, at):
+        super().__init__(0)
+        self.at, self.asked = at, 0
+
+    def _on_alloc(self, nbytes, stream, user):
+        self.asked += 1
+        if self.asked - 1 == self.at:
+            self.failed += 1
+            return None
+        return super()._on_alloc(nbytes, stream, user)
+
+
+REFUSED = {  # closures and pairs for which the buffers grow
+    "tc_slabs": ("tc", lambda: inputs.grid_dag(48)),
+    "tc_tiers": ("tc", lambda: [np.concatenate([x + np.uint32(120 * i) for i in range(400)]) for x in inputs.chain(120)]),
+    "tc_by_rank": ("tc", lambda: inputs.scatter_ids(*inputs.grid_dag(48), 28, seed=1)),
+    "sg_matrices": ("sg", lambda: inputs.rmat(12, 3_600, *inputs.RMAT_ABCD, seed=12)),
+    "sg_pairs": ("sg", lambda: inputs.binary_tree(11)),
+}
+
+
+@pytest.mark.parametrize("graph", sorted(REFUSED))
+def test_any_one_allocation_refused(graph):
+    """Wherever the memory is missing, also half way through a growth whose form then leaves the solve to
+    the iterations: the result is right or the solve out of memory, and the engine stays usable."""
+    query, make = REFUSED[graph]
+    src, dst = make()
+    s, d = to_gpu(src), to_gpu(dst)
+    plain = _RefusingAllocator(-1)
+    eng = wg.Engine(0, allocator=plain)
+    first = plain.asked
+    ref_s, ref_d, ref = eng.solve(query, s, d)
+    total, want = plain.asked, (ref_s.cpu().numpy(), ref_d.cpu().numpy())
+    eng.close()
+    ended = {True: 0, False: 0}
+    for at in range(first, total):
+        print(f"[gpu] {graph}: allocation {at} of {total} refused", flush=True, file=sys.stderr)
+        hook = _RefusingAllocator(at)
+        eng = wg.Engine(0, allocator=hook)
+        for again in (False, True):
+            try:
+                got_s, got_d, st = eng.solve(query, s, d)
+            except wg.WgError as error:
+                assert error.status == wg.WG_ERR_OUT_OF_MEMORY and not again
+                ended[False] += 1
+                continue
+            ended[True] += 1
+            np.testing.assert_array_equal(got_s.cpu().numpy(), want[0])
+            np.testing.assert_array_equal(got_d.cpu().numpy(), want[1])
+            assert st["delta_sizes"] == ref["delta_sizes"] and st["join_candidates"] == ref["join_candidates"]
+        assert hook.failed == 1
+        eng.close()
+    assert ended[True] > ended[False]
+
+
 def test_default_allocator_is_stream_ordered_and_exact():
     """NULL allocator: hipMallocAsync / hipFreeAsync on the solve's stream; growth from small
     buffers and a side stream keep the results exact."""
