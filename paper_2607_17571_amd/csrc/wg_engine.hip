@@ -841,11 +841,12 @@ void* graph_buffers(wg_engine* e, ReachGraph& g, uint64_t m, int w, bool slabs, 
 }
 
 // The growth for a fixpoint of F tuples and at most C candidates (or keys) per iteration: false when
-// a budget does not allow it.  The candidate buffers' contents are lost.
-bool grow_staged(wg_engine* e, uint64_t F, uint64_t C, uint64_t edges, bool* grown) {
+// a budget does not allow it.  kept: `rows` entries of rowa, rowb and off and the first cand1 bytes of
+// cand[1] are as they were; else the candidate and row buffers' contents are lost.
+bool grow_staged(wg_engine* e, uint64_t F, uint64_t C, uint64_t edges, uint64_t rows, uint64_t cand1, bool* kept) {
+  *kept = true;
   uint64_t cand_cap, full_cap;
   const uint64_t more = staged_growth(e, F, C, &cand_cap, &full_cap);
-  *grown = more != 0;
   if (more == 0) return true;
   if (e->budget && e->allocated + more > e->budget) {
     const uint64_t granted = e->grow_hook ? e->grow_hook(e->allocated + more) : 0;
@@ -856,6 +857,16 @@ bool grow_staged(wg_engine* e, uint64_t F, uint64_t C, uint64_t edges, bool* gro
   e->cand_cap = cand_cap;
   e->full_cap = full_cap;
   try {
+    try {
+      for (DevBuf* b : {&e->rowa, &e->rowb, &e->off})
+        if (rows) grow_keep(e, *b, std::max(cand_cap, e->row_cap) * 4, rows * 4);
+      if (cand1) grow_keep(e, e->cand[1], cand_cap * e->key_bytes, cand1);
+    } catch (const Fail& f) {
+      // (both sizes of a buffer at once are too much: without its contents)
+      if (f.st != WG_ERR_CAPACITY && f.st != WG_ERR_OUT_OF_MEMORY) throw;
+      e->err.clear();
+      *kept = false;
+    }
     IterRec seed{};
     seed.N = seed.F = seed.FA = edges;
     size_buffers(e, true, 0, &seed);
@@ -973,7 +984,7 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
         if (rc->stop & kReachPoolFull) pool = std::max<uint64_t>(pool, rc->cursor + rc->cursor / 8);
         if (rc->stop & kReachSlotsFull) bits = ((uint64_t)rc->queued[kBitsTier] + rc->queued[kBitsTier] / 8) * a.words;
         if (rc->stop & kReachSlabFull)
-          bits = (uint64_t)((rc->cols + rc->slab - 1) / rc->slab) * rc->rows * rc->slab / 32 + 4;
+          bits = (uint64_t)((rc->cols + rc->slab - 1) / rc->slab) * rc->rows * rc->slab / 32 * 9 / 8 + 4;
         if (pool > kMaxKeys) return false;
         continue;
       }
@@ -1006,28 +1017,30 @@ bool reach(wg_engine* e, uint64_t m, int w, const wg_options& o, wg_stats* st) {
         cand_total += l.d[form];
       }
       if (F > kMaxKeys || C > kMaxKeys) return false;  // (the iterations' launches say so)
-      // (once per size: the growth takes the buffers that hold the rows' counts along)
-      bool grown = false;
-      if (!grow_staged(e, F, C, rc->edges, &grown)) {
+      // the rows' counts, places and offsets, and the rows with bitmaps, outlast the growth
+      const uint64_t bit_rows = rc->slab ? 0 : rc->queued[kBitsTier];
+      bool kept;
+      if (!grow_staged(e, F, C, rc->edges, (uint64_t)rc->rows + 1, bit_rows ? (m + bit_rows) * 4 : 0, &kept)) {
         free_buf(e, e->rpool);
         free_buf(e, e->rbits);
         return false;
       }
-      if (!grown) break;
+      b = make_bufs<K>(e);
+      if (kept) break;
     }
     e->seen_cand.store(C, std::memory_order_relaxed);
     // round j of the loop joins level j - 1; the last round finds nothing
     if (o.max_iterations && lev.size() > o.max_iterations)
       fail(e, WG_ERR_ITER_LIMIT, "max_iterations reached before the fixpoint");
     ReachResult& r = e->res_reach;
-    r.cnt = a.cnt;
-    r.seg = a.seg;
+    r.cnt = b.rowa;
+    r.seg = b.rowb;
     r.off = b.off;
     r.rowkey = a.g.rowkey;
     r.colkey = a.g.colkey;
     r.pool = a.pool;
     r.bits = a.bits;
-    r.bit_rows = a.queue[kBitsTier];
+    r.bit_rows = (uint32_t*)b.cand[1] + m;
     r.rank = a.g.rank;
     r.n_bits = rc->slab ? 0 : rc->queued[kBitsTier];
     r.words = a.words;
@@ -1212,8 +1225,8 @@ bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_optio
         for (uint64_t i = 0; i < std::min<uint64_t>(st->delta_sizes_cap, (uint64_t)rounds + 1); ++i)
           st->delta_sizes[i] = found((uint32_t)i);
     }
-    bool grown = false;
-    if (!grow_staged(e, F, std::max({C, base, matrices ? 0 : F}), edges, &grown)) {
+    bool kept;
+    if (!grow_staged(e, F, std::max({C, base, matrices ? 0 : F}), edges, 0, 0, &kept)) {
       free_buf(e, e->rpool);
       free_buf(e, e->rbits);
       return false;
