@@ -1132,7 +1132,7 @@ bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_optio
     const uint64_t rows = rc->rows, cols = rc->cols, edges = rc->edges, base = sc->base;
     if (base > kMaxKeys) return false;
     const bool fits = cols <= kSlabRows32 && rows + cols + 2 <= kSlabLdsWords && e->num_inst <= 1;
-    const bool matrices = fits && (base * kSgDense >= cols * cols || sc->wide);
+    bool matrices = fits && (base * kSgDense >= cols * cols || sc->wide);
     if (!matrices && sc->wide) return false;
     auto at_fixpoint = [&](uint32_t known) {  // levels [0, known) are read back
       while (rounds < known && (lev[rounds].n | lev[rounds].found)) ++rounds;
@@ -1144,6 +1144,75 @@ bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_optio
     uint64_t diagonal = 0;
     const bool strict = (o.flags & WG_SG_IRREFLEXIVE) != 0;
     const uint32_t slabs = (uint32_t)((cols + 31) / 32);
+    if (!matrices) {
+      // slots: eight times the base candidates at first (two of which are one pair)
+      uint64_t slots = 1024;
+      while (slots < 8 * base) slots <<= 1;
+      bool heavy = false;  // more pairs than this form is for
+      const uint64_t per_round = fits ? kSgGrowing : kSgHeavy / 8;
+      auto clear = [&] {
+        hip_check(e, hipMemsetAsync(&a.sc->out, 0, sizeof(SgCtl) - offsetof(SgCtl, out) + level_bytes, e->stream), "memset");
+        rounds = 0;
+        deep.clear();
+        lev = pinned;
+      };
+      for (;; slots *= 4) {
+        if (slots > (1ull << 30)) return false;
+        // the table, then as many list entries as may fill half of it
+        ensure(e, e->rpool, slots * 20);
+        a.tab = (unsigned long long*)e->rpool.p;
+        a.mask = slots - 1;
+        a.keys = a.tab + slots;
+        const uint64_t room = slots / 2;
+        uint64_t so_far = 0;  // pairs of the rounds read back
+        const uint32_t first_rounds = base / 2 > kSgGrowing ? 1 : kSgPairRounds;
+        a.key_cap = std::min(room, (base / 2 + base / 8) * (first_rounds + 1) + per_round);
+        a.front = (uint4*)(a.keys + slots / 2);
+        a.front_cap = slots / 2;
+        hip_check(e, hipMemsetAsync(a.tab, 0xFF, slots * 8, e->stream), "memset");
+        launch_sg_pairs_base(e->stream, e->grid, e->d_ctrl, m, a);
+        uint32_t j = 1;
+        for (uint32_t k = first_rounds;;) {
+          for (; k > 0 && j + 1 < allotted; --k) launch_sg_pairs_round(e->stream, e->grid, a, j++);
+          SgArgs thin = a;  // (thin rounds may be many)
+          thin.key_cap = room;
+          launch_sg_pairs_tail(e->stream, thin, j);
+          read(j + kReachReadLevels);
+          if (sc->next > j + kReachReadLevels) read(sc->next);
+          heavy = (sc->stop & kSgListFull) && sc->next == j && a.key_cap < room;
+          j = sc->next;
+          if (sc->stop || at_fixpoint(j)) break;
+          check_limit(j);
+          const uint64_t last = (uint32_t)lev[j - 1].found, before = (uint32_t)lev[j - 2].found;
+          const bool growing = 2 * last >= 3 * before;
+          if ((last > kSgGrowing && growing) || (last > (fits ? kSgGrowing : kSgHeavy) && 20 * last >= 19 * before)) {
+            heavy = true;
+            break;
+          }
+          so_far = (uint64_t)lev[j - 1].kstart + last;
+          if (j + 1 >= allotted) return deeper();
+          // rounds until the pairs fit the tail, at their rate of change
+          const double f1 = (double)(lev[j - 1].found >> 32), f0 = (double)(lev[j - 2].found >> 32);
+          const double r = std::min(0.98, std::max(0.05, f1 / std::max(f0, 1.0)));
+          k = (uint32_t)std::min(16.0, std::max(1.0, std::ceil(std::log(kSgTail / f1) / std::log(r))));
+          if (last > before) k = std::min(k, growing ? 2u : 4u);
+          a.key_cap = std::min(room, so_far + std::max(2 * last, per_round) * (k + 1));
+        }
+        if (heavy) break;
+        if (sc->stop & kSgDeep) {
+          check_limit(a.lev_cap);
+          return deeper();
+        }
+        if (!sc->stop) break;
+        // too small: cleared and run again
+        clear();
+      }
+      if (heavy) {
+        if (!fits) return false;
+        matrices = true;
+        clear();
+      }
+    }
     if (matrices) {
       const uint64_t words = (uint64_t)slabs * cols;
       ensure(e, e->rbits, words * 4);
@@ -1165,47 +1234,6 @@ bool same_generation(wg_engine* e, uint64_t m, int w, int passes, const wg_optio
         check_limit(j);
       }
     } else {
-      // slots: eight times the base candidates at first (two of which are one pair)
-      uint64_t slots = 1024;
-      while (slots < 8 * base) slots <<= 1;
-      for (;; slots *= 4) {
-        if (slots > (1ull << 30)) return false;
-        // the table, then as many list entries as may fill half of it
-        ensure(e, e->rpool, slots * 20);
-        a.tab = (unsigned long long*)e->rpool.p;
-        a.mask = slots - 1;
-        a.keys = a.tab + slots;
-        a.key_cap = slots / 2;
-        a.front = (uint4*)(a.keys + slots / 2);
-        a.front_cap = slots / 2;
-        hip_check(e, hipMemsetAsync(a.tab, 0xFF, slots * 8, e->stream), "memset");
-        launch_sg_pairs_base(e->stream, e->grid, e->d_ctrl, m, a);
-        uint32_t j = 1;
-        rounds = 0;
-        deep.clear();
-        lev = pinned;
-        for (uint32_t k = kSgPairRounds;;) {
-          for (; k > 0 && j + 1 < allotted; --k) launch_sg_pairs_round(e->stream, e->grid, a, j++);
-          launch_sg_pairs_tail(e->stream, a, j);
-          read(j + kReachReadLevels);
-          if (sc->next > j + kReachReadLevels) read(sc->next);
-          j = sc->next;
-          if (sc->stop || at_fixpoint(j)) break;
-          check_limit(j);
-          if (j + 1 >= allotted) return deeper();
-          // rounds until the pairs fit the tail, at their rate of change
-          const double f1 = (double)(lev[j - 1].found >> 32), f0 = (double)(lev[j - 2].found >> 32);
-          const double r = std::min(0.98, std::max(0.05, f1 / std::max(f0, 1.0)));
-          k = (uint32_t)std::min(16.0, std::max(1.0, std::ceil(std::log(kSgTail / f1) / std::log(r))));
-        }
-        if (sc->stop & kSgDeep) {
-          check_limit(a.lev_cap);
-          return deeper();
-        }
-        if (!sc->stop) break;
-        // too small: cleared and run again
-        hip_check(e, hipMemsetAsync(&a.sc->out, 0, sizeof(SgCtl) - offsetof(SgCtl, out) + level_bytes, e->stream), "memset");
-      }
       for (uint32_t i = 0; i <= rounds; ++i) diagonal += lev[i].diag;
     }
     uint64_t F = 0, C = 0, cand_total = 0;

@@ -34,6 +34,17 @@ constexpr uint32_t kSgPairDegree = 64;
 // its own; us a pass on 500,000 vertices / a batch of 256 graphs: 128 pairs 894 / 598, 256 885 / 590,
 // 512 876 / 574, 1,024 888 / 584, 2,048 930 / 613).
 constexpr uint32_t kSgTail = 512;
+// The pairs' cost is their number (0.35 ns each: a compare-and-swap in memory, the list, a sort), the
+// iterations' and the matrices' mostly that of their rounds (100 us, 25 to 100).  So the pairs are left, to
+// matrices where the columns allow and else to the iterations, once a round finds more than kSgGrowing
+// and half as many again as the one before, or more than kSgHeavy (for matrices kSgGrowing) and not
+// fewer by 5%; and rounds end early that find more than an eighth of kSgHeavy (kSgGrowing), or than
+// twice the last one's, on average up to the next read.  (us, by pairs to the end / by the
+// iterations / so: trees of 8 children, 3,000 vertices 3,324 / 791 / 755, 30,000 466,008 / 24,546 / 25,524;
+// of 2, 30,000 52,464 / 13,067 / 13,333; random tree of 30,000 17,793 / 7,608 / 8,215; random graph of
+// 100,000 vertices with 105,000 edges, 234 rounds, 20,124 / 48,167 / 20,576.)
+constexpr uint64_t kSgGrowing = 1u << 17;
+constexpr uint64_t kSgHeavy = 1u << 22;
 constexpr uint32_t kSgProbes = 128;      // buckets of 4 slots probed before the table counts as full
 constexpr uint32_t kSgThreads = 1024;
 constexpr uint32_t kSgBuf = 2048;        // new pairs a block buffers
@@ -74,7 +85,7 @@ struct SgArgs {
   unsigned long long* tab;   // hash slots (a power of two), all ones when empty
   uint64_t mask;
   unsigned long long* keys;  // pairs in order of discovery
-  uint64_t key_cap;
+  uint64_t key_cap;          // ... that are kept: past it the rounds end
   uint4* front;              // ... {first edges of the two rows, edges of each} of those to expand
   uint64_t front_cap;
   // matrices: word [slab * cols + row]

@@ -102,12 +102,12 @@ struct SgWave {
   uint32_t mark[kWave];
 };
 
-// Expands the lanes' pairs f, 64 candidates a step: step(true if the lane's is new, its key, its
-// entry of the next round's list), by whole waves.  Returns the candidates.  The pair of
+// Expands the lanes' pairs f, 64 candidates a step until over(): step(true if the lane's is new, its key,
+// its entry of the next round's list), by whole waves.  Returns the candidates.  The pair of
 // candidate k is the one whose start is the last at or below k: its rank is counted from the
 // starts' bits (a bisection took ten LDS round trips, 4,000 cycles with 16 waves at it).
-template <bool Solo, typename Step>
-__device__ __forceinline__ uint32_t sg_expand(const SgArgs& a, SgWave& w, uint4 f, Step step) {
+template <bool Solo, typename Step, typename Over>
+__device__ __forceinline__ uint32_t sg_expand(const SgArgs& a, SgWave& w, uint4 f, Step step, Over over) {
   const uint32_t lane = (uint32_t)lane_id();
   const uint32_t n = f.z * f.w, incl = wave_incl_scan<uint32_t>(n), pre = incl - n;
   const uint32_t total = __shfl(incl, kWave - 1, kWave);
@@ -119,7 +119,7 @@ __device__ __forceinline__ uint32_t sg_expand(const SgArgs& a, SgWave& w, uint4 
     w.pre[at] = pre;
   }
   uint32_t pairs = 0;  // with a start before this step
-  for (uint32_t k0 = 0; k0 < total; k0 += kWave) {
+  for (uint32_t k0 = 0; k0 < total && !over(); k0 += kWave) {
     wave_lds_sync();
     w.mark[lane] = 0;
     wave_lds_sync();
@@ -193,6 +193,7 @@ struct SgOut {
   unsigned long long valid;      // ... that are in the buffers, once they were too small
   unsigned long long cand;
   uint32_t diag;
+  volatile uint32_t full;  // the list of keys is
 };
 
 __device__ __forceinline__ void sg_found(const SgArgs& a, SgOut& o, bool is_new, unsigned long long key, uint4 next,
@@ -206,18 +207,24 @@ __device__ __forceinline__ void sg_found(const SgArgs& a, SgOut& o, bool is_new,
     // full: straight to the lists (the first wave past the end notes where the buffers end)
     if (p.first <= kSgBuf && lane_id() == 0) o.valid = ((unsigned long long)p.front << 32) | p.first;
     p = sg_place(is_new, key, next, &out->found);
+    if ((uint64_t)kstart + p.first + p.keys > a.key_cap) o.full = 1;
     if (is_new) sg_put_key(a, (uint64_t)kstart + p.key, key);
     if (p.expand) sg_put_front(a, (uint64_t)fstart + p.front, next);
   }
 }
 
-// (the whole block) empties the buffers into the lists
-__device__ __forceinline__ void sg_flush(const SgArgs& a, SgOut& o, uint32_t kstart, uint32_t fstart, SgLevel* out) {
+// (the whole block) empties the buffers into the lists; true if that of the keys is full: the round is
+// over then
+__device__ __forceinline__ bool sg_flush(const SgArgs& a, SgOut& o, uint32_t kstart, uint32_t fstart, SgLevel* out) {
   block_lds_sync();
   const unsigned long long found = (uint32_t)o.found <= kSgBuf ? o.found : o.valid;
   const uint32_t nk = (uint32_t)found, nf = (uint32_t)(found >> 32);
   if (threadIdx.x == 0) {
-    if (nk) o.at = atomicAdd(&out->found, found);
+    o.full = 0;
+    if (nk) {
+      o.at = atomicAdd(&out->found, found);
+      o.full = (uint64_t)kstart + (uint32_t)o.at + nk > a.key_cap ? 1u : 0u;
+    }
     if (o.diag) atomicAdd(&out->diag, o.diag);
     if (o.cand) atomicAdd(&out->c, o.cand);
   }
@@ -225,12 +232,14 @@ __device__ __forceinline__ void sg_flush(const SgArgs& a, SgOut& o, uint32_t kst
   const uint64_t at_k = (uint64_t)kstart + (uint32_t)o.at, at_f = (uint64_t)fstart + (uint32_t)(o.at >> 32);
   for (uint32_t t = threadIdx.x; t < nk; t += kSgThreads) sg_put_key(a, at_k + t, o.keys[t]);
   for (uint32_t t = threadIdx.x; t < nf; t += kSgThreads) sg_put_front(a, at_f + t, o.front[t]);
+  const bool full = o.full != 0;
   block_lds_sync();
   if (threadIdx.x == 0) {
     o.found = o.cand = 0;
     o.diag = 0;
   }
   block_lds_sync();
+  return full;
 }
 
 // The base pairs: every edge with the later edges of its row.
@@ -242,7 +251,7 @@ __global__ __launch_bounds__(kSgThreads) void k_sg_pairs_base(const Ctrl* ctrl, 
   const uint32_t tid = threadIdx.x;
   if (tid == 0) {
     o.found = o.cand = 0;
-    o.diag = 0;
+    o.diag = o.full = 0;
   }
   block_lds_sync();
   for (uint64_t base = (uint64_t)blockIdx.x * T; base < n; base += (uint64_t)gridDim.x * T) {
@@ -254,8 +263,8 @@ __global__ __launch_bounds__(kSgThreads) void k_sg_pairs_base(const Ctrl* ctrl, 
     f.w = i < n ? a.edge[i].w - 1 : 0;
     sg_expand<false>(a, s_wave[tid / kWave], f, [&](bool is_new, unsigned long long key, uint4 next) {
       sg_found(a, o, is_new, key, next, 0, 0, &a.lev[0]);
-    });
-    sg_flush(a, o, 0, 0, &a.lev[0]);
+    }, [&] { return wave_uniform(o.full) != 0; });
+    if (sg_flush(a, o, 0, 0, &a.lev[0])) break;
   }
 }
 
@@ -285,7 +294,7 @@ __global__ __launch_bounds__(kSgThreads) void k_sg_pairs_round(SgArgs a, uint32_
   if ((uint64_t)blockIdx.x * kWaves * per >= fn) return;
   if (tid == 0) {
     o.found = o.cand = 0;
-    o.diag = 0;
+    o.diag = o.full = 0;
   }
   block_lds_sync();
   for (uint64_t base = (uint64_t)blockIdx.x * kWaves * per; base < fn; base += (uint64_t)waves * per) {
@@ -295,9 +304,9 @@ __global__ __launch_bounds__(kSgThreads) void k_sg_pairs_round(SgArgs a, uint32_
     if (lane < per && i < fn) f = a.front[prev.fstart + i];
     const uint32_t total = sg_expand<false>(a, s_wave[wid], f, [&](bool is_new, unsigned long long key, uint4 next) {
       sg_found(a, o, is_new, key, next, kstart, fstart, out);
-    });
+    }, [&] { return wave_uniform(o.full) != 0; });
     sg_count(&o.cand, f, total);
-    sg_flush(a, o, kstart, fstart, out);
+    if (sg_flush(a, o, kstart, fstart, out)) break;
   }
 }
 
@@ -351,7 +360,7 @@ __global__ __launch_bounds__(kSgThreads) void k_sg_pairs_tail(SgArgs a, uint32_t
           if (p.front < kSgTail) s_front[j & 1u][p.front] = next;
           else sg_put_front(a, (uint64_t)fstart + p.front, next);  // (for a round that goes back to the host)
         }
-      });
+      }, [] { return false; });
       sg_count(&cnt.cand, f, total);
     }
     block_lds_sync();
@@ -372,7 +381,7 @@ __global__ __launch_bounds__(kSgThreads) void k_sg_pairs_tail(SgArgs a, uint32_t
     kstart += nk;
     fstart += nf;
     fn = nf;
-    if (nk == 0 || nf > kSgTail || s_stop) {
+    if (nk == 0 || nf > kSgTail || s_stop || kstart > a.key_cap) {
       ++j;
       break;
     }

@@ -194,6 +194,25 @@ DEEP = {
 }
 
 
+def _tree(n, children):
+    v = np.arange(1, n, dtype=np.uint32)
+    return (v - 1) // np.uint32(children), v
+
+
+@pytest.mark.parametrize("n,children,forms", [(3_000, 8, True), (3_000, 2, True), (19_000, 8, False), (19_000, 2, False)])
+def test_pairs_that_grow(engine, n, children, forms):
+    """Pairs that multiply from round to round: matrices where the columns allow, else the iterations."""
+    import torch
+
+    s, d = map(to_gpu, _tree(n, children))
+    a_s, a_d, a = engine.solve("sg", s, d)
+    b_s, b_d, b = engine.solve("sg", s, d, wg.make_options(batch_k=2))
+    assert by_forms(a) == forms and sg_form(*_tree(n, children)) == "pairs"
+    assert torch.equal(a_s.view(torch.int32), b_s.view(torch.int32)) and torch.equal(a_d.view(torch.int32), b_d.view(torch.int32))
+    for key in ("iterations", "delta_sizes", "join_candidates"):
+        assert a[key] == b[key], key
+
+
 @pytest.mark.parametrize("n,hub", [(4_095, 0), (4_096, 0), (9_000, 0), (4_400, 70)])
 def test_same_generation_of_many_rounds(n, hub):
     """More rounds than are allotted at first, as pairs and (beside a vertex of 70 out-edges) as
