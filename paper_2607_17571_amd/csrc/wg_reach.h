@@ -45,9 +45,9 @@ constexpr int kReachTiers = 5;              // queues between the tiers: two gro
 constexpr int kThinTier = 2, kQueueTier = 3, kBitsTier = 4;
 // The queue tier holds a row's bitmap of all columns in LDS: from this many words on one or two rows
 // per CU.  The thin tier then takes the rows first, 24 per CU (ms a closure by the iterations' launches /
-// with the queue tier alone / with the thin tier: 1,000 chains of 300 vertices 37.7 / 171 / 26.6, 800 of
-// 300 36.2 / 69.5 / 21.0, 100 of 3,000 678 / 1,816 / 127; random graphs of 1,000,000 vertices with
-// 950,000 edges 13.6 / 6.0 / 3.2, of 700,000 with 630,000 6.6 / 1.45 / 1.21).  Up to kThinRounds rows
+// with the queue tier alone / with the thin tier: 1,000 chains of 300 vertices 37.7 / 171 / 18.5, 800 of
+// 300 36.2 / 69.5 / 14.9, 100 of 3,000 678 / 1,816 / 110; random graphs of 1,000,000 vertices with
+// 950,000 edges 13.6 / 6.0 / 2.8, of 700,000 with 630,000 6.6 / 1.45 / 1.17).  Up to kThinRounds rows
 // for each that the queue tier has in flight stay there: a binary tree of 2^18 vertices has 1,023, wide
 // ones among them, 1.45 ms so and 1.54 through both.
 constexpr uint32_t kThinWords = 4097;
@@ -104,7 +104,8 @@ enum : uint32_t {
   kReachHalt = kReachUnsupported | kReachDeep | kReachTooLarge | kReachCancelled,
 };
 // Rows and slabs, and the tail of same-generation, look at `stop` and the host's word every so many levels
-// (a load of 1 to 3 us every 64 levels of 1 us and more), queued rows at the host's word every so many rows.
+// (a load of 1 to 3 us every 64 levels of 1 us and more), tiers every so many rows or tiles of them: the
+// look waits for the atomics on its line (the queue tier of 256 random graphs: every row 322 us, 228 so).
 constexpr uint32_t kStopLevels = 64;
 constexpr uint32_t kStopRows = 16;
 constexpr unsigned long long kReachMaxTuples = 0xFFFFFFF0ull;

@@ -801,7 +801,7 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_group(ReachArgs a) {
     const uint64_t tile = (uint64_t)xcd_tile(iter, stretch) * (NW * PER);
     if (tile >= n) break;
     const uint64_t base = tile + (tid / kWave) * PER;
-    if (__builtin_amdgcn_readfirstlane((int)reach_halted(a.rc))) break;
+    if (iter % kStopRows == kStopRows - 1 && wave_uniform(reach_halted(a.rc))) break;
     const uint64_t k = base + (uint32_t)lane / G;
     const bool have = k < n;
     const uint32_t row = have ? a.queue[TIER][k] : 0u;
@@ -1010,6 +1010,10 @@ __device__ __forceinline__ void row_columns(const ReachArgs& a, uint32_t row, ui
 // that have columns are read back and cleared.  A level that outgrows the queue sends the row on, and so
 // does one that is not thin by the last level whose counts can still be taken back.
 // ---------------------------------------------------------------------------
+// Pool entries a wave reserves at a time, and rows between its looks at `stop`: both are on the one line that
+// all waves' atomics queue for (a reservation and a look for every row: 2,000 cycles of 70 vertices
+// 10.4 ms, 4.0 so).
+constexpr uint32_t kThinChunk = 1024;
 constexpr uint32_t kThinWaves = 4;  // (each for itself: a quarter of the blocks to start)
 template <uint32_t QCAP, uint32_t GROUPS>  // stretches of 1,024 columns
 __global__ __launch_bounds__(kThinWaves * kWave) void k_reach_thin(ReachArgs a) {
@@ -1038,10 +1042,11 @@ __global__ __launch_bounds__(kThinWaves * kWave) void k_reach_thin(ReachArgs a) 
   const uint2* __restrict__ edge = a.g.edge;
   const uint32_t edges = a.rc->edges;
   uint32_t* const vis = a.vis + ((uint64_t)blockIdx.x * kThinWaves + wid) * a.vis_words;
-  uint32_t share = 0, claims = 0;
+  uint32_t share = 0, claims = 0, left = 0;
+  uint64_t chunk = 0;  // pool entries left of the wave's
   for (;;) {
     uint32_t row = kReachNone;
-    if (lane == 0 && !reach_halted(a.rc) && !(++claims % kStopRows == 0 && cancelled(a.cancel, &a.rc->stop))) {
+    if (lane == 0 && !(claims++ % kStopRows == 0 && reach_look(a))) {
       const uint32_t at = reach_claim(a.rc, kThinTier, n, share);
       if (at != kReachNone) row = a.queue[kThinTier][at];
     }
@@ -1123,13 +1128,19 @@ __global__ __launch_bounds__(kThinWaves * kWave) void k_reach_thin(ReachArgs a) 
       }
     } else {
       for (uint32_t x = lane; x < lv && x < kReachLdsLevels; x += kWave) reach_count(s_lev, a, x, r.ln[x], r.ld[x]);
+      if (cnt > left) {  // (uniform)
+        left = max(cnt, kThinChunk);
+        if (lane == 0) chunk = reach_alloc(a, left);
+        chunk = __shfl(chunk, 0, kWave);
+      }
+      pos = chunk;
+      chunk += cnt;
+      left -= cnt;
       if (lane == 0) {
-        pos = reach_alloc(a, cnt);
         a.cnt[row] = cnt;
         a.seg[row] = (uint32_t)pos;
-        if (pos + cnt > a.pool_cap) pos = ~0ull;
       }
-      pos = __shfl(pos, 0, kWave);
+      if (chunk > a.pool_cap) pos = ~0ull;
     }
     // the stretches that have columns, in order (the queues are free)
     uint16_t* const list = (uint16_t*)&r.front[0][0];
@@ -1201,7 +1212,7 @@ __global__ __launch_bounds__(NW * kWave) void k_reach_queue(ReachArgs a) {
   __syncthreads();
   for (;;) {
     if (tid == 0) {
-      const bool over = reach_halted(a.rc) || (++claims % kStopRows == 0 && cancelled(a.cancel, &a.rc->stop));
+      const bool over = claims++ % kStopRows == 0 && reach_look(a);
       const uint32_t at = over ? kReachNone : reach_claim(a.rc, kQueueTier, n, share);
       s_row = at == kReachNone ? kReachNone : a.queue[kQueueTier][at];
       s_n[0] = s_n[1] = s_f[0] = s_f[1] = 0;
