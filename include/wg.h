@@ -94,7 +94,15 @@ typedef enum { WG_QUERY_TC = 0, WG_QUERY_SG = 1, WG_QUERY_TRIANGLES = 2 } wg_que
                                its size allows -- TC one source row at a time or as slabs of
                                columns, SG as pairs or bit matrices, triangles one rotation
                                each -- with the same result, iterations, delta sizes and
-                               candidates.  Everything else takes the iterations' launches: a
+                               candidates.  Left out are: fewer than 128 edges or ids; TC of
+                               fewer than 128 rows, of more than 2^20 columns an instance, of
+                               more than 2^32 - 16 tuples, or of more than 2^18 columns with a
+                               level of more than 3,072 vertices; SG with an out-degree above
+                               64 in a batch or past 18,431 columns, or whose pairs multiply
+                               past those columns; triangles of fewer than 32,768 edges.  What
+                               a graph shows on the way costs that way (5 to 40% of a solve of
+                               a few hundred microseconds, less of a longer one).  Those and
+                               everything else take the iterations' launches: a
                                device-resident loop checked by the host every 2
                                iterations (batch_k overrides), with a speculative batch
                                enqueued behind every check; and once the delta (at most
@@ -381,7 +389,8 @@ typedef struct {
 wg_status wg_get_sort_config(const wg_engine* engine, uint32_t key_bytes, wg_sort_config* out);
 wg_status wg_set_sort_config(wg_engine* engine, uint32_t key_bytes, const wg_sort_config* config);
 
-/* Autotuner: solve the given query (num_instances = 0 with d_offsets = NULL: a single
+/* Autotuner (of the iterations' launches, which its trials take; the sorts of a solve on the
+ * renumbered graph use the configuration too): solve the given query (num_instances = 0 with d_offsets = NULL: a single
  * instance, else a batch as in wg_tc_batch) once per candidate configuration -- digit
  * bits 8..11 x small or large tile x 2, 4 or 8 blocks per compute unit -- `repeats` timed
  * times each after one warm-up (0 = 2), and install the fastest for the solve's key

@@ -2929,8 +2929,6 @@ __global__ __launch_bounds__(kBlock) void k_offsets2(const K* __restrict__ A, ui
                         : lower_bound<K>(A, na, (K)i << shift) + lower_bound<K>(B, nb, (K)i << shift);
 }
 
-// The control block written from a kernel argument (captured when the launch is enqueued, so
-// no host staging buffer has to outlive the call that queues it).
 // Device memory into pinned host memory, then `seq` into the word the host polls.
 __global__ __launch_bounds__(kBlock) void k_fetch(uint32_t* __restrict__ dst, const uint32_t* __restrict__ src,
                                                   uint32_t words, uint32_t* flag, uint32_t seq) {
@@ -2940,6 +2938,8 @@ __global__ __launch_bounds__(kBlock) void k_fetch(uint32_t* __restrict__ dst, co
   if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// The control block written from a kernel argument (captured when the launch is enqueued, so
+// no host staging buffer has to outlive the call that queues it).
 __global__ void k_ctrl_set(Ctrl* ctrl, Ctrl v) {
   if (threadIdx.x == 0) *ctrl = v;
 }

@@ -64,7 +64,7 @@ constexpr uint32_t kReachLast = 0x80000000u;  // flag in an edge's column: the l
 constexpr int kReachXcds = 8;
 // Tiles of 256 rows that go to one XCD together: the instances of a batch lie one after the other, so
 // that an XCD's L2 then holds the edges its rows share (256 random graphs, 18 MB of edges: the
-// small group tier 400 -> 361 us with it, the thread tier 351 -> 331).
+// small group tier a tenth less with it, the thread tier 351 -> 331 us).
 constexpr uint32_t kReachTileStretch = 64;
 constexpr uint32_t kReachQueueStretch = 512;  // queued rows likewise
 constexpr uint32_t kReachEdgePad = 8;       // edge records readable past the last

@@ -751,7 +751,7 @@ __device__ __forceinline__ void sort_group(uint32_t (&v)[N], uint32_t gl) {
 // steps' latency (a dependent load and an LDS compare-and-swap) over the rows in flight, which
 // their LDS limits (192 of the small tier per CU, 48 of the large).  140,000 rows of 17 to some
 // thousand tuples: one tier of 16 lanes and 128 tuples took 780 us and left 720 to the queue
-// tier; 361, 286 and 327 so.
+// tier; 258, 249 and 219 so.
 // ---------------------------------------------------------------------------
 template <uint32_t H, uint32_t RING, uint32_t LMAX>
 struct ReachRow {
@@ -1183,7 +1183,7 @@ __global__ __launch_bounds__(kThinWaves * kWave) void k_reach_thin(ReachArgs a) 
 // Queue tier: one row per block of NW waves (one wave where the columns' bitmap is at most 8 KB).
 // The set is a bitmap of the instance's columns in LDS; a column whose bit a lane sets first is
 // found, and its row, if it has one, goes to the next level's queue.  Thin, deep rows pay per level
-// one edge load and a few LDS round trips (one wave keeps its counts in registers: 327 -> 293 us for
+// one edge load and a few LDS round trips (one wave keeps its counts in registers: a tenth less for
 // the rows past 256 tuples of 256 random graphs), and 5 to 24 of them run per CU.  A level that outgrows the
 // queue sends the row on.  The columns come out of the bitmap in order.
 // ---------------------------------------------------------------------------
