@@ -240,6 +240,7 @@ void worker(wg_server* sv, size_t i) {
   Slot& me = *sv->slots[i];
   (void)hipSetDevice(sv->device);
   std::unique_lock<std::mutex> lk(sv->core->mu);
+  bool looked = false;  // at the freed results, since the last wait
   for (;;) {
     if (me.trim_requested) {
       me.trim_requested = false;
@@ -250,21 +251,26 @@ void worker(wg_server* sv, size_t i) {
       sv->core->cv.notify_all();
       continue;
     }
-    if (wg::have_pending()) {
-      lk.unlock();
-      wg::free_pending();
-      lk.lock();
-    }
     if (sv->stop && sv->queue.empty()) break;
     uint64_t grant = 0;
     std::shared_ptr<JobState> job = pick(sv, i, &grant);
     if (!job) {
       if (me.trim_requested) continue;
+      // (a request that can start does not wait for the frees of results)
+      if (!looked && wg::have_pending()) {
+        looked = true;
+        lk.unlock();
+        wg::free_pending();
+        lk.lock();
+        continue;
+      }
+      looked = false;
       // (freed results whose copies are still queued: nothing notifies when those have run)
       if (wg::have_pending()) sv->core->cv.wait_for(lk, kPendingPoll);
       else sv->core->cv.wait(lk);
       continue;
     }
+    looked = false;
     JobState& j = *job;
     me.job = job;
     // (under the lock: until the solve itself starts, the engine still reports the previous
