@@ -100,7 +100,7 @@ typedef enum { WG_QUERY_TC = 0, WG_QUERY_SG = 1, WG_QUERY_TRIANGLES = 2 } wg_que
                                level of more than 3,072 vertices; SG with an out-degree above
                                64 in a batch or past 18,431 columns, or whose pairs multiply
                                past those columns; triangles of fewer than 32,768 edges.  What
-                               a graph shows on the way costs that way (5 to 40% of a solve of
+                               a graph shows on the way costs that way (3 to 40% of a solve of
                                a few hundred microseconds, less of a longer one).  Those and
                                everything else take the iterations' launches: a
                                device-resident loop checked by the host every 2
